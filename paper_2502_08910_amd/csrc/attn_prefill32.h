@@ -81,7 +81,7 @@ constexpr float kPfMaxSum = 1024.0f;                // row sum of a tile above w
 // PAGED: K and V are page pools read through the sequence's row of the block table; the page id of
 // every slot is looked up once, next to its position, and kept in LDS as well.
 template <int NQ, int G, bool WIDE, bool ROPE, bool PAGED, bool KV8 = false>
-__global__ __launch_bounds__(64 * NQ * G, NQ * G < 8 || ((ROPE || KV8) && NQ * G == 8) ? 2 : NQ * G == 8 ? 3 : 4) void attn_prefill32_kernel(const AttnPrefillArgs a)
+__global__ __launch_bounds__(64 * NQ * G, NQ * G <= 8 ? 2 : 4) void attn_prefill32_kernel(const AttnPrefillArgs a)
 {
     static_assert(!PAGED || WIDE, "paged pools are addressed with 64-bit offsets");
     static_assert(!KV8 || WIDE, "E4M3 rows are addressed with 64-bit offsets");
@@ -295,34 +295,37 @@ __global__ __launch_bounds__(64 * NQ * G, NQ * G < 8 || ((ROPE || KV8) && NQ * G
     };
 
     // first product of a tile: S^T = K Q^T for this wave's 32 queries
-    auto scores = [&](int st) -> f32x16 {
+    auto k_operands = [&](int st, bf16x8 (&ka)[8]) {
         const uint16_t *cK = stage_of(st) + n * kD;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) ka[ks] = *reinterpret_cast<const bf16x8 *>(&cK[((ks * 2 + half) ^ (n & 15)) * 8]);
+    };
+    auto scores = [&](const bf16x8 (&ka)[8]) -> f32x16 {
         f32x16 s;
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = 0.f;
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-            const bf16x8 ka = *reinterpret_cast<const bf16x8 *>(&cK[((ks * 2 + half) ^ (n & 15)) * 8]);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qb[ks], s, 0, 0, 0);
-        }
+        for (int ks = 0; ks < 8; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], qb[ks], s, 0, 0, 0);
         return s;
     };
-    // softmax update of a tile's scores: P (bf16) for the second product, running sum, rescale
-    auto softmax = [&](int tile, bool masked, f32x16 &s, bf16x8 (&pb)[2]) {
-        if (masked) {
+    // softmax update of a tile's scores: P (bf16) for the second product, running sum, rescale.
+    // mask_scores: keys that a lane's query must not see; exponentials: the common path, straight-line code;
+    // settle: running sum, and the exact path where the common one's reference was too far off.
+    auto mask_scores = [&](int tile, f32x16 &s) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int kp = sPos[tile * kPfTile + 8 * (r >> 2) + 4 * half + (r & 3)];
-                if (kp < 0 || kp > qpos) s[r] = -INFINITY;
-            }
+        for (int r = 0; r < 16; ++r) {
+            const int kp = sPos[tile * kPfTile + 8 * (r >> 2) + 4 * half + (r & 3)];
+            if (kp < 0 || kp > qpos) s[r] = -INFINITY;
         }
-        // Reference point m_run of the exponentials, in scaled (log2) units.  It only has to bound
-        // the scores from above loosely, so the common path takes the exponentials against the
-        // current one without looking for the tile maximum, and checks the row sums: a sum above
-        // kPfMaxSum (or an overflow) in any lane sends the whole wave to the exact path, which
-        // moves the reference to the maximum and rescales the accumulators (64 multiplies per
-        // lane).  p <= kPfMaxSum stays far inside the fp32 and bf16 ranges and out = o / l is
-        // unchanged.  The two lanes of a query (key halves) always share one reference.
+    };
+    // Reference point m_run of the exponentials, in scaled (log2) units.  It only has to bound
+    // the scores from above loosely, so the common path takes the exponentials against the
+    // current one without looking for the tile maximum, and checks the row sums: a sum above
+    // kPfMaxSum (or an overflow) in any lane sends the whole wave to the exact path, which
+    // moves the reference to the maximum and rescales the accumulators (64 multiplies per
+    // lane).  p <= kPfMaxSum stays far inside the fp32 and bf16 ranges and out = o / l is
+    // unchanged.  The two lanes of a query (key halves) always share one reference.
+    auto exponentials = [&](const f32x16 &s, bf16x8 (&pb)[2]) {
         float ps = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
@@ -330,6 +333,9 @@ __global__ __launch_bounds__(64 * NQ * G, NQ * G < 8 || ((ROPE || KV8) && NQ * G
             ps += pw;
             pb[r >> 3][r & 7] = (__bf16)pw;
         }
+        return ps;
+    };
+    auto settle = [&](const f32x16 &s, float ps, bf16x8 (&pb)[2]) {
         if (__any(!(ps <= kPfMaxSum))) {
             float mx = s[0];
 #pragma unroll
@@ -338,13 +344,7 @@ __global__ __launch_bounds__(64 * NQ * G, NQ * G < 8 || ((ROPE || KV8) && NQ * G
             const float mn = fmaxf(m_run, mx * a.scale_log2e);
             const float corr = __builtin_amdgcn_exp2f(m_run - mn);
             m_run = mn;
-            ps = 0.f;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float pw = __builtin_amdgcn_exp2f(fmaf(s[r], a.scale_log2e, -mn));
-                ps += pw;
-                pb[r >> 3][r & 7] = (__bf16)pw;
-            }
+            ps = exponentials(s, pb);
             l_run *= corr;
 #pragma unroll
             for (int dt = 0; dt < 4; ++dt) o[dt] *= corr;
@@ -370,13 +370,18 @@ __global__ __launch_bounds__(64 * NQ * G, NQ * G < 8 || ((ROPE || KV8) && NQ * G
             (__attribute__((address_space(3))) s16x4 *)(cV + voff[dt] + (16 * kk + 8) * kD));
         return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     };
-    auto accumulate = [&](int st, const bf16x8 (&pb)[2]) {
-        const uint16_t *cV = stage_of(st);
+    auto v_operands = [&](const uint16_t *cV, bf16x8 (&va)[4][2]) {
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-            for (int kk = 0; kk < 2; ++kk)
-                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(cV, dt, kk), pb[kk], o[dt], 0, 0, 0);
+            for (int kk = 0; kk < 2; ++kk) va[dt][kk] = v_operand(cV, dt, kk);
+    };
+    auto accumulate = [&](const bf16x8 (&va)[4][2], const bf16x8 (&pb)[2]) {
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt)
+                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[dt][kk], pb[kk], o[dt], 0, 0, 0);
     };
     // Tile t+D is requested at the start of period t (D = kPfStages-1); tile t+2 (ROPE: t+3) must
     // have landed at the barrier that ends it, so one newer request may still be on its way then
@@ -403,9 +408,12 @@ __global__ __launch_bounds__(64 * NQ * G, NQ * G < 8 || ((ROPE || KV8) && NQ * G
         __syncthreads();
         if constexpr (KV8) request(3, 3, rows_of(3));       // into the raw stage tile 0 has left
     }
-    f32x16 s_nxt = scores(0);
+    bf16x8 ka[8];
+    k_operands(0, ka);
+    f32x16 s_nxt = scores(ka);
     bf16x8 pb[2];
-    softmax(0, sMasked[0] != 0, s_nxt, pb);
+    if (sMasked[0] != 0) mask_scores(0, s_nxt);
+    settle(s_nxt, exponentials(s_nxt, pb), pb);
     int masked_nxt = n_tiles > 1 ? sMasked[1] : 0;      // read a period ahead, like the row positions
     // one tile period; ST = tile % kPfStages
     auto period = [&](auto st_c, int tile) {
@@ -415,9 +423,37 @@ __global__ __launch_bounds__(64 * NQ * G, NQ * G < 8 || ((ROPE || KV8) && NQ * G
         Table table_nxt{};
         if constexpr (ROPE) table_nxt = table_of(tile + 3);
         request(tile + D, ST + D, rows);
-        if (tile + 1 < n_tiles) s_nxt = scores(ST + 1);
-        accumulate(ST, pb);
-        if (tile + 1 < n_tiles) softmax(tile + 1, masked_nxt != 0, s_nxt, pb);
+        // All operands of the period are requested from LDS up front: the matrix products of a wave are
+        // a chain, and with two waves per SIMD an LDS round trip in front of every one or two of them
+        // is not covered.  64 more registers, which two waves per SIMD leave free (196 of 256).
+        // Measured with the interleaving below: 371 -> 350 us (4,096 queries, 32 heads, 5,440 key
+        // slots each), with RoPE 223 -> 211, E4M3 + RoPE 411 -> 387 (2,048 queries).  The same kernel
+        // without requests, barriers and softmax takes 248 us, and 234 with the operands held in
+        // registers: the chip's clock under dense matrix work is what is left.
+        bf16x8 va[4][2];
+        k_operands(ST + 1, ka);
+        v_operands(stage_of(ST), va);
+        s_nxt = scores(ka);
+        __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
+        if (masked_nxt != 0) mask_scores(tile + 1, s_nxt);
+        // The second product of this tile and the exponentials of the next one are independent: one
+        // straight-line block, interleaved so that the vector instructions run under the matrix ones.
+        bf16x8 pb_nxt[2];
+        accumulate(va, pb);
+        const float ps = exponentials(s_nxt, pb_nxt);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
+            __builtin_amdgcn_sched_group_barrier(0x002, 7, 1);
+        }
+        settle(s_nxt, ps, pb_nxt);
+        pb[0] = pb_nxt[0];
+        pb[1] = pb_nxt[1];
         masked_nxt = tile + 2 < n_tiles ? sMasked[tile + 2] : 0;
         rows = rows_of(tile + D + 1);
         if constexpr (kTouch) {
@@ -427,11 +463,11 @@ __global__ __launch_bounds__(64 * NQ * G, NQ * G < 8 || ((ROPE || KV8) && NQ * G
         landed(tile + D >= n_tiles);        // tile + 2 (ROPE, KV8: tile + 3)
         __syncthreads();
     };
-    auto periods = [&](int tile, auto... st) {      // up to kPfStages periods, stopping at the last tile
+    auto periods = [&](int tile, auto... st) {      // up to kPfStages periods, stopping before the last tile
         bool more = true;
-        ((more = more && tile + decltype(st)::value < n_tiles && (period(st, tile + decltype(st)::value), true)), ...);
+        ((more = more && tile + decltype(st)::value + 1 < n_tiles && (period(st, tile + decltype(st)::value), true)), ...);
     };
-    for (int tile = 0; tile < n_tiles; tile += kPfStages) {
+    for (int tile = 0; tile + 1 < n_tiles; tile += kPfStages) {
         if constexpr (kPfStages == 3)
             periods(tile, std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{},
                     std::integral_constant<int, 2>{});
@@ -445,6 +481,12 @@ __global__ __launch_bounds__(64 * NQ * G, NQ * G < 8 || ((ROPE || KV8) && NQ * G
             periods(tile, std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{},
                     std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{}, std::integral_constant<int, 4>{},
                     std::integral_constant<int, 5>{});
+    }
+
+    {                                       // second product of the last tile
+        bf16x8 va[4][2];
+        v_operands(stage_of(n_tiles - 1), va);
+        accumulate(va, pb);
     }
 
     float l = l_run;
