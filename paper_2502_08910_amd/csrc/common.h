@@ -342,12 +342,6 @@ __device__ inline uint4 rotate_fp8x8(const uint2 &k, const float4 c, const float
     unpack8_fp8(k, f);
     return rotate_f32x8(f, c, sn);
 }
-__device__ inline void rotate_fp8x8_split(const uint2 &k, const float4 c, const float4 sn, uint4 &hi, uint4 &lo)
-{
-    float f[8];
-    unpack8_fp8(k, f);
-    rotate_f32x8_split(f, c, sn, hi, lo);
-}
 
 // ---- cross-lane -----------------------------------------------------------
 template <int CTRL>

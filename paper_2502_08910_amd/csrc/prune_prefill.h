@@ -38,18 +38,24 @@ constexpr int kPrefillMaxIters = 4;     // chunk groups (of 32 chunks) per workg
 // side's rounded values are added on the matrix cores as well, so that a score agrees with the
 // product of the fp32 rotations to about 2^-16 relative and a selection is decided as an fp32
 // evaluation decides it.  Relative style: both rotated query sets have a rest (the keys are not
-// rotated: exact), twice the matrix work again.  Chunk-indexed style: queries and keys have one
-// (q_hi.k_hi + q_lo.k_hi + q_hi.k_lo; the rests' own product is below fp32 rounding), three times the
-// plain kernel's matrix work; the rests of a key tile live in a second LDS tile.
+// rotated: exact), twice the matrix work again.  Chunk-indexed style: the keys have one (q.k_hi + q.k_lo),
+// twice the plain kernel's matrix work; the rests of a key tile live in a second LDS tile.
 //
 // ROPE == 2: chunk-indexed style.  Every key of chunk j (index in the stage's chunk list) sits at
-// j, query t of the block at min(its own position, n_chunk - 1 + n_stream).  The queries differ in
-// position, so nothing folds: the query operands are rotated once (each row to its own position)
-// and every candidate row is rotated to its chunk's index after it has landed in LDS, each lane
-// turning in place the 16 bytes it fetched itself (tile row 4r + kq is candidate column 4(r%4) + kq
-// of tile r/4, whose chunk and therefore table row are the same at every level of a search: the 8
-// table pieces of a lane are fetched once per chunk group).  Same carried-score search and matrix
-// work as the plain kernel, plus 8 rotations and LDS round trips per level.
+// j, query t of the block at min(its own position, cap) with cap = n_chunk - 1 + n_stream.  With a table of true
+// rotations only differences of positions matter, so everything is turned back by cap: the keys of
+// chunk j by cap - j, a query by cap - its position, which is nothing at all for a block whose first
+// query is at or behind the cap -- every block but those of ranges that hold fewer keys than a block has queries.
+// Such queries stay the exact bf16 values they are: no second operand for them, a third of the matrix
+// work less than with rotated queries, and 64 registers less, which makes room for two waves per SIMD.
+// (Blocks before the cap turn their query operands where they are used, value and rest.)
+// A candidate row is turned on its way from global memory to LDS, each lane the 16 bytes it fetched
+// (tile row 4r + kq is candidate column 4(r%4) + kq of tile r/4, whose chunk and therefore table row
+// are the same at every level of a search: the 8 table pieces of a lane are fetched once per chunk
+// group); the value goes to the tile, the rest to a second tile.  Same carried-score search as the plain kernel.
+// What bounds it: the rotations' vector instructions (48 for 8 values), then the matrix work.  4,096 queries on 128K
+// keys, chunks of 64, 32 heads: 2267 us with rotated queries and keys (three products, one wave per SIMD, rows turned
+// in LDS), 1312 us this way.
 __device__ inline void rotate_operand_split(const bf16x8 x, const float *cos4, const float *sin4, bf16x8 &hi,
                                             bf16x8 &lo)
 {
@@ -59,6 +65,48 @@ __device__ inline void rotate_operand_split(const bf16x8 x, const float *cos4, c
     hi = __builtin_bit_cast(bf16x8, h);
     lo = __builtin_bit_cast(bf16x8, l);
 }
+
+// The inverse rotation (sin negated), kept to twice the mantissa like rotate_f32x8_split; the sums are fused
+// multiply-adds here (the kernel's time is its vector instructions).
+__device__ inline void turn_back_f32x8_split(const float (&f)[8], const float4 c, const float4 sn, uint4 &hi, uint4 &lo)
+{
+    const float cc[4] = {c.x, c.y, c.z, c.w}, ss[4] = {sn.x, sn.y, sn.z, sn.w};
+    uint32_t wh[4], wl[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float e = f[2 * i], o = f[2 * i + 1];
+        const float re = __fmaf_rn(e, cc[i], __fmul_rn(o, ss[i]));
+        const float ro = __fmaf_rn(o, cc[i], -__fmul_rn(e, ss[i]));
+        wh[i] = pack_bf16x2(re, ro);
+        wl[i] = pack_bf16x2(__fsub_rn(re, __uint_as_float(wh[i] << 16)),
+                            __fsub_rn(ro, __uint_as_float(wh[i] & 0xffff0000u)));
+    }
+    hi = make_uint4(wh[0], wh[1], wh[2], wh[3]);
+    lo = make_uint4(wl[0], wl[1], wl[2], wl[3]);
+}
+__device__ inline void turn_back_split(const uint4 x, const float4 c, const float4 sn, uint4 &hi, uint4 &lo)
+{
+    float f[8];
+    unpack_bf16x8(x, f);
+    turn_back_f32x8_split(f, c, sn, hi, lo);
+}
+__device__ inline void turn_back_split(const uint2 x, const float4 c, const float4 sn, uint4 &hi, uint4 &lo)
+{
+    float f[8];
+    unpack8_fp8(x, f);
+    turn_back_f32x8_split(f, c, sn, hi, lo);
+}
+__device__ inline void turn_back_operand_split(const bf16x8 x, const float *cos4, const float *sin4, bf16x8 &hi,
+                                               bf16x8 &lo)
+{
+    uint4 h, l;
+    turn_back_split(__builtin_bit_cast(uint4, x), *reinterpret_cast<const float4 *>(cos4),
+                    *reinterpret_cast<const float4 *>(sin4), h, l);
+    hi = __builtin_bit_cast(bf16x8, h);
+    lo = __builtin_bit_cast(bf16x8, l);
+}
+__device__ inline uint4 as_bf16x8(const uint2 &k) { return fp8x8_to_bf16x8(k); }
+__device__ inline uint4 as_bf16x8(const uint4 &k) { return k; }
 
 // PAGED: K is a page pool read through the sequence's row of the block table: the lane that owns a
 // candidate looks its page up and forms the row's element offset (64-bit) before the offsets are
@@ -82,7 +130,7 @@ __device__ inline void rotate_operand_split(const bf16x8 x, const float *cos4, c
 // other's maxima once the other's counter has reached the same turn.  Both write before they wait
 // and both are resident (one workgroup), so the wait ends; it is bounded all the same.
 template <int MT, int NT, int G, bool WIDE, int ROPE, bool PAGED, int PARTS = 1, bool KV8 = false, int QS = 1>
-__global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE && MT == 4) ? 1 : (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS == 1) ? 4 : 3) void prune_prefill_kernel(const PruneArgs a, const int iters,
+__global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE == 1 && MT == 4) ? 1 : (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS == 1) ? 4 : 3) void prune_prefill_kernel(const PruneArgs a, const int iters,
                                                                             const RopeView rope)
 {
     static_assert(NT == 2, "the shared first phase assumes two 16-chunk tiles per wave");
@@ -116,6 +164,8 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE && MT == 4) ? 1 : 
     // passes, one after the other, by the same waves
     constexpr int parts = PARTS;
     int h = pr.g * (G * PARTS) + hh;
+    using raw_t = typename std::conditional<KV8, uint2, uint4>::type;         // a lane's 8 elements of a row as fetched
+    constexpr bool kViaRegs = KV8 || ROPE == 2;      // rows are worked on between global memory and LDS
     using off_t = typename std::conditional<WIDE, int64_t, uint32_t>::type;   // element offset of a row
     const off_t k_st = (off_t)a.k_st;
 
@@ -170,15 +220,15 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE && MT == 4) ? 1 : 
                      : "s"(dst), "v"(src)
                      : "memory");
     };
-    // E4M3 keys: this lane's 8 bytes of row `row` (or of the row at element offset `at`), and their
-    // place in a four-row group of a tile
-    auto fetch8 = [&](const uint16_t *base, off_t stride, int row, int swz) {
+    // Keys that go through registers (E4M3, chunk-indexed RoPE): this lane's 8 elements of row `row` (or of the
+    // row at element offset `at`), and their place in a four-row group of a tile
+    auto fetch = [&](const uint16_t *base, off_t stride, int row, int swz) {
         const off_t r = (off_t)max(row, 0);
         const off_t at = WIDE ? r * stride : (off_t)__umul24((uint32_t)r, (uint32_t)stride);
-        return *reinterpret_cast<const uint2 *>(base + at + ((n ^ swz) << 2));
+        return *reinterpret_cast<const raw_t *>(base + at + (n ^ swz) * (int)(sizeof(raw_t) / 2));
     };
-    auto fetch8_at = [&](const uint16_t *base, int64_t at, int swz) {
-        return *reinterpret_cast<const uint2 *>(base + at + ((n ^ swz) << 2));
+    auto fetch_at = [&](const uint16_t *base, int64_t at, int swz) {
+        return *reinterpret_cast<const raw_t *>(base + at + (n ^ swz) * (int)(sizeof(raw_t) / 2));
     };
     auto put16 = [&](uint16_t *four_rows, const uint4 piece) {
         *reinterpret_cast<uint4 *>(four_rows + kq * kD + n * 8) = piece;
@@ -199,12 +249,14 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE && MT == 4) ? 1 : 
     for (int r = 0; r < NT * 4; ++r) dst_own[r] = lds_addr(tile + r * 4 * kD);
     bf16x8 qa[MTW][4];                               // relative RoPE: q_L
     bf16x8 qaR[ROPE == 1 ? MTW : 1][4];              // relative RoPE: q_R
-    bf16x8 qaLo[ROPE ? MTW : 1][4];                  // RoPE: what rounding the rotated queries to bf16 dropped
+    bf16x8 qaLo[ROPE == 1 ? MTW : 1][4];             // relative RoPE: what rounding the rotated queries to bf16 dropped
     bf16x8 qaRLo[ROPE == 1 ? MTW : 1][4];
     int q_cap = 0;                                   // chunk-indexed RoPE: the largest query position
+    bool q_capped = true;                            // ... and whether every query of the block sits there
     if constexpr (ROPE == 2) {
         __shared__ int sh_n_chunk;
         q_cap = stage_n_chunk(a, pr, p, 64 * NWV, &sh_n_chunk) - 1 + a.ge.n_stream;
+        q_capped = pr.E - a.ge.b_q >= q_cap;
     }
     auto stage_queries = [&]() {
         const uint16_t *qb = a.q + pr.b * a.q_sb + (int64_t)h * a.q_sh + (int64_t)(pr.m * a.ge.b_q) * a.q_st;
@@ -220,11 +272,6 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE && MT == 4) ? 1 : 
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks) {
                     qa[mt][ks] = operand(tile, (mt - m0) * 16, ks);
-                    if constexpr (ROPE == 2) {
-                        const int qpos = min(pr.E - a.ge.b_q + qrow0 + mt * 16 + n, q_cap);
-                        const int64_t at = (int64_t)qpos * (kD / 2) + ((ks << 2) + kq) * 4;
-                        rotate_operand_split(qa[mt][ks], rope.cos + at, rope.sin + at, qa[mt][ks], qaLo[mt][ks]);
-                    }
                     if constexpr (ROPE == 1) {
                         const int pair = ((ks << 2) + kq) * 4;       // first of this operand's 4 dim pairs
                         const int64_t posR = (int64_t)a.ge.n_stream * (kD / 2) + pair, posL = posR + kD / 2;
@@ -249,9 +296,49 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE && MT == 4) ? 1 : 
         return (int64_t)table[r >> a.paged.page_log2] * a.k_sb + (int64_t)(r & page_mask) * a.k_st;
     };
 
+    // Chunk-indexed RoPE, blocks with queries before the cap: the queries are read again, turned back to the cap (value
+    // and rest) and used at once, with nothing kept in registers.
+    auto scores_before_cap = [&](const uint16_t *src, float (&sig)[NT]) {
+        const uint16_t *qb = a.q + pr.b * a.q_sb + (int64_t)h * a.q_sh + (int64_t)(pr.m * a.ge.b_q) * a.q_st;
+        float best[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) best[t] = -INFINITY;
+#pragma unroll 1
+        for (int mt = 0; mt < MTW; ++mt) {
+            const int row = qrow0 + mt * 16 + n;
+            const int64_t back = (int64_t)max(q_cap - (pr.E - a.ge.b_q + row), 0) * (kD / 2);
+            f32x4 c[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) c[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int ks = 0; ks < 4; ++ks) {
+                const int piece = (ks << 2) + kq;
+                const bf16x8 q = *reinterpret_cast<const bf16x8 *>(qb + (int64_t)row * a.q_st + piece * 8);
+                bf16x8 hi, lo;
+                turn_back_operand_split(q, rope.cos + back + piece * 4, rope.sin + back + piece * 4, hi, lo);
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    const bf16x8 k = operand(src, t * 16, ks), k_rest = operand(src + kLo, t * 16, ks);
+                    c[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, k, c[t], 0, 0, 0);
+                    c[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, k_rest, c[t], 0, 0, 0);
+                    c[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, k, c[t], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < NT; ++t) best[t] = fmaxf(best[t], fmaxf(fmaxf(c[t][0], c[t][1]), fmaxf(c[t][2], c[t][3])));
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) sig[t] = max_over_rows(best[t]);
+    };
     // scores of the 32 rows of a tile (column n of 16-row tile t): max over the block's queries
     // (ROPE: sig against q_L, sigR against q_R)
     auto mfma_scores = [&](const uint16_t *src, float (&sig)[NT], float (&sigR)[NT]) {
+        if constexpr (ROPE == 2) {
+            if (!q_capped) {
+                scores_before_cap(src, sig);
+                return;
+            }
+        }
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             bf16x8 kr[4], krLo[ROPE == 2 ? 4 : 1];
@@ -264,7 +351,7 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE && MT == 4) ? 1 : 
 #pragma unroll
             for (int mt = 0; mt < MTW; ++mt) {
                 f32x4 c = {0.f, 0.f, 0.f, 0.f};
-                if constexpr (ROPE != 0) {           // the small terms first
+                if constexpr (ROPE == 1) {           // the small terms first
 #pragma unroll
                     for (int ks = 0; ks < 4; ++ks)
                         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qaLo[mt][ks], kr[ks], c, 0, 0, 0);
@@ -290,6 +377,7 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE && MT == 4) ? 1 : 
                 }
             }
             sig[t] = max_over_rows(best);
+            if constexpr (ROPE == 2) __builtin_amdgcn_sched_barrier(0);          // one tile's operands at a time
             if constexpr (ROPE == 1) {
                 sigR[t] = max_over_rows(bestR);
             }
@@ -321,53 +409,44 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE && MT == 4) ? 1 : 
             }
         }
     };
-    // chunk-indexed RoPE: table pieces of this lane's 8 rows of a tile (set per chunk group below) and
-    // the in-place rotation of the 16 bytes this lane fetched with load instruction r of a tile
+    // chunk-indexed RoPE: table pieces of this lane's 8 rows of a tile (set per chunk group below)
     float4 tb_cos[ROPE == 2 ? NT * 4 : 1], tb_sin[ROPE == 2 ? NT * 4 : 1];
-    auto rotate_piece = [&](uint16_t *four_rows, const float4 c, const float4 sn) {
-        uint4 *piece = reinterpret_cast<uint4 *>(four_rows + kq * kD + n * 8);
-        uint4 hi, lo;
-        rotate_bf16x8_split(*piece, c, sn, hi, lo);
-        *piece = hi;
-        *reinterpret_cast<uint4 *>(four_rows + kLo + kq * kD + n * 8) = lo;
-    };
-    auto rotate_own = [&](uint16_t *four_rows, int r) {      // r: compile-time after unrolling
-        rotate_piece(four_rows, tb_cos[ROPE == 2 ? r : 0], tb_sin[ROPE == 2 ? r : 0]);
-    };
-    // table piece of this lane for load instruction r of the chunk group at jt
+    // table piece of this lane for load instruction r of the chunk group at jt: chunk j's keys are
+    // turned back by q_cap - j
     auto table_at = [&](int jt, int r) {
-        const int j = min(jt + (r >> 2) * 16 + (r & 3) * 4 + kq, a.max_chunks - 1);
-        return (int64_t)j * (kD / 2) + ((n ^ ((r & 3) * 4 + kq)) << 2);
+        const int j = jt + (r >> 2) * 16 + (r & 3) * 4 + kq;
+        return (int64_t)max(q_cap - j, 0) * (kD / 2) + ((n ^ ((r & 3) * 4 + kq)) << 2);
     };
     // score of candidate rows pos[t] of this wave's own searches.  The scores of columns whose
     // search has ended are ignored by the caller.
     auto score = [&](const int (&pos)[NT], const bool (&ok)[NT], float (&sig)[NT], float (&sigR)[NT]) {
-        if constexpr (KV8) {
-            uint2 raw[NT * 4];
+        if constexpr (kViaRegs) {
+            raw_t raw[NT * 4];
             if constexpr (PAGED) {
                 int64_t at[NT];
 #pragma unroll
                 for (int t = 0; t < NT; ++t) at[t] = paged_at(ok[t] ? pos[t] : -1);
 #pragma unroll
                 for (int r = 0; r < NT * 4; ++r)
-                    raw[r] = fetch8_at(kb, __shfl(at[r >> 2], (r & 3) * 4 + kq, 64), (r & 3) * 4 + kq);
+                    raw[r] = fetch_at(kb, __shfl(at[r >> 2], (r & 3) * 4 + kq, 64), (r & 3) * 4 + kq);
             } else {
 #pragma unroll
                 for (int r = 0; r < NT * 4; ++r)
-                    raw[r] = fetch8(kb, k_st, __shfl(ok[r >> 2] ? pos[r >> 2] : -1, (r & 3) * 4 + kq, 64),
-                                    (r & 3) * 4 + kq);
+                    raw[r] = fetch(kb, k_st, __shfl(ok[r >> 2] ? pos[r >> 2] : -1, (r & 3) * 4 + kq, 64),
+                                   (r & 3) * 4 + kq);
             }
 #pragma unroll
             for (int r = 0; r < NT * 4; ++r) {
                 uint4 piece;
                 if constexpr (ROPE == 2) {
                     uint4 rest;
-                    rotate_fp8x8_split(raw[r], tb_cos[r], tb_sin[r], piece, rest);
+                    turn_back_split(raw[r], tb_cos[r], tb_sin[r], piece, rest);
                     put16(tile + kLo + r * 4 * kD, rest);
                 } else {
-                    piece = fp8x8_to_bf16x8(raw[r]);
+                    piece = as_bf16x8(raw[r]);
                 }
                 put16(tile + r * 4 * kD, piece);
+                if constexpr (ROPE == 2) __builtin_amdgcn_sched_barrier(0);      // one piece after the other: registers
             }
             // the wave reads back what its other lanes stored: LDS serves a wave's requests in order
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -394,10 +473,6 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE && MT == 4) ? 1 : 
         }
         // the loads count on vmcnt; the wave reads its own tile, so no barrier is needed
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if constexpr (ROPE == 2) {
-#pragma unroll
-            for (int r = 0; r < NT * 4; ++r) rotate_own(tile + r * 4 * kD, r);
-        }
         mfma_scores(tile, sig, sigR);
         pair_max(sig, sigR);
     };
@@ -429,14 +504,16 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE && MT == 4) ? 1 : 
             off[t] = 0;
             pos[t] = start[t];
         }
-        if constexpr (ROPE == 2) {
+        auto load_table = [&]() {
+            if constexpr (ROPE == 2) {
 #pragma unroll
-            for (int r = 0; r < NT * 4; ++r) {
-                const int64_t at = table_at(jt, r);
-                tb_cos[r] = *reinterpret_cast<const float4 *>(rope.cos + at);
-                tb_sin[r] = *reinterpret_cast<const float4 *>(rope.sin + at);
+                for (int r = 0; r < NT * 4; ++r) {
+                    const int64_t at = table_at(jt, r);
+                    tb_cos[r] = *reinterpret_cast<const float4 *>(rope.cos + at);
+                    tb_sin[r] = *reinterpret_cast<const float4 *>(rope.sin + at);
+                }
             }
-        }
+        };
         int half = a.chunk >> 1;
         if (kShare) {
             // The first key of a chunk and of its right half are the same rows for every head of
@@ -455,13 +532,13 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE && MT == 4) ? 1 : 
                 if constexpr (PAGED) cand_at[i] = __shfl(paged_at(c), (r & 3) * 4 + kq, 64);
                 else cand[i] = __shfl(max(c, 0), (r & 3) * 4 + kq, 64);
             }
-            if constexpr (KV8) {
-                uint2 raw[kPerWave];
+            if constexpr (kViaRegs) {
+                raw_t raw[kPerWave];
 #pragma unroll
                 for (int i = 0; i < kPerWave; ++i) {
                     const int r = (wv * kPerWave + i) & 7;
-                    if constexpr (PAGED) raw[i] = fetch8_at(kb, cand_at[i], (r & 3) * 4 + kq);
-                    else raw[i] = fetch8(kb, k_st, cand[i], (r & 3) * 4 + kq);
+                    if constexpr (PAGED) raw[i] = fetch_at(kb, cand_at[i], (r & 3) * 4 + kq);
+                    else raw[i] = fetch(kb, k_st, cand[i], (r & 3) * 4 + kq);
                 }
 #pragma unroll
                 for (int i = 0; i < kPerWave; ++i) {
@@ -470,13 +547,14 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE && MT == 4) ? 1 : 
                     if constexpr (ROPE == 2) {
                         const int64_t at = table_at(jt, ld & 7);
                         uint4 rest;
-                        rotate_fp8x8_split(raw[i], *reinterpret_cast<const float4 *>(rope.cos + at),
-                                           *reinterpret_cast<const float4 *>(rope.sin + at), piece, rest);
+                        turn_back_split(raw[i], *reinterpret_cast<const float4 *>(rope.cos + at),
+                                        *reinterpret_cast<const float4 *>(rope.sin + at), piece, rest);
                         put16(&sh_rows[kLo + ld * 4 * kD], rest);
                     } else {
-                        piece = fp8x8_to_bf16x8(raw[i]);
+                        piece = as_bf16x8(raw[i]);
                     }
                     put16(&sh_rows[ld * 4 * kD], piece);
+                    if constexpr (ROPE == 2) __builtin_amdgcn_sched_barrier(0);
                 }
             } else {
 #pragma unroll
@@ -487,18 +565,8 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE && MT == 4) ? 1 : 
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }
-            if constexpr (ROPE == 2 && !KV8) {
-#pragma unroll
-                for (int i = 0; i < kPerWave; ++i) {
-                    // which of the 16 loads this is depends on the wave: the piece is fetched again
-                    // rather than picked from the register array with a run-time index
-                    const int ld = wv * kPerWave + i;
-                    const int64_t at = table_at(jt, ld & 7);
-                    rotate_piece(&sh_rows[ld * 4 * kD], *reinterpret_cast<const float4 *>(rope.cos + at),
-                                 *reinterpret_cast<const float4 *>(rope.sin + at));
-                }
-            }
             __syncthreads();
+            load_table();                            // for the waves' own searches; there when the tiles below are scored
             float l0r[NT];
             mfma_scores(&sh_rows[0], sigma, l0r);
             pair_max(sigma, l0r);
@@ -517,6 +585,7 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE && MT == 4) ? 1 : 
             half >>= 1;
             __syncthreads();                         // tiles 0 and 1 go back to their waves
         } else {
+            load_table();
             score(pos, valid, sigma, sR);
             if constexpr (ROPE == 1) {
 #pragma unroll
