@@ -31,7 +31,8 @@ constexpr int kPrefillMaxIters = 4;     // chunk groups (of 32 chunks) per workg
 // rotations the key rotations fold into the queries: two rotated copies of the query operands,
 // q_L = R(n_stream+1) q and q_R = R(n_stream) q (rounded to bf16 for the matrix cores), and every
 // candidate row is scored against both, because a key that wins as the right branch is the left
-// branch of the next iteration.  Twice the matrix work and twice the query registers.
+// branch of the next iteration.  Twice the matrix work and twice the query registers: blocks of 16 and
+// 32 queries (64-query blocks: prune_relative.h).
 //
 // Precision of the rotated operands: a rotated vector is kept as two bf16 operands, its rounded
 // value and the rounded rest (rotate_bf16x8_split), and the products of the rests with the other
@@ -56,14 +57,17 @@ constexpr int kPrefillMaxIters = 4;     // chunk groups (of 32 chunks) per workg
 // What bounds it: the rotations' vector instructions (48 for 8 values), then the matrix work.  4,096 queries on 128K
 // keys, chunks of 64, 32 heads: 2267 us with rotated queries and keys (three products, one wave per SIMD, rows turned
 // in LDS), 1312 us this way.
+__device__ inline void rotate_operand_split(const bf16x8 x, const float4 c, const float4 sn, bf16x8 &hi, bf16x8 &lo)
+{
+    uint4 h, l;
+    rotate_bf16x8_split(__builtin_bit_cast(uint4, x), c, sn, h, l);
+    hi = __builtin_bit_cast(bf16x8, h);
+    lo = __builtin_bit_cast(bf16x8, l);
+}
 __device__ inline void rotate_operand_split(const bf16x8 x, const float *cos4, const float *sin4, bf16x8 &hi,
                                             bf16x8 &lo)
 {
-    uint4 h, l;
-    rotate_bf16x8_split(__builtin_bit_cast(uint4, x), *reinterpret_cast<const float4 *>(cos4),
-                        *reinterpret_cast<const float4 *>(sin4), h, l);
-    hi = __builtin_bit_cast(bf16x8, h);
-    lo = __builtin_bit_cast(bf16x8, l);
+    rotate_operand_split(x, *reinterpret_cast<const float4 *>(cos4), *reinterpret_cast<const float4 *>(sin4), hi, lo);
 }
 
 // The inverse rotation (sin negated), kept to twice the mantissa like rotate_f32x8_split; the sums are fused
@@ -118,34 +122,19 @@ __device__ inline uint4 as_bf16x8(const uint4 &k) { return k; }
 // trip through LDS); everything after that is the bf16 kernel.  The chunk score is multiplied by the
 // tensor's scale at the end.  K strides count 2-byte units.
 //
-// QS = 2: two waves per query head, each with half of the block's queries (relative-style RoPE with
-// 64-query blocks, whose four rotated operand sets of 64 queries leave room for one wave per SIMD
-// only; two waves of 32 queries fit a SIMD together).  The two walk the same searches on their own
-// copies of the candidate rows and exchange their maxima over the queries through LDS after every
-// scoring step, so that both take the same decisions.  The exchange is a handshake of the two
-// waves, not a workgroup barrier: a barrier per search level puts all waves of the workgroup in
-// step -- all wait for rows at once, then all multiply at once -- and the second wave per SIMD buys
-// nothing (3.86 ms on the first stage of cfg4 against 3.81 ms with one wave per SIMD).  Each wave
-// writes its maxima, then a turn counter (LDS keeps a wave's requests in order), and reads the
-// other's maxima once the other's counter has reached the same turn.  Both write before they wait
-// and both are resident (one workgroup), so the wait ends; it is bounded all the same.
-template <int MT, int NT, int G, bool WIDE, int ROPE, bool PAGED, int PARTS = 1, bool KV8 = false, int QS = 1>
-__global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE == 1 && MT == 4) ? 1 : (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS == 1) ? 4 : 3) void prune_prefill_kernel(const PruneArgs a, const int iters,
+template <int MT, int NT, int G, bool WIDE, int ROPE, bool PAGED, int PARTS = 1, bool KV8 = false>
+__global__ __launch_bounds__(64 * G, (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS == 1) ? 4 : 3) void prune_prefill_kernel(const PruneArgs a, const int iters,
                                                                             const RopeView rope)
 {
     static_assert(NT == 2, "the shared first phase assumes two 16-chunk tiles per wave");
     static_assert(!PAGED || WIDE, "paged pools are addressed with 64-bit offsets");
-    static_assert(QS == 1 || (QS == 2 && MT % 2 == 0), "one or two waves per head");
-    constexpr int NWV = G * QS;                      // waves of the workgroup
-    constexpr int MTW = MT / QS;                     // 16-query tiles of a wave
+    static_assert(ROPE != 1 || MT <= 2, "64-query blocks with the relative style have a kernel of their own");
+    constexpr int NWV = G;                           // waves of the workgroup
+    constexpr int MTW = MT;                          // 16-query tiles of a wave
     constexpr int kTile = NT * 16 * kD;              // one tile: 32 rows of 256 bytes, no padding
     constexpr bool kShare = NWV >= 2;                // two tiles are needed for the shared phase
     __shared__ float sh_sigma[2][G][NT * 16];       // two buffers: a chunk group writes while the last one is still read
     __shared__ float sh_best[kPrefillMaxIters][NT * 16];      // chunk scores over the head parts done so far
-    // QS == 2: a wave's maxima over its queries, for the other wave of its head (two buffers: a wave
-    // may write its next values while the other still reads the last ones)
-    __shared__ float sh_pair[QS == 2 ? 2 : 1][QS == 2 ? NWV : 1][2 * NT][16];
-    __shared__ uint32_t sh_pair_turn[QS == 2 ? NWV : 1];      // exchanges a wave has written so far
     constexpr int kLo = ROPE == 2 ? NWV * kTile : 0;  // ROPE == 2: from a tile to the tile of its rests
     __shared__ __attribute__((aligned(16))) uint16_t sh_rows[(ROPE == 2 ? 2 * NWV : NWV) * kTile];
     // Workgroups are dealt to the 8 XCDs round-robin by linear id; let the KV head be the fastest
@@ -155,15 +144,12 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE == 1 && MT == 4) ?
                   (blockIdx.x / a.ge.Hkv) % a.ge.Mq;
     const Problem pr = problem_of(a.ge, p);
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int hh = wv / QS, qs = wv % QS;             // the wave's query head of the group, and its share of the queries
-    const int qrow0 = qs * MTW * 16;                  // first query row of the block that is this wave's
-    if (QS == 2 && lane == 0) sh_pair_turn[wv] = 0;   // a workgroup barrier follows before the first exchange
     const int n = lane & 15, kq = lane >> 4;
     // G is the number of heads (waves) a pass works on; a group of G*PARTS heads (8, where 8 waves
     // of this many registers would leave room for one workgroup per CU only) is done in PARTS
     // passes, one after the other, by the same waves
     constexpr int parts = PARTS;
-    int h = pr.g * (G * PARTS) + hh;
+    int h = pr.g * (G * PARTS) + wv;
     using raw_t = typename std::conditional<KV8, uint2, uint4>::type;         // a lane's 8 elements of a row as fetched
     constexpr bool kViaRegs = KV8 || ROPE == 2;      // rows are worked on between global memory and LDS
     using off_t = typename std::conditional<WIDE, int64_t, uint32_t>::type;   // element offset of a row
@@ -265,7 +251,7 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE == 1 && MT == 4) ?
             constexpr int kRows = MTW >= 2 ? 32 : 16;
 #pragma unroll
             for (int r = 0; r < kRows / 4; ++r)
-                load4(qb, (off_t)a.q_st, dst_own[r], qrow0 + m0 * 16 + r * 4 + kq, (r & 3) * 4 + kq);
+                load4(qb, (off_t)a.q_st, dst_own[r], m0 * 16 + r * 4 + kq, (r & 3) * 4 + kq);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
             for (int mt = m0; mt < m0 + 2 && mt < MTW; ++mt)
@@ -305,7 +291,7 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE == 1 && MT == 4) ?
         for (int t = 0; t < NT; ++t) best[t] = -INFINITY;
 #pragma unroll 1
         for (int mt = 0; mt < MTW; ++mt) {
-            const int row = qrow0 + mt * 16 + n;
+            const int row = mt * 16 + n;
             const int64_t back = (int64_t)max(q_cap - (pr.E - a.ge.b_q + row), 0) * (kD / 2);
             f32x4 c[NT];
 #pragma unroll
@@ -383,32 +369,6 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE == 1 && MT == 4) ?
             }
         }
     };
-    // QS == 2: the maxima of mfma_scores over all the block's queries, from the two waves of a head
-    uint32_t pair_turn = 0;
-    auto pair_max = [&](float (&sig)[NT], float (&sigR)[NT]) {
-        if constexpr (QS == 2) {
-            float (*mine)[16] = sh_pair[pair_turn & 1][wv];
-            const float (*theirs)[16] = sh_pair[pair_turn & 1][wv ^ 1];
-            if (kq == 0) {
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    mine[t][n] = sig[t];
-                    if constexpr (ROPE == 1) mine[NT + t][n] = sigR[t];
-                }
-            }
-            ++pair_turn;
-            if (lane == 0) __hip_atomic_store(&sh_pair_turn[wv], pair_turn, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            int budget = 1 << 18;             // a wait is a few dozen turns of this loop; the bound is ~10 ms
-            while ((int32_t)(__hip_atomic_load(&sh_pair_turn[wv ^ 1], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) -
-                             pair_turn) < 0 && --budget > 0)
-                __builtin_amdgcn_s_sleep(1);
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                sig[t] = fmaxf(sig[t], theirs[t][n]);
-                if constexpr (ROPE == 1) sigR[t] = fmaxf(sigR[t], theirs[NT + t][n]);
-            }
-        }
-    };
     // chunk-indexed RoPE: table pieces of this lane's 8 rows of a tile (set per chunk group below)
     float4 tb_cos[ROPE == 2 ? NT * 4 : 1], tb_sin[ROPE == 2 ? NT * 4 : 1];
     // table piece of this lane for load instruction r of the chunk group at jt: chunk j's keys are
@@ -451,7 +411,6 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE == 1 && MT == 4) ?
             // the wave reads back what its other lanes stored: LDS serves a wave's requests in order
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             mfma_scores(tile, sig, sigR);
-            pair_max(sig, sigR);
             return;
         }
         if constexpr (PAGED) {
@@ -474,7 +433,6 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE == 1 && MT == 4) ?
         // the loads count on vmcnt; the wave reads its own tile, so no barrier is needed
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         mfma_scores(tile, sig, sigR);
-        pair_max(sig, sigR);
     };
 
     // destinations of this wave's share of the loads of the shared first phase
@@ -483,7 +441,7 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE == 1 && MT == 4) ?
     for (int i = 0; i < (kShare ? 16 / NWV : 1); ++i) dst_shared[i] = lds_addr(&sh_rows[(wv * (16 / NWV) + i) % (NWV * 8) * 4 * kD]);
     for (int part = 0; part < parts; ++part) {
     if constexpr (PARTS > 1) {
-        h = pr.g * (G * PARTS) + part * G + hh;
+        h = pr.g * (G * PARTS) + part * G + wv;
         stage_queries();
         if (kShare) __syncthreads();                 // other waves' tiles are written below
     }
@@ -569,9 +527,7 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE == 1 && MT == 4) ?
             load_table();                            // for the waves' own searches; there when the tiles below are scored
             float l0r[NT];
             mfma_scores(&sh_rows[0], sigma, l0r);
-            pair_max(sigma, l0r);
             mfma_scores(&sh_rows[kTile], s, sR);
-            pair_max(s, sR);
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const bool has_right = half >= 1 && half < len[t];
@@ -610,8 +566,8 @@ __global__ __launch_bounds__(64 * G * QS, QS == 2 ? 2 : (ROPE == 1 && MT == 4) ?
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const int j = jt + t * 16 + n;
-            if (kq == 0) sh_sigma[it & 1][hh][t * 16 + n] = sigma[t];
-            if (a.out_rep != nullptr && kq == 0 && qs == 0 && j < a.max_chunks) {
+            if (kq == 0) sh_sigma[it & 1][wv][t * 16 + n] = sigma[t];
+            if (a.out_rep != nullptr && kq == 0 && j < a.max_chunks) {
                 const int64_t row = ((int64_t)(pr.b * a.ge.Hq + h) * a.ge.Mq + pr.m);
                 a.out_rep[row * a.max_chunks + j] = valid[t] ? start[t] + off[t] : -1;
             }
@@ -649,18 +605,16 @@ static void launch_prefill_w(const PruneArgs &a, int P, const RopeView &rope, hi
     const int per_wg = NT * 16 * iters;
     dim3 grid(P, (a.max_chunks + per_wg - 1) / per_wg);
     KernelTimer timer(stage_name(kNamePrunePrefill, a.parent_starts == nullptr, a.chunk), st);
-    // relative-style RoPE on 64-query blocks: two waves per head, 32 queries each
-    constexpr int QS = (ROPE == 1 && MT == 4) ? 2 : 1;
     switch (a.ge.G) {
-    case 1: hipLaunchKernelGGL((prune_prefill_kernel<MT, NT, 1, WIDE, ROPE, PAGED, 1, KV8, QS>), grid, dim3(64 * QS), 0, st, a, iters, rope); break;
-    case 2: hipLaunchKernelGGL((prune_prefill_kernel<MT, NT, 2, WIDE, ROPE, PAGED, 1, KV8, QS>), grid, dim3(128 * QS), 0, st, a, iters, rope); break;
-    case 4: hipLaunchKernelGGL((prune_prefill_kernel<MT, NT, 4, WIDE, ROPE, PAGED, 1, KV8, QS>), grid, dim3(256 * QS), 0, st, a, iters, rope); break;
+    case 1: hipLaunchKernelGGL((prune_prefill_kernel<MT, NT, 1, WIDE, ROPE, PAGED, 1, KV8>), grid, dim3(64), 0, st, a, iters, rope); break;
+    case 2: hipLaunchKernelGGL((prune_prefill_kernel<MT, NT, 2, WIDE, ROPE, PAGED, 1, KV8>), grid, dim3(128), 0, st, a, iters, rope); break;
+    case 4: hipLaunchKernelGGL((prune_prefill_kernel<MT, NT, 4, WIDE, ROPE, PAGED, 1, KV8>), grid, dim3(256), 0, st, a, iters, rope); break;
     default:
         // 8 heads with 64-query blocks: 8 waves of ~160 registers fit a CU once only, two passes of 4
         // waves fit three times; with RoPE the query operands alone take more registers than 8 waves
         // leave each other
         if constexpr (MT == 4)
-            hipLaunchKernelGGL((prune_prefill_kernel<MT, NT, 4, WIDE, ROPE, PAGED, 2, KV8, QS>), grid, dim3(256 * QS), 0, st, a, iters, rope);
+            hipLaunchKernelGGL((prune_prefill_kernel<MT, NT, 4, WIDE, ROPE, PAGED, 2, KV8>), grid, dim3(256), 0, st, a, iters, rope);
         else
             hipLaunchKernelGGL((prune_prefill_kernel<MT, NT, 8, WIDE, ROPE, PAGED, 1, KV8>), grid, dim3(512), 0, st, a, iters, rope);
         break;

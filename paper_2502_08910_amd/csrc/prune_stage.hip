@@ -8,7 +8,7 @@
 // of a chunk are common to the heads, the rest are G independent loads in
 // flight).  U slots per group are interleaved to put more loads in flight.
 #include "prune_args.h"
-#include "prune_prefill.h"
+#include "prune_relative.h"
 #include <type_traits>
 
 namespace ihip {
@@ -176,14 +176,14 @@ static void launch_prefill(const PruneArgs &a, int P, int64_t max_seq_len, const
     const RopeView none{nullptr, nullptr, 0};
     if (a.paged.block_table) {
         if (rope && style == 2) launch_prefill_w<MT, true, 2, true>(a, P, *rope, st);
-        else if (rope) launch_prefill_w<MT, true, 1, true>(a, P, *rope, st);
+        else if (rope) launch_relative_w<MT, true, true>(a, P, *rope, st);
         else launch_prefill_w<MT, true, 0, true>(a, P, none, st);
     } else if (rope && style == 2) {
         if (wide) launch_prefill_w<MT, true, 2, false>(a, P, *rope, st);
         else launch_prefill_w<MT, false, 2, false>(a, P, *rope, st);
     } else if (rope) {
-        if (wide) launch_prefill_w<MT, true, 1, false>(a, P, *rope, st);
-        else launch_prefill_w<MT, false, 1, false>(a, P, *rope, st);
+        if (wide) launch_relative_w<MT, true, false>(a, P, *rope, st);
+        else launch_relative_w<MT, false, false>(a, P, *rope, st);
     } else {
         if (wide) launch_prefill_w<MT, true, 0, false>(a, P, none, st);
         else launch_prefill_w<MT, false, 0, false>(a, P, none, st);
