@@ -81,12 +81,12 @@ int32_t launch_select_blocks(const ihip_shape &, const float *, int, const int32
                              int32_t *, bool, hipStream_t);
 int32_t launch_attn_decode(const ihip_shape &, const ihip_tensor &, const ihip_tensor &,
                            const ihip_tensor &, const int32_t *, int, int, float, void *, float *,
-                           void *, const BankView *, const ihip_rope *, hipStream_t, const KvFormat * = nullptr);
+                           void *, bool, const BankView *, const ihip_rope *, hipStream_t, const KvFormat * = nullptr);
 BankView cache_bank_view(const ihip_cache *, int);
 void cache_describe(const ihip_cache *, int32_t *, int32_t *, int64_t *, ihip_tensor *, ihip_tensor *);
 bool cache_holds_fp8(const ihip_cache *);
 int32_t refuse_capture(const char *, hipStream_t);
-size_t attn_decode_workspace(const ihip_shape &, int, int);
+size_t attn_decode_workspace(const ihip_shape &, int, int, bool);
 int32_t launch_attn_prefill(const ihip_shape &, const ihip_tensor &, const ihip_tensor &,
                             const ihip_tensor &, const int32_t *, int, int, float, void *, float *,
                             const ihip_rope *, hipStream_t, const KvFormat * = nullptr);
@@ -221,6 +221,17 @@ static PlanLayout plan_layout(const ihip_shape &s, int n_stages, const int32_t *
     L.starts_off[1] = L.starts_off[0] + L.starts_bytes;
     L.total = L.starts_off[1] + L.starts_bytes;
     return L;
+}
+
+// Whether a decode layer's attention is cut into its fine splits (when the caller's scratch has room for them): always,
+// except for a plan that fits the static scratch array with the coarse ones only -- ihip_decode_layer_static takes such a
+// plan, and gives the same bits as ihip_decode_layer.
+static bool layer_splits_fine(const ihip_shape &s, int n_stages, const int32_t *chunks, const int32_t *keeps)
+{
+    const int last = n_stages - 1;
+    const size_t base = plan_layout(s, n_stages, chunks, keeps).total + align256((size_t)s.B * s.Hkv * keeps[last] * sizeof(int32_t));
+    return base + attn_decode_workspace(s, keeps[last], chunks[last], true) <= (size_t)IHIP_STATIC_SCRATCH_BYTES ||
+           base + attn_decode_workspace(s, keeps[last], chunks[last], false) > (size_t)IHIP_STATIC_SCRATCH_BYTES;
 }
 
 // The stages of Alg. 1 whose bit is set in `due`.  stage_out[i] receives stage i's kept starts; a
@@ -452,10 +463,11 @@ static int32_t attn_decode_entry(const char *who, const ihip_rope *rope, const K
     if (n_blocks < 0 || !pow2(block)) return fail(IHIP_ERR_INVALID_ARG, "%s: n_blocks = %d, block = %d", who, n_blocks, block);
     if (n_blocks > 0 && !block_starts) return fail(IHIP_ERR_INVALID_ARG, "%s: block_starts is NULL", who);
     if (!out) return fail(IHIP_ERR_INVALID_ARG, "%s: out is NULL", who);
-    const size_t need = attn_decode_workspace(*shape, n_blocks, block);
+    const size_t need = attn_decode_workspace(*shape, n_blocks, block, false);
     if (!ws || ws_bytes < need)
         return fail(IHIP_ERR_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", who, need, ws_bytes);
-    return launch_attn_decode(*shape, q, k, v, block_starts, n_blocks, block, sm_scale, out, out_lse, ws,
+    const bool fine = ws_bytes >= attn_decode_workspace(*shape, n_blocks, block, true);
+    return launch_attn_decode(*shape, q, k, v, block_starts, n_blocks, block, sm_scale, out, out_lse, ws, fine,
                               bank, rope, (hipStream_t)stream, fmt);
 }
 
@@ -606,7 +618,9 @@ static int32_t decode_layer_impl(const char *who, const ihip_shape *shape, ihip_
     const PlanLayout L = plan_layout(*shape, n_stages, chunk_sizes, keeps);
     const size_t P = (size_t)shape->B * shape->Hkv;
     const size_t blocks_bytes = align256(P * keeps[last] * sizeof(int32_t));
-    const size_t attn_bytes = attn_decode_workspace(*shape, keeps[last], chunk_sizes[last]);
+    const size_t attn_bytes = attn_decode_workspace(*shape, keeps[last], chunk_sizes[last], false);
+    const bool fine_plan = layer_splits_fine(*shape, n_stages, chunk_sizes, keeps);
+    const size_t fine_bytes = attn_decode_workspace(*shape, keeps[last], chunk_sizes[last], fine_plan);
     BankView mask_bank, sa_bank;
     if (cache) {
         if ((rc = refuse_capture(who, (hipStream_t)stream)) != IHIP_OK) return rc;
@@ -633,7 +647,8 @@ static int32_t decode_layer_impl(const char *who, const ihip_shape *shape, ihip_
                            hipMemcpyDeviceToDevice, (hipStream_t)stream) != hipSuccess)
             return fail(IHIP_ERR_HIP, "%s: copy of the final block list failed", who);
         return launch_attn_decode(*shape, q, k, v, stage_out[last], keeps[last], chunk_sizes[last], sm_scale, out,
-                                  out_lse, (char *)ws + L.scores_bytes, cache ? &sa_bank : nullptr, rope,
+                                  out_lse, (char *)ws + L.scores_bytes,
+                                  fine_plan && ws_bytes >= L.scores_bytes + fine_bytes, cache ? &sa_bank : nullptr, rope,
                                   (hipStream_t)stream, fmt);
     }
     if (first_stage != 0 || stage_due)
@@ -647,7 +662,8 @@ static int32_t decode_layer_impl(const char *who, const ihip_shape *shape, ihip_
                         all_heads, (hipStream_t)stream, fmt);
     if (rc != IHIP_OK) return rc;
     return launch_attn_decode(*shape, q, k, v, blocks, keeps[last], chunk_sizes[last], sm_scale, out, out_lse,
-                              w + L.total + blocks_bytes, cache ? &sa_bank : nullptr, rope, (hipStream_t)stream, fmt);
+                              w + L.total + blocks_bytes, fine_plan && ws_bytes >= L.total + blocks_bytes + fine_bytes,
+                              cache ? &sa_bank : nullptr, rope, (hipStream_t)stream, fmt);
 }
 
 int32_t ihip_decode_layer(const ihip_shape *shape, ihip_tensor q, ihip_tensor k, ihip_tensor v, int32_t n_stages,
@@ -702,7 +718,7 @@ int32_t ihip_decode_layer_static(const ihip_shape *shape, ihip_tensor q, ihip_te
     if ((rc = check_plan(who, shape, n_stages, chunk_sizes, keeps)) != IHIP_OK) return rc;
     const size_t need = plan_layout(*shape, n_stages, chunk_sizes, keeps).total +
                         align256((size_t)shape->B * shape->Hkv * keeps[n_stages - 1] * sizeof(int32_t)) +
-                        attn_decode_workspace(*shape, keeps[n_stages - 1], chunk_sizes[n_stages - 1]);
+                        attn_decode_workspace(*shape, keeps[n_stages - 1], chunk_sizes[n_stages - 1], false);
     if (need > (size_t)IHIP_STATIC_SCRATCH_BYTES)
         return fail(IHIP_ERR_WORKSPACE, "%s: this shape and plan need %zu bytes of scratch, the static array holds %zu",
                     who, need, (size_t)IHIP_STATIC_SCRATCH_BYTES);
@@ -1050,7 +1066,7 @@ size_t ihip_workspace_bytes(int32_t op, const ihip_shape *shape, int32_t n_stage
     const size_t P = (size_t)shape->B * shape->Hkv * (shape->Tq / shape->b_q);
     switch (op) {
     case IHIP_OP_ATTN_DECODE:
-        return std::max<size_t>(256, attn_decode_workspace(*shape, keeps[last], chunk_sizes[last]));
+        return std::max<size_t>(256, attn_decode_workspace(*shape, keeps[last], chunk_sizes[last], true));
     case IHIP_OP_ATTN_PREFILL:
         return 256;
     case IHIP_OP_PRUNE_ALL:         // (never 0, which stands for an error: an empty batch needs nothing)
@@ -1058,7 +1074,8 @@ size_t ihip_workspace_bytes(int32_t op, const ihip_shape *shape, int32_t n_stage
     case IHIP_OP_DECODE_LAYER:
         return std::max<size_t>(256, plan_layout(*shape, n_stages, chunk_sizes, keeps).total +
                                          align256(P * keeps[last] * sizeof(int32_t)) +
-                                         attn_decode_workspace(*shape, keeps[last], chunk_sizes[last]));
+                                         attn_decode_workspace(*shape, keeps[last], chunk_sizes[last],
+                                                               layer_splits_fine(*shape, n_stages, chunk_sizes, keeps)));
     case IHIP_OP_PREFILL_LAYER:
         return std::max<size_t>(256, plan_layout(*shape, n_stages, chunk_sizes, keeps).total +
                                          align256(P * keeps[last] * sizeof(int32_t)));

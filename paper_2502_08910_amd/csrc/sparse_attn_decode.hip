@@ -15,7 +15,8 @@ namespace ihip {
 
 constexpr int kAttnThreads = 256;
 constexpr int kAttnGroups = kAttnThreads / kRowLanes;   // 16 tokens in flight per step
-constexpr int kAttnMinSplit = 256, kAttnMaxSplit = 1024;   // slots of one split (a multiple of 16)
+constexpr int kAttnMaxSplit = 1024;                      // most slots of one split (a multiple of 16)
+constexpr int kAttnMinSplit = 256, kAttnMinSplitFine = 64;      // fewest; see decode_splits
 constexpr float kNegBig = -1.0e30f;                      // finite stand-in for -inf in running maxima
 
 struct AttnDecodeArgs {
@@ -331,17 +332,18 @@ __global__ __launch_bounds__(kAttnThreads) void attn_decode_split_kernel(const A
     }
 }
 
-// merge the splits: one workgroup of 128 threads per (problem, head), a thread per dim.  The partial
-// results of the first 16 splits (all of them in the usual shapes) are requested at once, before
-// anything is computed, and every thread takes the maximum over the splits itself: one trip to
-// memory and no barrier, where a reduction of the maxima first and the sums after it made two
-// dependent trips.  The sums run over the splits in order, so the result does not depend on this.
+// merge the splits: one workgroup per (problem, head), GROUPS x 128 threads, a thread per dim and group; group i takes splits
+// i, i + GROUPS, ...  The partial results of a group's first 16 splits (all of them in the usual shapes) are requested at
+// once, before anything is computed, and every thread takes the maximum over its splits itself: one trip to
+// memory, where a reduction of the maxima first and the sums after it made two dependent trips.  Up to 16 splits one
+// group does (no barrier); more take four, whose sums are merged through LDS: 50 splits 11.9 us with one group, 6.2 with four.
 constexpr int kMergeAhead = 16;
-__global__ __launch_bounds__(kD) void attn_decode_merge_kernel(const AttnDecodeArgs a)
+template <int GROUPS>
+__global__ __launch_bounds__(kD * GROUPS) void attn_decode_merge_kernel(const AttnDecodeArgs a)
 {
     const int G = a.ge.G;
     const int p = blockIdx.x / G, h = blockIdx.x % G;
-    const int c = threadIdx.x;
+    const int c = threadIdx.x % kD, grp = threadIdx.x / kD;
     const int b = p / a.ge.Hkv, g = p % a.ge.Hkv;            // decode: one problem per (sequence, KV head)
     const int64_t pbase = (int64_t)p * a.n_splits * G;
     const float2 *ml = reinterpret_cast<const float2 *>(a.part_ml);
@@ -349,31 +351,48 @@ __global__ __launch_bounds__(kD) void attn_decode_merge_kernel(const AttnDecodeA
     float av[kMergeAhead];
 #pragma unroll
     for (int s = 0; s < kMergeAhead; ++s) {
-        const int64_t r = pbase + (int64_t)min(s, a.n_splits - 1) * G + h;      // clamped: ignored beyond the last split
+        const int64_t r = pbase + (int64_t)min(s * GROUPS + grp, a.n_splits - 1) * G + h;      // clamped: ignored beyond the last split
         mlv[s] = ml[r];
         av[s] = a.part_acc[r * kD + c];
     }
     float M = kNegBig;
 #pragma unroll
     for (int s = 0; s < kMergeAhead; ++s)
-        if (s < a.n_splits) M = fmaxf(M, mlv[s].x);
-    for (int s = kMergeAhead; s < a.n_splits; ++s) M = fmaxf(M, ml[pbase + (int64_t)s * G + h].x);
+        if (s * GROUPS + grp < a.n_splits) M = fmaxf(M, mlv[s].x);
+    for (int s = kMergeAhead * GROUPS + grp; s < a.n_splits; s += GROUPS) M = fmaxf(M, ml[pbase + (int64_t)s * G + h].x);
     float L = 0.f, A = 0.f;
 #pragma unroll
     for (int s = 0; s < kMergeAhead; ++s) {
-        if (s < a.n_splits) {
+        if (s * GROUPS + grp < a.n_splits) {
             const float w = __builtin_amdgcn_exp2f(mlv[s].x - M);
             L = fmaf(w, mlv[s].y, L);
             A = fmaf(w, av[s], A);
         }
     }
 #pragma unroll 8
-    for (int s = kMergeAhead; s < a.n_splits; ++s) {
+    for (int s = kMergeAhead * GROUPS + grp; s < a.n_splits; s += GROUPS) {
         const int64_t r = pbase + (int64_t)s * G + h;
         const float2 x = ml[r];
         const float w = __builtin_amdgcn_exp2f(x.x - M);
         L = fmaf(w, x.y, L);
         A = fmaf(w, a.part_acc[r * kD + c], A);
+    }
+    if constexpr (GROUPS > 1) {
+        __shared__ float sh_m[GROUPS], sh_l[GROUPS], sh_a[GROUPS][kD];
+        sh_a[grp][c] = A;
+        if (c == 0) { sh_m[grp] = M; sh_l[grp] = L; }
+        __syncthreads();
+        if (grp != 0) return;
+        M = kNegBig;
+#pragma unroll
+        for (int i = 0; i < GROUPS; ++i) M = fmaxf(M, sh_m[i]);
+        L = A = 0.f;
+#pragma unroll
+        for (int i = 0; i < GROUPS; ++i) {
+            const float w = __builtin_amdgcn_exp2f(sh_m[i] - M);
+            L = fmaf(w, sh_l[i], L);
+            A = fmaf(w, sh_a[i][c], A);
+        }
     }
     const int hq = g * G + h;
     a.out[((int64_t)b * a.ge.Hq + hq) * kD + c] = (uint16_t)f32_to_bf16_bits(A / L * a.v_scale);
@@ -384,10 +403,14 @@ __global__ __launch_bounds__(kD) void attn_decode_merge_kernel(const AttnDecodeA
 // Splits of the slot list: as many workgroups as the chip holds at once (4 workgroups of 4 waves
 // per CU with the plain kernel's registers), so that no workgroup has to wait for a free slot and
 // run its whole latency chain after the others have drained -- with 256-slot splits the cfg3 shape
-// had 1344 workgroups for 1024 places.  Between 256 and 1024 slots per split, a multiple of 16.
+// had 1344 workgroups for 1024 places.  Up to 1024 slots per split, a multiple of 16, and at least 64 (`fine`), which is
+// one batch of loads of every 16-lane group: with few problems the kernel is one chain of latencies, and a
+// split of 256 slots walks its loop four times while most of the chip is idle (8 problems of 1,664 slots: 14.3 us with
+// 256, 8.9 with 64; of 3,200 slots 15.0 and 11.2).  Finer splits take more scratch; with scratch for the coarse
+// ones only (at least 256 slots), those are used.
 // wg_per_cu: 4 for the plain kernels, 3 for the RoPE instantiations (more registers).  The workspace
 // is sized for 4, which gives the most splits.
-static int decode_splits(const ihip_shape &s, int n_blocks, int block, int *slots_per_split, int wg_per_cu = 4)
+static int decode_splits(const ihip_shape &s, int n_blocks, int block, bool fine, int *slots_per_split, int wg_per_cu = 4)
 {
     static int n_cu = 0;
     if (n_cu == 0) {
@@ -400,15 +423,16 @@ static int decode_splits(const ihip_shape &s, int n_blocks, int block, int *slot
     const int P = std::max(1, s.B * s.Hkv);
     const int places = std::max(1, n_cu * wg_per_cu / P);      // splits per problem that run at once
     int per = ((total + places - 1) / places + 15) / 16 * 16;
-    per = std::min(kAttnMaxSplit, std::max(kAttnMinSplit, per));
+    per = std::min(kAttnMaxSplit, std::max(fine ? kAttnMinSplitFine : kAttnMinSplit, per));
     *slots_per_split = per;
     return (total + per - 1) / per;
 }
 
-size_t attn_decode_workspace(const ihip_shape &s, int n_blocks, int block)
+// scratch for the partial results of the fine or the coarse splits
+size_t attn_decode_workspace(const ihip_shape &s, int n_blocks, int block, bool fine)
 {
     int per;
-    const int ns = decode_splits(s, n_blocks, block, &per);
+    const int ns = decode_splits(s, n_blocks, block, fine, &per);
     const size_t P = (size_t)s.B * s.Hkv;
     const size_t G = s.Hq / s.Hkv;
     return P * ns * G * (2 + kD) * sizeof(float);
@@ -416,7 +440,7 @@ size_t attn_decode_workspace(const ihip_shape &s, int n_blocks, int block)
 
 int32_t launch_attn_decode(const ihip_shape &s, const ihip_tensor &q, const ihip_tensor &k,
                            const ihip_tensor &v, const int32_t *block_starts, int n_blocks, int block,
-                           float sm_scale, void *out, float *out_lse, void *ws, const BankView *bank,
+                           float sm_scale, void *out, float *out_lse, void *ws, bool fine, const BankView *bank,
                            const ihip_rope *rope, hipStream_t st, const KvFormat *fmt)
 {
     AttnDecodeArgs a;
@@ -455,7 +479,7 @@ int32_t launch_attn_decode(const ihip_shape &s, const ihip_tensor &q, const ihip
     a.block = block;
     a.block_log2 = __builtin_ctz(block);
     a.scale_log2e = sm_scale * 1.44269504088896340736f * (fp8 ? fmt->k_scale : 1.0f);
-    a.n_splits = decode_splits(s, n_blocks, block, &a.slots_per_split, use_rope ? 3 : 4);
+    a.n_splits = decode_splits(s, n_blocks, block, fine, &a.slots_per_split, use_rope ? 3 : 4);
     const int P = s.B * s.Hkv;
     const int G = a.ge.G;
     a.part_ml = (float *)ws;
@@ -491,7 +515,8 @@ int32_t launch_attn_decode(const ihip_shape &s, const ihip_tensor &q, const ihip
     int32_t rc = check_launch("sparse_attn_decode (split)");
     if (rc != IHIP_OK) return rc;
     KernelTimer timer("attn_decode_merge", st);
-    hipLaunchKernelGGL(attn_decode_merge_kernel, dim3(P * G), dim3(kD), 0, st, a);
+    if (a.n_splits <= kMergeAhead) hipLaunchKernelGGL(attn_decode_merge_kernel<1>, dim3(P * G), dim3(kD), 0, st, a);
+    else hipLaunchKernelGGL(attn_decode_merge_kernel<4>, dim3(P * G), dim3(kD * 4), 0, st, a);
     return check_launch("sparse_attn_decode (merge)");
 }
 

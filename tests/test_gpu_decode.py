@@ -302,3 +302,44 @@ def test_empty_batch_is_a_no_op(ihip):
     outp = Lp.prefill_layer(torch.empty((0, w.Hq, 64, w.d), dtype=torch.bfloat16, device="cuda"), k, k, chunks, keeps)
     torch.cuda.synchronize()
     assert outp.shape == (0, w.Hq, 64, w.d)
+
+
+@pytest.mark.parametrize("Hkv,G,n_blocks,block,n_stream", [
+    (1, 4, 1024, 4, 1024),        # one problem: 82 splits of 64 slots (merge: more than four groups request ahead)
+    (1, 8, 37, 16, 333),          # 17 splits, the last one of 13 slots: just past the one-group merge
+    (8, 4, 128, 4, 1024),         # 26 splits
+    (2, 1, 0, 4, 40),             # one split, no blocks
+    (8, 2, 512, 8, 1000),         # more slots per split than the least
+], ids=["82", "17", "26", "one", "8x5k"])
+def test_attention_splits_fine_and_coarse(ihip, orc, Hkv, G, n_blocks, block, n_stream):
+    """The split of the key list follows the scratch: with what ihip_workspace_bytes says splits of 64 slots and more,
+    with a byte less (and room for the coarse ones) of 256 and more, both against the oracle (4e-3, as every attention on
+    given blocks here) and each other; less than the coarse ones need is refused."""
+    w = configs.shrink(configs.CFG1, T=9001, Hq=Hkv * G, Hkv=Hkv, n_stream=n_stream, n_needles=0)
+    q, k, v, sl, _ = configs.make_inputs(w, 5)
+    n_mid = (w.T - w.n_stream - w.n_sink) // block
+    starts = torch.full((Hkv, n_blocks), -1, dtype=torch.int32)
+    for g in range(Hkv):
+        pick = gen.distinct_ints(6, 100 + g, min(n_blocks, n_mid), n_mid).sort().values[:max(0, n_blocks - g)]
+        starts[g, :len(pick)] = (w.n_sink + pick * block).to(torch.int32)
+    qd, kd, vd, sld, bd = (t.cuda() for t in (q, k, v, sl, starts))
+    L = ihip.Layer(qd, kd, sld, 1, w.n_sink, w.n_stream)
+    need = L.workspace_bytes(ihip.OP_ATTN_DECODE, [block], [max(n_blocks, 1)])
+    total = w.n_sink + n_blocks * block + n_stream
+    coarse = Hkv * G * (-(-total // 256)) * 130 * 4
+    o = orc.Oracle(q, k, v, sl.tolist(), 1, w.n_sink, w.n_stream)
+    got = []
+    for size in (need, max(need - 1, coarse)):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        out, lse = L.sparse_attn_decode(qd, kd, vd, bd, block, want_lse=True, ws=ws)
+        got.append(out.float().cpu())
+        for g in range(Hkv):
+            s = starts[g][starts[g] >= 0].numpy()
+            ref, ref_lse = o.attend(0, g, 0, s, np.minimum(block, w.T - w.n_stream - s).astype(np.int32))
+            assert np.abs(got[-1][0, g * G:(g + 1) * G].numpy() - ref).max() <= 4e-3, (size, g)
+            np.testing.assert_allclose(lse[0, g * G:(g + 1) * G].cpu().numpy(), ref_lse, rtol=2e-5, atol=2e-5)
+    assert (got[0] - got[1]).abs().max() <= 4e-3
+    if need > coarse:
+        small = torch.empty(Hkv * G * 130 * 4 // 2, dtype=torch.uint8, device="cuda")
+        with pytest.raises(ihip.IhipError):
+            L.sparse_attn_decode(qd, kd, vd, bd, block, ws=small)

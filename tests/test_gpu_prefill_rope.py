@@ -311,3 +311,19 @@ def test_chunk_indexed_queries_before_the_cap(ihip, orc, b_q, Hq, Hkv, stages):
     st, _, _, _ = gpu_prefill(ihip, w, q, k, v, sl, cos, sin, prune="chunk")
     _, (min_recall, _) = compare(w, o, st, None, None, exact=False, score_tol=2.3e-3, max_off=0.02, stagewise=True)
     assert min_recall >= 0.9
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(8, 8), (4, 2), (8, 2), (16, 2)], ids=["g1", "g2", "g4", "g8"])
+@pytest.mark.parametrize("stages", [((4, 65), (2, 97), (1, 150)), ((2, 130),), ((1, 300),), ((8, 70), (4, 70)), ((256, 3), (32, 20))],
+                         ids=["4-2-1", "2", "1", "8-4", "256-32"])
+def test_relative_64_query_blocks_at_the_edges(ihip, orc, Hq, Hkv, stages):
+    """The kernel of 64-query blocks walks 64 chunks per wave: chunks of one and two keys (no level after the first
+    comparison picks up the late scores), slot counts around 64 and 128, one and several groups of chunks per
+    workgroup, a last chunk cut short, empty slots.  Exact on the quarter-turn table."""
+    w = small(Tq=192, prefix=701, Hq=Hq, Hkv=Hkv, n_stream=100, n_sink=33, stages=stages)
+    q, k, v, sl, _ = configs.make_inputs(w, 6, kind="int")
+    cos, sin = gen.quarter_turn_table(w.T + 128, w.d)
+    o = orc.Oracle(q, k, v, sl.tolist(), w.b_q, w.n_sink, w.n_stream,
+                   rope=orc.RopeSpec(cos.numpy(), sin.numpy(), prune="relative", attn="streaming"))
+    st, out, lse, _ = gpu_prefill(ihip, w, q, k, v, sl, cos, sin, prune="relative")
+    compare(w, o, st, out, lse, exact=True)
