@@ -1,0 +1,360 @@
+// Decode pruning stage on the matrix cores (b_q == 1): Alg. 3's search and Alg. 2's chunk score, K from device memory
+// (strides or pages), without RoPE or with the relative style.  One query per head makes this a gather, not a contraction: what
+// it cannot do without are the rows.  The matrix cores take the arithmetic off the vector ALUs: 16 gathered rows
+// against 16 query columns is four v_mfma_f32_16x16x32_bf16 (E4M3 rows are widened, exact), of whose 256 products the 16
+// that are wanted are picked in the registers; the vector form needs some 30 instructions for every four rows (45 with
+// two rotated queries), and with 128-byte rows or two rotated queries those, not the rows, were the time.
+//
+// A wave walks 64 searches, one per lane: 64/G chunks x G heads, in four 16-row tiles.  Tile t, row r = 4*kq + i is owned
+// by lane (kq, n = 4t + i): the product's column n, rows 4*kq..+3 are in that lane's accumulator, so with column n
+// holding the query of head n % G the owner finds its own score in register n % 4 -- no value crosses lanes except the
+// row offsets, handed from the owners to the loading lanes (one shuffle per tile and level).
+// Relative style (see prune_relative.h): columns 0..7 hold q_L, 8..15 q_R; the two halves are exchanged by one row rotation.
+// The rotated queries are fp32, kept as three bf16 operands (value, rest, rest of the rest: 24 bits and more), so that a score is as
+// good as an fp32 one.
+//
+// Operand layout: lane (n, kq) holds 8 dims of row or column n; any assignment of dims to (step, kq) serves as long as both
+// sides agree.  bf16 rows: step ks, dims 32*ks + 8*kq.. (a 16-byte load per step, 64 contiguous bytes of 16 rows an
+// instruction).  E4M3 rows: a 16-byte load j brings dims 64*j + 16*kq..+15, steps 2j and 2j+1.
+#pragma once
+
+#include "prune_prefill.h"
+
+namespace ihip {
+
+// The query operands of a lane: column n16's head, 8 dims of group kq per step, PARTS bf16 operands each (1: the query as
+// it is; 3: rotated by table row `pos`, fp32 in three parts)
+template <bool KV8, int PARTS>
+__device__ inline void decode_query_operands(const uint16_t *q_row, int kq, const RopeView &rope, int pos, bf16x8 (&q)[PARTS][4])
+{
+    uint4 w[4];
+    float4 c[PARTS > 1 ? 4 : 1], s[PARTS > 1 ? 4 : 1];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        const int d0 = KV8 ? (ks >> 1) * 64 + kq * 16 + (ks & 1) * 8 : ks * 32 + kq * 8;
+        w[ks] = *reinterpret_cast<const uint4 *>(q_row + d0);
+        if constexpr (PARTS > 1) {
+            c[ks] = *reinterpret_cast<const float4 *>(rope.cos + (int64_t)pos * (kD / 2) + d0 / 2);
+            s[ks] = *reinterpret_cast<const float4 *>(rope.sin + (int64_t)pos * (kD / 2) + d0 / 2);
+        }
+    }
+    if constexpr (PARTS > 1) __builtin_amdgcn_sched_barrier(0);      // everything is requested before anything is turned
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        if constexpr (PARTS == 1) {
+            q[0][ks] = __builtin_bit_cast(bf16x8, w[ks]);
+        } else {
+            float x[8], y[8];
+            unpack8(w[ks], x);
+            const float cc[4] = {c[ks].x, c[ks].y, c[ks].z, c[ks].w}, ss[4] = {s[ks].x, s[ks].y, s[ks].z, s[ks].w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                y[2 * i] = x[2 * i] * cc[i] - x[2 * i + 1] * ss[i];
+                y[2 * i + 1] = x[2 * i] * ss[i] + x[2 * i + 1] * cc[i];
+            }
+#pragma unroll
+            for (int part = 0; part < PARTS; ++part) {
+                uint32_t u[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    u[i] = pack_bf16x2(y[2 * i], y[2 * i + 1]);
+                    y[2 * i] -= __uint_as_float(u[i] << 16);              // exact
+                    y[2 * i + 1] -= __uint_as_float(u[i] & 0xffff0000u);
+                }
+                q[part][ks] = __builtin_bit_cast(bf16x8, make_uint4(u[0], u[1], u[2], u[3]));
+            }
+        }
+    }
+}
+
+// 16 rows x 16 columns; raw: this lane's loads of row n16 (bf16: one per step, E4M3: one per two steps)
+template <bool KV8, int PARTS>
+__device__ inline f32x4 decode_products(const uint4 (&raw)[KV8 ? 2 : 4], const bf16x8 (&q)[PARTS][4])
+{
+    bf16x8 k[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        if constexpr (KV8) {
+            const uint4 w = raw[ks >> 1];
+            k[ks] = __builtin_bit_cast(bf16x8, fp8x8_to_bf16x8((ks & 1) ? make_uint2(w.z, w.w) : make_uint2(w.x, w.y)));
+        } else {
+            k[ks] = __builtin_bit_cast(bf16x8, raw[KV8 ? 0 : ks]);
+        }
+    }
+    f32x4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int part = PARTS - 1; part >= 0; --part)        // the small terms first
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[ks], q[part][ks], c, 0, 0, 0);
+    return c;
+}
+
+__device__ inline float pick4(const f32x4 c, int i)      // c[i], in registers
+{
+    const float a = (i & 1) ? c[1] : c[0], b = (i & 1) ? c[3] : c[2];
+    return (i & 2) ? b : a;
+}
+__device__ inline float row_ror8(float v) { return dpp_f32<0x128>(v); }
+__device__ inline float other_quad(float v) { return dpp_f32<0x1B>(dpp_f32<0x141>(v)); }   // lane n ^ 4 of a row: half mirror, then each quad reversed
+
+// Where the rows of (sequence, KV head) are, and how a lane's row offset is formed and handed round.  NARROW: byte offsets of 32 bits
+// from a scalar base (every row of the slab within 4 GB); otherwise elements in 64 bits; SRC 2: pages.
+template <int SRC, bool NARROW>
+struct DecodeRows {
+    const uint16_t *kb;
+    const int32_t *table;
+    int64_t k_sb, k_st;
+    int page_log2;
+    using off_t = typename std::conditional<NARROW, uint32_t, int64_t>::type;
+    __device__ DecodeRows(const PruneArgs &a, const Problem &pr)
+    {
+        kb = SRC == 2 ? a.k + pr.g * a.k_sh : a.k + pr.b * a.k_sb + pr.g * a.k_sh;
+        table = SRC == 2 ? a.paged.block_table + (int64_t)pr.b * a.paged.table_stride : nullptr;
+        k_sb = a.k_sb;
+        k_st = a.k_st;
+        page_log2 = a.paged.page_log2;
+    }
+    __device__ off_t at(int pos, int page) const         // page: of a paged pool
+    {
+        if constexpr (SRC == 2) return (int64_t)page * k_sb + (int64_t)(pos & ((1 << page_log2) - 1)) * k_st;
+        else if constexpr (NARROW) return (uint32_t)pos * (uint32_t)(k_st * 2);
+        else return (int64_t)pos * k_st;
+    }
+    // 16 bytes at byte `b` of the row at `off`
+    __device__ uint4 load(off_t off, int b) const
+    {
+        if constexpr (NARROW) return *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(kb) + (uint64_t)(off + (uint32_t)b));
+        else return *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(kb + off) + b);
+    }
+};
+
+constexpr int kDecodePages = 16;              // page ids of a chunk kept in LDS; further ones are looked up in the table
+
+template <int G, bool ROPE, int SRC, bool KV8, bool NARROW>
+__global__ __launch_bounds__(256) void prune_decode_tile_kernel(const PruneArgs a, const RopeView rope)
+{
+    static_assert(SRC == 0 || !NARROW, "paged pools are addressed with 64-bit offsets");
+    constexpr int PARTS = ROPE ? 3 : 1;
+    constexpr int NT = 4;                     // tiles of a wave
+    constexpr int kPerTile = 16 / G;          // chunks of a tile
+    constexpr int kChunks = NT * kPerTile;    // chunks of a wave
+    constexpr int kLoads = KV8 ? 2 : 4;
+    using Rows = DecodeRows<SRC, NARROW>;
+    using off_t = typename Rows::off_t;
+    __shared__ int32_t sh_pages[SRC == 2 ? 4 * kChunks * kDecodePages : 1];
+    const int p = blockIdx.y;
+    const Problem pr = problem_of(a.ge, p);
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int n = lane & 15, kq = lane >> 4, quad = n >> 2;
+    const int j0 = (blockIdx.x * (blockDim.x >> 6) + wv) * kChunks;
+    if (j0 >= a.max_chunks) return;
+
+    // this lane's search: chunk `ci` of the wave, head `hd` of the group
+    const int r = 4 * kq + (n & 3);
+    const int ci = quad * kPerTile + r / G, hd = r % G;
+    const int j = j0 + ci;
+    const int start = j < a.max_chunks ? slot_start(pr, a.parent_starts, a.n_parent, a.ratio_log2, a.chunk, p, j) : -1;
+    const bool valid = start >= 0;
+    const int len = valid ? min(a.chunk, pr.hi - start) : 0;
+
+    bf16x8 q[PARTS][4];
+    {
+        const int qh = G == 8 ? (n & 7) : n % G;
+        const uint16_t *qb = a.q + pr.b * a.q_sb + (int64_t)(pr.g * G + qh) * a.q_sh + (int64_t)pr.m * a.q_st;
+        decode_query_operands<KV8, PARTS>(qb, kq, rope, a.ge.n_stream + (n < 8 ? 1 : 0), q);
+    }
+    const Rows rows(a, pr);
+    const int base = max(start, 0);
+    int32_t *pages = &sh_pages[SRC == 2 ? wv * kChunks * kDecodePages : 0];
+    if constexpr (SRC == 2) {
+        // page ids of every chunk of the wave, 16 lanes a chunk
+#pragma unroll
+        for (int c0 = 0; c0 < kChunks; c0 += 4) {
+            const int c = c0 + kq, cr = (c % kPerTile) * G;
+            const int first = __shfl(base, (cr >> 2) * 16 + (c / kPerTile) * 4 + (cr & 3), 64) >> rows.page_log2;
+            const int e = min(first + n, a.paged.table_stride - 1);
+            // entries beyond a sequence's length may hold anything: fetched but not used
+            pages[c * kDecodePages + n] = rows.table[e];
+        }
+        asm volatile("" ::: "memory");        // lanes read what other lanes of the wave wrote (LDS keeps the order)
+    }
+    // offset of row `pos` of this lane's chunk
+    auto row_at = [&](int pos) -> off_t {
+        if constexpr (SRC == 2) {
+            const int idx = (pos >> rows.page_log2) - (base >> rows.page_log2);
+            int page = pages[ci * kDecodePages + min(idx, kDecodePages - 1)];
+            if (idx >= kDecodePages) page = rows.table[pos >> rows.page_log2];      // a chunk of more pages than that
+            return rows.at(pos, page);
+        } else {
+            return rows.at(pos, 0);
+        }
+    };
+    auto fetch = [&](off_t off, uint4 (&raw)[kLoads]) {
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) raw[i] = rows.load(off, i * 64 + kq * 16);
+    };
+    // a tile's products -> the owners' scores (sL: against the column's query, or q_L; sR: against q_R).  i: the owner's
+    // register; ix: the register that the owner in lane n ^ 8 wants
+    auto owned = [&](const f32x4 c, int i, int ix, float &sL, float &sR) {
+        float v = pick4(c, i);
+        if constexpr (G == 8) {               // heads 0..3 are in the even quads' columns, and in rows of even kq
+            const float w = other_quad(v);
+            v = ((quad ^ kq) & 1) ? w : v;
+        }
+        if constexpr (ROPE) {
+            const float w = row_ror8(i == ix ? v : pick4(c, ix));
+            sL = n < 8 ? v : w;
+            sR = n < 8 ? w : v;
+        } else {
+            sL = sR = v;
+        }
+    };
+    // scores of the lanes' rows at `off`
+    auto score = [&](off_t off, float &sL, float &sR) {
+        uint4 raw[NT][kLoads];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) fetch(__shfl(off, (n >> 2) * 16 + 4 * t + (n & 3), 64), raw[t]);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            float l, rr;
+            owned(decode_products<KV8, PARTS>(raw[t], q), n & 3, n & 3, l, rr);
+            sL = quad == t ? l : sL;
+            sR = quad == t ? rr : sR;
+        }
+    };
+
+    int half = a.chunk >> 1, off = 0;
+    // left: the left key's score as a left branch; value: what the chunk score takes from this head
+    float left = 0.f, value = 0.f, rL = 0.f, rR = 0.f;
+    const bool has_right = half >= 1 && half < len;
+    {
+        const off_t at0 = row_at(base), at1 = row_at(has_right ? base + half : base);
+        if constexpr (G == 4) {
+            // The first key of a chunk and of its right half are the same rows for all heads: one tile holds the first keys of the
+            // wave's 16 chunks, row 4*kq + t that of chunk (t, kq), so that the owner finds its score in register t.
+            uint4 r0[kLoads], r1[kLoads];
+            const int src = (n >> 2) * 16 + 4 * (n & 3);
+            fetch(__shfl(at0, src, 64), r0);
+            fetch(__shfl(at1, src, 64), r1);
+            owned(decode_products<KV8, PARTS>(r0, q), quad, quad ^ 2, left, value);
+            owned(decode_products<KV8, PARTS>(r1, q), quad, quad ^ 2, rL, rR);
+        } else {
+            score(at0, left, value);
+            score(at1, rL, rR);
+        }
+    }
+    if (has_right && rR > left) { off = half; left = rL; value = rR; }        // strict: tie keeps left
+    for (half >>= 1; half >= 1; half >>= 1) {
+        const bool ok = off + half < len;
+        score(row_at(ok ? start + off + half : base), rL, rR);
+        if (ok && rR > left) { off += half; left = rL; value = rR; }
+    }
+
+    if (a.out_rep != nullptr && j < a.max_chunks) {
+        const int64_t row = (int64_t)(pr.b * a.ge.Hq + pr.g * G + hd) * a.ge.Mq + pr.m;
+        a.out_rep[row * a.max_chunks + j] = valid ? start + off : -1;
+    }
+    // chunk score: max over the heads
+    float best = value;
+    if constexpr (G >= 2) best = fmaxf(best, dpp_f32<0xB1>(best));
+    if constexpr (G >= 4) best = fmaxf(best, dpp_f32<0x4E>(best));
+    if constexpr (G == 8) best = fmaxf(best, __shfl_xor(best, 16, 64));
+    if (hd == 0 && j < a.max_chunks) a.out_scores[(int64_t)p * a.max_chunks + j] = valid ? (KV8 ? best * a.k_scale : best) : -INFINITY;
+}
+
+// Chunks of four keys: the search reads every row of a chunk anyway (all four unless the heads agree), so a tile is four
+// whole chunks, one load of which brings 64 bytes of each of 16 rows in order, and a head's four scores of a
+// chunk are the four registers of one lane: no dependent loads, nothing crosses lanes.
+template <int G, bool ROPE, int SRC, bool KV8, bool NARROW>
+__global__ __launch_bounds__(256) void prune_decode_four_kernel(const PruneArgs a, const RopeView rope)
+{
+    static_assert(SRC == 0 || !NARROW, "paged pools are addressed with 64-bit offsets");
+    constexpr int PARTS = ROPE ? 3 : 1;
+    constexpr int NT = ROPE && !KV8 ? 2 : 4;  // tiles of a wave, all in flight at once
+    constexpr int kLoads = KV8 ? 2 : 4;
+    using Rows = DecodeRows<SRC, NARROW>;
+    const int p = blockIdx.y;
+    const Problem pr = problem_of(a.ge, p);
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int n = lane & 15, kq = lane >> 4;
+    const int j0 = (blockIdx.x * (blockDim.x >> 6) + wv) * NT * 4;
+    if (j0 >= a.max_chunks) return;
+    const Rows rows(a, pr);
+    const int hd = G == 8 ? (n & 7) : n % G;
+    bf16x8 q[PARTS][4];
+    decode_query_operands<KV8, PARTS>(a.q + pr.b * a.q_sb + (int64_t)(pr.g * G + hd) * a.q_sh + (int64_t)pr.m * a.q_st, kq, rope,
+                                      a.ge.n_stream + (n < 8 ? 1 : 0), q);
+    uint4 raw[NT][kLoads];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        // as the loader of row n: key n % 4 of chunk n / 4 of the tile (its first key where the chunk is cut short)
+        const int j = j0 + t * 4 + (n >> 2);
+        const int start = j < a.max_chunks ? slot_start(pr, a.parent_starts, a.n_parent, a.ratio_log2, a.chunk, p, j) : -1;
+        const int pos = start >= 0 ? (start + (n & 3) < pr.hi ? start + (n & 3) : start) : 0;
+        int page = 0;
+        if constexpr (SRC == 2) page = rows.table[pos >> rows.page_log2];
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) raw[t][i] = rows.load(rows.at(pos, page), i * 64 + kq * 16);
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int j = j0 + t * 4 + kq;        // as the owner: chunk kq of the tile, column n's head
+        const int start = j < a.max_chunks ? slot_start(pr, a.parent_starts, a.n_parent, a.ratio_log2, a.chunk, p, j) : -1;
+        const int len = start >= 0 ? min(4, pr.hi - start) : 0;
+        const f32x4 c = decode_products<KV8, PARTS>(raw[t], q);
+        f32x4 sL = c, sR = c;
+        if constexpr (ROPE) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float w = row_ror8(c[i]);
+                sL[i] = n < 8 ? c[i] : w;
+                sR[i] = n < 8 ? w : c[i];
+            }
+        }
+        // the halving search over keys 0..3
+        const bool right = 2 < len && sR[2] > sL[0];                          // strict: tie keeps left
+        float left = right ? sL[2] : sL[0], best = right ? sR[2] : sR[0];
+        int off = right ? 2 : 0;
+        const float next = right ? sR[3] : sR[1];
+        if (off + 1 < len && next > left) { off += 1; best = next; }
+        if (a.out_rep != nullptr && j < a.max_chunks && n < G) {
+            const int64_t row = (int64_t)(pr.b * a.ge.Hq + pr.g * G + hd) * a.ge.Mq + pr.m;
+            a.out_rep[row * a.max_chunks + j] = start >= 0 ? start + off : -1;
+        }
+        if constexpr (G >= 2) best = fmaxf(best, dpp_f32<0xB1>(best));
+        if constexpr (G >= 4) best = fmaxf(best, dpp_f32<0x4E>(best));
+        if constexpr (G == 8) best = fmaxf(best, other_quad(best));
+        if (n == 0 && j < a.max_chunks) a.out_scores[(int64_t)p * a.max_chunks + j] = start >= 0 ? (KV8 ? best * a.k_scale : best) : -INFINITY;
+    }
+}
+
+// b_q == 1, K through strides or pages
+template <int G, bool ROPE, int SRC, bool KV8, bool NARROW>
+static void launch_decode_tile_n(const PruneArgs &a, const RopeView &rope, int P, hipStream_t st)
+{
+    const int per_wave = a.chunk == 4 ? (ROPE && !KV8 ? 8 : 16) : 64 / G;
+    constexpr int wg = 4;                     // waves of a workgroup
+    const dim3 grid((a.max_chunks + per_wave * wg - 1) / (per_wave * wg), P), block(64 * wg);
+    KernelTimer timer(stage_name(kNamePruneDecode, a.parent_starts == nullptr, a.chunk), st);
+    if (a.chunk == 4) hipLaunchKernelGGL((prune_decode_four_kernel<G, ROPE, SRC, KV8, NARROW>), grid, block, 0, st, a, rope);
+    else hipLaunchKernelGGL((prune_decode_tile_kernel<G, ROPE, SRC, KV8, NARROW>), grid, block, 0, st, a, rope);
+}
+
+template <bool ROPE, int SRC, bool KV8, bool NARROW>
+static void launch_decode_tile_g(const PruneArgs &a, const RopeView &rope, int P, hipStream_t st)
+{
+    if (a.ge.G == 4) launch_decode_tile_n<4, ROPE, SRC, KV8, NARROW>(a, rope, P, st);
+    else launch_decode_tile_n<8, ROPE, SRC, KV8, NARROW>(a, rope, P, st);
+}
+
+template <bool ROPE, bool KV8>
+static void launch_decode_tile(const PruneArgs &a, const RopeView &rope, int P, int64_t max_seq_len, hipStream_t st)
+{
+    // byte offsets of 32 bits: every row of the slab within 4 GB of its base (strides are non-negative here or not narrow)
+    const bool narrow = a.k_st >= 0 && max_seq_len * a.k_st * 2 + 512 < ((int64_t)1 << 32);
+    if (a.paged.block_table != nullptr) launch_decode_tile_g<ROPE, 2, KV8, false>(a, rope, P, st);
+    else if (narrow) launch_decode_tile_g<ROPE, 0, KV8, true>(a, rope, P, st);
+    else launch_decode_tile_g<ROPE, 0, KV8, false>(a, rope, P, st);
+}
+
+}  // namespace ihip

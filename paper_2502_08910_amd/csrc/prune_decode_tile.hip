@@ -1,0 +1,16 @@
+// Decode pruning stages on the matrix cores over bf16 and E4M3 keys (kernels in prune_decode_tile.h).
+#include "prune_decode_tile.h"
+
+namespace ihip {
+
+// G in {4, 8}, K through strides or pages (the caller checks); rope: relative style, or nullptr
+void launch_prune_decode_tile(const PruneArgs &a, int P, bool fp8, const RopeView *rope, int64_t max_seq_len, hipStream_t st)
+{
+    const RopeView none{nullptr, nullptr, 0};
+    if (rope && fp8) launch_decode_tile<true, true>(a, *rope, P, max_seq_len, st);
+    else if (rope) launch_decode_tile<true, false>(a, *rope, P, max_seq_len, st);
+    else if (fp8) launch_decode_tile<false, true>(a, none, P, max_seq_len, st);
+    else launch_decode_tile<false, false>(a, none, P, max_seq_len, st);
+}
+
+}  // namespace ihip

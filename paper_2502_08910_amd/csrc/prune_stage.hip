@@ -229,8 +229,36 @@ static void launch_decode(const PruneArgs &a, int P, bool fp8, hipStream_t st)
         launch_decode_u<G, 1>(a, P, fp8, st);
 }
 
+void launch_prune_decode_tile(const PruneArgs &a, int P, bool fp8, const RopeView *rope, int64_t max_seq_len, hipStream_t st);
 int32_t launch_prune_stage_rope(const PruneArgs &a, const RopeView &rope, int style, int P, bool fp8, hipStream_t st);
 void launch_prune_prefill_fp8(const PruneArgs &a, int P, int b_q, const RopeView *rope, int style, hipStream_t st);
+
+// Which decode stages (K through strides or pages; no RoPE or the relative style) go to the matrix-core kernels of
+// prune_decode_tile.h.  Their waves do a fifth of the vector instructions for 64 searches at a time, but a level of
+// theirs is a longer chain, and their loads take 64 bytes of 16 rows where the vector kernels take whole rows: they win where
+// instructions are the bound and many searches run.  Measured (us, vector / tile kernels; 32/8 heads, 4 x 250K keys,
+// stages of 256, 64, 16 and 4, then one sequence of 128K):
+//   E4M3 pages           34.7/21.8 26.7/17.0 20.4/12.5 18.5/15.4;  14.3/12.4 12.7/10.7 10.2/9.5 8.7/10.7
+//   E4M3 pages, relative 39.4/31.3 31.4/24.1 23.9/17.6 26.8/17.9;  14.9/20.2 13.2/16.4 10.6/12.6 9.4/11.0
+//   E4M3                 24.7/26.0 19.1/18.2 14.0/12.8 14.9/12.7;  10.6/11.0 9.6/9.7 8.3/8.0 7.2/8.7
+//   E4M3, relative       30.7/29.9 24.3/23.0 18.6/17.0 21.7/15.5;  11.0/16.6 10.5/14.3 8.7/11.2 8.3/9.9
+//   bf16 pages           48.6/43.1 32.1/29.3 22.2/20.7 20.6/18.8;  14.9/14.5 13.3/13.0 10.4/10.3 8.7/10.3
+//   bf16 pages, relative 47.8/42.2 35.9/29.6 26.0/20.8 27.8/23.3;  15.3/21.1 14.1/17.8 11.1/13.4 9.9/10.2
+//   bf16, relative       42.2/45.9 28.7/29.5 21.1/20.6 22.6/20.8;  12.3/15.1 11.5/13.8 9.2/10.7 8.7/9.3
+//   bf16                 40.3/47.2 27.4/31.3 17.6/20.2 16.0/18.0  (8 heads per group, 2 x 100K: 22.3/25.4 14.8/17.2 14.8/11.1)
+// With one or two heads per group the vector kernels won at every size measured.
+static bool decode_on_tiles(const PruneArgs &a, int P, bool fp8, bool relative)
+{
+    const int G = a.ge.G;
+    if (G < 4) return false;
+    const bool paged = a.paged.block_table != nullptr;
+    const int64_t searches = (int64_t)P * a.max_chunks * G;
+    if (a.chunk == 4) return searches >= 3 * 65536 && (fp8 || paged || relative || G == 8);
+    if (!relative && paged) return searches >= 16384;
+    if (searches < (G == 8 ? 49152 : 98304)) return false;
+    if (fp8) return paged || relative || a.parent_starts != nullptr;
+    return paged || (relative && a.chunk <= (G == 8 ? 64 : 16));
+}
 
 int32_t launch_prune_stage(const ihip_shape &s, const ihip_tensor &q, const ihip_tensor &k,
                            const int32_t *parent_starts, int n_parent, int parent_chunk, int chunk,
@@ -274,9 +302,17 @@ int32_t launch_prune_stage(const ihip_shape &s, const ihip_tensor &q, const ihip
                         (long long)need);
         rope_view = RopeView{rope->cos, rope->sin, rope->n_pos};
         rope_style = style;
+        if (s.b_q == 1 && style == IHIP_ROPE_RELATIVE && !bank && decode_on_tiles(a, P, fp8, true)) {
+            launch_prune_decode_tile(a, P, fp8, &rope_view, s.max_seq_len, st);
+            return check_launch("prune_stage (decode, relative RoPE)");
+        }
         if (s.b_q == 1) return launch_prune_stage_rope(a, rope_view, style, P, fp8, st);
     }
     const RopeView *rv = rope_view.cos ? &rope_view : nullptr;
+    if (s.b_q == 1 && !bank && decode_on_tiles(a, P, fp8, false)) {
+        launch_prune_decode_tile(a, P, fp8, nullptr, s.max_seq_len, st);
+        return check_launch("prune_stage (decode)");
+    }
     if (s.b_q == 1) {
         switch (a.ge.G) {
         case 1: launch_decode<1>(a, P, fp8, st); break;

@@ -209,3 +209,56 @@ def test_keep_everything_with_all_variants_is_rotary_attention(ihip, T):
         logits = torch.einsum("hd,hnd->hn", qr, kr.repeat_interleave(G, 0)) / d ** 0.5
         ref = torch.einsum("hn,hnd->hd", torch.softmax(logits, -1), vf[b, :, :n].repeat_interleave(G, 0))
         assert (out[b, :, 0].cpu().double() - ref).abs().max().item() <= 2e-2, b
+
+
+# Shapes whose stages run on the matrix cores (enough searches, 4 or 8 heads per group), at the edges of those kernels:
+# chunks of 1, 2, 4, 8 and 32 keys, a chunk cut short at the end of the middle range, a last wave that is partly
+# empty, kept lists with holes, more pages per chunk than a wave keeps, K rows further apart than 32-bit offsets reach.
+TILE_CASES = [
+    dict(G=8, Hkv=2, B=1, T=52003, stages=((8, 6144), (4, 512)), rope=False, fp8=False, paged=0),
+    dict(G=8, Hkv=2, B=1, T=52003, stages=((8, 6144), (4, 512)), rope=True, fp8=False, paged=0),
+    dict(G=8, Hkv=2, B=1, T=52003, stages=((8, 6144), (4, 512)), rope=True, fp8=False, paged=0, far=True),
+    dict(G=8, Hkv=2, B=1, T=52003, stages=((8, 6144), (4, 512)), rope=False, fp8=True, paged=0),
+    dict(G=8, Hkv=2, B=1, T=52003, stages=((8, 6144), (4, 512)), rope=True, fp8=True, paged=16),
+    dict(G=4, Hkv=1, B=2, T=67003, stages=((32, 1024), (2, 256)), rope=False, fp8=False, paged=1),
+    dict(G=4, Hkv=4, B=1, T=51003, stages=((8, 6144), (4, 3072), (1, 500)), rope=True, fp8=True, paged=64),
+    dict(G=4, Hkv=4, B=1, T=51003, stages=((8, 6144), (1, 500)), rope=False, fp8=True, paged=0),
+    dict(G=4, Hkv=4, B=1, T=51003, stages=((8, 6144), (4, 3072)), rope=True, fp8=False, paged=16),
+]
+
+
+@pytest.mark.parametrize("c", TILE_CASES, ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items() if k != "stages"))
+def test_matrix_core_decode_stages(ihip, orc, c):
+    w = configs.shrink(configs.CFG1, T=c["T"], B=c["B"], Hq=c["Hkv"] * c["G"], Hkv=c["Hkv"], stages=c["stages"], n_needles=0)
+    sl = torch.tensor([w.T, w.T - 1001][:w.B], dtype=torch.int32)
+    case = Case(ihip, orc, w, sl, c["rope"], c["fp8"], c["paged"])
+    kd = case.kd
+    if c.get("far"):              # one token every 84 KB: the slab is 4.4 GB long
+        far = torch.empty((w.T, 42000), dtype=torch.bfloat16, device="cuda")
+        view = far[:, :w.Hkv * w.d].view(w.T, w.Hkv, w.d).permute(1, 0, 2).unsqueeze(0)
+        view.copy_(kd)
+        kd = view
+    qd, sld = case.q.cuda(), sl.cuda()
+    L = ihip.Layer(qd, kd, sld, 1, w.n_sink, w.n_stream)
+    blocks = torch.empty((L.P, case.keeps[-1]), dtype=torch.int32, device="cuda")
+    L.decode_layer(qd, kd, case.vd, case.chunks, case.keeps, out_blocks=blocks, **case.layer_kwargs())
+    o = case.oracle(orc)
+    prs = {}
+    for b in range(w.B):
+        for g in range(w.Hkv):
+            prs[b, g] = o.prune(b, g, 0, w.stages)
+            kp = blocks[b * w.Hkv + g].cpu().numpy()
+            assert np.array_equal(kp[kp >= 0], prs[b, g].block_starts), (b, g)
+    if c["fp8"] or c["paged"]:
+        return
+    # scores and representatives of every stage, which the layer call does not return
+    parents, pchunk = None, 0
+    for i, (l_c, keep) in enumerate(w.stages):
+        scores, rep = L.prune_stage(qd, kd, l_c, parents, pchunk, want_rep=True, rope=case.rope)
+        parents, pchunk = L.select_blocks(scores, l_c, keep, parents, pchunk), l_c
+        for (b, g), pr in prs.items():
+            st = pr.stages[i]
+            n, p = len(st.starts), b * w.Hkv + g
+            assert np.array_equal(scores[p, :n].cpu().numpy(), st.scores) and torch.isneginf(scores[p, n:]).all(), (b, g, i)
+            rp = rep[b, g * w.G:(g + 1) * w.G, 0].cpu().numpy()
+            assert np.array_equal(rp[:, :n], st.reps) and (rp[:, n:] == -1).all(), (b, g, i)
