@@ -250,6 +250,13 @@ def test_select_blocks_many_problems(ihip, orc, n, keep, ties):
     select_case(ihip, orc, 260, n, keep, ties)
 
 
+@pytest.mark.parametrize("n", [1025, 1536, 1537, 2049, 2560, 2561, 3073, 3584, 3585, 4096, 4097, 5120, 5121, 6145, 7168,
+                               7169, 8193])
+def test_select_blocks_slots_per_thread(ihip, orc, n):
+    """Many problems: the edges between 6, 8, 10, 12, 14 and 16 slots per thread in 256 and 512 threads."""
+    select_case(ihip, orc, 257, n, n // 7, n % 2 == 0)
+
+
 def test_decode_layer_under_graph_capture(ihip, orc):
     """The fused layer call allocates nothing and never synchronises, so it can be captured into a
     HIP graph; every replay (with eager work in between, new queries written in place) must give
