@@ -19,6 +19,7 @@
 // stamp (every slot would look "touched in this call" and replacement would
 // stop), so calls on a stream under capture are refused (refuse_capture).
 #include "block_select.h"
+#include <algorithm>
 
 namespace ihip {
 
@@ -88,11 +89,16 @@ __global__ void cache_init_kernel(const Bank b, const int n_gb)
     if (blockIdx.x == 0 && threadIdx.x < 8) b.counters[threadIdx.x] = 0;
 }
 
-// miss flags -> ascending miss list; counts; clears the flags.  One workgroup;
+// miss flags -> ascending miss list; counts; clears the flags.  One workgroup per bank;
 // the 0/1 byte flags are read 16 at a time (the arrays are padded and zeroed
 // to a multiple of 16).
-__global__ __launch_bounds__(kCacheThreads) void cache_collect_kernel(const Bank b, const int n_gb)
+// The three update kernels take both banks: the banks have nothing to do with each other, and one bank's workgroup
+// leaves the chip idle (an update of two small banks is six launches' latencies, or three).
+struct BankPair { Bank b[2]; };
+
+__global__ __launch_bounds__(kCacheThreads) void cache_collect_kernel(const BankPair banks, const int n_gb)
 {
+    const Bank &b = banks.b[blockIdx.x];
     __shared__ uint32_t wave_miss[kCacheThreads / 64], wave_touch[kCacheThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int n16 = (n_gb + 15) >> 4;
@@ -137,9 +143,10 @@ __global__ __launch_bounds__(kCacheThreads) void cache_collect_kernel(const Bank
 // The least recently used slots that will be replaced, ascending slot order:
 // as many as there were misses, but only slots not touched in this call
 // (swapping two blocks that were both just used would only burn host-link
-// bandwidth).  One workgroup.
-__global__ __launch_bounds__(kCacheThreads) void cache_victims_kernel(const Bank b, const uint32_t stamp)
+// bandwidth).  One workgroup per bank.
+__global__ __launch_bounds__(kCacheThreads) void cache_victims_kernel(const BankPair banks, const uint32_t stamp)
 {
+    const Bank &b = banks.b[blockIdx.x];
     __shared__ SelectScratch<kCacheThreads> scratch;
     __shared__ uint32_t sh_eligible;
     if (threadIdx.x == 0) sh_eligible = 0;
@@ -160,15 +167,16 @@ __global__ __launch_bounds__(kCacheThreads) void cache_victims_kernel(const Bank
         scratch);
 }
 
-// workgroup i: evict victims[i], install miss_list[i] there and copy its rows from host memory
-__global__ __launch_bounds__(256) void cache_insert_kernel(const Bank b, const ihip_tensor hk, const ihip_tensor hv,
+// workgroup i (of bank blockIdx.y): evict victims[i], install miss_list[i] there and copy its rows from host memory
+__global__ __launch_bounds__(256) void cache_insert_kernel(const BankPair banks, const ihip_tensor hk, const ihip_tensor hv,
                                                            const int Hkv, const int64_t T_alloc, const int block_log2,
                                                            const int blocks_per_head, const uint32_t stamp,
                                                            const int row_units, const int32_t *host_table,
                                                            const int host_table_stride, const int host_page_log2)
 {
+    const Bank &b = banks.b[blockIdx.y];
     const int i = blockIdx.x;
-    if (i >= (int)b.counters[4]) return;
+    if (i >= (int)b.counters[4]) return;             // at most n_slots of them
     const int gb = b.miss_list[i];
     const int slot = b.victims[i];
     if (threadIdx.x == 0) {
@@ -386,25 +394,23 @@ int32_t ihip_cache_update(ihip_cache *c, void *stream)
     hipStream_t st = (hipStream_t)stream;
     const int32_t rc = refuse_capture("ihip_cache_update", st);
     if (rc != IHIP_OK) return rc;
-    for (int w = 0; w < 2; ++w) {
-        const Bank &b = c->bank[w];
-        {
-            KernelTimer t(w == 0 ? "cache_collect.mask" : "cache_collect.sa", st);
-            hipLaunchKernelGGL(cache_collect_kernel, dim3(1), dim3(kCacheThreads), 0, st, b, c->n_gb);
-        }
-        {
-            KernelTimer t(w == 0 ? "cache_victims.mask" : "cache_victims.sa", st);
-            hipLaunchKernelGGL(cache_victims_kernel, dim3(1), dim3(kCacheThreads), 0, st, b, c->stamp);
-        }
-        {
-            KernelTimer t(w == 0 ? "cache_insert.mask" : "cache_insert.sa", st);
-            ihip_tensor hk = c->host_k, hv = c->host_v;      // the kernel counts in 2-byte units
-            if (c->row_units != kD)
-                for (ihip_tensor *x : {&hk, &hv}) { x->stride_b /= 2; x->stride_h /= 2; x->stride_t /= 2; }
-            hipLaunchKernelGGL(cache_insert_kernel, dim3(b.n_slots), dim3(256), 0, st, b, hk, hv, c->Hkv,
-                               c->T_alloc, c->block_log2, c->blocks_per_head, c->stamp, c->row_units,
-                               c->host_table, c->host_table_stride, c->host_page_log2);
-        }
+    const BankPair banks{{c->bank[0], c->bank[1]}};
+    {
+        KernelTimer t("cache_collect", st);
+        hipLaunchKernelGGL(cache_collect_kernel, dim3(2), dim3(kCacheThreads), 0, st, banks, c->n_gb);
+    }
+    {
+        KernelTimer t("cache_victims", st);
+        hipLaunchKernelGGL(cache_victims_kernel, dim3(2), dim3(kCacheThreads), 0, st, banks, c->stamp);
+    }
+    {
+        KernelTimer t("cache_insert", st);
+        ihip_tensor hk = c->host_k, hv = c->host_v;      // the kernel counts in 2-byte units
+        if (c->row_units != kD)
+            for (ihip_tensor *x : {&hk, &hv}) { x->stride_b /= 2; x->stride_h /= 2; x->stride_t /= 2; }
+        hipLaunchKernelGGL(cache_insert_kernel, dim3(std::max(c->bank[0].n_slots, c->bank[1].n_slots), 2), dim3(256), 0, st,
+                           banks, hk, hv, c->Hkv, c->T_alloc, c->block_log2, c->blocks_per_head, c->stamp, c->row_units,
+                           c->host_table, c->host_table_stride, c->host_page_log2);
     }
     c->stamp += 1;
     return check_launch("cache update");
