@@ -403,11 +403,12 @@ __global__ __launch_bounds__(kD * GROUPS) void attn_decode_merge_kernel(const At
 // Splits of the slot list: as many workgroups as the chip holds at once (4 workgroups of 4 waves
 // per CU with the plain kernel's registers), so that no workgroup has to wait for a free slot and
 // run its whole latency chain after the others have drained -- with 256-slot splits the cfg3 shape
-// had 1344 workgroups for 1024 places.  Up to 1024 slots per split, a multiple of 16, and at least 64 (`fine`), which is
-// one batch of loads of every 16-lane group: with few problems the kernel is one chain of latencies, and a
-// split of 256 slots walks its loop four times while most of the chip is idle (8 problems of 1,664 slots: 14.3 us with
-// 256, 8.9 with 64; of 3,200 slots 15.0 and 11.2).  Finer splits take more scratch; with scratch for the coarse
-// ones only (at least 256 slots), those are used.
+// had 1344 workgroups for 1024 places.  Between 256 and 1024 slots per split, a multiple of 16.
+// `fine`: where splits of 256 slots would not even give every CU one workgroup, the kernel is one chain of latencies and a
+// split walks its loop four times while most of the chip is idle; splits then go down to 64 slots, one
+// batch of loads of every 16-lane group, but to no more than 64 splits, which the merge takes in one trip (8 problems of
+// 1,664 slots: 14.3 us with 256, 8.9 with 64; of 3,200 slots 15.0 and 11.2; but 24 problems of 3,152 slots with 8 heads 27.7 and
+// 30.6).  Finer splits take more scratch; with scratch for the coarse ones only, those are used.
 // wg_per_cu: 4 for the plain kernels, 3 for the RoPE instantiations (more registers).  The workspace
 // is sized for 4, which gives the most splits.
 static int decode_splits(const ihip_shape &s, int n_blocks, int block, bool fine, int *slots_per_split, int wg_per_cu = 4)
@@ -423,7 +424,10 @@ static int decode_splits(const ihip_shape &s, int n_blocks, int block, bool fine
     const int P = std::max(1, s.B * s.Hkv);
     const int places = std::max(1, n_cu * wg_per_cu / P);      // splits per problem that run at once
     int per = ((total + places - 1) / places + 15) / 16 * 16;
-    per = std::min(kAttnMaxSplit, std::max(fine ? kAttnMinSplitFine : kAttnMinSplit, per));
+    int least = kAttnMinSplit;
+    if (fine && (int64_t)P * ((total + kAttnMinSplit - 1) / kAttnMinSplit) < n_cu)
+        least = std::min(kAttnMinSplit, std::max(kAttnMinSplitFine, ((total + 63) / 64 + 15) & ~15));
+    per = std::min(kAttnMaxSplit, std::max(least, per));
     *slots_per_split = per;
     return (total + per - 1) / per;
 }

@@ -312,12 +312,13 @@ def test_empty_batch_is_a_no_op(ihip):
 
 
 @pytest.mark.parametrize("Hkv,G,n_blocks,block,n_stream", [
-    (1, 4, 1024, 4, 1024),        # one problem: 82 splits of 64 slots (merge: more than four groups request ahead)
+    (1, 4, 1024, 4, 1024),        # one problem: 55 splits of 96 slots
     (1, 8, 37, 16, 333),          # 17 splits, the last one of 13 slots: just past the one-group merge
     (8, 4, 128, 4, 1024),         # 26 splits
-    (2, 1, 0, 4, 40),             # one split, no blocks
-    (8, 2, 512, 8, 1000),         # more slots per split than the least
-], ids=["82", "17", "26", "one", "8x5k"])
+    (2, 1, 0, 4, 40),             # splits of 64 slots, no blocks
+    (8, 2, 512, 8, 1000),         # the most splits
+    (16, 2, 128, 8, 3200),        # 18 coarse splits each already fill the chip: the same splits either way
+], ids=["55", "17", "26", "short", "8x5k", "16x4k"])
 def test_attention_splits_fine_and_coarse(ihip, orc, Hkv, G, n_blocks, block, n_stream):
     """The split of the key list follows the scratch: with what ihip_workspace_bytes says splits of 64 slots and more,
     with a byte less (and room for the coarse ones) of 256 and more, both against the oracle (4e-3, as every attention on
