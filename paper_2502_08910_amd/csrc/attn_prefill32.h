@@ -14,9 +14,11 @@
 // kk stands for key 16*kk + 8*(i/4) + 4*half + i%4, and the A operand (V^T) is
 // read to match.
 //
-// On this chip vector and matrix instructions of the waves of a SIMD mostly
-// take turns rather than overlap, so the design goal is few vector
-// instructions per tile besides the softmax itself:
+// A SIMD issues one instruction at a time: a product holds the matrix pipe for
+// 32 cycles but the issue port for about 8, and the vector instructions of
+// another wave fit beside it only if that wave is at its softmax just then.
+// With two waves per SIMD that is often not so, hence few vector instructions
+// per tile besides the softmax itself:
 //  * K and V rows go from global memory straight into LDS (global_load_lds,
 //    16 bytes per lane: 16 lanes fetch one 256-byte row, 4 rows per
 //    instruction, landing at base + lane*16): no staging registers, no LDS

@@ -25,12 +25,13 @@
 // keys: 150 -> 116 us, in pages 151 -> 117.  Two groups of 32 chunks in turn, one group's rows on their way while the other's are
 // multiplied, were no faster than one (850): twice the LDS round trips.
 //
-// Two waves per query head, 32 queries each.  They fetch half of a level's candidate rows each into a tile of the head and exchange their maxima over the queries through LDS.  Both are handshakes of the two
-// waves, not workgroup barriers (which would put all waves of the workgroup in step): a wave does its part, raises its turn
-// counter (LDS keeps a wave's requests in order) and goes on once the other's counter has reached the same
-// turn.  Both raise before they wait and both are resident (one workgroup), so the wait ends; it is bounded all the same.  Two tiles per
-// head: rows of the next level land in one while late scores read the other.
-// QS = 1 (smaller blocks): one wave and one tile per head; late scores come before the next request.
+// Two waves per query head, 32 queries each.  They fetch half of a level's candidate rows each into a tile of the head and
+// exchange their maxima over the queries through LDS.  Both are handshakes of the two waves, not workgroup barriers
+// (which would put all waves of the workgroup in step): a wave does its part, raises its turn counter (LDS keeps a
+// wave's requests in order) and goes on once the other's counter has reached the same turn.  Both raise before they
+// wait and both are resident (one workgroup), so the wait ends; it is bounded all the same.  Two tiles per head: rows of
+// the next level land in one while late scores read the other.  Blocks of 16 and 32 queries need one wave per head and
+// run in prune_prefill_kernel.
 #pragma once
 
 #include "prune_prefill.h"
