@@ -141,8 +141,9 @@ __global__ __launch_bounds__(kAttnThreads) void attn_decode_split_kernel(const A
         block_slots = a.n_blocks << a.block_log2;
         block_tokens = sh_block_tokens;
         const int n_sel = n_sink_eff + block_tokens + max(0, pr.E - w0);
-        const float4 c = *reinterpret_cast<const float4 *>(a.rope_cos + (int64_t)(n_sel - 1) * (kD / 2) + l16 * 4);
-        const float4 sn = *reinterpret_cast<const float4 *>(a.rope_sin + (int64_t)(n_sel - 1) * (kD / 2) + l16 * 4);
+        const int64_t q_at = (int64_t)max(n_sel - 1, 0) * (kD / 2) + l16 * 4;      // (an empty sequence attends to nothing)
+        const float4 c = *reinterpret_cast<const float4 *>(a.rope_cos + q_at);
+        const float4 sn = *reinterpret_cast<const float4 *>(a.rope_sin + q_at);
         const float cc[4] = {c.x, c.y, c.z, c.w}, ss[4] = {sn.x, sn.y, sn.z, sn.w};
 #pragma unroll
         for (int h = 0; h < G; ++h) {

@@ -262,3 +262,45 @@ def test_matrix_core_decode_stages(ihip, orc, c):
             assert np.array_equal(scores[p, :n].cpu().numpy(), st.scores) and torch.isneginf(scores[p, n:]).all(), (b, g, i)
             rp = rep[b, g * w.G:(g + 1) * w.G, 0].cpu().numpy()
             assert np.array_equal(rp[:, :n], st.reps) and (rp[:, n:] == -1).all(), (b, g, i)
+
+
+# Batches with idle places (no keys) and sequences that end before their middle range.
+IDLE_CASES = [
+    dict(G=4, Hkv=2, T=9003, stages=((16, 128), (4, 64)), rope=True, fp8=False, paged=0),
+    dict(G=4, Hkv=2, T=9003, stages=((16, 128), (4, 64)), rope=True, fp8=False, paged=16, prune_style="chunk"),
+    dict(G=1, Hkv=2, T=9003, stages=((16, 128), (4, 64)), rope=False, fp8=True, paged=16),
+]
+
+
+@pytest.mark.parametrize("c", IDLE_CASES, ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items() if k != "stages"))
+def test_idle_and_short_sequences_in_a_decode_batch(ihip, orc, c):
+    """Every key and every page behind a sequence's length holds NaN (block-table entries there name such pages):
+    nothing of it may reach another sequence, a sequence without chunks keeps no block, one without keys reads none."""
+    w = configs.shrink(configs.CFG1, T=c["T"], B=4, Hq=c["Hkv"] * c["G"], Hkv=c["Hkv"], stages=c["stages"], n_needles=0)
+    sl = torch.tensor([0, w.T, w.n_sink + w.n_stream - 1, w.T - 1001], dtype=torch.int32)
+    case = Case(ihip, orc, w, sl, c["rope"], c["fp8"], c["paged"], prune_style=c.get("prune_style", "relative"))
+    nan = 0x7f if c["fp8"] else float("nan")
+    for b, n in enumerate(sl.tolist()):
+        case.kd[b, :, n:] = nan
+        case.vd[b, :, n:] = nan
+        if case.paged is not None:
+            behind = case.paged.block_table[b, -(-n // c["paged"]):].long()
+            case.paged.k_pool[behind] = nan
+            case.paged.v_pool[behind] = nan
+    qd = case.q.cuda()
+    L = ihip.Layer(qd, case.kd, sl.cuda(), 1, w.n_sink, w.n_stream)
+    blocks = torch.empty((L.P, case.keeps[-1]), dtype=torch.int32, device="cuda")
+    out = L.decode_layer(qd, case.kd, case.vd, case.chunks, case.keeps, out_blocks=blocks, **case.layer_kwargs())
+    torch.cuda.synchronize()
+    o = case.oracle(orc)
+    for b in range(w.B):
+        for g in range(w.Hkv):
+            kp = blocks[b * w.Hkv + g].cpu().numpy()
+            if b in (0, 2):
+                assert (kp == -1).all(), (b, g)
+            if b == 0:
+                continue
+            pr = o.prune(b, g, 0, w.stages)
+            assert np.array_equal(kp[kp >= 0], pr.block_starts), (b, g)
+            ref, _ = o.attend(b, g, 0, pr.block_starts, pr.block_lens)
+            assert np.abs(out[b, g * w.G:(g + 1) * w.G, 0].float().cpu().numpy() - ref[:, 0]).max() <= 2e-2, (b, g)
