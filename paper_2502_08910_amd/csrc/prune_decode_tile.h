@@ -128,6 +128,20 @@ struct DecodeRows {
     }
 };
 
+// What a wave without a single chunk writes for its n <= 64 slots j0..
+template <int G>
+__device__ inline void write_no_chunks(const PruneArgs &a, const Problem &pr, int p, int j0, int n)
+{
+    const int i = threadIdx.x & 63, j = j0 + i;
+    if (i >= n || j >= a.max_chunks) return;
+    a.out_scores[(int64_t)p * a.max_chunks + j] = -INFINITY;
+    if (a.out_rep == nullptr) return;
+    for (int h = 0; h < G; ++h) {
+        const int64_t row = (int64_t)(pr.b * a.ge.Hq + pr.g * G + h) * a.ge.Mq + pr.m;
+        a.out_rep[row * a.max_chunks + j] = -1;
+    }
+}
+
 constexpr int kDecodePages = 16;              // page ids of a chunk kept in LDS; further ones are looked up in the table
 
 template <int G, bool ROPE, int SRC, bool KV8, bool NARROW>
@@ -156,6 +170,13 @@ __global__ __launch_bounds__(256) void prune_decode_tile_kernel(const PruneArgs 
     const int start = j < a.max_chunks ? slot_start(pr, a.parent_starts, a.n_parent, a.ratio_log2, a.chunk, p, j) : -1;
     const bool valid = start >= 0;
     const int len = valid ? min(a.chunk, pr.hi - start) : 0;
+    // No chunk at all (a sequence that ends before its middle range, an idle place of the batch, the tail of a short list):
+    // nothing may be read.  Where the wave has a chunk, lanes without one read key 0 of the sequence: it is there, since a
+    // chunk starts below pr.hi <= its length.
+    if (__ballot(valid) == 0) {
+        write_no_chunks<G>(a, pr, p, j0, kChunks);
+        return;
+    }
 
     bf16x8 q[PARTS][4];
     {
@@ -172,9 +193,8 @@ __global__ __launch_bounds__(256) void prune_decode_tile_kernel(const PruneArgs 
         for (int c0 = 0; c0 < kChunks; c0 += 4) {
             const int c = c0 + kq, cr = (c % kPerTile) * G;
             const int first = __shfl(base, (cr >> 2) * 16 + (c / kPerTile) * 4 + (cr & 3), 64) >> rows.page_log2;
-            const int e = min(first + n, a.paged.table_stride - 1);
-            // entries beyond a sequence's length may hold anything: fetched but not used
-            pages[c * kDecodePages + n] = rows.table[e];
+            // entries beyond the sequence's length are not read
+            pages[c * kDecodePages + n] = rows.table[min(first + n, (pr.hi - 1) >> rows.page_log2)];
         }
         asm volatile("" ::: "memory");        // lanes read what other lanes of the wave wrote (LDS keeps the order)
     }
@@ -280,6 +300,21 @@ __global__ __launch_bounds__(256) void prune_decode_four_kernel(const PruneArgs 
     const int j0 = (blockIdx.x * (blockDim.x >> 6) + wv) * NT * 4;
     if (j0 >= a.max_chunks) return;
     const Rows rows(a, pr);
+    // as the loader of row n: key n % 4 of chunk n / 4 of the tile (its first key where the chunk is cut short; without a
+    // chunk key 0 of the sequence, unless the whole wave has none: see prune_decode_tile_kernel)
+    int key[NT];
+    bool any = false;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int j = j0 + t * 4 + (n >> 2);
+        const int start = j < a.max_chunks ? slot_start(pr, a.parent_starts, a.n_parent, a.ratio_log2, a.chunk, p, j) : -1;
+        key[t] = start >= 0 ? (start + (n & 3) < pr.hi ? start + (n & 3) : start) : 0;
+        any = any || start >= 0;
+    }
+    if (__ballot(any) == 0) {
+        write_no_chunks<G>(a, pr, p, j0, NT * 4);
+        return;
+    }
     const int hd = G == 8 ? (n & 7) : n % G;
     bf16x8 q[PARTS][4];
     decode_query_operands<KV8, PARTS>(a.q + pr.b * a.q_sb + (int64_t)(pr.g * G + hd) * a.q_sh + (int64_t)pr.m * a.q_st, kq, rope,
@@ -287,14 +322,10 @@ __global__ __launch_bounds__(256) void prune_decode_four_kernel(const PruneArgs 
     uint4 raw[NT][kLoads];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-        // as the loader of row n: key n % 4 of chunk n / 4 of the tile (its first key where the chunk is cut short)
-        const int j = j0 + t * 4 + (n >> 2);
-        const int start = j < a.max_chunks ? slot_start(pr, a.parent_starts, a.n_parent, a.ratio_log2, a.chunk, p, j) : -1;
-        const int pos = start >= 0 ? (start + (n & 3) < pr.hi ? start + (n & 3) : start) : 0;
         int page = 0;
-        if constexpr (SRC == 2) page = rows.table[pos >> rows.page_log2];
+        if constexpr (SRC == 2) page = rows.table[key[t] >> rows.page_log2];
 #pragma unroll
-        for (int i = 0; i < kLoads; ++i) raw[t][i] = rows.load(rows.at(pos, page), i * 64 + kq * 16);
+        for (int i = 0; i < kLoads; ++i) raw[t][i] = rows.load(rows.at(key[t], page), i * 64 + kq * 16);
     }
 #pragma unroll
     for (int t = 0; t < NT; ++t) {

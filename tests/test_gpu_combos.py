@@ -269,6 +269,10 @@ IDLE_CASES = [
     dict(G=4, Hkv=2, T=9003, stages=((16, 128), (4, 64)), rope=True, fp8=False, paged=0),
     dict(G=4, Hkv=2, T=9003, stages=((16, 128), (4, 64)), rope=True, fp8=False, paged=16, prune_style="chunk"),
     dict(G=1, Hkv=2, T=9003, stages=((16, 128), (4, 64)), rope=False, fp8=True, paged=16),
+    # large enough for the matrix-core kernels
+    dict(G=8, Hkv=2, T=52003, stages=((8, 6144), (4, 512)), rope=True, fp8=False, paged=16),
+    dict(G=4, Hkv=4, T=51003, stages=((8, 6144), (4, 512)), rope=False, fp8=True, paged=16),
+    dict(G=4, Hkv=4, T=51003, stages=((8, 6144), (4, 512)), rope=True, fp8=True, paged=0),
 ]
 
 
