@@ -22,6 +22,16 @@ int32_t fail(int32_t code, const char *fmt, ...)
     return code;
 }
 
+int compute_units()
+{
+    static const int n = [] {
+        int dev = 0, cu = 0;
+        return hipGetDevice(&dev) == hipSuccess &&
+                       hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cu > 0 ? cu : 256;
+    }();
+    return n;
+}
+
 int32_t check_launch(const char *what)
 {
     const hipError_t e = hipGetLastError();

@@ -19,6 +19,8 @@ constexpr int kWave = 64;
 int32_t fail(int32_t code, const char *fmt, ...);
 int32_t check_launch(const char *what);
 
+int compute_units();                // of the current device at the first call (api.hip)
+
 // ---- optional per-kernel timing (api.hip) ----------------------------------
 // When profiling is on, a KernelTimer brackets one kernel launch with two HIP
 // events on the launch stream; ihip_profile_read() sums them up per name.

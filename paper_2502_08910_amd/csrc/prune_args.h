@@ -27,6 +27,13 @@ struct PruneArgs {
                               // count 2-byte units of the byte rows)
 };
 
+// Decode on the matrix cores (prune_decode_tile.h): chunks a wave works on, and waves of a workgroup
+constexpr int kDecodeTileWaves = 4;
+__host__ __device__ constexpr int decode_tile_chunks(int G, int chunk, bool rope, bool fp8)
+{
+    return chunk == 4 ? (rope && !fp8 ? 8 : 16) : 64 / G;
+}
+
 // Chunk-indexed RoPE needs the number of chunks this stage really has for problem p (valid slots are
 // a prefix of the slot list: parents are ascending with the empty ones last, and only the last chunk
 // before the end of the middle range can be cut short).  Every thread of the workgroup calls it

@@ -290,7 +290,7 @@ __global__ __launch_bounds__(256) void prune_decode_four_kernel(const PruneArgs 
 {
     static_assert(SRC == 0 || !NARROW, "paged pools are addressed with 64-bit offsets");
     constexpr int PARTS = ROPE ? 3 : 1;
-    constexpr int NT = ROPE && !KV8 ? 2 : 4;  // tiles of a wave, all in flight at once
+    constexpr int NT = decode_tile_chunks(G, 4, ROPE, KV8) / 4;  // tiles of a wave, all in flight at once
     constexpr int kLoads = KV8 ? 2 : 4;
     using Rows = DecodeRows<SRC, NARROW>;
     const int p = blockIdx.y;
@@ -363,9 +363,8 @@ __global__ __launch_bounds__(256) void prune_decode_four_kernel(const PruneArgs 
 template <int G, bool ROPE, int SRC, bool KV8, bool NARROW>
 static void launch_decode_tile_n(const PruneArgs &a, const RopeView &rope, int P, hipStream_t st)
 {
-    const int per_wave = a.chunk == 4 ? (ROPE && !KV8 ? 8 : 16) : 64 / G;
-    constexpr int wg = 4;                     // waves of a workgroup
-    const dim3 grid((a.max_chunks + per_wave * wg - 1) / (per_wave * wg), P), block(64 * wg);
+    const int per_wg = decode_tile_chunks(G, a.chunk, ROPE, KV8) * kDecodeTileWaves;
+    const dim3 grid((a.max_chunks + per_wg - 1) / per_wg, P), block(64 * kDecodeTileWaves);
     KernelTimer timer(stage_name(kNamePruneDecode, a.parent_starts == nullptr, a.chunk), st);
     if (a.chunk == 4) hipLaunchKernelGGL((prune_decode_four_kernel<G, ROPE, SRC, KV8, NARROW>), grid, block, 0, st, a, rope);
     else hipLaunchKernelGGL((prune_decode_tile_kernel<G, ROPE, SRC, KV8, NARROW>), grid, block, 0, st, a, rope);

@@ -235,29 +235,45 @@ void launch_prune_prefill_fp8(const PruneArgs &a, int P, int b_q, const RopeView
 
 // Which decode stages (K through strides or pages; no RoPE or the relative style) go to the matrix-core kernels of
 // prune_decode_tile.h.  Their waves do a fifth of the vector instructions for 64 searches at a time, but a level of
-// theirs is a longer chain, and their loads take 64 bytes of 16 rows where the vector kernels take whole rows: they win where
-// instructions are the bound and many searches run.  Measured (us, vector / tile kernels; 32/8 heads, 4 x 250K keys,
-// stages of 256, 64, 16 and 4, then one sequence of 128K):
-//   E4M3 pages           34.7/21.8 26.7/17.0 20.4/12.5 18.5/15.4;  14.3/12.4 12.7/10.7 10.2/9.5 8.7/10.7
-//   E4M3 pages, relative 39.4/31.3 31.4/24.1 23.9/17.6 26.8/17.9;  14.9/20.2 13.2/16.4 10.6/12.6 9.4/11.0
-//   E4M3                 24.7/26.0 19.1/18.2 14.0/12.8 14.9/12.7;  10.6/11.0 9.6/9.7 8.3/8.0 7.2/8.7
-//   E4M3, relative       30.7/29.9 24.3/23.0 18.6/17.0 21.7/15.5;  11.0/16.6 10.5/14.3 8.7/11.2 8.3/9.9
-//   bf16 pages           48.6/43.1 32.1/29.3 22.2/20.7 20.6/18.8;  14.9/14.5 13.3/13.0 10.4/10.3 8.7/10.3
-//   bf16 pages, relative 47.8/42.2 35.9/29.6 26.0/20.8 27.8/23.3;  15.3/21.1 14.1/17.8 11.1/13.4 9.9/10.2
-//   bf16, relative       42.2/45.9 28.7/29.5 21.1/20.6 22.6/20.8;  12.3/15.1 11.5/13.8 9.2/10.7 8.7/9.3
-//   bf16                 40.3/47.2 27.4/31.3 17.6/20.2 16.0/18.0  (8 heads per group, 2 x 100K: 22.3/25.4 14.8/17.2 14.8/11.1)
-// With one or two heads per group the vector kernels won at every size measured.
+// theirs is a longer chain, their loads take 64 bytes of 16 rows where the vector kernels take whole rows, and their
+// workgroups are a quarter (4 heads) or half as many: they win where instructions are the bound (128-byte rows, two rotated
+// queries, page lookups, 8 heads) and workgroups are no longer scarce, so the lines are drawn in workgroups of theirs per compute
+// unit.  Beside each: time of the vector kernel / time of theirs, below the line and from it on (stages of 1 to 256 keys in layers
+// of 1 to 32 sequences of 16K to 1M keys, 4 and 8 KV heads, 256 CUs).
 static bool decode_on_tiles(const PruneArgs &a, int P, bool fp8, bool relative)
 {
-    const int G = a.ge.G;
-    if (G < 4) return false;
-    const bool paged = a.paged.block_table != nullptr;
-    const int64_t searches = (int64_t)P * a.max_chunks * G;
-    if (a.chunk == 4) return searches >= 3 * 65536 && (fp8 || paged || relative || G == 8);
-    if (!relative && paged) return searches >= 16384;
-    if (searches < (G == 8 ? 49152 : 98304)) return false;
-    if (fp8) return paged || relative || a.parent_starts != nullptr;
-    return paged || (relative && a.chunk <= (G == 8 ? 64 : 16));
+    const int G = a.ge.G, chunk = a.chunk;
+    if (G < 4) return false;                 // one or two heads: the vector kernels won at every size
+    const bool paged = a.paged.block_table != nullptr, many = G == 8;
+    const int per_wg = decode_tile_chunks(G, chunk, relative, fp8) * kDecodeTileWaves;
+    const int64_t wgs = (int64_t)P * ((a.max_chunks + per_wg - 1) / per_wg), cu = compute_units();
+    auto at_least = [&](double per_cu) { return (double)wgs >= per_cu * (double)cu; };
+    auto at_most = [&](double per_cu) { return (double)wgs <= per_cu * (double)cu; };
+    if (chunk == 4) {                        // prune_decode_four_kernel
+        if (many) return at_least(1);        // 0.78-1.18 / 1.00-4.22
+        if (!fp8 && !paged && !relative) return false;                            // 0.72-0.95 throughout
+        return at_least(relative && !fp8 ? 4 : 2);                                // 0.73-1.08 / 1.01-1.95
+    }
+    if (relative && many && chunk < 4) return at_least(5);                        // 0.75-1.26 / 0.97-1.38
+    if (relative && paged) return at_least(!many ? 1.5 : fp8 && chunk >= 16 ? 0.75 : 1.25);      // 0.64-1.17 / 0.99-2.2
+    if (relative && fp8) return at_least(many ? 1.25 : 1.875);                    // 0.55-1.08 / 1.01-2.4
+    if (relative) {
+        if (chunk <= 16) return at_least(1.5);                                    // 0.67-1.05 / 0.98-1.5
+        return many && chunk <= 64 && at_least(5);                                // 0.70-1.22 / 1.02-1.25; longer ones 0.55-1.09
+    }
+    if (fp8 && chunk < 4) return at_least(many ? 4 : 2);                          // 0.91-1.14 / 1.03-1.54
+    if (fp8 && paged) return at_least(0.25);                                      // 1.03-1.88
+    if (fp8) return a.parent_starts != nullptr && at_least(many ? 0.75 : 1.5);    // 0.89-1.2 / 0.96-1.47; first stages 0.93-1.36
+    if (!paged) return false;                                                     // 0.44-1.06 throughout
+    if (!many) {
+        if (chunk <= 16) return at_least(2);                                      // 0.86-1.07 / 1.03-1.32
+        // long chunks: a tie at best, except where two workgroups on every CU leave none idle and none with one more
+        // (1.06-1.19; 0.81-0.95 between one and two, 0.80-1.07 beyond)
+        return at_least(1.875) && at_most(2);
+    }
+    if (chunk < 4) return false;                                                  // 0.79-1.02 throughout
+    if (chunk < 16) return at_least(3);                                           // 0.94-1.03 / 1.10-1.18
+    return (at_least(0.75) && at_most(1)) || at_least(2.5);                       // 0.94-1.09, 1.02-1.16; between them 0.89-1.05, 0.93-1.26
 }
 
 int32_t launch_prune_stage(const ihip_shape &s, const ihip_tensor &q, const ihip_tensor &k,

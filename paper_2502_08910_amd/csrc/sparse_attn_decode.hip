@@ -414,13 +414,7 @@ __global__ __launch_bounds__(kD * GROUPS) void attn_decode_merge_kernel(const At
 // is sized for 4, which gives the most splits.
 static int decode_splits(const ihip_shape &s, int n_blocks, int block, bool fine, int *slots_per_split, int wg_per_cu = 4)
 {
-    static int n_cu = 0;
-    if (n_cu == 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
-            n_cu = 256;
-    }
+    const int n_cu = compute_units();
     const int total = s.n_sink + n_blocks * block + s.n_stream;
     const int P = std::max(1, s.B * s.Hkv);
     const int places = std::max(1, n_cu * wg_per_cu / P);      // splits per problem that run at once

@@ -211,19 +211,22 @@ def test_keep_everything_with_all_variants_is_rotary_attention(ihip, T):
         assert (out[b, :, 0].cpu().double() - ref).abs().max().item() <= 2e-2, b
 
 
-# Shapes whose stages run on the matrix cores (enough searches, 4 or 8 heads per group), at the edges of those kernels:
-# chunks of 1, 2, 4, 8 and 32 keys, a chunk cut short at the end of the middle range, a last wave that is partly
+# Shapes whose stages run on the matrix cores (4 or 8 heads per group, workgroups enough for the compute units), at the edges of
+# those kernels: chunks of 1, 2, 4, 8, 16 and 32 keys, a chunk cut short at the end of the middle range, a last wave that is partly
 # empty, kept lists with holes, more pages per chunk than a wave keeps, K rows further apart than 32-bit offsets reach.
 TILE_CASES = [
     dict(G=8, Hkv=2, B=1, T=52003, stages=((8, 6144), (4, 512)), rope=False, fp8=False, paged=0),
-    dict(G=8, Hkv=2, B=1, T=52003, stages=((8, 6144), (4, 512)), rope=True, fp8=False, paged=0),
-    dict(G=8, Hkv=2, B=1, T=52003, stages=((8, 6144), (4, 512)), rope=True, fp8=False, paged=0, far=True),
+    dict(G=8, Hkv=4, B=1, T=52003, stages=((8, 6144), (4, 512)), rope=True, fp8=False, paged=0),
+    dict(G=8, Hkv=4, B=1, T=52003, stages=((8, 6144), (4, 512)), rope=True, fp8=False, paged=0, far=True),
     dict(G=8, Hkv=2, B=1, T=52003, stages=((8, 6144), (4, 512)), rope=False, fp8=True, paged=0),
-    dict(G=8, Hkv=2, B=1, T=52003, stages=((8, 6144), (4, 512)), rope=True, fp8=True, paged=16),
-    dict(G=4, Hkv=1, B=2, T=67003, stages=((32, 1024), (2, 256)), rope=False, fp8=False, paged=1),
-    dict(G=4, Hkv=4, B=1, T=51003, stages=((8, 6144), (4, 3072), (1, 500)), rope=True, fp8=True, paged=64),
+    dict(G=8, Hkv=4, B=1, T=52003, stages=((8, 6144), (4, 512)), rope=True, fp8=True, paged=16),
+    dict(G=8, Hkv=1, B=2, T=110003, stages=((32, 1024), (4, 256)), rope=False, fp8=False, paged=1),
+    dict(G=4, Hkv=2, B=2, T=67003, stages=((32, 1024), (2, 256)), rope=False, fp8=True, paged=1),
+    dict(G=4, Hkv=4, B=2, T=76003, stages=((16, 4096), (2, 512)), rope=False, fp8=False, paged=4),
+    dict(G=4, Hkv=8, B=1, T=51003, stages=((8, 6144), (4, 3072), (1, 500)), rope=True, fp8=True, paged=64),
     dict(G=4, Hkv=4, B=1, T=51003, stages=((8, 6144), (1, 500)), rope=False, fp8=True, paged=0),
-    dict(G=4, Hkv=4, B=1, T=51003, stages=((8, 6144), (4, 3072)), rope=True, fp8=False, paged=16),
+    dict(G=4, Hkv=8, B=1, T=51003, stages=((8, 6144), (4, 3072)), rope=True, fp8=False, paged=16),
+    dict(G=4, Hkv=8, B=1, T=51003, stages=((8, 6144), (4, 3072), (1, 500)), rope=True, fp8=False, paged=0),
 ]
 
 
@@ -249,12 +252,13 @@ def test_matrix_core_decode_stages(ihip, orc, c):
             prs[b, g] = o.prune(b, g, 0, w.stages)
             kp = blocks[b * w.Hkv + g].cpu().numpy()
             assert np.array_equal(kp[kp >= 0], prs[b, g].block_starts), (b, g)
-    if c["fp8"] or c["paged"]:
-        return
+    if c["rope"] + c["fp8"] + bool(c["paged"]) > 1:
+        return                    # the single-stage call takes one variant at a time
     # scores and representatives of every stage, which the layer call does not return
+    variant = dict(rope=case.rope, k_scale=case.scales[0] if c["fp8"] else None, paged=case.paged)
     parents, pchunk = None, 0
     for i, (l_c, keep) in enumerate(w.stages):
-        scores, rep = L.prune_stage(qd, kd, l_c, parents, pchunk, want_rep=True, rope=case.rope)
+        scores, rep = L.prune_stage(qd, kd, l_c, parents, pchunk, want_rep=True, **variant)
         parents, pchunk = L.select_blocks(scores, l_c, keep, parents, pchunk), l_c
         for (b, g), pr in prs.items():
             st = pr.stages[i]
@@ -262,6 +266,44 @@ def test_matrix_core_decode_stages(ihip, orc, c):
             assert np.array_equal(scores[p, :n].cpu().numpy(), st.scores) and torch.isneginf(scores[p, n:]).all(), (b, g, i)
             rp = rep[b, g * w.G:(g + 1) * w.G, 0].cpu().numpy()
             assert np.array_equal(rp[:, :n], st.reps) and (rp[:, n:] == -1).all(), (b, g, i)
+
+
+@pytest.mark.parametrize("G,Hkv,stages", [(4, 8, ((8, 6144), (4, 512))), (8, 4, ((8, 6144), (4, 512)))], ids=["g4", "g8"])
+def test_matrix_core_decode_rotates_to_fp32(ihip, orc, G, Hkv, stages):
+    """Relative style on a real rotary table: the rotated queries are three bf16 operands (value, rest, rest of the rest).
+    Against the score of the kernel's own representative in 64 bits, RMS over N(0,1) rows: 128 fp32 sums of about 11 give 4e-6,
+    without the last operand (2^-18 of every query element) it is 2.5e-5, without the second 1e-2.  The searches against
+    the fp32 oracle: near ties, within 1e-4 of a difference that has standard deviation 16, are 1e-5 of the six comparisons
+    of 8 keys at most."""
+    w = configs.shrink(configs.CFG1, T=51003, B=1, Hq=Hkv * G, Hkv=Hkv, stages=stages, n_needles=0)
+    q, k, v, sl, _ = configs.make_inputs(w, 8)
+    cos, sin = gen.rope_table(w.n_stream + 2, w.d)
+    o = orc.Oracle(q, k, v, sl.tolist(), 1, w.n_sink, w.n_stream, rope=orc.RopeSpec(cos.numpy(), sin.numpy(), prune="relative"))
+    qd, kd = q.cuda(), k.cuda()
+    L = ihip.Layer(qd, kd, sl.cuda(), 1, w.n_sink, w.n_stream)
+    rope = ihip.Rope(cos.cuda(), sin.cuda(), ihip.ROPE_RELATIVE, ihip.ROPE_NONE)
+    prs = [o.prune(0, g, 0, stages) for g in range(Hkv)]
+    c, s = cos[w.n_stream].double().cuda(), sin[w.n_stream].double().cuda()
+    x = qd[0, :, 0].double()
+    qr = torch.stack((x[:, 0::2] * c - x[:, 1::2] * s, x[:, 0::2] * s + x[:, 1::2] * c), dim=-1).flatten(1)
+    parents, pchunk = None, 0
+    for i, (l_c, keep) in enumerate(stages):
+        scores, rep = L.prune_stage(qd, kd, l_c, parents, pchunk, want_rep=True, rope=rope)
+        flips = total = 0
+        for g in range(Hkv):
+            st = prs[g].stages[i]
+            n, heads = len(st.starts), slice(g * G, (g + 1) * G)
+            r = rep[0, heads, 0, :n].long()
+            exact = torch.stack([(kd[0, g][r[h]].double() * qr[g * G + h]).sum(-1) for h in range(G)]).amax(0)
+            err = scores[g, :n].double() - exact
+            assert err.pow(2).mean().sqrt().item() <= 1e-5 and err.abs().max().item() <= 1e-4, (i, g)
+            flips += (r.cpu().numpy() != st.reps).sum()
+            total += r.numel()
+        assert flips <= 1e-4 * total, (i, flips, total)
+        starts = np.full((Hkv, keep), -1, np.int32)          # the oracle's list, so that the stages stay comparable
+        for g in range(Hkv):
+            starts[g, :len(prs[g].stages[i].kept_starts)] = prs[g].stages[i].kept_starts
+        parents, pchunk = torch.from_numpy(starts).cuda(), l_c
 
 
 # Batches with idle places (no keys) and sequences that end before their middle range.
