@@ -89,6 +89,11 @@ __global__ __launch_bounds__(64 * NQ * G, NQ * G <= 8 ? 2 : 4) void attn_prefill
     static_assert(!KV8 || WIDE, "E4M3 rows are addressed with 64-bit offsets");
     constexpr int kPfStages = KV8 ? kPfStagesFp8 : ROPE ? kPfStagesRope : kPfStagesPlain;
     constexpr bool kTouch = ROPE || KV8;             // a tile is worked on in LDS between landing and first read
+    // A period's operands are requested up front (see there), unless the table pieces that one or two waves hold for their
+    // rotations, 64 or 32 registers, leave no room: 1,024 queries, 3,200 key slots each, two waves 164 us in order, 300 with
+    // operands spilled (72-140 bytes per lane), E4M3 170 and 283, one wave 783 and 846.  One wave over pages spills more than
+    // 300 bytes either way: 970 and 936.
+    constexpr bool kUpFront = !ROPE || NQ * G > 2 || (NQ * G == 1 && PAGED && !KV8);
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     uint16_t *raw0 = smem + kPfStages * kPfStageEl;                          // KV8: the raw stages
     int *sPos = reinterpret_cast<int *>(raw0 + (KV8 ? kPfRawStages * kPfTileEl : 0));   // one int per key slot
@@ -372,6 +377,27 @@ __global__ __launch_bounds__(64 * NQ * G, NQ * G <= 8 ? 2 : 4) void attn_prefill
             (__attribute__((address_space(3))) s16x4 *)(cV + voff[dt] + (16 * kk + 8) * kD));
         return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     };
+    // the same two products with every operand read where it is used
+    auto scores_in_order = [&](int st) -> f32x16 {
+        const uint16_t *cK = stage_of(st) + n * kD;
+        f32x16 s;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            const bf16x8 ka = *reinterpret_cast<const bf16x8 *>(&cK[((ks * 2 + half) ^ (n & 15)) * 8]);
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qb[ks], s, 0, 0, 0);
+        }
+        return s;
+    };
+    auto accumulate_in_order = [&](int st, const bf16x8 (&pb)[2]) {
+        const uint16_t *cV = stage_of(st);
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk)
+                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(cV, dt, kk), pb[kk], o[dt], 0, 0, 0);
+    };
     auto v_operands = [&](const uint16_t *cV, bf16x8 (&va)[4][2]) {
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt)
@@ -411,8 +437,7 @@ __global__ __launch_bounds__(64 * NQ * G, NQ * G <= 8 ? 2 : 4) void attn_prefill
         if constexpr (KV8) request(3, 3, rows_of(3));       // into the raw stage tile 0 has left
     }
     bf16x8 ka[8];
-    k_operands(0, ka);
-    f32x16 s_nxt = scores(ka);
+    f32x16 s_nxt = scores_in_order(0);
     bf16x8 pb[2];
     if (sMasked[0] != 0) mask_scores(0, s_nxt);
     settle(s_nxt, exponentials(s_nxt, pb), pb);
@@ -425,37 +450,47 @@ __global__ __launch_bounds__(64 * NQ * G, NQ * G <= 8 ? 2 : 4) void attn_prefill
         Table table_nxt{};
         if constexpr (ROPE) table_nxt = table_of(tile + 3);
         request(tile + D, ST + D, rows);
-        // All operands of the period are requested from LDS up front: the matrix products of a wave are
-        // a chain, and with two waves per SIMD an LDS round trip in front of every one or two of them
-        // is not covered.  64 more registers, which two waves per SIMD leave free (196 of 256).
-        // Measured with the interleaving below: 371 -> 350 us (4,096 queries, 32 heads, 5,440 key
-        // slots each), with RoPE 223 -> 211, E4M3 + RoPE 411 -> 387 (2,048 queries).  The same kernel
-        // without requests, barriers and softmax takes 248 us, and 234 with the operands held in
-        // registers: the chip's clock under dense matrix work is what is left.
-        bf16x8 va[4][2];
-        k_operands(ST + 1, ka);
-        v_operands(stage_of(ST), va);
-        s_nxt = scores(ka);
-        __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+        if constexpr (!kUpFront) {
+            s_nxt = scores_in_order(ST + 1);
+            accumulate_in_order(ST, pb);
+            if (masked_nxt != 0) mask_scores(tile + 1, s_nxt);
+            settle(s_nxt, exponentials(s_nxt, pb), pb);
+        } else {
+            // All operands of the period are requested from LDS up front: the matrix products of a wave are
+            // a chain, and with two waves per SIMD an LDS round trip in front of every one or two of them
+            // is not covered.  30 more registers (four waves and more: 194-198 without RoPE, 214-244 with it), which two
+            // waves per SIMD leave free.  The plain kernel's 166 had room for a third in workgroups of four waves; two
+            // are faster all the same (32-query blocks of four heads 87 -> 82 us, 64-query blocks of two 85 -> 74; 1,024
+            // queries, 3,200 key slots each).
+            // Measured with the interleaving below: 371 -> 350 us (4,096 queries, 32 heads, 5,440 key
+            // slots each), with RoPE 223 -> 211, E4M3 + RoPE 411 -> 387 (2,048 queries).  The same kernel
+            // without requests, barriers and softmax takes 248 us, and 234 with the operands held in
+            // registers: the chip's clock under dense matrix work is what is left.
+            bf16x8 va[4][2];
+            k_operands(ST + 1, ka);
+            v_operands(stage_of(ST), va);
+            s_nxt = scores(ka);
+            __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        }
-        if (masked_nxt != 0) mask_scores(tile + 1, s_nxt);
-        // The second product of this tile and the exponentials of the next one are independent: one
-        // straight-line block, interleaved so that the vector instructions run under the matrix ones.
-        bf16x8 pb_nxt[2];
-        accumulate(va, pb);
-        const float ps = exponentials(s_nxt, pb_nxt);
+            for (int i = 0; i < 8; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            }
+            if (masked_nxt != 0) mask_scores(tile + 1, s_nxt);
+            // The second product of this tile and the exponentials of the next one are independent: one
+            // straight-line block, interleaved so that the vector instructions run under the matrix ones.
+            bf16x8 pb_nxt[2];
+            accumulate(va, pb);
+            const float ps = exponentials(s_nxt, pb_nxt);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
-            __builtin_amdgcn_sched_group_barrier(0x002, 7, 1);
+            for (int i = 0; i < 8; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
+                __builtin_amdgcn_sched_group_barrier(0x002, 7, 1);
+            }
+            settle(s_nxt, ps, pb_nxt);
+            pb[0] = pb_nxt[0];
+            pb[1] = pb_nxt[1];
         }
-        settle(s_nxt, ps, pb_nxt);
-        pb[0] = pb_nxt[0];
-        pb[1] = pb_nxt[1];
         masked_nxt = tile + 2 < n_tiles ? sMasked[tile + 2] : 0;
         rows = rows_of(tile + D + 1);
         if constexpr (kTouch) {
@@ -485,11 +520,7 @@ __global__ __launch_bounds__(64 * NQ * G, NQ * G <= 8 ? 2 : 4) void attn_prefill
                     std::integral_constant<int, 5>{});
     }
 
-    {                                       // second product of the last tile
-        bf16x8 va[4][2];
-        v_operands(stage_of(n_tiles - 1), va);
-        accumulate(va, pb);
-    }
+    accumulate_in_order(n_tiles - 1, pb);   // second product of the last tile
 
     float l = l_run;
     l += __shfl_xor(l, 32, 64);

@@ -250,6 +250,46 @@ def test_streaming_attention_alone_on_oracle_indices(ihip, orc):
         assert np.abs(got - ref).max() <= 2e-2
 
 
+@pytest.mark.parametrize("variant", ["bf16", "fp8", "paged"])
+@pytest.mark.parametrize("b_q,Hq,Hkv", [(64, 2, 2), (32, 2, 2), (32, 4, 2), (64, 4, 2)], ids=["bq64-g1", "bq32-g1", "bq32-g2", "bq64-g2"])
+def test_streaming_attention_of_one_two_and_four_waves(ihip, orc, b_q, Hq, Hkv, variant):
+    """The rotations of one- and two-wave workgroups take another loop body than those of four and more; several tiles, a
+    masked and an unmasked one, first and last.  2e-2 as above: operands rounded to bf16 after their rotation."""
+    w = small(Tq=128, prefix=1500, b_q=b_q, Hq=Hq, Hkv=Hkv, stages=((64, 6), (16, 20)))
+    q, k, v, sl, _ = configs.make_inputs(w, 9)
+    cos, sin = gen.rope_table(2048, w.d)
+    scales = (1.0 / 32, 1.0 / 64) if variant == "fp8" else None
+    if scales:
+        k, v = gen.to_e4m3(k, scales[0]), gen.to_e4m3(v, scales[1])
+    o = orc.Oracle(q, k, v, sl.tolist(), w.b_q, w.n_sink, w.n_stream,
+                   rope=orc.RopeSpec(cos.numpy(), sin.numpy(), attn="streaming"), kv_scales=scales)
+    qd, kd, vd = q.cuda(), k.cuda(), v.cuda()
+    paged = None
+    if variant == "paged":
+        n = -(-w.T // 16)
+        order = gen.distinct_ints(4, 5, n, n + 3)
+        pools = []
+        for t in (k, v):
+            pool = torch.full((n + 3, w.Hkv, 16, w.d), 7.0, dtype=torch.bfloat16)
+            pool[order] = torch.nn.functional.pad(t[0], (0, 0, 0, n * 16 - w.T)).view(w.Hkv, n, 16, w.d).permute(1, 0, 2, 3)
+            pools.append(pool.cuda())
+        paged = ihip.PagedKV(pools[0], pools[1], order.to(torch.int32).view(1, n).cuda())
+    L = ihip.Layer(qd, kd, sl.cuda(), w.b_q, w.n_sink, w.n_stream)
+    starts = np.full((w.Hkv * w.Mq, 20), -1, np.int32)
+    refs = {}
+    for g in range(w.Hkv):
+        for m in range(w.Mq):
+            pr = o.prune(0, g, m, w.stages)
+            starts[g * w.Mq + m, :len(pr.block_starts)] = pr.block_starts
+            refs[(g, m)] = o.attend(0, g, m, pr.block_starts, pr.block_lens)[0]
+    rp = ihip.Rope(cos.cuda(), sin.cuda(), ihip.ROPE_NONE, ihip.ROPE_STREAMING)
+    out, _ = L.sparse_attn_prefill(qd, kd, vd, torch.from_numpy(starts).cuda(), 16, rope=rp, paged=paged, kv_scales=scales)
+    torch.cuda.synchronize()
+    for (g, m), ref in refs.items():
+        got = out[0, g * w.G:(g + 1) * w.G, m * w.b_q:(m + 1) * w.b_q].float().cpu().numpy()
+        assert np.abs(got - ref).max() <= 2e-2, (g, m)
+
+
 def rotary(x, cos, sin, positions):
     """Standard RoPE in fp64: pair (2j, 2j+1) of row t turned by the table row of positions[t]."""
     c = cos[positions].double().view(1, 1, -1, cos.shape[1])
