@@ -48,7 +48,8 @@ constexpr int kPrefillMaxIters = 4;     // chunk groups (of 32 chunks) per workg
 // chunk j by cap - j, a query by cap - its position, which is nothing at all for a block whose first
 // query is at or behind the cap -- every block but those of ranges that hold fewer keys than a block has queries.
 // Such queries stay the exact bf16 values they are: no second operand for them, a third of the matrix
-// work less than with rotated queries, and 64 registers less, which makes room for two waves per SIMD.
+// work less than with rotated queries, and 64 registers less, which makes room for two waves per SIMD (64-query blocks
+// at the price of 60-84 bytes of scratch per lane, 120-256 with 8 heads).
 // (Blocks before the cap turn their query operands where they are used, value and rest.)
 // A candidate row is turned on its way from global memory to LDS, each lane the 16 bytes it fetched
 // (tile row 4r + kq is candidate column 4(r%4) + kq of tile r/4, whose chunk and therefore table row
@@ -247,12 +248,17 @@ __global__ __launch_bounds__(64 * G, (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS =
     }
     auto stage_queries = [&]() {
         const uint16_t *qb = a.q + pr.b * a.q_sb + (int64_t)h * a.q_sh + (int64_t)(pr.m * a.ge.b_q) * a.q_st;
+        // PARTS > 1: the row addresses are formed here, not carried over the passes.  Carried, they cost the chunk-indexed
+        // style up to 512 bytes of scratch per lane: 64-query blocks, 8 heads, pages 902 -> 444 us a layer (1,024 queries
+        // on 32K keys; E4M3 pages 847 -> 573, contiguous rows 465 -> 391)
+        int row0 = 0;
+        if constexpr (PARTS > 1) asm volatile("" : "+v"(row0));
 #pragma unroll
         for (int m0 = 0; m0 < MTW; m0 += 2) {
             constexpr int kRows = MTW >= 2 ? 32 : 16;
 #pragma unroll
             for (int r = 0; r < kRows / 4; ++r)
-                load4(qb, (off_t)a.q_st, dst_own[r], m0 * 16 + r * 4 + kq, (r & 3) * 4 + kq);
+                load4(qb, (off_t)a.q_st, dst_own[r], row0 + m0 * 16 + r * 4 + kq, (r & 3) * 4 + kq);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
             for (int mt = m0; mt < m0 + 2 && mt < MTW; ++mt)
@@ -364,7 +370,7 @@ __global__ __launch_bounds__(64 * G, (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS =
                 }
             }
             sig[t] = max_over_rows(best);
-            if constexpr (ROPE == 2) __builtin_amdgcn_sched_barrier(0);          // one tile's operands at a time
+            if constexpr (ROPE == 2 && MT > 1) __builtin_amdgcn_sched_barrier(0);    // one tile's operands at a time
             if constexpr (ROPE == 1) {
                 sigR[t] = max_over_rows(bestR);
             }
@@ -473,6 +479,10 @@ __global__ __launch_bounds__(64 * G, (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS =
                 }
             }
         };
+        // 16-query blocks multiply too little to cover the table's way from memory, and have the registers for it: asked
+        // for ahead of the first keys (that and both tiles' operands at once above: two heads per group 164 -> 149 us)
+        constexpr bool kTableFirst = MT == 1;
+        if constexpr (kTableFirst) load_table();
         int half = a.chunk >> 1;
         if (kShare) {
             // The first key of a chunk and of its right half are the same rows for every head of
@@ -525,7 +535,7 @@ __global__ __launch_bounds__(64 * G, (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS =
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }
             __syncthreads();
-            load_table();                            // for the waves' own searches; there when the tiles below are scored
+            if constexpr (!kTableFirst) load_table();        // for the waves' own searches; there when the tiles below are scored
             float l0r[NT];
             mfma_scores(&sh_rows[0], sigma, l0r);
             mfma_scores(&sh_rows[kTile], s, sR);
@@ -542,7 +552,7 @@ __global__ __launch_bounds__(64 * G, (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS =
             half >>= 1;
             __syncthreads();                         // tiles 0 and 1 go back to their waves
         } else {
-            load_table();
+            if constexpr (!kTableFirst) load_table();
             score(pos, valid, sigma, sR);
             if constexpr (ROPE == 1) {
 #pragma unroll
