@@ -264,10 +264,11 @@ int32_t ihip_sparse_attn_prefill(const ihip_shape *shape, ihip_tensor q, ihip_te
  * Scratch bytes an operation needs.  n_stages / chunk_sizes / keeps describe
  * the stage plan (for the attention-only ops pass n_stages = 1 with
  * chunk_sizes[0] = block and keeps[0] = n_blocks).  Returns 0 on bad arguments.
- * Decode attention
- * splits the key list over the chip and merges the parts; with the bytes reported here it cuts it as fine as it can
- * use.  Calls that get less, but enough for parts of at least 256 keys, cut it coarser (results equal up to fp32
- * rounding; calls with at least the reported bytes give identical bits).
+ * Decode attention splits the key list over the chip and merges the parts; with the bytes reported here it cuts it as fine as
+ * it can use.  Calls that get less, but enough for parts of at least 256 keys, cut it coarser (results equal up to fp32
+ * rounding; calls with at least the reported bytes give identical bits).  One exception: a decode layer whose scratch
+ * fits IHIP_STATIC_SCRATCH_BYTES with the coarse parts but not with the fine ones is always cut coarse, and the coarse
+ * bytes are reported, so that ihip_decode_layer_static takes it and gives the same bits.
  */
 size_t ihip_workspace_bytes(int32_t op, const ihip_shape *shape, int32_t n_stages,
                             const int32_t *chunk_sizes, const int32_t *keeps);

@@ -406,10 +406,12 @@ __global__ __launch_bounds__(kD * GROUPS) void attn_decode_merge_kernel(const At
 // run its whole latency chain after the others have drained -- with 256-slot splits the cfg3 shape
 // had 1344 workgroups for 1024 places.  Between 256 and 1024 slots per split, a multiple of 16.
 // `fine`: where splits of 256 slots would not even give every CU one workgroup, the kernel is one chain of latencies and a
-// split walks its loop four times while most of the chip is idle; splits then go down to 64 slots, one
-// batch of loads of every 16-lane group, but to no more than 64 splits, which the merge takes in one trip (8 problems of
-// 1,664 slots: 14.3 us with 256, 8.9 with 64; of 3,200 slots 15.0 and 11.2; but 24 problems of 3,152 slots with 8 heads 27.7 and
-// 30.6).  Finer splits take more scratch; with scratch for the coarse ones only, those are used.
+// split walks its loop four times while most of the chip is idle; splits then go down to 64 slots, one batch of loads of
+// every 16-lane group, to two workgroups per CU at most (more of them share what a CU has and cost the merge) and to 64 splits,
+// which the merge takes in one trip.  Split and merge, 256-slot splits / four workgroups per CU / two (us):
+// 4 heads, 8 problems of 1,664 slots 19.4/14.7/15.1, 8 of 5,248 20.7/19.0/19.5, 32 of 1,664 21.0/22.0/19.7; 8 heads
+// 25.6/17.8/17.4, 26.7/25.0/24.8, 27.0/30.8/25.1, 16 of 3,200 27.2/30.3/25.4.  Finer splits take more scratch; with
+// scratch for the coarse ones only, those are used.
 // wg_per_cu: 4 for the plain kernels, 3 for the RoPE instantiations (more registers).  The workspace
 // is sized for 4, which gives the most splits.
 static int decode_splits(const ihip_shape &s, int n_blocks, int block, bool fine, int *slots_per_split, int wg_per_cu = 4)
@@ -417,11 +419,10 @@ static int decode_splits(const ihip_shape &s, int n_blocks, int block, bool fine
     const int n_cu = compute_units();
     const int total = s.n_sink + n_blocks * block + s.n_stream;
     const int P = std::max(1, s.B * s.Hkv);
-    const int places = std::max(1, n_cu * wg_per_cu / P);      // splits per problem that run at once
+    const bool spread = fine && (int64_t)P * ((total + kAttnMinSplit - 1) / kAttnMinSplit) < n_cu;
+    const int places = std::max(1, n_cu * (spread ? 2 : wg_per_cu) / P);      // splits per problem that run at once
     int per = ((total + places - 1) / places + 15) / 16 * 16;
-    int least = kAttnMinSplit;
-    if (fine && (int64_t)P * ((total + kAttnMinSplit - 1) / kAttnMinSplit) < n_cu)
-        least = std::min(kAttnMinSplit, std::max(kAttnMinSplitFine, ((total + 63) / 64 + 15) & ~15));
+    const int least = spread ? std::min(kAttnMinSplit, std::max(kAttnMinSplitFine, ((total + 63) / 64 + 15) & ~15)) : kAttnMinSplit;
     per = std::min(kAttnMaxSplit, std::max(least, per));
     *slots_per_split = per;
     return (total + per - 1) / per;

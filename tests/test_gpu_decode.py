@@ -318,7 +318,8 @@ def test_empty_batch_is_a_no_op(ihip):
     (2, 1, 0, 4, 40),             # splits of 64 slots, no blocks
     (8, 2, 512, 8, 1000),         # the most splits
     (16, 2, 128, 8, 3200),        # 18 coarse splits each already fill the chip: the same splits either way
-], ids=["55", "17", "26", "short", "8x5k", "16x4k"])
+    (32, 1, 96, 4, 1152),         # 15 splits of 112 slots: two workgroups per compute unit, not more
+], ids=["55", "17", "26", "short", "8x5k", "16x4k", "32x1.7k"])
 def test_attention_splits_fine_and_coarse(ihip, orc, Hkv, G, n_blocks, block, n_stream):
     """The split of the key list follows the scratch: with what ihip_workspace_bytes says splits of 64 slots and more,
     with a byte less (and room for the coarse ones) of 256 and more, both against the oracle (4e-3, as every attention on
@@ -351,3 +352,31 @@ def test_attention_splits_fine_and_coarse(ihip, orc, Hkv, G, n_blocks, block, n_
         small = torch.empty(Hkv * G * 130 * 4 // 2, dtype=torch.uint8, device="cuda")
         with pytest.raises(ihip.IhipError):
             L.sparse_attn_decode(qd, kd, vd, bd, block, ws=small)
+
+
+def test_attention_splits_at_the_static_array(ihip):
+    """A plan that fits the static scratch array with the coarse splits only: the reported bytes are the coarse ones, and the
+    static call and the workspace call, with that much scratch or more, give identical bits."""
+    B, Hkv, G, keep, limit = 2, 1, 8, 4096, 8 << 20
+    q = torch.randn((B, Hkv * G, 1, 128), device="cuda").bfloat16()
+    extra = B * Hkv * G * 130 * 4 * (55 - 21)             # 5,248 key slots: 55 fine splits, 21 coarse ones
+
+    def layer(T):
+        shape = torch.empty((B, Hkv, T, 0), dtype=torch.bfloat16)
+        return ihip.Layer(q, shape, torch.full((B,), T, dtype=torch.int32, device="cuda"), 1, 128, 1024)
+
+    T = 1 << 20
+    while layer(T).workspace_bytes(ihip.OP_DECODE_LAYER, [1], [keep]) + extra // 2 > limit:      # a call more or less in the middle
+        T -= 4096
+    L = layer(T)
+    need = L.workspace_bytes(ihip.OP_DECODE_LAYER, [1], [keep])
+    assert need <= limit < need + extra
+    k, v = (torch.randn((B, Hkv, T, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    outs = [torch.empty((B, Hkv * G, 1, 128), dtype=torch.bfloat16, device="cuda") for _ in range(3)]
+    for size, out in ((need, outs[0]), (need + extra, outs[1])):
+        L.decode_layer(q, k, v, [1], [keep], ws=torch.empty(size, dtype=torch.uint8, device="cuda"), out=out)
+    L.decode_layer_static(q, k, v, [1], [keep], outs[2])
+    torch.cuda.synchronize()
+    assert torch.isfinite(outs[0]).all() and torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    with pytest.raises(ihip.IhipError):
+        L.decode_layer(q, k, v, [1], [keep], ws=torch.empty(need - 1, dtype=torch.uint8, device="cuda"))
