@@ -268,14 +268,16 @@ static void launch_rope_u(const PruneArgs &a, const RopeView &rope, int style, i
     else hipLaunchKernelGGL((prune_decode_rope_kernel<G, U, 2, SRC, KV8>), grid, dim3(256), 0, st, a, rope);
 }
 
-// U chunks per 16-lane group: one everywhere (most waves per SIMD, finest cut of the work) except on
-// a large first stage over contiguous E4M3 rows, where three chunks per group put more of the short
-// rows in flight (cfg3: 193 us against 207 us).
+// U chunks per 16-lane group: one everywhere (most waves per SIMD, finest cut of the work) except on a large first stage
+// over contiguous E4M3 rows with few heads, where three chunks per group put more of the short rows in flight: relative
+// style, chunks of 128, 8 x 1M keys on 8 KV heads, one and three: one head per group 137 and 106 us, two heads 174 and 159;
+// chunk-indexed 134 and 119, with two heads a tie (166 and 168), with four, whose three rotated query sets per head do not fit,
+// 259 and 354.
 template <int G, int SRC, bool KV8>
 static void launch_rope(const PruneArgs &a, const RopeView &rope, int style, int P, hipStream_t st)
 {
-    if constexpr (SRC == 0 && KV8) {
-        if (a.parent_starts == nullptr && a.chunk >= 128 && (int64_t)P * a.max_chunks >= 65536) {
+    if constexpr (SRC == 0 && KV8 && G <= 2) {
+        if ((style == 1 || G == 1) && a.parent_starts == nullptr && a.chunk >= 128 && (int64_t)P * a.max_chunks >= 65536) {
             launch_rope_u<G, SRC, KV8, 3>(a, rope, style, P, st);
             return;
         }

@@ -7,7 +7,7 @@ import torch
 
 pytestmark = pytest.mark.gpu
 
-from workloads import configs  # noqa: E402
+from workloads import configs, gen  # noqa: E402
 
 
 @pytest.fixture(scope="module")
@@ -220,8 +220,7 @@ def test_cfg3_decode_full_size_rope_fp8_pages(ihip, orc):
         assert np.array_equal(got[got >= 0], pr.block_starts), (b, g)
         ref, _ = o.attend(0, 0, 0, pr.block_starts, pr.block_lens)
         assert np.abs(out[b, g * G:(g + 1) * G, 0].float().cpu().numpy() - ref[:, 0]).max() <= 2e-2, (b, g)
-    # the same rows contiguous (no pages): the large first stage takes the RoPE kernel's three-chunks-per-
-    # lane-group variant; same arithmetic, so the same bits
+    # the same rows contiguous (no pages): the same arithmetic, so the same bits
     del pg
     torch.cuda.empty_cache()
     blocks2 = torch.empty_like(blocks)
@@ -230,6 +229,37 @@ def test_cfg3_decode_full_size_rope_fp8_pages(ihip, orc):
     assert torch.equal(blocks2, blocks) and torch.equal(out2, out)
     del k8, v8
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("prune_style", ["relative", "chunk"])
+def test_large_first_stage_with_rope_one_head_per_group(ihip, orc, prune_style):
+    """65,536 first-stage chunks of contiguous E4M3 rows with one head per group: three chunks per lane group, the last
+    group of a problem partly empty.  Kept lists of sampled problems bit-exact, outputs within 2e-2."""
+    w, dev = configs.shrink(configs.CFG3, T=132263, Hq=8, stages=((128, 64), (16, 128)), n_needles=0), torch.device("cuda:0")
+    q, k, v, _, _ = configs.make_inputs(w, 2, device=dev, kind="int")
+    sl = torch.full((w.B,), w.T, dtype=torch.int32)
+    sl[3] -= 1001
+    scales = (0.5, 0.25)
+    k8, v8 = gen.to_e4m3(k, scales[0]), gen.to_e4m3(v, scales[1])
+    del k, v
+    cos, sin = gen.quarter_turn_table(4096, w.d)
+    rp = ihip.Rope(cos.to(dev), sin.to(dev), {"relative": ihip.ROPE_RELATIVE, "chunk": ihip.ROPE_CHUNK_INDEXED}[prune_style],
+                   ihip.ROPE_STREAMING)
+    spec = orc.RopeSpec(cos.numpy(), sin.numpy(), prune=prune_style, attn="streaming")
+    chunks, keeps = [s[0] for s in w.stages], [s[1] for s in w.stages]
+    L = ihip.Layer(q, k8, sl.to(dev), 1, w.n_sink, w.n_stream)
+    assert L.P * L.stage1_slots(chunks[0]) >= 65536
+    blocks = torch.empty((L.P, keeps[-1]), dtype=torch.int32, device=dev)
+    out = L.decode_layer(q, k8, v8, chunks, keeps, out_blocks=blocks, rope=rp, kv_scales=scales)
+    torch.cuda.synchronize()
+    for (b, g) in [(0, 0), (3, 2), (7, 7)]:
+        o = orc.Oracle(q[b:b + 1, g:g + 1].cpu(), k8[b:b + 1, g:g + 1].cpu(), v8[b:b + 1, g:g + 1].cpu(), [int(sl[b])], 1,
+                       w.n_sink, w.n_stream, rope=spec, kv_scales=scales)
+        pr = o.prune(0, 0, 0, w.stages)
+        got = blocks[b * w.Hkv + g].cpu().numpy()
+        assert np.array_equal(got[got >= 0], pr.block_starts), (b, g)
+        ref, _ = o.attend(0, 0, 0, pr.block_starts, pr.block_lens)
+        assert np.abs(out[b, g:g + 1, 0].float().cpu().numpy() - ref[:, 0]).max() <= 2e-2, (b, g)
 
 
 def test_cfg4_prefill_full_size_rope_fp8_pages(ihip, orc):
