@@ -67,7 +67,6 @@
 
 namespace ihip {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
@@ -83,8 +82,9 @@ constexpr float kPfMaxSum = 1024.0f;                // row sum of a tile above w
 // PAGED: K and V are page pools read through the sequence's row of the block table; the page id of
 // every slot is looked up once, next to its position, and kept in LDS as well.
 template <int NQ, int G, bool WIDE, bool ROPE, bool PAGED, bool KV8 = false>
-__global__ __launch_bounds__(64 * NQ * G, NQ * G <= 8 ? 2 : 4) void attn_prefill32_kernel(const AttnPrefillArgs a)
+__global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const AttnPrefillArgs a)
 {
+    static_assert(NQ * G <= 8, "at most eight waves");
     static_assert(!PAGED || WIDE, "paged pools are addressed with 64-bit offsets");
     static_assert(!KV8 || WIDE, "E4M3 rows are addressed with 64-bit offsets");
     constexpr int kPfStages = KV8 ? kPfStagesFp8 : ROPE ? kPfStagesRope : kPfStagesPlain;
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(64 * NQ * G, NQ * G <= 8 ? 2 : 4) void attn_prefill
     constexpr int kLoadsPerTile = KV8 ? 8 : 16;
     constexpr int kLoadsPerWave = kLoadsPerTile / NW;
     static_assert(kLoadsPerWave * NW == kLoadsPerTile, "wave count must divide the loads of a tile");
-    // The loads are written as assembly: a compiler-visible LDS-bound load makes the compiler
+    // The loads are written as assembly (global_to_lds): a compiler-visible LDS-bound load makes the compiler
     // drain the vector-memory counter before the next LDS read it cannot tell apart from the
     // destination, which would undo the prefetch distance.  landed() below is the only wait.
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);
@@ -215,12 +215,7 @@ __global__ __launch_bounds__(64 * NQ * G, NQ * G <= 8 ? 2 : 4) void attn_prefill
                 src += (lane & 7) * 8;
                 const uint32_t dst = __builtin_amdgcn_readfirstlane(
                     (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)(stage + j * 512));
-                uint32_t m0_saved;       // M0 is put back: the compiler is not told that it changes
-                asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\t"
-                             "s_mov_b32 m0, %0"
-                             : "=&s"(m0_saved)
-                             : "s"(dst), "v"(src)
-                             : "memory");
+                global_to_lds(dst, src);
             }
             return;
         }
@@ -242,12 +237,7 @@ __global__ __launch_bounds__(64 * NQ * G, NQ * G <= 8 ? 2 : 4) void attn_prefill
             else src = (is_v ? vb : kb) + (__umul24((uint32_t)pos, (uint32_t)(is_v ? a.v_st : a.k_st)) + (uint32_t)(chunk * 8));
             const uint32_t dst = __builtin_amdgcn_readfirstlane(
                 (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)(stage + j * 4 * kD));
-            uint32_t m0_saved;           // M0 is put back: the compiler is not told that it changes
-            asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\t"
-                         "s_mov_b32 m0, %0"
-                         : "=&s"(m0_saved)
-                         : "s"(dst), "v"(src)
-                         : "memory");
+            global_to_lds(dst, src);
         }
     };
 

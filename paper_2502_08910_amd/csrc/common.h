@@ -345,6 +345,37 @@ __device__ inline uint4 rotate_fp8x8(const uint2 &k, const float4 c, const float
     return rotate_f32x8(f, c, sn);
 }
 
+__device__ inline uint4 as_bf16x8(const uint2 &k) { return fp8x8_to_bf16x8(k); }
+__device__ inline uint4 as_bf16x8(const uint4 &k) { return k; }
+
+// ---- global memory -> LDS ---------------------------------------------------
+// 16 bytes per lane, lane l's from src to the LDS byte address dst + 16*l (dst wave-uniform).  Counts on vmcnt; written as
+// assembly because a compiler-visible LDS-bound load makes the compiler wait for it before LDS reads it cannot tell apart.
+// M0 is put back: the compiler is not told that it changes.
+__device__ inline void global_to_lds(uint32_t dst, const uint16_t *src)
+{
+    uint32_t m0_saved;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\t"
+                 "s_mov_b32 m0, %0"
+                 : "=&s"(m0_saved)
+                 : "s"(dst), "v"(src)
+                 : "memory");
+}
+// the same from a wave-uniform base (scalar registers) and a lane's byte offset
+__device__ inline void global_to_lds(uint32_t dst, const uint16_t *base, uint32_t byte_off)
+{
+    const uint64_t b64 = (uint64_t)(uintptr_t)base;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b64);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b64 >> 32));
+    const uint64_t sbase = ((uint64_t)hi << 32) | lo;
+    uint32_t m0_saved;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\t"
+                 "s_mov_b32 m0, %0"
+                 : "=&s"(m0_saved)
+                 : "s"(dst), "v"(byte_off), "s"(sbase)
+                 : "memory");
+}
+
 // ---- cross-lane -----------------------------------------------------------
 template <int CTRL>
 __device__ inline float dpp_f32(float v)

@@ -366,8 +366,12 @@ static void launch_decode_tile_n(const PruneArgs &a, const RopeView &rope, int P
     const int per_wg = decode_tile_chunks(G, a.chunk, ROPE, KV8) * kDecodeTileWaves;
     const dim3 grid((a.max_chunks + per_wg - 1) / per_wg, P), block(64 * kDecodeTileWaves);
     KernelTimer timer(stage_name(kNamePruneDecode, a.parent_starts == nullptr, a.chunk), st);
-    if (a.chunk == 4) hipLaunchKernelGGL((prune_decode_four_kernel<G, ROPE, SRC, KV8, NARROW>), grid, block, 0, st, a, rope);
-    else hipLaunchKernelGGL((prune_decode_tile_kernel<G, ROPE, SRC, KV8, NARROW>), grid, block, 0, st, a, rope);
+    // contiguous bf16 rows without RoPE: only chunks of four with eight heads come here (decode_on_tiles)
+    constexpr bool kPlain = !ROPE && SRC == 0 && !KV8;
+    if constexpr (!kPlain || G == 8)
+        if (a.chunk == 4) hipLaunchKernelGGL((prune_decode_four_kernel<G, ROPE, SRC, KV8, NARROW>), grid, block, 0, st, a, rope);
+    if constexpr (!kPlain)
+        if (a.chunk != 4) hipLaunchKernelGGL((prune_decode_tile_kernel<G, ROPE, SRC, KV8, NARROW>), grid, block, 0, st, a, rope);
 }
 
 template <bool ROPE, int SRC, bool KV8, bool NARROW>

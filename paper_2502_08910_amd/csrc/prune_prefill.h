@@ -22,6 +22,7 @@ namespace ihip {
 // ---------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kPrefillMaxIters = 4;     // chunk groups (of 32 chunks) per workgroup, at most
 
 //
@@ -111,8 +112,6 @@ __device__ inline void turn_back_operand_split(const bf16x8 x, const float *cos4
     hi = __builtin_bit_cast(bf16x8, h);
     lo = __builtin_bit_cast(bf16x8, l);
 }
-__device__ inline uint4 as_bf16x8(const uint2 &k) { return fp8x8_to_bf16x8(k); }
-__device__ inline uint4 as_bf16x8(const uint4 &k) { return k; }
 
 // PAGED: K is a page pool read through the sequence's row of the block table: the lane that owns a
 // candidate looks its page up and forms the row's element offset (64-bit) before the offsets are
@@ -177,36 +176,14 @@ __global__ __launch_bounds__(64 * G, (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS =
     auto load4 = [&](const uint16_t *base, off_t stride, uint32_t dst, int row, int swz) {
         const off_t r = (off_t)row;
         if constexpr (WIDE) {
-            const uint16_t *src = base + r * stride + ((n ^ swz) << 3);
-            uint32_t m0_saved;           // M0 is put back: the compiler is not told that it changes
-            asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\t"
-                         "s_mov_b32 m0, %0"
-                         : "=&s"(m0_saved)
-                         : "s"(dst), "v"(src)
-                         : "memory");
+            global_to_lds(dst, base + r * stride + ((n ^ swz) << 3));
         } else {
-            const uint32_t byte_off = __umul24((uint32_t)r, (uint32_t)stride * 2u) + (uint32_t)((n ^ swz) << 4);
-            const uint64_t b64 = (uint64_t)(uintptr_t)base;
-            const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b64);
-            const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b64 >> 32));
-            const uint64_t sbase = ((uint64_t)hi << 32) | lo;
-            uint32_t m0_saved;
-            asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\t"
-                         "s_mov_b32 m0, %0"
-                         : "=&s"(m0_saved)
-                         : "s"(dst), "v"(byte_off), "s"(sbase)
-                         : "memory");
+            global_to_lds(dst, base, __umul24((uint32_t)r, (uint32_t)stride * 2u) + (uint32_t)((n ^ swz) << 4));
         }
     };
     // the same with the row's element offset already formed (paged K)
     auto load4_at = [&](const uint16_t *base, int64_t at, uint32_t dst, int swz) {
-        const uint16_t *src = base + at + ((n ^ swz) << 3);
-        uint32_t m0_saved;
-        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\t"
-                     "s_mov_b32 m0, %0"
-                     : "=&s"(m0_saved)
-                     : "s"(dst), "v"(src)
-                     : "memory");
+        global_to_lds(dst, base + at + ((n ^ swz) << 3));
     };
     // Keys that go through registers (E4M3, chunk-indexed RoPE): this lane's 8 elements of row `row` (or of the
     // row at element offset `at`), and their place in a four-row group of a tile

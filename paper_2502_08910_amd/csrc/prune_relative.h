@@ -38,8 +38,6 @@
 
 namespace ihip {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
 // PARTS, WIDE, PAGED, KV8: as in prune_prefill_kernel
 template <int G, bool WIDE, bool PAGED, int PARTS, bool KV8>
 __global__ __launch_bounds__(128 * G, 2) void prune_relative_kernel(const PruneArgs a, const int iters, const RopeView rope)
@@ -91,26 +89,8 @@ __global__ __launch_bounds__(128 * G, 2) void prune_relative_kernel(const PruneA
     // dst + lane*16; piece c of tile row R sits in slot c ^ (R%16) (applied on the source side), so that the rows of an
     // operand read hit different bank groups.  swz = R%16 of this lane's row.  Written as assembly, as in prune_prefill_kernel.
     auto load4 = [&](off_t at, uint32_t dst, int swz) {
-        uint32_t m0_saved;               // M0 is put back: the compiler is not told that it changes
-        if constexpr (WIDE) {
-            const uint16_t *src = kb + at + ((n16 ^ swz) << 3);
-            asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\t"
-                         "s_mov_b32 m0, %0"
-                         : "=&s"(m0_saved)
-                         : "s"(dst), "v"(src)
-                         : "memory");
-        } else {
-            const uint32_t byte_off = at + (uint32_t)((n16 ^ swz) << 4);
-            const uint64_t b64 = (uint64_t)(uintptr_t)kb;
-            const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b64);
-            const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b64 >> 32));
-            const uint64_t sbase = ((uint64_t)hi << 32) | lo;
-            asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\t"
-                         "s_mov_b32 m0, %0"
-                         : "=&s"(m0_saved)
-                         : "s"(dst), "v"(byte_off), "s"(sbase)
-                         : "memory");
-        }
+        if constexpr (WIDE) global_to_lds(dst, kb + at + ((n16 ^ swz) << 3));
+        else global_to_lds(dst, kb, at + (uint32_t)((n16 ^ swz) << 4));
     };
     // E4M3 (always WIDE): through registers, widened on the way
     auto fetch = [&](off_t at, int swz) { return *reinterpret_cast<const raw_t *>(kb + at + (n16 ^ swz) * (int)(sizeof(raw_t) / 2)); };

@@ -114,21 +114,23 @@ int32_t launch_select_blocks(const ihip_shape &s, const float *scores, int max_c
     // is unrolled for all of them (4,143 slots, 9 per thread, 512 problems: 16 per thread 11.1 us, 12 9.75, 10 9.4).
 #define IHIP_SEL(NTV, ITV) hipLaunchKernelGGL((select_blocks_fast_kernel<NTV, ITV>), dim3(P), dim3(NTV), 0, st, a)
 #define IHIP_SEL_BY_ITEMS(NTV)                                                                                      \
-    switch ((max_chunks + 2 * NTV - 1) / (2 * NTV)) {                                                               \
-    case 3: IHIP_SEL(NTV, 6); break;                                                                                \
-    case 4: IHIP_SEL(NTV, 8); break;                                                                                \
     case 5: IHIP_SEL(NTV, 10); break;                                                                               \
     case 6: IHIP_SEL(NTV, 12); break;                                                                               \
     case 7: IHIP_SEL(NTV, 14); break;                                                                               \
-    default: IHIP_SEL(NTV, 16); break;                                                                              \
-    }
+    default: IHIP_SEL(NTV, 16); break;
     const bool few = P <= 256;
     if (max_chunks <= 256 * 4) IHIP_SEL(256, 4);
     else if (few && max_chunks <= 512 * 4) IHIP_SEL(512, 4);
     else if (few && max_chunks <= 1024 * 4) IHIP_SEL(1024, 4);
     else if (few && max_chunks <= 1024 * 8) IHIP_SEL(1024, 8);
-    else if (max_chunks <= 256 * kFastItems) IHIP_SEL_BY_ITEMS(256)
-    else if (max_chunks <= 512 * kFastItems) IHIP_SEL_BY_ITEMS(512)
+    else if (max_chunks <= 256 * kFastItems)
+        switch ((max_chunks + 2 * 256 - 1) / (2 * 256)) {
+        case 3: IHIP_SEL(256, 6); break;
+        case 4: IHIP_SEL(256, 8); break;
+        IHIP_SEL_BY_ITEMS(256)
+        }
+    else if (max_chunks <= 512 * kFastItems)         // more than 8 slots per thread here
+        switch ((max_chunks + 2 * 512 - 1) / (2 * 512)) { IHIP_SEL_BY_ITEMS(512) }
     else if (max_chunks <= 1024 * kFastItems) IHIP_SEL(1024, kFastItems);
 #undef IHIP_SEL_BY_ITEMS
 #undef IHIP_SEL

@@ -39,9 +39,6 @@ struct AttnDecodeArgs {
                          // scale_log2e; K/V strides then count 2-byte units of the byte rows)
 };
 
-__device__ inline uint4 as_bf16x8(const uint4 &k) { return k; }
-__device__ inline uint4 as_bf16x8(const uint2 &k) { return fp8x8_to_bf16x8(k); }
-
 // SRC 0: K/V in HBM through strides; 1: host tier with the on-GPU bank; 2: paged pools
 template <int SRC> struct KvSource;
 template <> struct KvSource<0> {

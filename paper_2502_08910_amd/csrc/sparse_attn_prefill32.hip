@@ -31,17 +31,18 @@ void launch_attn_prefill32(const AttnPrefillArgs &a, int P, int64_t max_seq_len,
     if (WV && paged) {                                                                                       \
         if (use_rope) IHIP_PF32_R(NQV, GV, true, true, true) else IHIP_PF32_R(NQV, GV, true, false, true)    \
     } else if (use_rope) IHIP_PF32_R(NQV, GV, WV, true, false) else IHIP_PF32_R(NQV, GV, WV, false, false)
-#define IHIP_PF32_BY_G(NQV, WV)             \
-    switch (heads_per_wg) {                 \
-    case 1: IHIP_PF32(NQV, 1, WV); break;   \
-    case 2: IHIP_PF32(NQV, 2, WV); break;   \
-    case 4: IHIP_PF32(NQV, 4, WV); break;   \
-    default: IHIP_PF32(NQV, 8, WV); break;  \
+    // at most 8 waves: a workgroup of 64-query blocks has at most 4 heads
+#define IHIP_PF32_BY_G(WV)                                                 \
+    switch (heads_per_wg * NQ) {                                           \
+    case 1: IHIP_PF32(1, 1, WV); break;                                    \
+    case 2: if (NQ == 1) { IHIP_PF32(1, 2, WV); } else { IHIP_PF32(2, 1, WV); } break; \
+    case 4: if (NQ == 1) { IHIP_PF32(1, 4, WV); } else { IHIP_PF32(2, 2, WV); } break; \
+    default: if (NQ == 1) { IHIP_PF32(1, 8, WV); } else { IHIP_PF32(2, 4, WV); } break; \
     }
     if (wide) {
-        if (NQ == 1) { IHIP_PF32_BY_G(1, true) } else { IHIP_PF32_BY_G(2, true) }
+        IHIP_PF32_BY_G(true)
     } else {
-        if (NQ == 1) { IHIP_PF32_BY_G(1, false) } else { IHIP_PF32_BY_G(2, false) }
+        IHIP_PF32_BY_G(false)
     }
 #undef IHIP_PF32_BY_G
 #undef IHIP_PF32
