@@ -144,8 +144,11 @@ __device__ inline void write_no_chunks(const PruneArgs &a, const Problem &pr, in
 
 constexpr int kDecodePages = 16;              // page ids of a chunk kept in LDS; further ones are looked up in the table
 
+// Eight heads over bf16 pages with rotated queries: left alone the compiler takes 172 registers, two waves per SIMD; told to
+// leave room for three it takes 124 (28 sequences of 100K keys: a layer 756 -> 685 us).  The same for chunks of four below: 90
+// instead of 96-100, five waves instead of four.
 template <int G, bool ROPE, int SRC, bool KV8, bool NARROW>
-__global__ __launch_bounds__(256) void prune_decode_tile_kernel(const PruneArgs a, const RopeView rope)
+__global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) void prune_decode_tile_kernel(const PruneArgs a, const RopeView rope)
 {
     static_assert(SRC == 0 || !NARROW, "paged pools are addressed with 64-bit offsets");
     constexpr int PARTS = ROPE ? 3 : 1;
@@ -286,7 +289,7 @@ __global__ __launch_bounds__(256) void prune_decode_tile_kernel(const PruneArgs 
 // whole chunks, one load of which brings 64 bytes of each of 16 rows in order, and a head's four scores of a
 // chunk are the four registers of one lane: no dependent loads, nothing crosses lanes.
 template <int G, bool ROPE, int SRC, bool KV8, bool NARROW>
-__global__ __launch_bounds__(256) void prune_decode_four_kernel(const PruneArgs a, const RopeView rope)
+__global__ __launch_bounds__(256, !ROPE && !KV8 ? 5 : 1) void prune_decode_four_kernel(const PruneArgs a, const RopeView rope)
 {
     static_assert(SRC == 0 || !NARROW, "paged pools are addressed with 64-bit offsets");
     constexpr int PARTS = ROPE ? 3 : 1;
