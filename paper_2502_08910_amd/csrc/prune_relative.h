@@ -22,7 +22,8 @@
 // handful of vector instructions to decide, and the two waves of a head share the candidate rows, each fetching half.
 // First stage, 2,048 queries on 128K keys, chunks of 64, 32 heads: 898 us with every candidate scored both ways, 32
 // chunks per wave and own copies of the rows; 850 us with late scores alone; 675 us this way.  E4M3 rows, 1,024 queries on 32K
-// keys: 150 -> 116 us, in pages 151 -> 117.  Two groups of 32 chunks in turn, one group's rows on their way while the other's are
+// keys: 150 -> 116 us, in pages 151 -> 117 (48-80 bytes of scratch per lane).  Few workgroups walk 32 searches per wave (see
+// launch_relative).  Two groups of 32 chunks in turn, one group's rows on their way while the other's are
 // multiplied, were no faster than one (850): twice the LDS round trips.
 //
 // Two waves per query head, 32 queries each.  They fetch half of a level's candidate rows each into a tile of the head and
@@ -38,19 +39,21 @@
 
 namespace ihip {
 
+// COLS: searches of a wave, 64 or 32 (lanes 32.. then walk the same searches as lanes 0..31)
 // PARTS, WIDE, PAGED, KV8: as in prune_prefill_kernel
-template <int G, bool WIDE, bool PAGED, int PARTS, bool KV8>
+template <int COLS, int G, bool WIDE, bool PAGED, int PARTS, bool KV8>
 __global__ __launch_bounds__(128 * G, 2) void prune_relative_kernel(const PruneArgs a, const int iters, const RopeView rope)
 {
     static_assert(!PAGED || WIDE, "paged pools are addressed with 64-bit offsets");
     constexpr int QS = 2;                            // waves of a head
-    constexpr int kCols = 64;                        // searches of a wave
+    static_assert(COLS == 64 || COLS == 32, "one search per lane, or one per two");
+    constexpr int kCols = COLS;
     constexpr int NWV = G * QS;                      // waves of the workgroup
     constexpr int MTW = 2;                           // 16-query tiles of a wave
-    constexpr int kTile = kCols * kD;                // 64 rows of 256 bytes, no padding
+    constexpr int kTile = kCols * kD;                // rows of 256 bytes, no padding
     constexpr int kBufs = 2;                         // tiles of a head
     constexpr int kTiles = G * kBufs;
-    constexpr int kLoads = 16 / QS;                  // four-row loads of a level that are this wave's
+    constexpr int kLoads = kCols / 4 / QS;           // four-row loads of a level that are this wave's
     constexpr uint32_t kFourRows = 4 * kD * 2, kTileBytes = kTile * 2;
     using raw_t = typename std::conditional<KV8, uint2, uint4>::type;         // a lane's 8 elements of a row as fetched
     using off_t = typename std::conditional<WIDE, int64_t, uint32_t>::type;   // byte (WIDE: element) offset of a row
@@ -69,7 +72,7 @@ __global__ __launch_bounds__(128 * G, 2) void prune_relative_kernel(const PruneA
     const int p = ((blockIdx.x / a.ge.Hkv / a.ge.Mq) * a.ge.Hkv + blockIdx.x % a.ge.Hkv) * a.ge.Mq +
                   (blockIdx.x / a.ge.Hkv) % a.ge.Mq;
     const Problem pr = problem_of(a.ge, p);
-    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, col = lane & (kCols - 1), wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int hh = wv / QS, qs = wv % QS;            // the wave's query head of the group, and its share of the queries
     if (lane == 0) sh_turn[wv] = 0;                  // a workgroup barrier follows before the first handshake
     const int n16 = lane & 15, kq = lane >> 4;       // 16x16x32 operands: row / column and group of 8 dims
@@ -168,13 +171,14 @@ __global__ __launch_bounds__(128 * G, 2) void prune_relative_kernel(const PruneA
         for (int r = 1; r < 16; ++r) best = fmaxf(best, c[r]);
         return best;
     };
-    // the maxima of two tiles (columns 0..31 and 32..63), each lane its own column's
+    // the maxima of two products (columns 0..31 and 32..63, or the same 32 twice), each lane its own column's
     auto both_halves = [&](float x0, float x1) {
         const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x0), __float_as_uint(x1), false, false);
         return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
     };
     auto right_scores = [&](const uint16_t *src) {
         const float x0 = right_half(src, n32);
+        if constexpr (kCols == 32) return both_halves(x0, x0);
         const float x1 = right_half(src, 32 + n32);
         return both_halves(x0, x1);
     };
@@ -198,6 +202,7 @@ __global__ __launch_bounds__(128 * G, 2) void prune_relative_kernel(const PruneA
     };
     // the columns whose lane has `need` set, packed: sh_list[0..count)
     auto pack = [&](bool need) {
+        need = need && lane < kCols;
         const uint64_t mask = __ballot(need);
         const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
         if (need) sh_list[wv][rank] = (uint8_t)lane;
@@ -208,9 +213,9 @@ __global__ __launch_bounds__(128 * G, 2) void prune_relative_kernel(const PruneA
         const int cnt = pack(need);
 #pragma unroll 1
         for (int at = 0; at < cnt; at += 16) {
-            const int col = at + n16 < cnt ? sh_list[wv][at + n16] : n16;
-            const float v = left_score(src, col);
-            if (kq == 0 && at + n16 < cnt) out[col] = v;
+            const int c = at + n16 < cnt ? sh_list[wv][at + n16] : n16;
+            const float v = left_score(src, c);
+            if (kq == 0 && at + n16 < cnt) out[c] = v;
         }
         asm volatile("" ::: "memory");        // the list is written again only after it has been read
     };
@@ -218,10 +223,10 @@ __global__ __launch_bounds__(128 * G, 2) void prune_relative_kernel(const PruneA
         const int cnt = pack(need);
 #pragma unroll 1
         for (int at = 0; at < cnt; at += 32) {
-            const int col = at + n32 < cnt ? sh_list[wv][at + n32] : n32;
-            const float x = right_half(src, col);
+            const int c = at + n32 < cnt ? sh_list[wv][at + n32] : n32;
+            const float x = right_half(src, c);
             const float v = both_halves(x, x);
-            if (kh == 0 && at + n32 < cnt) out[col] = v;
+            if (kh == 0 && at + n32 < cnt) out[c] = v;
         }
         asm volatile("" ::: "memory");
     };
@@ -238,13 +243,13 @@ __global__ __launch_bounds__(128 * G, 2) void prune_relative_kernel(const PruneA
     int xbuf = 0;                             // buffer of the next exchange
     // maximum of kind `what` for this lane's column in the last exchange, over all the block's queries
     auto exchanged = [&](int what) {
-        return fmaxf(sh_max[xbuf ^ 1][wv][what][lane], sh_max[xbuf ^ 1][wv ^ 1][what][lane]);
+        return fmaxf(sh_max[xbuf ^ 1][wv][what][col], sh_max[xbuf ^ 1][wv ^ 1][what][col]);
     };
     auto exchange = [&](float right) {        // -> the right-branch maximum; the late ones of this turn can be read
-        sh_max[xbuf][wv][0][lane] = right;
+        sh_max[xbuf][wv][0][col] = right;
         handshake();
         xbuf ^= 1;
-        return fmaxf(right, sh_max[xbuf ^ 1][wv ^ 1][0][lane]);
+        return fmaxf(right, sh_max[xbuf ^ 1][wv ^ 1][0][col]);
     };
 
     if constexpr (PARTS == 1) load_queries();
@@ -258,20 +263,21 @@ __global__ __launch_bounds__(128 * G, 2) void prune_relative_kernel(const PruneA
     for (int it = 0; it < iters; ++it) {
         const int jt = (blockIdx.y * iters + it) * kCols;
         if (jt >= a.max_chunks) break;               // the whole workgroup
-        const int j = jt + lane;
+        const int j = jt + col;
         const int start = j < a.max_chunks ? slot_start(pr, a.parent_starts, a.n_parent, a.ratio_log2, a.chunk, p, j) : -1;
         const int len = start >= 0 ? min(a.chunk, pr.hi - start) : 0;
         int off = 0, half = a.chunk >> 1;
-        // The first key of a chunk and of its right half are the same rows for every head of the group: fetched once, 32
+        // The first key of a chunk and of its right half are the same rows for every head of the group: fetched once, the
         // four-row loads dealt to the waves.
         {
-            constexpr int kPerWave = 32 / NWV;
+            constexpr int kOfTile = kCols / 4, kPerWave = 2 * kOfTile / NWV;
+            static_assert(kPerWave * NWV == 2 * kOfTile, "the wave count divides the loads");
             const off_t at0 = row_at(max(start, 0)), at1 = row_at(half >= 1 && half < len ? start + half : 0);
             raw_t raw[KV8 ? kPerWave : 1];
 #pragma unroll
             for (int i = 0; i < kPerWave; ++i) {
-                const int ld = wv * kPerWave + i, r = ld & 15;       // wave-uniform
-                const off_t at = from_lane(ld < 16 ? at0 : at1, r * 4 + kq);
+                const int ld = wv * kPerWave + i, r = ld % kOfTile;  // wave-uniform
+                const off_t at = from_lane(ld < kOfTile ? at0 : at1, r * 4 + kq);
                 if constexpr (KV8) raw[i] = fetch(at, (r & 3) * 4 + kq);
                 else load4(at, lds_addr(sh_rows) + ld * kFourRows, (r & 3) * 4 + kq);
             }
@@ -316,15 +322,16 @@ __global__ __launch_bounds__(128 * G, 2) void prune_relative_kernel(const PruneA
         // first comparison: first keys as left branches, first keys of the right halves as right branches
         float l0;
         {
-            float l[4];
+            float l[kCols / 16];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
+            for (int t = 0; t < kCols / 16; ++t) {
                 l[t] = left_score(&sh_rows[0], t * 16 + n16);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            l0 = kq == 0 ? l[0] : kq == 1 ? l[1] : kq == 2 ? l[2] : l[3];
+            if constexpr (kCols == 32) l0 = (kq & 1) == 0 ? l[0] : l[1];
+            else l0 = kq == 0 ? l[0] : kq == 1 ? l[1] : kq == 2 ? l[2] : l[3];
         }
-        sh_max[xbuf][wv][1][lane] = l0;
+        sh_max[xbuf][wv][1][col] = l0;
         // sL: the current left key as a left branch; sigma: the same key as a right branch, which is what the chunk score
         // takes.  `won`: sL is still to come (the key won the last level); `ahead`: sigma is (the first key has not lost).
         float sigma = exchange(right_scores(&sh_rows[kTile]));
@@ -361,18 +368,18 @@ __global__ __launch_bounds__(128 * G, 2) void prune_relative_kernel(const PruneA
         }
         // chunk score = max over the group's heads (waves)
         if (qs == 0) {
-            sh_sigma[it & 1][hh][lane] = sigma;
-            if (a.out_rep != nullptr && j < a.max_chunks) {
+            sh_sigma[it & 1][hh][col] = sigma;
+            if (a.out_rep != nullptr && lane < kCols && j < a.max_chunks) {
                 const int64_t row = ((int64_t)(pr.b * a.ge.Hq + h) * a.ge.Mq + pr.m);
                 a.out_rep[row * a.max_chunks + j] = start >= 0 ? start + off : -1;
             }
         }
         __syncthreads();
-        if (wv == 0 && j < a.max_chunks) {
-            float best = sh_sigma[it & 1][0][lane];
-            for (int g2 = 1; g2 < G; ++g2) best = fmaxf(best, sh_sigma[it & 1][g2][lane]);
-            if (part > 0) best = fmaxf(best, sh_best[it][lane]);
-            if (part + 1 < PARTS) sh_best[it][lane] = best;
+        if (wv == 0 && lane < kCols && j < a.max_chunks) {
+            float best = sh_sigma[it & 1][0][col];
+            for (int g2 = 1; g2 < G; ++g2) best = fmaxf(best, sh_sigma[it & 1][g2][col]);
+            if (part > 0) best = fmaxf(best, sh_best[it][col]);
+            if (part + 1 < PARTS) sh_best[it][col] = best;
             else a.out_scores[(int64_t)p * a.max_chunks + j] = start >= 0 ? (KV8 ? best * a.k_scale : best) : -INFINITY;
         }
         // no barrier here: every wave has left its searches (the barrier above), the next iteration writes the other
@@ -382,24 +389,38 @@ __global__ __launch_bounds__(128 * G, 2) void prune_relative_kernel(const PruneA
 }
 
 // 64-query blocks
-template <bool WIDE, bool PAGED, bool KV8>
-static void launch_relative(const PruneArgs &a, int P, const RopeView &rope, hipStream_t st)
+template <int COLS, bool WIDE, bool PAGED, bool KV8>
+static void launch_relative_c(const PruneArgs &a, int P, const RopeView &rope, hipStream_t st)
 {
-    // several iterations of 64 chunks per workgroup amortise the rotation of the queries, as long as the launch still has
+    // several iterations per workgroup amortise the rotation of the queries, as long as the launch still has
     // a few thousand workgroups
-    int iters = kPrefillMaxIters / 2;
-    while (iters > 1 && (int64_t)P * ((a.max_chunks + 64 * iters - 1) / (64 * iters)) < 2048) iters >>= 1;
-    const int per_wg = 64 * iters;
+    int iters = COLS == 32 ? 1 : kPrefillMaxIters / 2;
+    while (iters > 1 && (int64_t)P * ((a.max_chunks + COLS * iters - 1) / (COLS * iters)) < 2048) iters >>= 1;
+    const int per_wg = COLS * iters;
     dim3 grid(P, (a.max_chunks + per_wg - 1) / per_wg);
     KernelTimer timer(stage_name(kNamePrunePrefill, a.parent_starts == nullptr, a.chunk), st);
     switch (a.ge.G) {
-    case 1: hipLaunchKernelGGL((prune_relative_kernel<1, WIDE, PAGED, 1, KV8>), grid, dim3(128), 0, st, a, iters, rope); break;
-    case 2: hipLaunchKernelGGL((prune_relative_kernel<2, WIDE, PAGED, 1, KV8>), grid, dim3(256), 0, st, a, iters, rope); break;
-    case 4: hipLaunchKernelGGL((prune_relative_kernel<4, WIDE, PAGED, 1, KV8>), grid, dim3(512), 0, st, a, iters, rope); break;
+    case 1: hipLaunchKernelGGL((prune_relative_kernel<COLS, 1, WIDE, PAGED, 1, KV8>), grid, dim3(128), 0, st, a, iters, rope); break;
+    case 2: hipLaunchKernelGGL((prune_relative_kernel<COLS, 2, WIDE, PAGED, 1, KV8>), grid, dim3(256), 0, st, a, iters, rope); break;
+    case 4: hipLaunchKernelGGL((prune_relative_kernel<COLS, 4, WIDE, PAGED, 1, KV8>), grid, dim3(512), 0, st, a, iters, rope); break;
     default:                                         // 8 heads: two passes of 4
-        hipLaunchKernelGGL((prune_relative_kernel<4, WIDE, PAGED, 2, KV8>), grid, dim3(512), 0, st, a, iters, rope);
+        hipLaunchKernelGGL((prune_relative_kernel<COLS, 4, WIDE, PAGED, 2, KV8>), grid, dim3(512), 0, st, a, iters, rope);
         break;
     }
+}
+
+template <bool WIDE, bool PAGED, bool KV8>
+static void launch_relative(const PruneArgs &a, int P, const RopeView &rope, hipStream_t st)
+{
+    // While the workgroups of 32 searches all run at once (eight waves of 256 registers fill a compute unit, two leave room for
+    // four of them), half the products per level make the shorter chain: 64 queries, 32 heads, chunks of 64, 16K keys 24.1 us
+    // with 64 searches per wave, 18.1 with 32; 64K keys (256 workgroups) 24.4 and 18.8.  Beyond, 64 do more per row:
+    // 128K keys 27.0 and 36.2.  One head per group, chunks of 64, 1,024 workgroups 20.9 and 18.7, chunks of 4, 936 of them
+    // 12.8 and 13.5; two heads, 512, 18.8 and 19.2.
+    const int per_cu = a.ge.G > 1 ? 1 : a.chunk >= 16 ? 4 : 2;
+    const bool few = (int64_t)P * ((a.max_chunks + 31) / 32) <= (int64_t)per_cu * compute_units();
+    if (few) launch_relative_c<32, WIDE, PAGED, KV8>(a, P, rope, st);
+    else launch_relative_c<64, WIDE, PAGED, KV8>(a, P, rope, st);
 }
 
 // Relative-style RoPE: 64-query blocks have a kernel of their own, smaller blocks (whose rotated operand sets fit one wave

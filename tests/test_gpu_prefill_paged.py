@@ -92,8 +92,9 @@ def test_paged_prefill_matches_contiguous_path_and_oracle(ihip, orc, w, page):
         assert np.abs(got - ref).max() <= 2e-2
 
 
-@pytest.mark.parametrize("w", [small(), small(b_q=16, Tq=64, Hq=4, Hkv=2, stages=((32, 8), (8, 16), (2, 40)))],
-                         ids=["llama", "bq16-3stage"])
+@pytest.mark.parametrize("w", [small(), small(b_q=16, Tq=64, Hq=4, Hkv=2, stages=((32, 8), (8, 16), (2, 40))),
+                               small(Tq=1024, prefix=8192, stages=((32, 64), (8, 64)))],
+                         ids=["llama", "bq16-3stage", "many-blocks"])
 def test_paged_prefill_with_rope_and_pooling_equals_contiguous(ihip, w):
     q, k, v, sl, _ = configs.make_inputs(w, 1)
     cos, sin = gen.rope_table(w.T, w.d)

@@ -357,10 +357,25 @@ def test_chunk_indexed_queries_before_the_cap(ihip, orc, b_q, Hq, Hkv, stages):
 @pytest.mark.parametrize("stages", [((4, 65), (2, 97), (1, 150)), ((2, 130),), ((1, 300),), ((8, 70), (4, 70)), ((256, 3), (32, 20))],
                          ids=["4-2-1", "2", "1", "8-4", "256-32"])
 def test_relative_64_query_blocks_at_the_edges(ihip, orc, Hq, Hkv, stages):
-    """The kernel of 64-query blocks walks 64 chunks per wave: chunks of one and two keys (no level after the first
-    comparison picks up the late scores), slot counts around 64 and 128, one and several groups of chunks per
-    workgroup, a last chunk cut short, empty slots.  Exact on the quarter-turn table."""
-    w = small(Tq=192, prefix=701, Hq=Hq, Hkv=Hkv, n_stream=100, n_sink=33, stages=stages)
+    """The kernel of 64-query blocks, few workgroups (32 chunks per wave): chunks of one and two keys (no level after the
+    first comparison picks up the late scores), slot counts around 64 and 128, a last chunk cut short, empty slots.
+    Exact on the quarter-turn table."""
+    relative_64_case(ihip, orc, small(Tq=192, prefix=701, Hq=Hq, Hkv=Hkv, n_stream=100, n_sink=33, stages=stages))
+
+
+@pytest.mark.parametrize("kw", [
+    dict(Hq=8, Hkv=8, B=2, prefix=701, stages=((1, 300),)),
+    dict(Hq=4, Hkv=2, B=2, prefix=1701, stages=((2, 530), (1, 600))),
+    dict(Hq=8, Hkv=2, B=2, prefix=3701, stages=((4, 430), (2, 450), (1, 500))),
+    dict(Hq=16, Hkv=2, B=1, prefix=1701, stages=((1, 1700),)),
+    dict(Hq=8, Hkv=2, B=1, Tq=1024, prefix=4701, stages=((16, 100), (4, 160))),
+], ids=["g1-1", "g2-2-1", "g4-4-2-1", "g8-1", "g4-16-4"])
+def test_relative_64_query_blocks_many_workgroups(ihip, orc, kw):
+    """The same with more workgroups than run at once: 64 chunks per wave."""
+    relative_64_case(ihip, orc, small(**{"Tq": 192, "n_stream": 100, "n_sink": 33, **kw}))
+
+
+def relative_64_case(ihip, orc, w):
     q, k, v, sl, _ = configs.make_inputs(w, 6, kind="int")
     cos, sin = gen.quarter_turn_table(w.T + 128, w.d)
     o = orc.Oracle(q, k, v, sl.tolist(), w.b_q, w.n_sink, w.n_stream,
