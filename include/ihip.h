@@ -61,7 +61,9 @@ typedef struct {
 typedef struct {
     int32_t B, Hq, Hkv, d;       /* d must be 128; Hq/Hkv in {1,2,4,8} */
     int32_t Tq, b_q;             /* new query tokens and query block size; decode: 1, 1 */
-    const int32_t *seq_lens;     /* device [B]: keys visible per sequence, the Tq new tokens included */
+    const int32_t *seq_lens;     /* device [B]: keys visible per sequence, the Tq new tokens included.  Decode: 0 for
+                                  * an idle place of the batch, of which no key and no block-table entry is read;
+                                  * its lists come out empty, its output unspecified */
     int32_t max_seq_len;         /* host-side upper bound of seq_lens (sizes the launch) */
     int32_t n_sink, n_stream;
     int32_t b_q_range;           /* 0 or b_q: every query block has its own candidate range.  Otherwise a
@@ -93,7 +95,8 @@ typedef struct {
  * prefill from device memory (all queries of a block share the relative
  * position; query t of a block gets its own chunk-indexed position and its own
  * streaming id, the latter from the number of keys it attends to).  The prefill
- * kernels round the rotated Q and K operands to bf16 for the matrix cores.
+ * attention rounds the rotated Q and K operands to bf16 for the matrix cores; the
+ * pruning kernels keep them to two bf16 operands or more, close to fp32.
  * Other uses return IHIP_ERR_UNSUPPORTED.
  */
 #define IHIP_ROPE_NONE          0
@@ -145,7 +148,7 @@ typedef struct ihip_cache ihip_cache;
  * pages, stride_h = between the KV heads of a page, stride_t = between the
  * tokens of a page.  block_table: device int32 [B][table_stride], the page id
  * of logical page i (tokens [i*page_tokens, (i+1)*page_tokens)) of sequence b;
- * entries beyond a sequence's length are never read.  page_tokens is a power
+ * entries beyond a sequence's length may hold anything, none is used.  page_tokens is a power
  * of two and table_stride * page_tokens >= max_seq_len.  Everything else as in
  * the entry points of the same names without the suffix.  Built for decode
  * and chunked prefill from bf16 pools; FP8 pools and the other variants
