@@ -56,6 +56,22 @@ __host__ __device__ inline Geometry make_geometry(const ihip_shape &s)
     return g;
 }
 
+// A decode launch's grid: `per_problem` workgroups for each of P problems.  Workgroups are dealt to the eight XCDs round-robin by
+// linear id; with the problem as the fastest index, and a multiple of eight KV heads, every workgroup of a problem, in every
+// kernel of a step, runs on the same XCD: its scores and lists are written and read through one L2, whole lines at a time, and
+// the rows that a later stage reads again may still be there.  With other head counts the XCDs would get different sequences
+// of a batch, whose lengths differ (4 KV heads, 16 ragged sequences of 250K: 290.9 / 299.3 us), or none: the part stays
+// fastest.  Layers, part / problem fastest (us): 8 problems of 8K keys 39.1 / 38.6, of
+// 128K 59.2 / 57.5, 64 of 1M 441.9 / 436.2, 32 of 250K in E4M3 pages 137.0 / 135.8.  Behind the host tier the link is the bound
+// and the order stays (867.8 / 871.8).
+struct DecodeGrid {
+    int problems_first;       // problems are the grid's x
+    __device__ int problem() const { return problems_first ? blockIdx.x : blockIdx.y; }
+    __device__ int part() const { return problems_first ? blockIdx.y : blockIdx.x; }
+    dim3 dims(int P, int per_problem) const { return problems_first ? dim3(P, per_problem) : dim3(per_problem, P); }
+};
+inline DecodeGrid decode_grid(const Geometry &ge, int per_problem, bool host_tier) { return DecodeGrid{!host_tier && ge.Hkv % 8 == 0 && per_problem <= 65535}; }
+
 struct Problem {
     int b, g, m;
     int lo, hi, E;      // middle range [lo, hi), visible keys [0, E)

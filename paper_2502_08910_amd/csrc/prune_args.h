@@ -23,6 +23,7 @@ struct PruneArgs {
     int32_t *out_rep;
     BankView bank;            // used by the cached instantiations only (K then points to host memory)
     PagedView paged;          // paged instantiations only: K is the page pool, k_sb the page stride
+    DecodeGrid grid;          // decode
     float k_scale;            // FP8 instantiations only: the scores are multiplied by it (K strides then
                               // count 2-byte units of the byte rows)
 };

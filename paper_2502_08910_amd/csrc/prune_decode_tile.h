@@ -159,11 +159,11 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
     using Rows = DecodeRows<SRC, NARROW>;
     using off_t = typename Rows::off_t;
     __shared__ int32_t sh_pages[SRC == 2 ? 4 * kChunks * kDecodePages : 1];
-    const int p = blockIdx.y;
+    const int p = a.grid.problem();
     const Problem pr = problem_of(a.ge, p);
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int n = lane & 15, kq = lane >> 4, quad = n >> 2;
-    const int j0 = (blockIdx.x * (blockDim.x >> 6) + wv) * kChunks;
+    const int j0 = (a.grid.part() * (blockDim.x >> 6) + wv) * kChunks;
     if (j0 >= a.max_chunks) return;
 
     // this lane's search: chunk `ci` of the wave, head `hd` of the group
@@ -296,11 +296,11 @@ __global__ __launch_bounds__(256, !ROPE && !KV8 ? 5 : 1) void prune_decode_four_
     constexpr int NT = decode_tile_chunks(G, 4, ROPE, KV8) / 4;  // tiles of a wave, all in flight at once
     constexpr int kLoads = KV8 ? 2 : 4;
     using Rows = DecodeRows<SRC, NARROW>;
-    const int p = blockIdx.y;
+    const int p = a.grid.problem();
     const Problem pr = problem_of(a.ge, p);
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int n = lane & 15, kq = lane >> 4;
-    const int j0 = (blockIdx.x * (blockDim.x >> 6) + wv) * NT * 4;
+    const int j0 = (a.grid.part() * (blockDim.x >> 6) + wv) * NT * 4;
     if (j0 >= a.max_chunks) return;
     const Rows rows(a, pr);
     // as the loader of row n: key n % 4 of chunk n / 4 of the tile (its first key where the chunk is cut short; without a
@@ -364,10 +364,12 @@ __global__ __launch_bounds__(256, !ROPE && !KV8 ? 5 : 1) void prune_decode_four_
 
 // b_q == 1, K through strides or pages
 template <int G, bool ROPE, int SRC, bool KV8, bool NARROW>
-static void launch_decode_tile_n(const PruneArgs &a, const RopeView &rope, int P, hipStream_t st)
+static void launch_decode_tile_n(PruneArgs a, const RopeView &rope, int P, hipStream_t st)
 {
     const int per_wg = decode_tile_chunks(G, a.chunk, ROPE, KV8) * kDecodeTileWaves;
-    const dim3 grid((a.max_chunks + per_wg - 1) / per_wg, P), block(64 * kDecodeTileWaves);
+    const int per_problem = (a.max_chunks + per_wg - 1) / per_wg;
+    a.grid = decode_grid(a.ge, per_problem, false);
+    const dim3 grid = a.grid.dims(P, per_problem), block(64 * kDecodeTileWaves);
     KernelTimer timer(stage_name(kNamePruneDecode, a.parent_starts == nullptr, a.chunk), st);
     // contiguous bf16 rows without RoPE: only chunks of four with eight heads come here (decode_on_tiles)
     constexpr bool kPlain = !ROPE && SRC == 0 && !KV8;

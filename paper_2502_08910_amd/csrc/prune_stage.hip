@@ -19,11 +19,11 @@ template <int G, int U, int SRC, bool KV8>
 __global__ __launch_bounds__(256) void prune_decode_kernel(const PruneArgs a)
 {
     using piece_t = typename std::conditional<KV8, uint2, uint4>::type;     // a lane's share of a row
-    const int p = blockIdx.y;
+    const int p = a.grid.problem();
     const Problem pr = problem_of(a.ge, p);
     const int l16 = threadIdx.x & 15;
     const int grp = threadIdx.x >> 4;
-    const int j0 = (blockIdx.x * 16 + grp) * U;
+    const int j0 = (a.grid.part() * 16 + grp) * U;
     if (j0 >= a.max_chunks) return;
 
     // this lane's 8 dims of the G query vectors
@@ -197,9 +197,11 @@ static void launch_prefill(const PruneArgs &a, int P, int64_t max_seq_len, const
 // (cfg3: 278 us against 283 us with U = 1 and 294 us with U = 2, whose 97 registers miss the fifth
 // wave by one).
 template <int G, int U>
-static void launch_decode_u(const PruneArgs &a, int P, bool fp8, hipStream_t st)
+static void launch_decode_u(PruneArgs a, int P, bool fp8, hipStream_t st)
 {
-    dim3 grid((a.max_chunks + 16 * U - 1) / (16 * U), P);
+    const int per_problem = (a.max_chunks + 16 * U - 1) / (16 * U);
+    a.grid = decode_grid(a.ge, per_problem, a.bank.page_table != nullptr);
+    const dim3 grid = a.grid.dims(P, per_problem);
     KernelTimer timer(stage_name(kNamePruneDecode, a.parent_starts == nullptr, a.chunk), st);
     if constexpr (U == 1) {
         if (fp8 && a.bank.page_table != nullptr)

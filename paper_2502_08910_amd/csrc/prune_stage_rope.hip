@@ -45,11 +45,11 @@ __global__ __launch_bounds__(256) void prune_decode_rope_kernel(const PruneArgs 
 {
     using piece_t = typename std::conditional<KV8, uint2, uint4>::type;     // a lane's share of a row
     constexpr int kLaneOff = KV8 ? 4 : 8;                                   // in 2-byte units
-    const int p = blockIdx.y;
+    const int p = a.grid.problem();
     const Problem pr = problem_of(a.ge, p);
     const int l16 = threadIdx.x & 15;
     const int grp = threadIdx.x >> 4;
-    const int j0 = (blockIdx.x * 16 + grp) * U;
+    const int j0 = (a.grid.part() * 16 + grp) * U;
 
     // chunk-indexed: the number of chunks this stage really has for this problem
     __shared__ int sh_n_chunk;
@@ -260,9 +260,11 @@ __global__ __launch_bounds__(256) void prune_decode_rope_kernel(const PruneArgs 
 }
 
 template <int G, int SRC, bool KV8, int U>
-static void launch_rope_u(const PruneArgs &a, const RopeView &rope, int style, int P, hipStream_t st)
+static void launch_rope_u(PruneArgs a, const RopeView &rope, int style, int P, hipStream_t st)
 {
-    dim3 grid((a.max_chunks + 16 * U - 1) / (16 * U), P);
+    const int per_problem = (a.max_chunks + 16 * U - 1) / (16 * U);
+    a.grid = decode_grid(a.ge, per_problem, a.bank.page_table != nullptr);
+    const dim3 grid = a.grid.dims(P, per_problem);
     KernelTimer timer(stage_name(kNamePruneDecode, a.parent_starts == nullptr, a.chunk), st);
     if (style == 1) hipLaunchKernelGGL((prune_decode_rope_kernel<G, U, 1, SRC, KV8>), grid, dim3(256), 0, st, a, rope);
     else hipLaunchKernelGGL((prune_decode_rope_kernel<G, U, 2, SRC, KV8>), grid, dim3(256), 0, st, a, rope);

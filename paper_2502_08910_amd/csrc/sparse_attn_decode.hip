@@ -28,6 +28,7 @@ struct AttnDecodeArgs {
     int n_blocks, block, block_log2;
     float scale_log2e;
     int n_splits, slots_per_split;
+    DecodeGrid grid;
     float *part_ml;      // [P, n_splits, G, 2]   (running max in log2 units, sum)
     float *part_acc;     // [P, n_splits, G, 128]
     uint16_t *out;       // bf16 [B, Hq, 1, d]
@@ -105,7 +106,7 @@ __global__ __launch_bounds__(kAttnThreads) void attn_decode_split_kernel(const A
 {
     using piece_t = typename std::conditional<KV8, uint2, uint4>::type;     // a lane's share of a row
     constexpr int kLaneOff = KV8 ? 4 : 8;                                   // in 2-byte units
-    const int p = blockIdx.y, split = blockIdx.x;
+    const int p = a.grid.problem(), split = a.grid.part();
     const Problem pr = problem_of(a.ge, p);
     const int l16 = threadIdx.x & 15, grp = threadIdx.x >> 4;
     const int n_sink_eff = min(a.ge.n_sink, pr.E);
@@ -484,7 +485,8 @@ int32_t launch_attn_decode(const ihip_shape &s, const ihip_tensor &q, const ihip
     a.out = (uint16_t *)out;
     a.out_lse = out_lse;
     if (P == 0) return IHIP_OK;
-    dim3 grid(a.n_splits, P);
+    a.grid = decode_grid(a.ge, a.n_splits, bank != nullptr);
+    const dim3 grid = a.grid.dims(P, a.n_splits);
     {
     KernelTimer timer("attn_decode_split", st);
     switch (G) {
