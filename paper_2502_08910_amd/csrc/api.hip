@@ -8,6 +8,8 @@
 #include <vector>
 
 #include "common.h"
+#include "select_chain.h"
+#include "prune_nest_args.h"
 
 namespace ihip {
 
@@ -85,7 +87,7 @@ void profile_end(hipStream_t st)
 // kernels' host launchers
 int32_t launch_prune_stage(const ihip_shape &, const ihip_tensor &, const ihip_tensor &, const int32_t *,
                            int, int, int, int, float *, int32_t *, const BankView *, const ihip_rope *, hipStream_t,
-                           const KvFormat * = nullptr);
+                           const KvFormat * = nullptr, const NestArgs * = nullptr);
 int32_t launch_subdivide_blocks(const ihip_shape &, const int32_t *, int, int, int32_t *, hipStream_t);
 int32_t launch_select_blocks(const ihip_shape &, const float *, int, const int32_t *, int, int, int, int,
                              int32_t *, bool, hipStream_t);
@@ -244,16 +246,100 @@ static bool layer_splits_fine(const ihip_shape &s, int n_stages, const int32_t *
            base + attn_decode_workspace(s, keeps[last], chunks[last], false) > (size_t)IHIP_STATIC_SCRATCH_BYTES;
 }
 
+// ---- all stages in one pass (prune_decode_nest.h, select_chain.hip) -------------
+// Scores per problem of all stages of a plan, 0 where the two kernels do not take it.  Rows of whole 256 bytes: a line is then
+// one workgroup's.
+static size_t nest_scores_per_problem(const ihip_shape &s, int n_stages, const int32_t *chunks, const int32_t *keeps)
+{
+    if (s.b_q != 1 || n_stages < 2 || n_stages > kChainMaxStages || chunks[n_stages - 1] < 4 || chunks[0] > (4 << (kNestLevels - 1))) return 0;
+    const int64_t slots = stage1_slots(s, chunks[0]);
+    if (slots == 0 || slots > kChainMaxSlots) return 0;
+    int64_t scores = 0;
+    for (int i = 0; i < n_stages; ++i) {
+        scores += (slots * (chunks[0] / chunks[i]) + 63) & ~63ll;
+        if (keeps[i] > kChainMaxKeep) return 0;
+        if (i > 0 && (chunks[i] == chunks[i - 1] || (int64_t)keeps[i - 1] * (chunks[i - 1] / chunks[i]) > kChainMaxSlots)) return 0;
+    }
+    return scores <= kChainMaxScores ? (size_t)scores : 0;
+}
+
+// Where one pass over all keys is the faster way.  It saves some 9 us of launches and latencies (more where the searches are
+// bound by instructions: E4M3 rows, RoPE, pages), and costs the keys that the stage-by-stage way does not read: all
+// but about 0.7 of the rows that the later stages' searches touch, at some 5.5 TB/s.  Stage by stage / in one pass (us) around the
+// lines, bf16 rows, 8 heads: 1 sequence of 24K keys 41.1 / 35.3, of 32K 41.5 / 38.9, 4 of 8K 54.0 / 45.3, of 16K 55.5 / 58.1,
+// 16 of 8K 117 / 108, of 16K 137 / 176; pages and RoPE 4 of 16K 72.0 / 69.2; E4M3 rows 4 of 16K 53.2 / 46.6, with pages and RoPE
+// 66.9 / 58.6, 16 of 16K 150.5 / 148.8.  Beyond some 400 MB of bf16 rows even short sequences gain nothing (32 of 8K 208.9 / 211.7).
+static bool nest_pays(const ihip_shape &s, int n_stages, const int32_t *chunks, const int32_t *keeps, bool fp8, bool heavy)
+{
+    const int64_t slots = stage1_slots(s, chunks[0]);
+    double later = 0;                         // rows that the later stages' searches touch, about 3.2 per level beyond the first
+    int64_t n = slots;
+    for (int i = 1; i < n_stages; ++i) {
+        n = std::min<int64_t>(keeps[i - 1], n) * (chunks[i - 1] / chunks[i]);
+        later += (double)n * std::min<double>(chunks[i], 2 + 3.2 * (__builtin_ctz(chunks[i]) - 1));
+    }
+    const double keys = (double)slots * chunks[0], row = fp8 ? 128 : 256, mega = 1.0 / (1 << 20), all = (double)s.B * s.Hkv * row * mega;
+    return all * keys <= 400 && all * (keys - 0.7 * later) <= (fp8 ? 120 : heavy ? 70 : 42);
+}
+
+static size_t nest_bytes(const ihip_shape &s, int n_stages, const int32_t *chunks, const int32_t *keeps)
+{
+    const size_t scores = nest_scores_per_problem(s, n_stages, chunks, keeps);
+    return scores && nest_pays(s, n_stages, chunks, keeps, true, true) ? align256((size_t)s.B * s.Hkv * scores * sizeof(float)) : 0;
+}
+
+// Scratch of a decode layer.  The scores of all stages taken together come last and are left out where a plan fits the
+// static array only without them, for the same reason as the fine splits.
+static size_t decode_layer_scratch(const ihip_shape &s, int n_stages, const int32_t *chunks, const int32_t *keeps, size_t *nest_part = nullptr)
+{
+    const int last = n_stages - 1;
+    const size_t base = plan_layout(s, n_stages, chunks, keeps).total + align256((size_t)s.B * s.Hkv * keeps[last] * sizeof(int32_t)) +
+                        attn_decode_workspace(s, keeps[last], chunks[last], layer_splits_fine(s, n_stages, chunks, keeps));
+    const size_t nest = nest_bytes(s, n_stages, chunks, keeps);
+    const bool count = nest > 0 && (align256(base) + nest <= (size_t)IHIP_STATIC_SCRATCH_BYTES || base > (size_t)IHIP_STATIC_SCRATCH_BYTES);
+    if (nest_part) *nest_part = count ? nest : 0;
+    return count ? align256(base) + nest : base;
+}
+
 // The stages of Alg. 1 whose bit is set in `due`.  stage_out[i] receives stage i's kept starts; a
 // stage that is re-run reads the list of the stage before it as it stands, re-run in this call or
 // cached from an earlier one (Alg. 4: a stage is re-run when its counter says so, with the current
 // lists of the earlier stages; a stage that is not due keeps its list).
+// nest_scores: room for the scores of all stages taken together (nest_bytes), or null: each stage on its own.
 static int32_t prune_stages_impl(const ihip_shape &s, const ihip_tensor &q, const ihip_tensor &k, int n_stages,
                                  const int32_t *chunks, const int32_t *keeps, uint32_t due,
                                  int32_t *const *stage_out, float *scores, const BankView *bank,
                                  const ihip_rope *rope, bool all_heads, hipStream_t st,
-                                 const KvFormat *fmt = nullptr)
+                                 const KvFormat *fmt = nullptr, float *nest_scores = nullptr)
 {
+    const uint32_t every = (1u << n_stages) - 1u;
+    const bool relative = rope && rope->prune_style == IHIP_ROPE_RELATIVE, paged = fmt && fmt->paged.block_table;
+    if (nest_scores && !bank && (due & every) == every && !(rope && rope->prune_style == IHIP_ROPE_CHUNK_INDEXED) &&
+        nest_pays(s, n_stages, chunks, keeps, fmt && fmt->fp8, relative || paged)) {
+        const int slots = stage1_slots(s, chunks[0]);
+        NestArgs nest{};
+        ChainPlan chain{};
+        nest.top = __builtin_ctz(chunks[0]) - 2;
+        nest.stride = chain.stride = (int)nest_scores_per_problem(s, n_stages, chunks, keeps);
+        chain.n_stages = n_stages;
+        chain.pool = all_heads ? s.Hkv : 1;
+        chain.scores = nest_scores;
+        int at = 0;
+        for (int i = 0; i < n_stages; ++i) {
+            const int lv = __builtin_ctz(chunks[i]) - 2, n = slots * (chunks[0] / chunks[i]);
+            nest.out[lv] = nest_scores + at;
+            nest.slots[lv] = n;
+            chain.at[i] = at;
+            chain.out[i] = stage_out[i];
+            chain.slots[i] = n;
+            chain.ratio_log2[i] = i == 0 ? 0 : __builtin_ctz(chunks[i - 1] / chunks[i]);
+            chain.chunk[i] = chunks[i];
+            chain.keep[i] = keeps[i];
+            at += (n + 63) & ~63;
+        }
+        const int32_t rc = launch_prune_stage(s, q, k, nullptr, 0, 0, chunks[0], slots, nullptr, nullptr, bank, rope, st, fmt, &nest);
+        return rc != IHIP_OK ? rc : launch_select_chain(s, chain, st);
+    }
     for (int i = 0; i < n_stages; ++i) {
         if (!((due >> i) & 1u)) continue;
         const int32_t *parents = i == 0 ? nullptr : stage_out[i - 1];
@@ -310,13 +396,14 @@ static int32_t prune_all_subdivided(const ihip_shape &s, const ihip_tensor &q, c
 static int32_t prune_all_impl(const ihip_shape &s, const ihip_tensor &q, const ihip_tensor &k, int n_stages,
                               const int32_t *chunks, const int32_t *keeps, int32_t *out_block_starts,
                               char *ws, const BankView *bank, const ihip_rope *rope, bool all_heads, hipStream_t st,
-                              const KvFormat *fmt = nullptr)
+                              const KvFormat *fmt = nullptr, float *nest_scores = nullptr)
 {
     const PlanLayout L = plan_layout(s, n_stages, chunks, keeps);
     int32_t *stage_out[8];
     for (int i = 0; i < n_stages; ++i)
         stage_out[i] = (i + 1 == n_stages) ? out_block_starts : (int32_t *)(ws + L.starts_off[i & 1]);
-    return prune_stages_impl(s, q, k, n_stages, chunks, keeps, ~0u, stage_out, (float *)(ws + L.scores_off), bank, rope, all_heads, st, fmt);
+    return prune_stages_impl(s, q, k, n_stages, chunks, keeps, ~0u, stage_out, (float *)(ws + L.scores_off), bank, rope, all_heads, st, fmt,
+                             nest_scores);
 }
 
 }  // namespace ihip
@@ -601,8 +688,9 @@ int32_t ihip_prune_all(const ihip_shape *shape, ihip_tensor q, ihip_tensor k, in
     const size_t need = plan_layout(*shape, n_stages, chunk_sizes, keeps).total;
     if (!ws || ws_bytes < need)
         return fail(IHIP_ERR_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", who, need, ws_bytes);
+    const size_t nested = nest_bytes(*shape, n_stages, chunk_sizes, keeps);
     return prune_all_impl(*shape, q, k, n_stages, chunk_sizes, keeps, out_block_starts, (char *)ws, nullptr, nullptr,
-                          false, (hipStream_t)stream);
+                          false, (hipStream_t)stream, nullptr, nested > 0 && ws_bytes >= need + nested ? (float *)((char *)ws + need) : nullptr);
 }
 
 // stage_starts != NULL: mask caching (the caller's per-stage lists; stages first_stage.. are recomputed,
@@ -631,6 +719,11 @@ static int32_t decode_layer_impl(const char *who, const ihip_shape *shape, ihip_
     const size_t attn_bytes = attn_decode_workspace(*shape, keeps[last], chunk_sizes[last], false);
     const bool fine_plan = layer_splits_fine(*shape, n_stages, chunk_sizes, keeps);
     const size_t fine_bytes = attn_decode_workspace(*shape, keeps[last], chunk_sizes[last], fine_plan);
+    size_t nested = 0;
+    (void)decode_layer_scratch(*shape, n_stages, chunk_sizes, keeps, &nested);
+    auto nest_scores = [&](size_t used) -> float * {      // behind the attention's scratch, where there is room
+        return nested > 0 && !cache && ws_bytes >= align256(used) + nested ? (float *)((char *)ws + align256(used)) : nullptr;
+    };
     BankView mask_bank, sa_bank;
     if (cache) {
         if ((rc = refuse_capture(who, (hipStream_t)stream)) != IHIP_OK) return rc;
@@ -650,7 +743,8 @@ static int32_t decode_layer_impl(const char *who, const ihip_shape *shape, ihip_
         for (int i = 0; i < n_stages; ++i)
             if (stage_due ? stage_due[i] != 0 : i >= first_stage) due |= 1u << i;
         rc = prune_stages_impl(*shape, q, k, n_stages, chunk_sizes, keeps, due, stage_out, (float *)ws,
-                               cache ? &mask_bank : nullptr, rope, all_heads, (hipStream_t)stream, fmt);
+                               cache ? &mask_bank : nullptr, rope, all_heads, (hipStream_t)stream, fmt,
+                               nest_scores(L.scores_bytes + fine_bytes));
         if (rc != IHIP_OK) return rc;
         if (out_block_starts &&
             hipMemcpyAsync(out_block_starts, stage_out[last], P * keeps[last] * sizeof(int32_t),
@@ -669,7 +763,7 @@ static int32_t decode_layer_impl(const char *who, const ihip_shape *shape, ihip_
     char *w = (char *)ws;
     int32_t *blocks = out_block_starts ? out_block_starts : (int32_t *)(w + L.total);
     rc = prune_all_impl(*shape, q, k, n_stages, chunk_sizes, keeps, blocks, w, cache ? &mask_bank : nullptr, rope,
-                        all_heads, (hipStream_t)stream, fmt);
+                        all_heads, (hipStream_t)stream, fmt, nest_scores(need - attn_bytes + fine_bytes));
     if (rc != IHIP_OK) return rc;
     return launch_attn_decode(*shape, q, k, v, blocks, keeps[last], chunk_sizes[last], sm_scale, out, out_lse,
                               w + L.total + blocks_bytes, fine_plan && ws_bytes >= L.total + blocks_bytes + fine_bytes,
@@ -1080,12 +1174,9 @@ size_t ihip_workspace_bytes(int32_t op, const ihip_shape *shape, int32_t n_stage
     case IHIP_OP_ATTN_PREFILL:
         return 256;
     case IHIP_OP_PRUNE_ALL:         // (never 0, which stands for an error: an empty batch needs nothing)
-        return std::max<size_t>(256, plan_layout(*shape, n_stages, chunk_sizes, keeps).total);
+        return std::max<size_t>(256, plan_layout(*shape, n_stages, chunk_sizes, keeps).total + nest_bytes(*shape, n_stages, chunk_sizes, keeps));
     case IHIP_OP_DECODE_LAYER:
-        return std::max<size_t>(256, plan_layout(*shape, n_stages, chunk_sizes, keeps).total +
-                                         align256(P * keeps[last] * sizeof(int32_t)) +
-                                         attn_decode_workspace(*shape, keeps[last], chunk_sizes[last],
-                                                               layer_splits_fine(*shape, n_stages, chunk_sizes, keeps)));
+        return std::max<size_t>(256, decode_layer_scratch(*shape, n_stages, chunk_sizes, keeps));
     case IHIP_OP_PREFILL_LAYER:
         return std::max<size_t>(256, plan_layout(*shape, n_stages, chunk_sizes, keeps).total +
                                          align256(P * keeps[last] * sizeof(int32_t)));

@@ -8,6 +8,7 @@
 // of a chunk are common to the heads, the rest are G independent loads in
 // flight).  U slots per group are interleaved to put more loads in flight.
 #include "prune_args.h"
+#include "prune_nest_args.h"
 #include "prune_relative.h"
 #include <type_traits>
 
@@ -232,6 +233,7 @@ static void launch_decode(const PruneArgs &a, int P, bool fp8, hipStream_t st)
 }
 
 void launch_prune_decode_tile(const PruneArgs &a, int P, bool fp8, const RopeView *rope, int64_t max_seq_len, hipStream_t st);
+void launch_prune_decode_nest(const PruneArgs &a, const NestArgs &nest, int P, bool fp8, const RopeView *rope, int64_t max_seq_len, hipStream_t st);
 int32_t launch_prune_stage_rope(const PruneArgs &a, const RopeView &rope, int style, int P, bool fp8, hipStream_t st);
 void launch_prune_prefill_fp8(const PruneArgs &a, int P, int b_q, const RopeView *rope, int style, hipStream_t st);
 
@@ -278,10 +280,11 @@ static bool decode_on_tiles(const PruneArgs &a, int P, bool fp8, bool relative)
     return (at_least(0.75) && at_most(1)) || at_least(2.5);                       // 0.94-1.09, 1.02-1.16; between them 0.89-1.05, 0.93-1.26
 }
 
+// nest: score this decode stage and the ones after it together (no host tier, no chunk-indexed style)
 int32_t launch_prune_stage(const ihip_shape &s, const ihip_tensor &q, const ihip_tensor &k,
                            const int32_t *parent_starts, int n_parent, int parent_chunk, int chunk,
                            int max_chunks, float *out_scores, int32_t *out_rep, const BankView *bank,
-                           const ihip_rope *rope, hipStream_t st, const KvFormat *fmt)
+                           const ihip_rope *rope, hipStream_t st, const KvFormat *fmt, const NestArgs *nest)
 {
     PruneArgs a;
     const bool fp8 = fmt && fmt->fp8;
@@ -320,6 +323,10 @@ int32_t launch_prune_stage(const ihip_shape &s, const ihip_tensor &q, const ihip
                         (long long)need);
         rope_view = RopeView{rope->cos, rope->sin, rope->n_pos};
         rope_style = style;
+        if (nest) {
+            launch_prune_decode_nest(a, *nest, P, fp8, &rope_view, s.max_seq_len, st);
+            return check_launch("prune_stage (decode, several stages, relative RoPE)");
+        }
         if (s.b_q == 1 && style == IHIP_ROPE_RELATIVE && !bank && decode_on_tiles(a, P, fp8, true)) {
             launch_prune_decode_tile(a, P, fp8, &rope_view, s.max_seq_len, st);
             return check_launch("prune_stage (decode, relative RoPE)");
@@ -327,6 +334,10 @@ int32_t launch_prune_stage(const ihip_shape &s, const ihip_tensor &q, const ihip
         if (s.b_q == 1) return launch_prune_stage_rope(a, rope_view, style, P, fp8, st);
     }
     const RopeView *rv = rope_view.cos ? &rope_view : nullptr;
+    if (nest) {
+        launch_prune_decode_nest(a, *nest, P, fp8, nullptr, s.max_seq_len, st);
+        return check_launch("prune_stage (decode, several stages)");
+    }
     if (s.b_q == 1 && !bank && decode_on_tiles(a, P, fp8, false)) {
         launch_prune_decode_tile(a, P, fp8, nullptr, s.max_seq_len, st);
         return check_launch("prune_stage (decode)");

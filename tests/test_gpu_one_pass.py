@@ -1,0 +1,107 @@
+"""Decode plans whose stages are scored in one pass over the middle range (prune_decode_nest.h, select_chain.hip) against the
+stage-by-stage kernels.  The same call takes the one or the other by its workspace: the scores of the one pass come last, and a
+byte less than ihip_workspace_bytes says leaves no room for them.  Inputs are small whole numbers (and quarter turns), so every
+score is exact in both and the lists and outputs have to be the same bits, ties included."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ihip():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2502_08910_amd as pkg
+    pkg.lib()
+    return pkg
+
+
+def _case(ihip, Hq, Hkv, lens, stages, fmt, rope, spread=3, n_sink=64, n_stream=256, pooling=None, seed=0):
+    g = torch.Generator().manual_seed(seed)
+    B, T, D = len(lens), max(lens), 128
+    whole = lambda *shape: torch.randint(-spread, spread + 1, shape, generator=g).float()
+    q, k, v = whole(B, Hq, 1, D).bfloat16().cuda(), whole(B, Hkv, T, D), whole(B, Hkv, T, D)
+    kw = {}
+    if "fp8" in fmt:
+        k, v = (t.to(torch.float8_e4m3fn).view(torch.uint8) for t in (k, v))
+        kw["kv_scales"] = (1.0, 1.0)
+    else:
+        k, v = k.bfloat16(), v.bfloat16()
+    k, v = k.cuda(), v.cuda()
+    if "paged" in fmt:
+        page = 16
+        n = -(-T // page)
+        order = torch.randperm(B * n, generator=g).cuda()
+        pools = []
+        for t in (k, v):
+            full = torch.zeros((B, Hkv, n * page, D), dtype=t.dtype, device="cuda")
+            full[:, :, :T] = t
+            pool = torch.empty((B * n, Hkv, page, D), dtype=t.dtype, device="cuda")
+            pool[order] = full.view(B, Hkv, n, page, D).permute(0, 2, 1, 3, 4).reshape(B * n, Hkv, page, D)
+            pools.append(pool)
+        kw["paged"] = ihip.binding.PagedKV(pools[0], pools[1], order.to(torch.int32).view(B, n).contiguous())
+    if rope:
+        turn = torch.arange(T + n_sink + n_stream + stages[-1][0] * stages[-1][1]) % 4          # quarter turns: cos and sin are 0 and +-1
+        c = torch.tensor([1.0, 0.0, -1.0, 0.0])[turn].view(-1, 1).repeat(1, D // 2).contiguous().cuda()
+        s = torch.tensor([0.0, 1.0, 0.0, -1.0])[turn].view(-1, 1).repeat(1, D // 2).contiguous().cuda()
+        kw["rope"] = ihip.binding.Rope(c, s, ihip.binding.ROPE_RELATIVE, ihip.binding.ROPE_STREAMING)
+    if pooling:
+        kw["pooling"] = ihip.binding.POOL_ALL_HEADS
+    chunks, keeps = [s[0] for s in stages], [s[1] for s in stages]
+    shape = torch.empty((B, Hkv, T, 0), dtype=torch.bfloat16)
+    L = ihip.Layer(q, shape, torch.tensor(lens, dtype=torch.int32, device="cuda"), 1, n_sink, n_stream)
+    need = L.workspace_bytes(ihip.OP_DECODE_LAYER, chunks, keeps)
+    got = []
+    for size in (need, need - 1):
+        ws = torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda")
+        blocks = torch.empty((L.P, keeps[-1]), dtype=torch.int32, device="cuda")
+        lse = torch.empty((B, Hq), dtype=torch.float32, device="cuda")
+        out = L.decode_layer(q, k, v, chunks, keeps, ws=ws, out_blocks=blocks, lse=lse, **kw)
+        torch.cuda.synchronize()
+        # the tail of the workspace says which way the call went
+        got.append((out.cpu(), lse.cpu(), blocks.cpu(), bool((ws[-256:] == 0xA5).all()) if size == need else None))
+    assert not got[0][3], "the plan was not scored in one pass"
+    assert torch.equal(got[0][2], got[1][2])
+    assert torch.equal(got[0][0].view(torch.int16), got[1][0].view(torch.int16)) and torch.equal(got[0][1], got[1][1])
+    return got[0][2]
+
+
+THREE = ((64, 12), (16, 20), (4, 40))
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "fp8", "paged", "fp8-paged"])
+@pytest.mark.parametrize("rope", [False, True], ids=["plain", "relative"])
+@pytest.mark.parametrize("Hq,Hkv", [(32, 8), (64, 8), (6, 3), (4, 4)])
+def test_storage_rope_and_groups(ihip, Hq, Hkv, fmt, rope):
+    _case(ihip, Hq, Hkv, [2405, 1501], THREE, fmt, rope)
+
+
+@pytest.mark.parametrize("stages", [
+    ((256, 5), (16, 30), (4, 60)), ((128, 9), (32, 17), (8, 33)), ((32, 50), (4, 100)), ((16, 64), (8, 65)), ((8, 200), (4, 200)),
+    ((256, 6), (64, 12), (16, 24), (4, 48)), ((64, 2048), (16, 1024), (4, 2048)), ((64, 1), (4, 1)),
+], ids=lambda s: "-".join("%d:%d" % x for x in s))
+@pytest.mark.parametrize("T", [4099, 5000, 400])
+def test_plans_and_lengths(ihip, stages, T):
+    """400: the middle range is shorter than a wave's 64 keys; the last chunk is cut short at 79 and 4 keys past a multiple of 256."""
+    _case(ihip, 8, 2, [T], stages, "bf16", T == 5000)
+
+
+def test_ragged_batch_with_idle_places(ihip):
+    """Sequences shorter than sink and window, and an empty place: their lists are empty."""
+    lens = [3000, 320, 1, 0, 321, 700]
+    blocks = _case(ihip, 32, 8, lens, THREE, "bf16", False)
+    for b, T in enumerate(lens):
+        assert (blocks.view(len(lens), 8, -1)[b] >= 0).any() == (T > 320), (b, T)
+    _case(ihip, 32, 8, lens, THREE, "fp8-paged", True)
+
+
+def test_pooled_over_all_heads(ihip):
+    blocks = _case(ihip, 16, 4, [2000, 1200], THREE, "bf16", False, pooling=True)
+    assert (blocks.view(2, 4, -1) == blocks.view(2, 4, -1)[:, :1]).all()
+
+
+def test_heavy_ties(ihip):
+    """All scores equal (more candidates in one bin than threads): the lowest positions are kept."""
+    blocks = _case(ihip, 8, 2, [9000], ((8, 800), (4, 900)), "bf16", False, spread=0)
+    assert torch.equal(blocks[0], 64 + 4 * torch.arange(900, dtype=torch.int32))
