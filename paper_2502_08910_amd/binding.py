@@ -397,10 +397,12 @@ class Layer:
             sm_scale = 1.0 / math.sqrt(self.d) if sm_scale is None else sm_scale
             out = torch.empty((self.B, self.Hq, self.Tq, self.d), dtype=torch.bfloat16, device=self.device)
             lse = torch.empty((self.B, self.Hq, self.Tq), dtype=torch.float32, device=self.device) if want_lse else None
+            if ws is None:
+                ws = self.workspace(OP_ATTN_PREFILL, [block], [max(block_starts.shape[-1], 1)])
             _check(lib().ihip_sparse_attn_prefill_fp8kv(
                 ctypes.byref(self.shape), _tensor(q, "q"), _tensor8(k, "k"), _tensor8(v, "v"), _ptr(block_starts),
                 block_starts.shape[-1], block, sm_scale, kv_scales[0], kv_scales[1],
-                rope.ref() if rope is not None else None, _ptr(out), _ptr(lse), None, 0, _stream()))
+                rope.ref() if rope is not None else None, _ptr(out), _ptr(lse), _ptr(ws), ws.numel(), _stream()))
             return out, lse
         if paged is not None:
             def fn(shape, tq, tk, tv, bs, n_blocks, blk, scale, out, lse, w, w_bytes, stream):

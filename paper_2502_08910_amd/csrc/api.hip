@@ -101,7 +101,8 @@ int32_t refuse_capture(const char *, hipStream_t);
 size_t attn_decode_workspace(const ihip_shape &, int, int, bool);
 int32_t launch_attn_prefill(const ihip_shape &, const ihip_tensor &, const ihip_tensor &,
                             const ihip_tensor &, const int32_t *, int, int, float, void *, float *,
-                            const ihip_rope *, hipStream_t, const KvFormat * = nullptr);
+                            void *, size_t, const ihip_rope *, hipStream_t, const KvFormat * = nullptr);
+size_t attn_prefill_workspace(const ihip_shape &, int, int);
 
 static bool pow2(int x) { return x > 0 && (x & (x - 1)) == 0; }
 
@@ -616,7 +617,6 @@ static int32_t attn_prefill_entry(const char *who, const ihip_rope *rope, const 
                                   size_t ws_bytes, void *stream)
 {
     int32_t rc;
-    (void)ws; (void)ws_bytes;       // this kernel needs no scratch
     if ((rc = check_shape(shape, who)) != IHIP_OK) return rc;
     if (shape->B == 0) return IHIP_OK;          // an empty batch: nothing to do, no pointer is looked at
     if (shape->b_q != 16 && shape->b_q != 32 && shape->b_q != 64)
@@ -627,7 +627,7 @@ static int32_t attn_prefill_entry(const char *who, const ihip_rope *rope, const 
     if (n_blocks < 0 || !pow2(block)) return fail(IHIP_ERR_INVALID_ARG, "%s: n_blocks = %d, block = %d", who, n_blocks, block);
     if (n_blocks > 0 && !block_starts) return fail(IHIP_ERR_INVALID_ARG, "%s: block_starts is NULL", who);
     if (!out) return fail(IHIP_ERR_INVALID_ARG, "%s: out is NULL", who);
-    return launch_attn_prefill(*shape, q, k, v, block_starts, n_blocks, block, sm_scale, out, out_lse, rope,
+    return launch_attn_prefill(*shape, q, k, v, block_starts, n_blocks, block, sm_scale, out, out_lse, ws, ws_bytes, rope,
                                (hipStream_t)stream, fmt);
 }
 
@@ -1077,8 +1077,9 @@ static int32_t prefill_layer_impl(const char *who, bool all_heads, const ihip_ro
                             (hipStream_t)stream, fmt);
     }
     if (rc != IHIP_OK) return rc;
+    // the attention's scratch, where there is room for it, comes behind the lists
     return launch_attn_prefill(attn_shape, q, k, v, blocks, keeps[last], chunk_sizes[last], sm_scale, out, out_lse,
-                               rope, (hipStream_t)stream, fmt);
+                               w + need, ws_bytes - need, rope, (hipStream_t)stream, fmt);
 }
 
 int32_t ihip_prefill_layer(const ihip_shape *shape, ihip_tensor q, ihip_tensor k, ihip_tensor v, int32_t n_stages,
@@ -1172,14 +1173,15 @@ size_t ihip_workspace_bytes(int32_t op, const ihip_shape *shape, int32_t n_stage
     case IHIP_OP_ATTN_DECODE:
         return std::max<size_t>(256, attn_decode_workspace(*shape, keeps[last], chunk_sizes[last], true));
     case IHIP_OP_ATTN_PREFILL:
-        return 256;
+        return std::max<size_t>(256, attn_prefill_workspace(*shape, keeps[last], chunk_sizes[last]));
     case IHIP_OP_PRUNE_ALL:         // (never 0, which stands for an error: an empty batch needs nothing)
         return std::max<size_t>(256, plan_layout(*shape, n_stages, chunk_sizes, keeps).total + nest_bytes(*shape, n_stages, chunk_sizes, keeps));
     case IHIP_OP_DECODE_LAYER:
         return std::max<size_t>(256, decode_layer_scratch(*shape, n_stages, chunk_sizes, keeps));
     case IHIP_OP_PREFILL_LAYER:
         return std::max<size_t>(256, plan_layout(*shape, n_stages, chunk_sizes, keeps).total +
-                                         align256(P * keeps[last] * sizeof(int32_t)));
+                                         align256(P * keeps[last] * sizeof(int32_t)) +
+                                         attn_prefill_workspace(*shape, keeps[last], chunk_sizes[last]));
     default:
         fail(IHIP_ERR_INVALID_ARG, "ihip_workspace_bytes: unknown op %d", op);
         return 0;

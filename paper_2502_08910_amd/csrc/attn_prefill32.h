@@ -97,20 +97,14 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     uint16_t *raw0 = smem + kPfStages * kPfStageEl;                          // KV8: the raw stages
     int *sPos = reinterpret_cast<int *>(raw0 + (KV8 ? kPfRawStages * kPfTileEl : 0));   // one int per key slot
-    // the most slots this geometry can have
-    const int slots_cap = (a.ge.n_sink + a.n_blocks * a.block + a.ge.n_stream + kPfTile - 1) / kPfTile * kPfTile;
+    const int slots_cap = a.slots_cap;
     int *sPage = sPos + slots_cap;                                           // PAGED: one page id per key slot
     // one flag per tile, behind the per-slot arrays
     uint8_t *sMasked = reinterpret_cast<uint8_t *>(sPos + (PAGED ? 2 : 1) * slots_cap);
 
-    int p = blockIdx.x, head_part = 0;
-    if (a.ge.G != G) {                               // blocks of 8 problems x (G_total/G) parts
-        const int parts = a.ge.G / G;
-        const int r = blockIdx.x % (8 * parts);
-        p = blockIdx.x / (8 * parts) * 8 + (r & 7);
-        head_part = r >> 3;
-        if (p >= a.ge.B * a.ge.Hkv * a.ge.Mq) return;
-    }
+    const PfWorkgroup wg = pf_workgroup(blockIdx.x, a.ge.G / G);
+    const int p = wg.p, head_part = wg.head_part;
+    if (p >= a.ge.B * a.ge.Hkv * a.ge.Mq) return;
     const Problem pr = problem_of(a.ge, p);
     constexpr int NW = NQ * G;
     constexpr int nthreads = 64 * NW;
@@ -127,11 +121,19 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
     const int n_sink_eff = min(a.ge.n_sink, pr.E);
     const int w0 = max(pr.hi, a.ge.n_sink);
     const int total = n_sink_eff + (a.n_blocks << a.block_log2) + max(0, pr.E - w0);
-    const int n_tiles = (total + kPfTile - 1) / kPfTile;     // host guarantees n_tiles*32 <= kPf32MaxSlots
+    // tiles are numbered within the split, whose first key slot is slot0; host guarantees n_tiles*32 <= slots_cap
+    const int slot0 = blockIdx.y * a.tiles_per_split * kPfTile;
+    const int n_tiles = min((total + kPfTile - 1) / kPfTile - (int)blockIdx.y * a.tiles_per_split, a.tiles_per_split);
+    if (n_tiles <= 0) {                              // a sequence too short for this split: nothing, with weight 0
+        float4 *to = a.part_o + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * NW * 16 * 64;
+        for (int i = tid; i < NW * 16 * 64; i += nthreads) to[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        a.part_ml[((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * nthreads + tid] = make_float2(kNegBigPf, 0.f);
+        return;
+    }
 
     // a tile needs masking if it has an empty slot or a key at or after the block's first query
     for (int slot = tid; slot < n_tiles * kPfTile; slot += nthreads) {
-        const int pos = slot < total ? pf_slot_to_pos(a, pr, p, slot, n_sink_eff, w0) : -1;
+        const int pos = slot0 + slot < total ? pf_slot_to_pos(a, pr, p, slot0 + slot, n_sink_eff, w0) : -1;
         sPos[slot] = pos;
         if constexpr (PAGED)        // an empty slot fetches row 0 of the sequence
             sPage[slot] = a.paged.block_table[(int64_t)pr.b * a.paged.table_stride + (max(pos, 0) >> a.paged.page_log2)];
@@ -253,7 +255,7 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
 #pragma unroll
             for (int i = 0; i < kPieces; ++i) {
                 const int item = tid + i * nthreads, r = (item >> 4) & (kPfTile - 1), sl = item & 15;
-                const int slot = tile * kPfTile + r;
+                const int slot = slot0 + tile * kPfTile + r;
                 const int id = tile < n_tiles && slot < total ? ids.key(slot) : 0;
                 const int64_t at = (int64_t)id * (kD / 2) + ((KV8 ? sl : sl ^ (r & 15)) << 2);
                 tb.c[i] = *reinterpret_cast<const float4 *>(a.rope_cos + at);
@@ -514,6 +516,17 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
 
     float l = l_run;
     l += __shfl_xor(l, 32, 64);
+    if (a.n_splits > 1) {
+        const int64_t unit = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * NW + wave;
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4)
+                a.part_o[(unit * 16 + dt * 4 + r4) * 64 + lane] =
+                    make_float4(o[dt][r4 * 4], o[dt][r4 * 4 + 1], o[dt][r4 * 4 + 2], o[dt][r4 * 4 + 3]);
+        a.part_ml[unit * 64 + lane] = make_float2(m_run, l);
+        return;
+    }
     const float inv = KV8 ? a.v_scale / l : 1.0f / l;
     const int64_t row = ((int64_t)pr.b * a.ge.Hq + h) * a.ge.Tq + q0 + n;
 #pragma unroll

@@ -28,7 +28,21 @@ struct AttnPrefillArgs {
     PagedView paged;                    // paged instantiations only: k / v are the page pools, k_sb / v_sb
                                         // the page strides
     float v_scale;                      // E4M3 instantiations only (K, V strides then count 2-byte units)
+    // The key list of a problem may be cut into splits (blockIdx.y), whose results are merged by a second kernel
+    int n_splits, tiles_per_split;      // 1 and all tiles: the kernel writes the output itself
+    int slots_cap;                      // key slots of a split, a multiple of the tile (what a kernel may keep in LDS)
+    float4 *part_o;                     // [split][wave][i][lane]: a lane's accumulators, four at a time (waves of all workgroups)
+    float2 *part_ml;                    // [split][wave][query tile][lane]: reference of the exponentials (log2 units) and sum
 };
+
+// Which (problem, part of the head group) workgroup `wg` of a split works on, and a wave's unit
+struct PfWorkgroup { int p, head_part; };
+__device__ inline PfWorkgroup pf_workgroup(int wg, int parts)
+{
+    if (parts == 1) return PfWorkgroup{wg, 0};
+    const int r = wg % (8 * parts);                  // blocks of 8 problems x parts
+    return PfWorkgroup{wg / (8 * parts) * 8 + (r & 7), r >> 3};
+}
 
 // Streaming-style positions (Sec. 4 "Dynamic RoPE for OOL generalization"): the keys a query
 // attends to, in position order, sit at 0, 1, ..., n-1 and the query at n-1.  Attended slots are a
@@ -105,6 +119,11 @@ constexpr int kPf32MaxSlotsFp8Paged = pf32_max_slots(kPfFp8StageBytes, 2);
 static_assert(kPf32MaxSlots * 4 + kPf32MaxSlots / kPfTile + kPfStagesPlain * kPfStageBytes + 64 <= kPf32MaxLds, "LDS");
 static_assert(kPf32MaxSlotsFp8Paged * 8 + kPf32MaxSlotsFp8Paged / kPfTile + kPfFp8StageBytes + 64 <= kPf32MaxLds, "LDS");
 
+// dynamic LDS of a launch: stages, slot positions (and pages), per-tile flags
+inline size_t pf32_lds(int slots, bool rope, bool paged, bool fp8)
+{
+    return (fp8 ? kPfFp8StageBytes : (rope ? kPfStagesRope : kPfStagesPlain) * kPfStageBytes) + (size_t)slots * 4 * (paged ? 2 : 1) + slots / kPfTile;
+}
 void launch_attn_prefill32(const AttnPrefillArgs &a, int P, int64_t max_seq_len, hipStream_t st);
 void launch_attn_prefill32_fp8(const AttnPrefillArgs &a, int P, hipStream_t st);   // E4M3 K and V
 

@@ -17,6 +17,7 @@
 // key kq*4+j-4 of the second for j >= 4 -- exactly what a lane's two S^T
 // accumulators hold.  V is transposed on its way into LDS.
 #include "attn_prefill_args.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace ihip {
@@ -51,7 +52,8 @@ __global__ __launch_bounds__(64 * G) void attn_prefill_kernel(const AttnPrefillA
     const int n_sink_eff = min(a.ge.n_sink, pr.E);
     const int w0 = max(pr.hi, a.ge.n_sink);
     const int total = n_sink_eff + (a.n_blocks << a.block_log2) + max(0, pr.E - w0);
-    const int n_tiles = (total + kPfTile - 1) / kPfTile;
+    const int first_tile = blockIdx.y * a.tiles_per_split;
+    const int n_tiles = min((total + kPfTile - 1) / kPfTile, first_tile + a.tiles_per_split);      // up to here, in this split
     StreamIds ids{n_sink_eff, a.n_blocks << a.block_log2, 0, w0};
     if constexpr (ROPE) {
         __shared__ int sh_tokens;
@@ -167,8 +169,8 @@ __global__ __launch_bounds__(64 * G) void attn_prefill_kernel(const AttnPrefillA
         if (need_mask) sFlag[tile & 1] = 1;
     };
 
-    if (n_tiles > 0) fetch(0);
-    for (int tile = 0; tile < n_tiles; ++tile) {
+    if (first_tile < n_tiles) fetch(first_tile);
+    for (int tile = first_tile; tile < n_tiles; ++tile) {
         if (tid == 0) sFlag[tile & 1] = 0;     // last read two tiles (and two barriers) ago
         __syncthreads();                       // previous tile fully consumed, flag cleared
         stash(tile);
@@ -249,6 +251,14 @@ __global__ __launch_bounds__(64 * G) void attn_prefill_kernel(const AttnPrefillA
         float l = l_run[qt];
         l += __shfl_xor(l, 16, 64);
         l += __shfl_xor(l, 32, 64);
+        if (a.n_splits > 1) {
+            const int64_t unit = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * G + hh;
+#pragma unroll
+            for (int dt = 0; dt < 8; ++dt)
+                a.part_o[(unit * 8 * QT + dt * QT + qt) * 64 + lane] = make_float4(o[dt][qt][0], o[dt][qt][1], o[dt][qt][2], o[dt][qt][3]);
+            a.part_ml[(unit * QT + qt) * 64 + lane] = make_float2(m_run[qt], l);
+            continue;
+        }
         const float inv = KV8 ? a.v_scale / l : 1.0f / l;
         const int64_t row = ((int64_t)pr.b * a.ge.Hq + h) * a.ge.Tq + q0 + qt * 16 + n;
 #pragma unroll
@@ -264,9 +274,154 @@ __global__ __launch_bounds__(64 * G) void attn_prefill_kernel(const AttnPrefillA
     }
 }
 
+// Merges the splits: one workgroup per wave of a split's launch, wave w of it takes a quarter of the lane's float4s.
+// QT 0: the 32x32 kernel's layout (query lane % 32, element dt*4 + r4: dims 32*dt + 8*r4 + 4*(lane/32)..+3), in
+// workgroups of `waves` waves with `heads` heads; otherwise the 16x16 kernel's (query tile i % QT, element i / QT = dt: dims
+// 16*dt + 4*(lane/16)..+3).
+template <int QT>
+__global__ __launch_bounds__(256) void attn_prefill_merge_kernel(const AttnPrefillArgs a, const int n_units, const int waves, const int heads)
+{
+    constexpr int kElements = QT == 0 ? 16 : 8 * QT, kPerWave = kElements / 4, kTiles = QT == 0 ? 1 : QT;
+    const int unit = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const PfWorkgroup wg = pf_workgroup(unit / waves, QT == 0 ? a.ge.G / heads : 1);
+    if (wg.p >= a.ge.B * a.ge.Hkv * a.ge.Mq) return;
+    const int wave = unit % waves, m = wg.p % a.ge.Mq, bg = wg.p / a.ge.Mq, g = bg % a.ge.Hkv, b = bg / a.ge.Hkv;
+    const int h = g * a.ge.G + wg.head_part * heads + wave % heads;
+    float M[kTiles], L[kTiles];
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t) { M[t] = kNegBigPf; L[t] = 0.f; }
+    for (int s = 0; s < a.n_splits; ++s)
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t) M[t] = fmaxf(M[t], a.part_ml[(((int64_t)s * n_units + unit) * kTiles + t) * 64 + lane].x);
+    float4 acc[kPerWave];
+#pragma unroll
+    for (int i = 0; i < kPerWave; ++i) acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 2
+    for (int s = 0; s < a.n_splits; ++s) {
+        const int64_t at = (int64_t)s * n_units + unit;
+        float w[kTiles];
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t) {
+            const float2 ml = a.part_ml[(at * kTiles + t) * 64 + lane];
+            w[t] = __builtin_amdgcn_exp2f(ml.x - M[t]);
+            L[t] = fmaf(w[t], ml.y, L[t]);
+        }
+#pragma unroll
+        for (int i = 0; i < kPerWave; ++i) {
+            const float4 x = a.part_o[(at * kElements + wv * kPerWave + i) * 64 + lane];
+            const float ww = w[(wv * kPerWave + i) % kTiles];
+            acc[i].x = fmaf(ww, x.x, acc[i].x);
+            acc[i].y = fmaf(ww, x.y, acc[i].y);
+            acc[i].z = fmaf(ww, x.z, acc[i].z);
+            acc[i].w = fmaf(ww, x.w, acc[i].w);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kPerWave; ++i) {
+        const int e = wv * kPerWave + i;
+        const int t = e % kTiles, query = QT == 0 ? wave / heads * 32 + (lane & 31) : t * 16 + (lane & 15);
+        const int dim = QT == 0 ? e * 8 + (lane >> 5) * 4 : e / kTiles * 16 + (lane >> 4) * 4;
+        const float inv = a.v_scale / L[t];
+        const int64_t row = ((int64_t)b * a.ge.Hq + h) * a.ge.Tq + m * a.ge.b_q + query;
+        uint2 w;
+        w.x = f32_to_bf16_bits(acc[i].x * inv) | (f32_to_bf16_bits(acc[i].y * inv) << 16);
+        w.y = f32_to_bf16_bits(acc[i].z * inv) | (f32_to_bf16_bits(acc[i].w * inv) << 16);
+        *reinterpret_cast<uint2 *>(a.out + row * kD + dim) = w;
+        if (a.out_lse != nullptr && dim == 0) a.out_lse[row] = (M[t] + log2f(L[t])) * 0.69314718055994530942f;
+    }
+}
+
+// Splits of the key lists, and the scratch for them.
+struct PfSplits {
+    int n, tiles_each, units, elements, query_tiles, waves, heads;       // units: waves of a split's launch
+    size_t bytes;
+};
+static bool prefill_on_32(const ihip_shape &s, int n_blocks, int block, bool rope, bool paged, bool fp8)
+{
+    // the 32x32 kernel keeps every slot's position in LDS; longer key lists take the 16x16 one
+    const int limit = fp8 ? (paged ? kPf32MaxSlotsFp8Paged : kPf32MaxSlotsFp8)
+                          : rope ? (paged ? kPf32MaxSlotsRopePaged : kPf32MaxSlotsRope) : (paged ? kPf32MaxSlotsPaged : kPf32MaxSlots);
+    return s.b_q >= 32 && (int64_t)s.n_sink + (int64_t)n_blocks * block + s.n_stream <= limit;
+}
+// A launch of few workgroups leaves compute units idle while each walks its whole key list: as many splits then as the
+// chip holds at once (eight waves per compute unit with these kernels' registers, but not more than two workgroups: more
+// waves of fewer workgroups cost the merge what they gain), of eight tiles and more (16-query blocks: six; a split starts and
+// ends for about six tiles' time), at most 16.  What a split costs is its partial result, 16 KB a wave written and read again,
+// 33 MB each way with the chip full: two splits have to save 16 tiles of time, and 48 where the second workgroup of a compute
+// unit is what they add.  One split / these (us), 100 tiles of 32 keys, 32 heads on 8: 64-query blocks, 16 workgroups 87 / 28, 64
+// 89 / 44, 128 92 / 70, (256 112 / 133, not split); 32-query blocks 16 67 / 23, 128 70 / 46, 256 77 / 75; 16-query blocks 16 191 / 32,
+// 64 203 / 46, 256 203 / 125; streaming RoPE 64 121 / 59; E4M3 rows 64 100 / 46.
+static PfSplits prefill_splits(const ihip_shape &s, int n_blocks, int block, bool on_32, bool one_per_cu = false)
+{
+    const int G = s.Hq / s.Hkv, P = s.B * s.Hkv * (s.Tq / s.b_q);
+    PfSplits r{};
+    if (on_32) {
+        const int NQ = s.b_q / 32;
+        r.heads = NQ * G > 8 ? G / 2 : G;
+        r.waves = NQ * r.heads;
+        r.units = (G == r.heads ? P : (P + 7) / 8 * 8 * (G / r.heads)) * r.waves;
+        r.elements = 16;
+        r.query_tiles = 1;
+    } else {
+        r.heads = r.waves = G;
+        r.units = P * G;
+        r.query_tiles = s.b_q / 16;
+        r.elements = 8 * r.query_tiles;
+    }
+    const int tiles = (int)(((int64_t)s.n_sink + (int64_t)n_blocks * block + s.n_stream + kPfTile - 1) / kPfTile);
+    const int wgs = std::max(1, r.units / r.waves), cu = compute_units(), places = cu * (one_per_cu ? 1 : std::max(1, std::min(2, 8 / r.waves)));
+    int n = std::min({places / wgs, tiles / (s.b_q == 16 ? 6 : 8), 16});
+    if (n < 2 || tiles - tiles / n < (on_32 && n * wgs > cu && wgs > cu / 2 ? 48 : 16)) n = 1;
+    r.tiles_each = (tiles + n - 1) / n;
+    r.n = (tiles + r.tiles_each - 1) / r.tiles_each;
+    r.bytes = r.n > 1 ? (size_t)r.n * r.units * 64 * (r.elements * sizeof(float4) + r.query_tiles * sizeof(float2)) : 0;
+    return r;
+}
+// whatever the storage and style are
+size_t attn_prefill_workspace(const ihip_shape &s, int n_blocks, int block)
+{
+    return std::max(prefill_splits(s, n_blocks, block, s.b_q >= 32).bytes, prefill_splits(s, n_blocks, block, false).bytes);
+}
+
+static int32_t launch_attn_prefill_splits(const ihip_shape &s, const AttnPrefillArgs &a, int P, bool on_32, bool use_rope, bool paged, bool fp8,
+                                          hipStream_t st)
+{
+    KernelTimer timer("attn_prefill", st);
+    const dim3 block_dim(64 * a.ge.G), grid(P, a.n_splits);
+#define IHIP_PF_BY_G3(KERNEL, QT, RP, PG, F8)                                                      \
+    switch (a.ge.G) {                                                                              \
+    case 1: hipLaunchKernelGGL((KERNEL<QT, 1, RP, PG, F8>), grid, block_dim, 0, st, a); break;     \
+    case 2: hipLaunchKernelGGL((KERNEL<QT, 2, RP, PG, F8>), grid, block_dim, 0, st, a); break;     \
+    case 4: hipLaunchKernelGGL((KERNEL<QT, 4, RP, PG, F8>), grid, block_dim, 0, st, a); break;     \
+    default: hipLaunchKernelGGL((KERNEL<QT, 8, RP, PG, F8>), grid, block_dim, 0, st, a); break;    \
+    }
+#define IHIP_PF_BY_G2(KERNEL, QT, RP, PG)                                                          \
+    if (fp8) { IHIP_PF_BY_G3(KERNEL, QT, RP, PG, true) } else { IHIP_PF_BY_G3(KERNEL, QT, RP, PG, false) }
+#define IHIP_PF_BY_G(KERNEL, QT)                                                                   \
+    if (use_rope && paged) { IHIP_PF_BY_G2(KERNEL, QT, true, true) }                               \
+    else if (use_rope) { IHIP_PF_BY_G2(KERNEL, QT, true, false) }                                  \
+    else if (paged) { IHIP_PF_BY_G2(KERNEL, QT, false, true) }                                     \
+    else { IHIP_PF_BY_G2(KERNEL, QT, false, false) }
+    if (on_32) {
+        if (fp8) launch_attn_prefill32_fp8(a, P, st);
+        else launch_attn_prefill32(a, P, s.max_seq_len, st);
+        return check_launch("sparse_attn_prefill");
+    }
+    switch (s.b_q) {
+    case 16: IHIP_PF_BY_G(attn_prefill_kernel, 1); break;
+    case 32: IHIP_PF_BY_G(attn_prefill_kernel, 2); break;
+    case 64: IHIP_PF_BY_G(attn_prefill_kernel, 4); break;
+    default: return fail(IHIP_ERR_UNSUPPORTED, "sparse_attn_prefill: b_q = %d not in {16, 32, 64}", s.b_q);
+    }
+#undef IHIP_PF_BY_G
+#undef IHIP_PF_BY_G2
+#undef IHIP_PF_BY_G3
+    return check_launch("sparse_attn_prefill");
+}
+
 int32_t launch_attn_prefill(const ihip_shape &s, const ihip_tensor &q, const ihip_tensor &k,
                             const ihip_tensor &v, const int32_t *block_starts, int n_blocks, int block,
-                            float sm_scale, void *out, float *out_lse, const ihip_rope *rope, hipStream_t st,
+                            float sm_scale, void *out, float *out_lse, void *ws, size_t ws_bytes, const ihip_rope *rope, hipStream_t st,
                             const KvFormat *fmt)
 {
     AttnPrefillArgs a;
@@ -306,43 +461,29 @@ int32_t launch_attn_prefill(const ihip_shape &s, const ihip_tensor &q, const ihi
     a.out_lse = out_lse;
     const int P = s.B * s.Hkv * (s.Tq / s.b_q);
     if (P == 0) return IHIP_OK;
-    KernelTimer timer("attn_prefill", st);
-    const dim3 block_dim(64 * a.ge.G), grid(P);
-#define IHIP_PF_BY_G3(KERNEL, QT, RP, PG, F8)                                                      \
-    switch (a.ge.G) {                                                                              \
-    case 1: hipLaunchKernelGGL((KERNEL<QT, 1, RP, PG, F8>), grid, block_dim, 0, st, a); break;     \
-    case 2: hipLaunchKernelGGL((KERNEL<QT, 2, RP, PG, F8>), grid, block_dim, 0, st, a); break;     \
-    case 4: hipLaunchKernelGGL((KERNEL<QT, 4, RP, PG, F8>), grid, block_dim, 0, st, a); break;     \
-    default: hipLaunchKernelGGL((KERNEL<QT, 8, RP, PG, F8>), grid, block_dim, 0, st, a); break;    \
+    const bool on_32 = prefill_on_32(s, n_blocks, block, use_rope, paged, fp8);
+    PfSplits splits = prefill_splits(s, n_blocks, block, on_32);
+    // two workgroups of a compute unit only where its LDS holds both
+    if (on_32 && splits.n > 1 && 2 * pf32_lds(splits.tiles_each * kPfTile, use_rope, paged, fp8) > kPf32MaxLds)
+        splits = prefill_splits(s, n_blocks, block, on_32, true);
+    if (!ws || ((uintptr_t)ws & 15) || ws_bytes < splits.bytes) {      // without scratch: one split
+        splits.tiles_each = (int)(((int64_t)s.n_sink + (int64_t)n_blocks * block + s.n_stream + kPfTile - 1) / kPfTile);
+        splits.n = 1;
     }
-#define IHIP_PF_BY_G2(KERNEL, QT, RP, PG)                                                          \
-    if (fp8) { IHIP_PF_BY_G3(KERNEL, QT, RP, PG, true) } else { IHIP_PF_BY_G3(KERNEL, QT, RP, PG, false) }
-#define IHIP_PF_BY_G(KERNEL, QT)                                                                   \
-    if (use_rope && paged) { IHIP_PF_BY_G2(KERNEL, QT, true, true) }                               \
-    else if (use_rope) { IHIP_PF_BY_G2(KERNEL, QT, true, false) }                                  \
-    else if (paged) { IHIP_PF_BY_G2(KERNEL, QT, false, true) }                                     \
-    else { IHIP_PF_BY_G2(KERNEL, QT, false, false) }
-    // the 32x32 kernel keeps every slot's position in LDS; longer key lists take the 16x16 one
-    const int slot_limit = use_rope ? (paged ? kPf32MaxSlotsRopePaged : kPf32MaxSlotsRope)
-                                    : (paged ? kPf32MaxSlotsPaged : kPf32MaxSlots);
-    if (fp8 && s.b_q >= 32 && s.n_sink + n_blocks * block + s.n_stream <= (paged ? kPf32MaxSlotsFp8Paged : kPf32MaxSlotsFp8)) {
-        launch_attn_prefill32_fp8(a, P, st);
-        return check_launch("sparse_attn_prefill");
-    }
-    if (!fp8 && s.b_q >= 32 && s.n_sink + n_blocks * block + s.n_stream <= slot_limit) {
-        launch_attn_prefill32(a, P, s.max_seq_len, st);
-        return check_launch("sparse_attn_prefill");
-    }
-    switch (s.b_q) {
-    case 16: IHIP_PF_BY_G(attn_prefill_kernel, 1); break;
-    case 32: IHIP_PF_BY_G(attn_prefill_kernel, 2); break;
-    case 64: IHIP_PF_BY_G(attn_prefill_kernel, 4); break;
-    default: return fail(IHIP_ERR_UNSUPPORTED, "sparse_attn_prefill: b_q = %d not in {16, 32, 64}", s.b_q);
-    }
-#undef IHIP_PF_BY_G
-#undef IHIP_PF_BY_G2
-#undef IHIP_PF_BY_G3
-    return check_launch("sparse_attn_prefill");
+    a.n_splits = splits.n;
+    a.tiles_per_split = splits.tiles_each;
+    a.slots_cap = splits.tiles_each * kPfTile;
+    a.part_o = (float4 *)ws;
+    a.part_ml = (float2 *)(a.part_o + (size_t)splits.n * splits.units * 64 * splits.elements);
+    const int32_t rc = launch_attn_prefill_splits(s, a, P, on_32, use_rope, paged, fp8, st);
+    if (rc != IHIP_OK || splits.n == 1) return rc;
+    KernelTimer timer("attn_prefill_merge", st);
+    const dim3 grid(splits.units);
+    if (on_32) hipLaunchKernelGGL(attn_prefill_merge_kernel<0>, grid, dim3(256), 0, st, a, splits.units, splits.waves, splits.heads);
+    else if (s.b_q == 16) hipLaunchKernelGGL(attn_prefill_merge_kernel<1>, grid, dim3(256), 0, st, a, splits.units, splits.waves, splits.heads);
+    else if (s.b_q == 32) hipLaunchKernelGGL(attn_prefill_merge_kernel<2>, grid, dim3(256), 0, st, a, splits.units, splits.waves, splits.heads);
+    else hipLaunchKernelGGL(attn_prefill_merge_kernel<4>, grid, dim3(256), 0, st, a, splits.units, splits.waves, splits.heads);
+    return check_launch("sparse_attn_prefill (merge)");
 }
 
 }  // namespace ihip

@@ -9,11 +9,9 @@ void launch_attn_prefill32(const AttnPrefillArgs &a, int P, int64_t max_seq_len,
     const int NQ = a.ge.b_q / 32;
     const int heads_per_wg = NQ * a.ge.G > 8 ? a.ge.G / 2 : a.ge.G;
     const int parts = a.ge.G / heads_per_wg;
-    const dim3 block_dim(64 * NQ * heads_per_wg), grid(parts == 1 ? P : (P + 7) / 8 * 8 * parts);
-    const int slots = (a.ge.n_sink + a.n_blocks * a.block + a.ge.n_stream + kPfTile - 1) / kPfTile * kPfTile;
+    const dim3 block_dim(64 * NQ * heads_per_wg), grid(parts == 1 ? P : (P + 7) / 8 * 8 * parts, a.n_splits);
     const bool use_rope = a.rope_cos != nullptr, paged = a.paged.block_table != nullptr;
-    const size_t lds = (size_t)(use_rope ? kPfStagesRope : kPfStagesPlain) * kPfStageEl * sizeof(uint16_t) +
-                       (size_t)slots * sizeof(int) * (paged ? 2 : 1) + slots / kPfTile;   // stages, slot positions (and pages), per-tile flags
+    const size_t lds = pf32_lds(a.slots_cap, use_rope, paged, false);
     const int64_t lim = (int64_t)1 << 31, lim24 = (int64_t)1 << 24;
     const bool wide = paged || max_seq_len >= lim24 || a.k_st < 0 || a.v_st < 0 || a.k_st >= lim24 || a.v_st >= lim24 ||
                       max_seq_len * a.k_st + kD >= lim || max_seq_len * a.v_st + kD >= lim;

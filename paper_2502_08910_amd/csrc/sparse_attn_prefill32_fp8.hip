@@ -12,11 +12,9 @@ void launch_attn_prefill32_fp8(const AttnPrefillArgs &a, int P, hipStream_t st)
     const int NQ = a.ge.b_q / 32;
     const int heads_per_wg = NQ * a.ge.G > 8 ? a.ge.G / 2 : a.ge.G;
     const int parts = a.ge.G / heads_per_wg;
-    const dim3 block_dim(64 * NQ * heads_per_wg), grid(parts == 1 ? P : (P + 7) / 8 * 8 * parts);
-    const int slots = (a.ge.n_sink + a.n_blocks * a.block + a.ge.n_stream + kPfTile - 1) / kPfTile * kPfTile;
+    const dim3 block_dim(64 * NQ * heads_per_wg), grid(parts == 1 ? P : (P + 7) / 8 * 8 * parts, a.n_splits);
     const bool use_rope = a.rope_cos != nullptr, paged = a.paged.block_table != nullptr;
-    const size_t lds = (size_t)(kPfStagesFp8 * kPfStageEl + kPfRawStages * kPfTileEl) * sizeof(uint16_t) +
-                       (size_t)slots * sizeof(int) * (paged ? 2 : 1) + slots / kPfTile;
+    const size_t lds = pf32_lds(a.slots_cap, use_rope, paged, true);
 #define IHIP_PF32_R(NQV, GV, RV, PV)                                                                         \
     {                                                                                                        \
         static bool attr_set = false;     /* allow more than 64 KiB of dynamic LDS, once per kernel */       \
