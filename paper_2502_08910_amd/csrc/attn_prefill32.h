@@ -81,7 +81,9 @@ constexpr float kPfMaxSum = 1024.0f;                // row sum of a tile above w
 // and strides are below 2^24, so an offset is one full-rate 24-bit multiply.
 // PAGED: K and V are page pools read through the sequence's row of the block table; the page id of
 // every slot is looked up once, next to its position, and kept in LDS as well.
-template <int NQ, int G, bool WIDE, bool ROPE, bool PAGED, bool KV8 = false>
+// SPLIT: the workgroup takes one split of the key list (blockIdx.y) and writes a partial result.  Instantiations of their own: one
+// kernel for both takes up to 30 registers more (one wave with RoPE 188 -> 247 us, over pages 378 -> 648).
+template <int NQ, int G, bool WIDE, bool ROPE, bool PAGED, bool KV8, bool SPLIT>
 __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const AttnPrefillArgs a)
 {
     static_assert(NQ * G <= 8, "at most eight waves");
@@ -122,14 +124,9 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
     const int w0 = max(pr.hi, a.ge.n_sink);
     const int total = n_sink_eff + (a.n_blocks << a.block_log2) + max(0, pr.E - w0);
     // tiles are numbered within the split, whose first key slot is slot0; host guarantees n_tiles*32 <= slots_cap
-    const int slot0 = blockIdx.y * a.tiles_per_split * kPfTile;
-    const int n_tiles = min((total + kPfTile - 1) / kPfTile - (int)blockIdx.y * a.tiles_per_split, a.tiles_per_split);
-    if (n_tiles <= 0) {                              // a sequence too short for this split: nothing, with weight 0
-        float4 *to = a.part_o + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * NW * 16 * 64;
-        for (int i = tid; i < NW * 16 * 64; i += nthreads) to[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        a.part_ml[((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * nthreads + tid] = make_float2(kNegBigPf, 0.f);
-        return;
-    }
+    const int slot0 = SPLIT ? blockIdx.y * a.tiles_per_split * kPfTile : 0;
+    const int n_tiles = SPLIT ? min((total + kPfTile - 1) / kPfTile - (int)blockIdx.y * a.tiles_per_split, a.tiles_per_split) : (total + kPfTile - 1) / kPfTile;
+    if (SPLIT && n_tiles <= 0) return;               // a sequence too short for this split, which the merge leaves out
 
     // a tile needs masking if it has an empty slot or a key at or after the block's first query
     for (int slot = tid; slot < n_tiles * kPfTile; slot += nthreads) {
@@ -516,15 +513,17 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
 
     float l = l_run;
     l += __shfl_xor(l, 32, 64);
-    if (a.n_splits > 1) {
-        const int64_t unit = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * NW + wave;
+    if constexpr (SPLIT) {
+        int at = threadIdx.x;                        // opaque: the addresses are formed here, not carried through the loop
+        asm volatile("" : "+v"(at));
+        const int64_t unit = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * NW + __builtin_amdgcn_readfirstlane(at >> 6);
+        float4 *to = a.part_o + unit * 16 * 64 + (at & 63);
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4)
-                a.part_o[(unit * 16 + dt * 4 + r4) * 64 + lane] =
-                    make_float4(o[dt][r4 * 4], o[dt][r4 * 4 + 1], o[dt][r4 * 4 + 2], o[dt][r4 * 4 + 3]);
-        a.part_ml[unit * 64 + lane] = make_float2(m_run, l);
+                to[(dt * 4 + r4) * 64] = make_float4(o[dt][r4 * 4], o[dt][r4 * 4 + 1], o[dt][r4 * 4 + 2], o[dt][r4 * 4 + 3]);
+        a.part_ml[unit * 64 + (at & 63)] = make_float2(m_run, l);
         return;
     }
     const float inv = KV8 ? a.v_scale / l : 1.0f / l;

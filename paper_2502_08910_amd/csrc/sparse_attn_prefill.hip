@@ -28,7 +28,8 @@ namespace ihip {
 // KV8: K and V rows are 128 bytes of E4M3 (strides in 2-byte units); a piece stays 8 bytes in the
 // staging registers and is repacked as bf16 (exact) on its way into LDS.  The K scale is folded into
 // the softmax scale, the V scale into the final normalisation.
-template <int QT, int G, bool ROPE, bool PAGED, bool KV8 = false>   // query tiles of 16 (b_q = 16*QT); G query heads = G waves per workgroup
+// SPLIT: as in attn_prefill32_kernel
+template <int QT, int G, bool ROPE, bool PAGED, bool KV8, bool SPLIT>   // query tiles of 16 (b_q = 16*QT); G query heads = G waves per workgroup
 __global__ __launch_bounds__(64 * G) void attn_prefill_kernel(const AttnPrefillArgs a)
 {
     using raw_t = typename std::conditional<KV8, uint2, uint4>::type;     // 8 elements of a row as fetched
@@ -52,8 +53,8 @@ __global__ __launch_bounds__(64 * G) void attn_prefill_kernel(const AttnPrefillA
     const int n_sink_eff = min(a.ge.n_sink, pr.E);
     const int w0 = max(pr.hi, a.ge.n_sink);
     const int total = n_sink_eff + (a.n_blocks << a.block_log2) + max(0, pr.E - w0);
-    const int first_tile = blockIdx.y * a.tiles_per_split;
-    const int n_tiles = min((total + kPfTile - 1) / kPfTile, first_tile + a.tiles_per_split);      // up to here, in this split
+    const int first_tile = SPLIT ? blockIdx.y * a.tiles_per_split : 0;
+    const int all_tiles = (total + kPfTile - 1) / kPfTile, n_tiles = SPLIT ? min(all_tiles, first_tile + a.tiles_per_split) : all_tiles;      // up to here
     StreamIds ids{n_sink_eff, a.n_blocks << a.block_log2, 0, w0};
     if constexpr (ROPE) {
         __shared__ int sh_tokens;
@@ -251,7 +252,7 @@ __global__ __launch_bounds__(64 * G) void attn_prefill_kernel(const AttnPrefillA
         float l = l_run[qt];
         l += __shfl_xor(l, 16, 64);
         l += __shfl_xor(l, 32, 64);
-        if (a.n_splits > 1) {
+        if constexpr (SPLIT) {
             const int64_t unit = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * G + hh;
 #pragma unroll
             for (int dt = 0; dt < 8; ++dt)
@@ -285,19 +286,23 @@ __global__ __launch_bounds__(256) void attn_prefill_merge_kernel(const AttnPrefi
     const int unit = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const PfWorkgroup wg = pf_workgroup(unit / waves, QT == 0 ? a.ge.G / heads : 1);
     if (wg.p >= a.ge.B * a.ge.Hkv * a.ge.Mq) return;
-    const int wave = unit % waves, m = wg.p % a.ge.Mq, bg = wg.p / a.ge.Mq, g = bg % a.ge.Hkv, b = bg / a.ge.Hkv;
+    const Problem pr = problem_of(a.ge, wg.p);
+    const int wave = unit % waves, m = pr.m, g = pr.g, b = pr.b;
+    // splits that hold a key slot of this problem
+    const int slots = min(a.ge.n_sink, pr.E) + (a.n_blocks << a.block_log2) + max(0, pr.E - max(pr.hi, a.ge.n_sink));
+    const int n_splits = min(a.n_splits, (slots + a.tiles_per_split * kPfTile - 1) / (a.tiles_per_split * kPfTile));
     const int h = g * a.ge.G + wg.head_part * heads + wave % heads;
     float M[kTiles], L[kTiles];
 #pragma unroll
     for (int t = 0; t < kTiles; ++t) { M[t] = kNegBigPf; L[t] = 0.f; }
-    for (int s = 0; s < a.n_splits; ++s)
+    for (int s = 0; s < n_splits; ++s)
 #pragma unroll
         for (int t = 0; t < kTiles; ++t) M[t] = fmaxf(M[t], a.part_ml[(((int64_t)s * n_units + unit) * kTiles + t) * 64 + lane].x);
     float4 acc[kPerWave];
 #pragma unroll
     for (int i = 0; i < kPerWave; ++i) acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 2
-    for (int s = 0; s < a.n_splits; ++s) {
+    for (int s = 0; s < n_splits; ++s) {
         const int64_t at = (int64_t)s * n_units + unit;
         float w[kTiles];
 #pragma unroll
@@ -388,13 +393,15 @@ static int32_t launch_attn_prefill_splits(const ihip_shape &s, const AttnPrefill
 {
     KernelTimer timer("attn_prefill", st);
     const dim3 block_dim(64 * a.ge.G), grid(P, a.n_splits);
-#define IHIP_PF_BY_G3(KERNEL, QT, RP, PG, F8)                                                      \
+#define IHIP_PF_BY_G4(KERNEL, QT, RP, PG, F8, SP)                                                  \
     switch (a.ge.G) {                                                                              \
-    case 1: hipLaunchKernelGGL((KERNEL<QT, 1, RP, PG, F8>), grid, block_dim, 0, st, a); break;     \
-    case 2: hipLaunchKernelGGL((KERNEL<QT, 2, RP, PG, F8>), grid, block_dim, 0, st, a); break;     \
-    case 4: hipLaunchKernelGGL((KERNEL<QT, 4, RP, PG, F8>), grid, block_dim, 0, st, a); break;     \
-    default: hipLaunchKernelGGL((KERNEL<QT, 8, RP, PG, F8>), grid, block_dim, 0, st, a); break;    \
+    case 1: hipLaunchKernelGGL((KERNEL<QT, 1, RP, PG, F8, SP>), grid, block_dim, 0, st, a); break; \
+    case 2: hipLaunchKernelGGL((KERNEL<QT, 2, RP, PG, F8, SP>), grid, block_dim, 0, st, a); break; \
+    case 4: hipLaunchKernelGGL((KERNEL<QT, 4, RP, PG, F8, SP>), grid, block_dim, 0, st, a); break; \
+    default: hipLaunchKernelGGL((KERNEL<QT, 8, RP, PG, F8, SP>), grid, block_dim, 0, st, a); break; \
     }
+#define IHIP_PF_BY_G3(KERNEL, QT, RP, PG, F8)                                                      \
+    if (a.n_splits > 1) { IHIP_PF_BY_G4(KERNEL, QT, RP, PG, F8, true) } else { IHIP_PF_BY_G4(KERNEL, QT, RP, PG, F8, false) }
 #define IHIP_PF_BY_G2(KERNEL, QT, RP, PG)                                                          \
     if (fp8) { IHIP_PF_BY_G3(KERNEL, QT, RP, PG, true) } else { IHIP_PF_BY_G3(KERNEL, QT, RP, PG, false) }
 #define IHIP_PF_BY_G(KERNEL, QT)                                                                   \
@@ -416,6 +423,7 @@ static int32_t launch_attn_prefill_splits(const ihip_shape &s, const AttnPrefill
 #undef IHIP_PF_BY_G
 #undef IHIP_PF_BY_G2
 #undef IHIP_PF_BY_G3
+#undef IHIP_PF_BY_G4
     return check_launch("sparse_attn_prefill");
 }
 

@@ -15,16 +15,18 @@ void launch_attn_prefill32(const AttnPrefillArgs &a, int P, int64_t max_seq_len,
     const int64_t lim = (int64_t)1 << 31, lim24 = (int64_t)1 << 24;
     const bool wide = paged || max_seq_len >= lim24 || a.k_st < 0 || a.v_st < 0 || a.k_st >= lim24 || a.v_st >= lim24 ||
                       max_seq_len * a.k_st + kD >= lim || max_seq_len * a.v_st + kD >= lim;
-#define IHIP_PF32_R(NQV, GV, WV, RV, PV)                                                                     \
+#define IHIP_PF32_S(NQV, GV, WV, RV, PV, SV)                                                                 \
     {                                                                                                        \
         static bool attr_set = false;     /* allow more than 64 KiB of dynamic LDS, once per kernel */       \
         if (!attr_set) {                                                                                     \
-            (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_prefill32_kernel<NQV, GV, WV, RV, PV>), \
+            (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_prefill32_kernel<NQV, GV, WV, RV, PV, false, SV>), \
                                       hipFuncAttributeMaxDynamicSharedMemorySize, kPf32MaxLds - (RV ? 64 : 0)); \
             attr_set = true;                                                                                 \
         }                                                                                                    \
-        hipLaunchKernelGGL((attn_prefill32_kernel<NQV, GV, WV, RV, PV>), grid, block_dim, lds, st, a);      \
+        hipLaunchKernelGGL((attn_prefill32_kernel<NQV, GV, WV, RV, PV, false, SV>), grid, block_dim, lds, st, a);      \
     }
+#define IHIP_PF32_R(NQV, GV, WV, RV, PV)                                                                     \
+    { if (a.n_splits > 1) IHIP_PF32_S(NQV, GV, WV, RV, PV, true) else IHIP_PF32_S(NQV, GV, WV, RV, PV, false) }
 #define IHIP_PF32(NQV, GV, WV)                                                                               \
     if (WV && paged) {                                                                                       \
         if (use_rope) IHIP_PF32_R(NQV, GV, true, true, true) else IHIP_PF32_R(NQV, GV, true, false, true)    \
@@ -45,6 +47,7 @@ void launch_attn_prefill32(const AttnPrefillArgs &a, int P, int64_t max_seq_len,
 #undef IHIP_PF32_BY_G
 #undef IHIP_PF32
 #undef IHIP_PF32_R
+#undef IHIP_PF32_S
 }
 
 }  // namespace ihip

@@ -15,17 +15,19 @@ void launch_attn_prefill32_fp8(const AttnPrefillArgs &a, int P, hipStream_t st)
     const dim3 block_dim(64 * NQ * heads_per_wg), grid(parts == 1 ? P : (P + 7) / 8 * 8 * parts, a.n_splits);
     const bool use_rope = a.rope_cos != nullptr, paged = a.paged.block_table != nullptr;
     const size_t lds = pf32_lds(a.slots_cap, use_rope, paged, true);
-#define IHIP_PF32_R(NQV, GV, RV, PV)                                                                         \
+#define IHIP_PF32_S(NQV, GV, RV, PV, SV)                                                                         \
     {                                                                                                        \
         static bool attr_set = false;     /* allow more than 64 KiB of dynamic LDS, once per kernel */       \
         if (!attr_set) {                                                                                     \
             (void)hipFuncSetAttribute(                                                                       \
-                reinterpret_cast<const void *>(&attn_prefill32_kernel<NQV, GV, true, RV, PV, true>),         \
+                reinterpret_cast<const void *>(&attn_prefill32_kernel<NQV, GV, true, RV, PV, true, SV>),         \
                 hipFuncAttributeMaxDynamicSharedMemorySize, kPf32MaxLds - (RV ? 64 : 0));                    \
             attr_set = true;                                                                                 \
         }                                                                                                    \
-        hipLaunchKernelGGL((attn_prefill32_kernel<NQV, GV, true, RV, PV, true>), grid, block_dim, lds, st, a); \
+        hipLaunchKernelGGL((attn_prefill32_kernel<NQV, GV, true, RV, PV, true, SV>), grid, block_dim, lds, st, a); \
     }
+#define IHIP_PF32_R(NQV, GV, RV, PV)                                                                         \
+    { if (a.n_splits > 1) IHIP_PF32_S(NQV, GV, RV, PV, true) else IHIP_PF32_S(NQV, GV, RV, PV, false) }
 #define IHIP_PF32(NQV, GV)                                                                                   \
     if (paged) {                                                                                             \
         if (use_rope) IHIP_PF32_R(NQV, GV, true, true) else IHIP_PF32_R(NQV, GV, false, true)                \
@@ -47,6 +49,7 @@ void launch_attn_prefill32_fp8(const AttnPrefillArgs &a, int P, hipStream_t st)
     }
 #undef IHIP_PF32
 #undef IHIP_PF32_R
+#undef IHIP_PF32_S
 }
 
 }  // namespace ihip
