@@ -54,7 +54,8 @@
 //
 // KV8 (K and V rows are 128 bytes of E4M3): the direct loads bring the raw rows (16 bytes per
 // lane: 8 lanes a row, 8 rows an instruction, 8 instructions a tile) into a ring of three raw
-// stages; the tile is widened to bf16 (exact) into one of three bf16 stages, every thread 8 bytes
+// stages; the tile is widened to bf16 (exact) into one of two bf16 K tiles (K(t) has been read when K(t+2) is written) and one
+// of three V tiles, 64 KB with the raw ones, so that two workgroups of four waves share a compute unit; every thread 8 bytes
 // of K and 8 of V, in the period the RoPE variant uses for its rotation (and rotated on the way
 // with ROPE), in the swizzled layout the reads below expect.  The raw ring puts requests a period
 // further ahead than ROPE does: tile t+4 is requested at the start of period t, tile t+3 must have
@@ -90,6 +91,7 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
     static_assert(!PAGED || WIDE, "paged pools are addressed with 64-bit offsets");
     static_assert(!KV8 || WIDE, "E4M3 rows are addressed with 64-bit offsets");
     constexpr int kPfStages = KV8 ? kPfStagesFp8 : ROPE ? kPfStagesRope : kPfStagesPlain;
+    constexpr int kUnroll = KV8 ? 6 : kPfStages;     // periods after which the stages repeat
     constexpr bool kTouch = ROPE || KV8;             // a tile is worked on in LDS between landing and first read
     // A period's operands are requested up front (see there), unless the table pieces that one or two waves hold for their
     // rotations, 64 or 32 registers, leave no room: 1,024 queries, 3,200 key slots each, two waves 164 us in order, 300 with
@@ -97,7 +99,7 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
     // 300 bytes either way: 970 and 936.
     constexpr bool kUpFront = !ROPE || NQ * G > 2 || (NQ * G == 1 && PAGED && !KV8);
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
-    uint16_t *raw0 = smem + kPfStages * kPfStageEl;                          // KV8: the raw stages
+    uint16_t *raw0 = smem + (KV8 ? (kPfKTilesFp8 + kPfVTilesFp8) * kPfTileEl : kPfStages * kPfStageEl);       // KV8: the raw stages
     int *sPos = reinterpret_cast<int *>(raw0 + (KV8 ? kPfRawStages * kPfTileEl : 0));   // one int per key slot
     const int slots_cap = a.slots_cap;
     int *sPage = sPos + slots_cap;                                           // PAGED: one page id per key slot
@@ -179,7 +181,8 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);
     // the stage of a tile (tile % kPfStages) is a compile-time constant in the unrolled loop below,
     // so LDS addresses are per-lane constants plus immediates
-    auto stage_of = [&](int st) { return smem + (st % kPfStages) * kPfStageEl; };
+    auto k_stage = [&](int st) { return smem + (KV8 ? (st % kPfKTilesFp8) * kPfTileEl : (st % kPfStages) * kPfStageEl); };
+    auto v_stage = [&](int st) { return smem + (KV8 ? (kPfKTilesFp8 + st % kPfVTilesFp8) * kPfTileEl : (st % kPfStages) * kPfStageEl + kPfTileEl); };
     auto raw_of = [&](int st) { return raw0 + (st % kPfRawStages) * kPfTileEl; };
     // key positions of this lane's rows in the loads of a tile (read a period ahead of the request)
     struct Rows { int pos[kLoadsPerWave]; int page[PAGED ? kLoadsPerWave : 1]; };
@@ -218,7 +221,7 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
             }
             return;
         }
-        uint16_t *stage = stage_of(st);
+        uint16_t *stage = k_stage(st);               // K tile, then V tile
 #pragma unroll
         for (int i = 0; i < kLoadsPerWave; ++i) {
             // instruction j of the tile: j < 8 fetches K rows 4j..4j+3, j >= 8 V rows 4(j-8)..
@@ -263,8 +266,9 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
     };
     auto rotate_k = [&](int tile, int st, const Table &tb) {
         if (tile >= n_tiles) return;
-        uint16_t *stage = stage_of(st);
+        uint16_t *stage = k_stage(st);
         if constexpr (KV8) {
+            uint16_t *to_v = v_stage(st);
             const uint16_t *raw = raw_of(st);
 #pragma unroll
             for (int i = 0; i < kPieces; ++i) {
@@ -277,7 +281,7 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
                 else wk = fp8x8_to_bf16x8(rk);
                 const uint4 wv = fp8x8_to_bf16x8(*reinterpret_cast<const uint2 *>(raw + kPfTileEl / 2 + item * 4));
                 *reinterpret_cast<uint4 *>(stage + r * kD + ((c ^ (r & 15)) << 3)) = wk;
-                *reinterpret_cast<uint4 *>(stage + kPfTileEl + r * kD + ((c ^ ((r & 3) << 2)) << 3)) = wv;
+                *reinterpret_cast<uint4 *>(to_v + r * kD + ((c ^ ((r & 3) << 2)) << 3)) = wv;
             }
             return;
         }
@@ -292,7 +296,7 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
 
     // first product of a tile: S^T = K Q^T for this wave's 32 queries
     auto k_operands = [&](int st, bf16x8 (&ka)[8]) {
-        const uint16_t *cK = stage_of(st) + n * kD;
+        const uint16_t *cK = k_stage(st) + n * kD;
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) ka[ks] = *reinterpret_cast<const bf16x8 *>(&cK[((ks * 2 + half) ^ (n & 15)) * 8]);
     };
@@ -356,7 +360,7 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt) {
             const int chunk = dt * 4 + ((n >> 4) << 1) + ((i & 3) >> 1);
-            voff[dt] = kPfTileEl + key * kD + ((chunk ^ ((key & 3) << 2)) << 3) + ((i & 1) << 2);
+            voff[dt] = key * kD + ((chunk ^ ((key & 3) << 2)) << 3) + ((i & 1) << 2);
         }
     }
     auto v_operand = [&](const uint16_t *cV, int dt, int kk) {
@@ -368,7 +372,7 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
     };
     // the same two products with every operand read where it is used
     auto scores_in_order = [&](int st) -> f32x16 {
-        const uint16_t *cK = stage_of(st) + n * kD;
+        const uint16_t *cK = k_stage(st) + n * kD;
         f32x16 s;
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = 0.f;
@@ -380,7 +384,7 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
         return s;
     };
     auto accumulate_in_order = [&](int st, const bf16x8 (&pb)[2]) {
-        const uint16_t *cV = stage_of(st);
+        const uint16_t *cV = v_stage(st);
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
@@ -431,7 +435,8 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
     if (sMasked[0] != 0) mask_scores(0, s_nxt);
     settle(s_nxt, exponentials(s_nxt, pb), pb);
     int masked_nxt = n_tiles > 1 ? sMasked[1] : 0;      // read a period ahead, like the row positions
-    // one tile period; ST = tile % kPfStages
+    if constexpr (KV8) __syncthreads();     // K(0) has been read: period 0 writes K(2) in its place
+    // one tile period; ST = tile % kUnroll
     auto period = [&](auto st_c, int tile) {
         constexpr int ST = decltype(st_c)::value;
         // the table loads come before the request: the wait the compiler puts before their use then
@@ -457,7 +462,7 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
             // registers: the chip's clock under dense matrix work is what is left.
             bf16x8 va[4][2];
             k_operands(ST + 1, ka);
-            v_operands(stage_of(ST), va);
+            v_operands(v_stage(ST), va);
             s_nxt = scores(ka);
             __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
 #pragma unroll
@@ -489,20 +494,17 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
         landed(tile + D >= n_tiles);        // tile + 2 (ROPE, KV8: tile + 3)
         __syncthreads();
     };
-    auto periods = [&](int tile, auto... st) {      // up to kPfStages periods, stopping before the last tile
+    auto periods = [&](int tile, auto... st) {      // up to kUnroll periods, stopping before the last tile
         bool more = true;
         ((more = more && tile + decltype(st)::value + 1 < n_tiles && (period(st, tile + decltype(st)::value), true)), ...);
     };
-    for (int tile = 0; tile + 1 < n_tiles; tile += kPfStages) {
-        if constexpr (kPfStages == 3)
+    for (int tile = 0; tile + 1 < n_tiles; tile += kUnroll) {
+        if constexpr (kUnroll == 3)
             periods(tile, std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{},
                     std::integral_constant<int, 2>{});
-        else if constexpr (kPfStages == 4)
+        else if constexpr (kUnroll == 4)
             periods(tile, std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{},
                     std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{});
-        else if constexpr (kPfStages == 5)
-            periods(tile, std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{},
-                    std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{}, std::integral_constant<int, 4>{});
         else
             periods(tile, std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{},
                     std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{}, std::integral_constant<int, 4>{},
