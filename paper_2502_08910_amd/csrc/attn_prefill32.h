@@ -55,8 +55,9 @@
 // KV8 (K and V rows are 128 bytes of E4M3): the direct loads bring the raw rows (16 bytes per
 // lane: 8 lanes a row, 8 rows an instruction, 8 instructions a tile) into a ring of three raw
 // stages; the tile is widened to bf16 (exact) into one of two bf16 K tiles (K(t) has been read when K(t+2) is written) and one
-// of three V tiles, 64 KB with the raw ones, so that two workgroups of four waves share a compute unit; every thread 8 bytes
-// of K and 8 of V, in the period the RoPE variant uses for its rotation (and rotated on the way
+// of three V tiles, 64 KB with the raw ones, so that two workgroups of four waves share a compute unit (with three K tiles, 72 KB,
+// one: 512 workgroups of 100 tiles, four heads 164 / 139 us, one head 185 / 122, with RoPE 211 / 165 and 325 / 194); every thread
+// 8 bytes of K and 8 of V, in the period the RoPE variant uses for its rotation (and rotated on the way
 // with ROPE), in the swizzled layout the reads below expect.  The raw ring puts requests a period
 // further ahead than ROPE does: tile t+4 is requested at the start of period t, tile t+3 must have
 // landed at its end, tile t+2 is widened during it, K(t+1) and V(t) are read.  The K scale is folded into the softmax scale on the host,
@@ -90,7 +91,7 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
     static_assert(NQ * G <= 8, "at most eight waves");
     static_assert(!PAGED || WIDE, "paged pools are addressed with 64-bit offsets");
     static_assert(!KV8 || WIDE, "E4M3 rows are addressed with 64-bit offsets");
-    constexpr int kPfStages = KV8 ? kPfStagesFp8 : ROPE ? kPfStagesRope : kPfStagesPlain;
+    constexpr int kPfStages = KV8 ? kPfVTilesFp8 : ROPE ? kPfStagesRope : kPfStagesPlain;
     constexpr int kUnroll = KV8 ? 6 : kPfStages;     // periods after which the stages repeat
     constexpr bool kTouch = ROPE || KV8;             // a tile is worked on in LDS between landing and first read
     // A period's operands are requested up front (see there), unless the table pieces that one or two waves hold for their

@@ -98,7 +98,7 @@ __device__ inline int pf_slot_to_pos(const AttnPrefillArgs &a, const Problem &pr
 // LDS of the 32x32 kernel: K/V stages of 16 KB (32 rows of 256 bytes each), for E4M3 also raw stages of
 // 8 KB; then an int per key slot (two with paged K/V: the page id) and a flag per tile.  The most key
 // slots a kernel can take follow from the 160 KB of a CU (64 bytes are left for static variables).
-constexpr int kPfStagesPlain = 3, kPfStagesRope = 4, kPfStagesFp8 = 3;
+constexpr int kPfStagesPlain = 3, kPfStagesRope = 4;
 constexpr int kPfKTilesFp8 = 2, kPfVTilesFp8 = 3;   // E4M3: widened K and V tiles
 constexpr int kPfRawStages = 3;                     // E4M3: raw stages of one K or V tile's size
 constexpr int kPfTileEl = kPfTile * kD;             // elements of one K (or V) tile: 32 rows of 256 bytes
@@ -115,7 +115,8 @@ constexpr int kPf32MaxSlots = pf32_max_slots(kPfStagesPlain * kPfStageBytes, 1);
 constexpr int kPf32MaxSlotsRope = pf32_max_slots(kPfStagesRope * kPfStageBytes, 1);         // 24,352
 constexpr int kPf32MaxSlotsPaged = pf32_max_slots(kPfStagesPlain * kPfStageBytes, 2);       // 14,272: a page id per slot as well
 constexpr int kPf32MaxSlotsRopePaged = pf32_max_slots(kPfStagesRope * kPfStageBytes, 2);
-constexpr int kPf32MaxSlotsFp8 = pf32_max_slots(kPfFp8StageBytes + kPfRawBytes, 1);                      // E4M3, with or without RoPE
+// E4M3, with or without RoPE (the lengths that a third K tile would leave)
+constexpr int kPf32MaxSlotsFp8 = pf32_max_slots(kPfFp8StageBytes + kPfRawBytes, 1);
 constexpr int kPf32MaxSlotsFp8Paged = pf32_max_slots(kPfFp8StageBytes + kPfRawBytes, 2);
 static_assert(kPf32MaxSlots * 4 + kPf32MaxSlots / kPfTile + kPfStagesPlain * kPfStageBytes + 64 <= kPf32MaxLds, "LDS");
 static_assert(kPf32MaxSlotsFp8Paged * 8 + kPf32MaxSlotsFp8Paged / kPfTile + kPfFp8StageBytes + 64 <= kPf32MaxLds, "LDS");
