@@ -49,16 +49,15 @@ constexpr int kPrefillMaxIters = 4;     // chunk groups (of 32 chunks) per workg
 // chunk j by cap - j, a query by cap - its position, which is nothing at all for a block whose first
 // query is at or behind the cap -- every block but those of ranges that hold fewer keys than a block has queries.
 // Such queries stay the exact bf16 values they are: no second operand for them, a third of the matrix
-// work less than with rotated queries, and 64 registers less, which makes room for two waves per SIMD (64-query blocks
-// at the price of 60-84 bytes of scratch per lane, 120-256 with 8 heads).
+// work less than with rotated queries, and 64 registers less, which makes room for two and three waves per SIMD.
 // (Blocks before the cap turn their query operands where they are used, value and rest.)
 // A candidate row is turned on its way from global memory to LDS, each lane the 16 bytes it fetched
 // (tile row 4r + kq is candidate column 4(r%4) + kq of tile r/4, whose chunk and therefore table row
 // are the same at every level of a search: the 8 table pieces of a lane are fetched once per chunk
 // group); the value goes to the tile, the rest to a second tile.  Same carried-score search as the plain kernel.
-// What bounds it: the rotations' vector instructions (48 for 8 values), then the matrix work.  4,096 queries on 128K
-// keys, chunks of 64, 32 heads: 2267 us with rotated queries and keys (three products, one wave per SIMD, rows turned
-// in LDS), 1312 us this way.  Error against 64 bits on the same shape, twelve inputs: searches that end in another leaf
+// What bounds it: the rotations' vector instructions (40 for 8 values: 48 with the rests by shift, mask and subtraction), then the
+// matrix work.  4,096 queries on 128K keys, chunks of 64, 32 heads: 2267 us with rotated queries and keys (three products, one
+// wave per SIMD, rows turned in LDS), 1312 us this way with 32 rows at a time and the turns in registers, 1180 with 16 (kTurn16).  Error against 64 bits on the same shape, twelve inputs: searches that end in another leaf
 // (near ties) 178 -> 95 of 12.7 million scores, all other scores 1.47e-6 -> 8.2e-7 relative.
 __device__ inline void rotate_operand_split(const bf16x8 x, const float4 c, const float4 sn, bf16x8 &hi, bf16x8 &lo)
 {
@@ -85,8 +84,13 @@ __device__ inline void turn_back_f32x8_split(const float (&f)[8], const float4 c
         const float re = __fmaf_rn(e, cc[i], __fmul_rn(o, ss[i]));
         const float ro = __fmaf_rn(o, cc[i], -__fmul_rn(e, ss[i]));
         wh[i] = pack_bf16x2(re, ro);
-        wl[i] = pack_bf16x2(__fsub_rn(re, __uint_as_float(wh[i] << 16)),
-                            __fsub_rn(ro, __uint_as_float(wh[i] & 0xffff0000u)));
+        // re - hi and ro - hi, exact, one v_dot2_f32_bf16 each against (-1, 0) and (0, -1).  (The constants come from registers: as
+        // an inline constant the first one reaches the instruction in the other half.)
+        uint32_t minus_low = 0x0000bf80u, minus_high = 0xbf800000u;
+        asm("" : "+s"(minus_low), "+s"(minus_high));
+        const bf16x2_t h2 = __builtin_bit_cast(bf16x2_t, wh[i]);
+        wl[i] = pack_bf16x2(__builtin_amdgcn_fdot2_f32_bf16(h2, __builtin_bit_cast(bf16x2_t, minus_low), re, false),
+                            __builtin_amdgcn_fdot2_f32_bf16(h2, __builtin_bit_cast(bf16x2_t, minus_high), ro, false));
     }
     hi = make_uint4(wh[0], wh[1], wh[2], wh[3]);
     lo = make_uint4(wl[0], wl[1], wl[2], wl[3]);
@@ -123,8 +127,10 @@ __device__ inline void turn_back_operand_split(const bf16x8 x, const float *cos4
 // trip through LDS); everything after that is the bf16 kernel.  The chunk score is multiplied by the
 // tensor's scale at the end.  K strides count 2-byte units.
 //
-template <int MT, int NT, int G, bool WIDE, int ROPE, bool PAGED, int PARTS = 1, bool KV8 = false>
-__global__ __launch_bounds__(64 * G, (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS == 1) ? 4 : 3) void prune_prefill_kernel(const PruneArgs a, const int iters,
+// FEW: chunk-indexed RoPE, 64-query blocks, four waves: registers for two waves per SIMD instead of three, without scratch, where
+// there are no workgroups for a third
+template <int MT, int NT, int G, bool WIDE, int ROPE, bool PAGED, int PARTS = 1, bool KV8 = false, bool FEW = false>
+__global__ __launch_bounds__(64 * G, ROPE == 2 ? (G == 4 && PARTS == 1 && !FEW ? 3 : 2) : (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS == 1) ? 4 : 3) void prune_prefill_kernel(const PruneArgs a, const int iters,
                                                                             const RopeView rope)
 {
     static_assert(NT == 2, "the shared first phase assumes two 16-chunk tiles per wave");
@@ -136,8 +142,18 @@ __global__ __launch_bounds__(64 * G, (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS =
     constexpr bool kShare = NWV >= 2;                // two tiles are needed for the shared phase
     __shared__ float sh_sigma[2][G][NT * 16];       // two buffers: a chunk group writes while the last one is still read
     __shared__ float sh_best[kPrefillMaxIters][NT * 16];      // chunk scores over the head parts done so far
-    constexpr int kLo = ROPE == 2 ? NWV * kTile : 0;  // ROPE == 2: from a tile to the tile of its rests
-    __shared__ __attribute__((aligned(16))) uint16_t sh_rows[(ROPE == 2 ? 2 * NWV : NWV) * kTile];
+    // ROPE == 2, workgroups of four waves: a wave turns and scores 16 rows at a time, values and then rests in its tile (in the shared
+    // first phase the rests of the two tiles lie behind them), and the turns of a chunk group are in LDS for all waves, [cos, sin]
+    // [chunk][piece].  49 KB and 168 registers: three workgroups on a compute unit, three waves per SIMD (64-query blocks, 100 bytes of scratch per lane;
+    // two where the launch has no more, 20.9 / 18.4 us for 16 problems, and for two passes of four heads, 297 / 277).  Other workgroups
+    // turn 32 rows at a time, rests in a second tile, each lane's turns in registers, two waves per SIMD: one and two waves
+    // share a table too little, eight would not fit three times.  Registers / LDS: four heads, 64-query blocks, chunks of 64, 4,096
+    // queries on 128K keys 1302 / 1169 us, 32-query blocks (1,024 on 32K) 66 / 60, 16 99 / 89; two heads 63 / 67, one 64 / 110.
+    constexpr bool kTurn16 = ROPE == 2 && NWV == 4;
+    constexpr int kLo = kTurn16 ? 16 * kD : ROPE == 2 ? NWV * kTile : 0, kLoShared = kTurn16 ? 2 * kTile : kLo;
+    __shared__ __attribute__((aligned(16))) uint16_t sh_rows[(ROPE == 2 && !kTurn16 ? 2 * NWV : NWV) * kTile];
+    __shared__ float4 sh_table[kTurn16 ? 2 : 1][kTurn16 ? NT * 16 * 16 : 1];
+    float4 tb_cos[ROPE == 2 && !kTurn16 ? NT * 4 : 1], tb_sin[ROPE == 2 && !kTurn16 ? NT * 4 : 1];
     // Workgroups are dealt to the 8 XCDs round-robin by linear id; let the KV head be the fastest
     // index, so that (with 8 KV heads) one XCD's L2 only ever holds one head's K rows and all
     // query blocks that share those rows run on that XCD at about the same time.
@@ -268,55 +284,66 @@ __global__ __launch_bounds__(64 * G, (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS =
 
     // Chunk-indexed RoPE, blocks with queries before the cap: the queries are read again, turned back to the cap (value
     // and rest) and used at once, with nothing kept in registers.
-    auto scores_before_cap = [&](const uint16_t *src, float (&sig)[NT]) {
+    auto scores_before_cap = [&](const uint16_t *src, int lo_at) {
         const uint16_t *qb = a.q + pr.b * a.q_sb + (int64_t)h * a.q_sh + (int64_t)(pr.m * a.ge.b_q) * a.q_st;
-        float best[NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) best[t] = -INFINITY;
+        float best = -INFINITY;
 #pragma unroll 1
         for (int mt = 0; mt < MTW; ++mt) {
             const int row = mt * 16 + n;
             const int64_t back = (int64_t)max(q_cap - (pr.E - a.ge.b_q + row), 0) * (kD / 2);
-            f32x4 c[NT];
-#pragma unroll
-            for (int t = 0; t < NT; ++t) c[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            f32x4 c = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
             for (int ks = 0; ks < 4; ++ks) {
                 const int piece = (ks << 2) + kq;
                 const bf16x8 q = *reinterpret_cast<const bf16x8 *>(qb + (int64_t)row * a.q_st + piece * 8);
                 bf16x8 hi, lo;
                 turn_back_operand_split(q, rope.cos + back + piece * 4, rope.sin + back + piece * 4, hi, lo);
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const bf16x8 k = operand(src, t * 16, ks), k_rest = operand(src + kLo, t * 16, ks);
-                    c[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, k, c[t], 0, 0, 0);
-                    c[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, k_rest, c[t], 0, 0, 0);
-                    c[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, k, c[t], 0, 0, 0);
-                }
+                const bf16x8 k = operand(src, 0, ks), k_rest = operand(src + lo_at, 0, ks);
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, k, c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, k_rest, c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, k, c, 0, 0, 0);
             }
-#pragma unroll
-            for (int t = 0; t < NT; ++t) best[t] = fmaxf(best[t], fmaxf(fmaxf(c[t][0], c[t][1]), fmaxf(c[t][2], c[t][3])));
+            best = fmaxf(best, fmaxf(fmaxf(c[0], c[1]), fmaxf(c[2], c[3])));
         }
+        return max_over_rows(best);
+    };
+    // chunk-indexed RoPE: scores of 16 turned rows (values at src, rests lo_at behind them)
+    auto turned_scores = [&](const uint16_t *src, int lo_at) {
+        if (!q_capped) return scores_before_cap(src, lo_at);
+        bf16x8 kr[4], kr_rest[4];
 #pragma unroll
-        for (int t = 0; t < NT; ++t) sig[t] = max_over_rows(best[t]);
+        for (int ks = 0; ks < 4; ++ks) {
+            kr[ks] = operand(src, 0, ks);
+            kr_rest[ks] = operand(src + lo_at, 0, ks);
+        }
+        float best = -INFINITY;
+#pragma unroll
+        for (int mt = 0; mt < MTW; ++mt) {
+            f32x4 c = {0.f, 0.f, 0.f, 0.f};          // the small terms first
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[mt][ks], kr_rest[ks], c, 0, 0, 0);
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[mt][ks], kr[ks], c, 0, 0, 0);
+            best = fmaxf(best, fmaxf(fmaxf(c[0], c[1]), fmaxf(c[2], c[3])));
+        }
+        return max_over_rows(best);
     };
     // scores of the 32 rows of a tile (column n of 16-row tile t): max over the block's queries
     // (ROPE: sig against q_L, sigR against q_R)
-    auto mfma_scores = [&](const uint16_t *src, float (&sig)[NT], float (&sigR)[NT]) {
+    auto mfma_scores = [&](const uint16_t *src, float (&sig)[NT], float (&sigR)[NT]) {      // (kTurn16: of the shared first phase)
         if constexpr (ROPE == 2) {
-            if (!q_capped) {
-                scores_before_cap(src, sig);
-                return;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                sig[t] = turned_scores(src + t * 16 * kD, kLoShared);
+                if constexpr (MT > 1 || kTurn16) __builtin_amdgcn_sched_barrier(0);      // one tile's operands at a time
             }
+            return;
         }
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            bf16x8 kr[4], krLo[ROPE == 2 ? 4 : 1];
+            bf16x8 kr[4];
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                kr[ks] = operand(src, t * 16, ks);
-                if constexpr (ROPE == 2) krLo[ks] = operand(src + kLo, t * 16, ks);
-            }
+            for (int ks = 0; ks < 4; ++ks) kr[ks] = operand(src, t * 16, ks);
             float best = -INFINITY, bestR = -INFINITY;
 #pragma unroll
             for (int mt = 0; mt < MTW; ++mt) {
@@ -325,11 +352,6 @@ __global__ __launch_bounds__(64 * G, (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS =
 #pragma unroll
                     for (int ks = 0; ks < 4; ++ks)
                         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qaLo[mt][ks], kr[ks], c, 0, 0, 0);
-                }
-                if constexpr (ROPE == 2) {
-#pragma unroll
-                    for (int ks = 0; ks < 4; ++ks)
-                        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[mt][ks], krLo[ks], c, 0, 0, 0);
                 }
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks)
@@ -347,14 +369,11 @@ __global__ __launch_bounds__(64 * G, (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS =
                 }
             }
             sig[t] = max_over_rows(best);
-            if constexpr (ROPE == 2 && MT > 1) __builtin_amdgcn_sched_barrier(0);    // one tile's operands at a time
             if constexpr (ROPE == 1) {
                 sigR[t] = max_over_rows(bestR);
             }
         }
     };
-    // chunk-indexed RoPE: table pieces of this lane's 8 rows of a tile (set per chunk group below)
-    float4 tb_cos[ROPE == 2 ? NT * 4 : 1], tb_sin[ROPE == 2 ? NT * 4 : 1];
     // table piece of this lane for load instruction r of the chunk group at jt: chunk j's keys are
     // turned back by q_cap - j
     auto table_at = [&](int jt, int r) {
@@ -379,12 +398,32 @@ __global__ __launch_bounds__(64 * G, (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS =
                     raw[r] = fetch(kb, k_st, __shfl(ok[r >> 2] ? pos[r >> 2] : -1, (r & 3) * 4 + kq, 64),
                                    (r & 3) * 4 + kq);
             }
+            if constexpr (kTurn16) {
+                // 16 rows at a time: turned (one piece after the other: registers), stored, scored
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int at = (t * 16 + i * 4 + kq) * 16 + (n ^ (i * 4 + kq));
+                        uint4 piece, rest;
+                        turn_back_split(raw[t * 4 + i], sh_table[0][at], sh_table[1][at], piece, rest);
+                        put16(tile + i * 4 * kD, piece);
+                        put16(tile + kLo + i * 4 * kD, rest);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    // the wave reads back what its other lanes stored: LDS serves a wave's requests in order
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    sig[t] = turned_scores(tile, kLo);
+                    asm volatile("" ::: "memory");
+                }
+                return;
+            }
 #pragma unroll
             for (int r = 0; r < NT * 4; ++r) {
                 uint4 piece;
                 if constexpr (ROPE == 2) {
                     uint4 rest;
-                    turn_back_split(raw[r], tb_cos[r], tb_sin[r], piece, rest);
+                    turn_back_split(raw[r], tb_cos[kTurn16 ? 0 : r], tb_sin[kTurn16 ? 0 : r], piece, rest);
                     put16(tile + kLo + r * 4 * kD, rest);
                 } else {
                     piece = as_bf16x8(raw[r]);
@@ -447,12 +486,12 @@ __global__ __launch_bounds__(64 * G, (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS =
             pos[t] = start[t];
         }
         auto load_table = [&]() {
-            if constexpr (ROPE == 2) {
+            if constexpr (ROPE == 2 && !kTurn16) {
 #pragma unroll
                 for (int r = 0; r < NT * 4; ++r) {
                     const int64_t at = table_at(jt, r);
-                    tb_cos[r] = *reinterpret_cast<const float4 *>(rope.cos + at);
-                    tb_sin[r] = *reinterpret_cast<const float4 *>(rope.sin + at);
+                    tb_cos[kTurn16 ? 0 : r] = *reinterpret_cast<const float4 *>(rope.cos + at);
+                    tb_sin[kTurn16 ? 0 : r] = *reinterpret_cast<const float4 *>(rope.sin + at);
                 }
             }
         };
@@ -460,6 +499,19 @@ __global__ __launch_bounds__(64 * G, (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS =
         // for ahead of the first keys (that and both tiles' operands at once above: two heads per group 164 -> 149 us)
         constexpr bool kTableFirst = MT == 1;
         if constexpr (kTableFirst) load_table();
+        // kTurn16: the chunk group's turns are requested ahead of the first keys and stored once those are on their way
+        // (every wave has left the last group's: the barrier at its end)
+        constexpr int kTurns = kTurn16 ? NT * 16 * 16 / (64 * NWV) : 1;
+        float4 turn_cos[kTurns], turn_sin[kTurns];
+        if constexpr (kTurn16) {
+#pragma unroll
+            for (int i = 0; i < kTurns; ++i) {
+                const int item = (int)threadIdx.x + i * 64 * NWV;
+                const int64_t at = (int64_t)max(q_cap - (jt + (item >> 4)), 0) * (kD / 2) + ((item & 15) << 2);
+                turn_cos[i] = *reinterpret_cast<const float4 *>(rope.cos + at);
+                turn_sin[i] = *reinterpret_cast<const float4 *>(rope.sin + at);
+            }
+        }
         int half = a.chunk >> 1;
         if (kShare) {
             // The first key of a chunk and of its right half are the same rows for every head of
@@ -486,6 +538,13 @@ __global__ __launch_bounds__(64 * G, (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS =
                     if constexpr (PAGED) raw[i] = fetch_at(kb, cand_at[i], (r & 3) * 4 + kq);
                     else raw[i] = fetch(kb, k_st, cand[i], (r & 3) * 4 + kq);
                 }
+                if constexpr (kTurn16) {
+#pragma unroll
+                    for (int i = 0; i < kTurns; ++i) {
+                        sh_table[0][(int)threadIdx.x + i * 64 * NWV] = turn_cos[i];
+                        sh_table[1][(int)threadIdx.x + i * 64 * NWV] = turn_sin[i];
+                    }
+                }
 #pragma unroll
                 for (int i = 0; i < kPerWave; ++i) {
                     const int ld = wv * kPerWave + i;
@@ -495,7 +554,7 @@ __global__ __launch_bounds__(64 * G, (ROPE || (KV8 && PARTS > 1)) ? 2 : (PARTS =
                         uint4 rest;
                         turn_back_split(raw[i], *reinterpret_cast<const float4 *>(rope.cos + at),
                                         *reinterpret_cast<const float4 *>(rope.sin + at), piece, rest);
-                        put16(&sh_rows[kLo + ld * 4 * kD], rest);
+                        put16(&sh_rows[kLoShared + ld * 4 * kD], rest);
                     } else {
                         piece = as_bf16x8(raw[i]);
                     }
@@ -596,7 +655,15 @@ static void launch_prefill_w(const PruneArgs &a, int P, const RopeView &rope, hi
     switch (a.ge.G) {
     case 1: hipLaunchKernelGGL((prune_prefill_kernel<MT, NT, 1, WIDE, ROPE, PAGED, 1, KV8>), grid, dim3(64), 0, st, a, iters, rope); break;
     case 2: hipLaunchKernelGGL((prune_prefill_kernel<MT, NT, 2, WIDE, ROPE, PAGED, 1, KV8>), grid, dim3(128), 0, st, a, iters, rope); break;
-    case 4: hipLaunchKernelGGL((prune_prefill_kernel<MT, NT, 4, WIDE, ROPE, PAGED, 1, KV8>), grid, dim3(256), 0, st, a, iters, rope); break;
+    case 4:
+        if constexpr (ROPE == 2 && MT == 4) {
+            if ((int64_t)grid.x * grid.y <= 2ll * compute_units()) {
+                hipLaunchKernelGGL((prune_prefill_kernel<MT, NT, 4, WIDE, ROPE, PAGED, 1, KV8, true>), grid, dim3(256), 0, st, a, iters, rope);
+                break;
+            }
+        }
+        hipLaunchKernelGGL((prune_prefill_kernel<MT, NT, 4, WIDE, ROPE, PAGED, 1, KV8>), grid, dim3(256), 0, st, a, iters, rope);
+        break;
     default:
         // 8 heads with 64-query blocks: 8 waves of ~160 registers fit a CU once only, two passes of 4
         // waves fit three times; with RoPE the query operands alone take more registers than 8 waves
