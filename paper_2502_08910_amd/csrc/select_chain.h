@@ -7,7 +7,7 @@ namespace ihip {
 
 constexpr int kChainMaxStages = 4;
 constexpr int kChainMaxScores = 16384;    // of a problem, all stages
-constexpr int kChainMaxSlots = 4096;      // candidates of one selection
+constexpr int kChainMaxSlots = 2048;      // candidates of one selection: four to each of 512 threads; larger plans run stage by stage
 constexpr int kChainMaxKeep = 2048;
 
 struct ChainPlan {

@@ -12,7 +12,6 @@
 // itself, so every wave finds the K-th best's bin without a barrier.  Heavy ties (more candidates in that bin than
 // threads) go through the radix selection of block_select.h.  Four barriers a stage.
 #include "select_chain.h"
-#include <algorithm>
 
 namespace ihip {
 
@@ -192,11 +191,9 @@ int32_t launch_select_chain(const ihip_shape &s, const ChainPlan &plan, hipStrea
 {
     const int P = s.B * (plan.pool > 1 ? 1 : s.Hkv);
     KernelTimer timer(stage_name(kNameSelect, true, plan.chunk[0]), st);
-    int most = plan.slots[0];
-    for (int i = 1; i < plan.n_stages; ++i) most = std::max(most, plan.keep[i - 1] << plan.ratio_log2[i]);
     const ChainArgs args{make_geometry(s), plan};
-    if (most <= 2048) hipLaunchKernelGGL(select_chain_kernel<512>, dim3(P), dim3(512), 0, st, args);
-    else hipLaunchKernelGGL(select_chain_kernel<1024>, dim3(P), dim3(1024), 0, st, args);
+    // 512 threads for every plan (one sequence of 8K keys 24.2 us a layer, 256 threads 24.8)
+    hipLaunchKernelGGL(select_chain_kernel<512>, dim3(P), dim3(512), 0, st, args);
     return check_launch("select_blocks (several stages)");
 }
 
