@@ -248,11 +248,11 @@ static bool layer_splits_fine(const ihip_shape &s, int n_stages, const int32_t *
 }
 
 // ---- all stages in one pass (prune_decode_nest.h, select_chain.hip) -------------
-// Scores per problem of all stages of a plan, 0 where the two kernels do not take it.  Rows of whole 256 bytes: a line is then
-// one workgroup's.
+// Scores per problem of all stages of a plan, 0 where the two kernels do not take it (ihip_prune_all also takes several
+// single-query blocks, which the two kernels do not know).  Rows of whole 256 bytes: a line is then one workgroup's.
 static size_t nest_scores_per_problem(const ihip_shape &s, int n_stages, const int32_t *chunks, const int32_t *keeps)
 {
-    if (s.b_q != 1 || n_stages < 2 || n_stages > kChainMaxStages || chunks[n_stages - 1] < 4 || chunks[0] > (4 << (kNestLevels - 1))) return 0;
+    if (s.b_q != 1 || s.Tq != 1 || n_stages < 2 || n_stages > kChainMaxStages || chunks[n_stages - 1] < 4 || chunks[0] > (4 << (kNestLevels - 1))) return 0;
     const int64_t slots = stage1_slots(s, chunks[0]);
     if (slots == 0 || slots > kChainMaxSlots) return 0;
     int64_t scores = 0;

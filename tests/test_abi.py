@@ -74,6 +74,21 @@ def test_static_scratch_limit_needs_no_gpu(built_lib):
     assert need > (8 << 20)
 
 
+def test_scratch_of_several_single_query_blocks(built_lib):
+    """ihip_prune_all takes Tq > 1 with b_q = 1: a problem per query.  Its scratch is that of the stages one by one; the scores
+    of all stages in one pass, which exist for one query only, are no part of it."""
+    from paper_2502_08910_amd.binding import Shape, OP_PRUNE_ALL
+    L = built_lib.lib()
+    chunks, keeps = (ctypes.c_int32 * 2)(64, 16), (ctypes.c_int32 * 2)(20, 40)
+    up = lambda x: (x + 255) // 256 * 256  # noqa: E731
+    for Tq in (1, 2, 5):
+        P, slots = 2 * Tq, -(-(4000 - 64 - 256) // 64)
+        plan = up(P * max(slots, 20 * 4) * 4) + 2 * up(P * 20 * 4)
+        one_pass = up(P * (64 + (slots * 4 + 63) // 64 * 64) * 4) if Tq == 1 else 0
+        s = Shape(1, 8, 2, 128, Tq, 1, 1, 4000, 64, 256)
+        assert L.ihip_workspace_bytes(OP_PRUNE_ALL, ctypes.byref(s), 2, chunks, keeps) == plan + one_pass, Tq
+
+
 def test_argument_checks_of_the_variants_need_no_gpu(built_lib):
     """Dynamic RoPE, FP8 K/V, paged K/V and pooled selection: what they refuse, before any launch."""
     from paper_2502_08910_amd.binding import Shape, Tensor, RopeStruct, PagedStruct

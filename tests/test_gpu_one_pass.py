@@ -105,3 +105,15 @@ def test_heavy_ties(ihip):
     """All scores equal (more candidates in one bin than threads): the lowest positions are kept."""
     blocks = _case(ihip, 8, 2, [9000], ((8, 800), (4, 900)), "bf16", False, spread=0)
     assert torch.equal(blocks[0], 64 + 4 * torch.arange(900, dtype=torch.int32))
+
+
+def test_several_single_query_blocks(ihip):
+    """ihip_prune_all with Tq = 3, b_q = 1 (a problem per query): every query's list is that of a call for it alone."""
+    g = torch.Generator().manual_seed(1)
+    T, chunks, keeps = 3000, [64, 16], [12, 20]
+    q, k = (torch.randint(-3, 4, s, generator=g).bfloat16().cuda() for s in ((2, 8, 3, 128), (2, 2, T, 128)))
+    layer = lambda x, back: ihip.Layer(x, k, torch.tensor([T - back, T - 700 - back], dtype=torch.int32, device="cuda"), 1, 64, 256)  # noqa: E731
+    got = layer(q, 0).prune_all(q, k, chunks, keeps).view(2, 2, 3, -1)
+    for t in range(3):
+        one = q[:, :, t:t + 1].contiguous()
+        assert torch.equal(got[:, :, t], layer(one, 2 - t).prune_all(one, k, chunks, keeps).view(2, 2, -1)), t
