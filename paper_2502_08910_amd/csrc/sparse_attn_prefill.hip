@@ -382,9 +382,10 @@ static PfSplits prefill_splits(const ihip_shape &s, int n_blocks, int block, boo
     r.bytes = r.n > 1 ? (size_t)r.n * r.units * 64 * (r.elements * sizeof(float4) + r.query_tiles * sizeof(float2)) : 0;
     return r;
 }
-// whatever the storage and style are
+// Whatever the storage and style are; nothing for block sizes that the attention refuses (and prefill_splits does not know).
 size_t attn_prefill_workspace(const ihip_shape &s, int n_blocks, int block)
 {
+    if (s.b_q != 16 && s.b_q != 32 && s.b_q != 64) return 0;
     return std::max(prefill_splits(s, n_blocks, block, s.b_q >= 32).bytes, prefill_splits(s, n_blocks, block, false).bytes);
 }
 

@@ -89,6 +89,23 @@ def test_scratch_of_several_single_query_blocks(built_lib):
         assert L.ihip_workspace_bytes(OP_PRUNE_ALL, ctypes.byref(s), 2, chunks, keeps) == plan + one_pass, Tq
 
 
+@pytest.mark.parametrize("b_q", [1, 8, 48, 128, 256, 288, 512])
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_scratch_of_block_sizes_without_a_prefill_kernel(built_lib, G, b_q):
+    """Block sizes that the shape check takes and the prefill kernels refuse: the sizes are the plain ones, without the
+    attention's scratch."""
+    from paper_2502_08910_amd.binding import Shape, OP_ATTN_PREFILL, OP_PREFILL_LAYER
+    L = built_lib.lib()
+    chunks, keeps = (ctypes.c_int32 * 2)(64, 16), (ctypes.c_int32 * 2)(20, 40)
+    up = lambda x: (x + 255) // 256 * 256  # noqa: E731
+    Tq, T = 2 * b_q, 8192
+    s = Shape(1, 8 * G, 8, 128, Tq, b_q, 1, T, 64, 1024)
+    P, slots = 8 * 2, -(-(T - 64 - 1024) // 64)
+    assert L.ihip_workspace_bytes(OP_ATTN_PREFILL, ctypes.byref(s), 2, chunks, keeps) == 256
+    assert L.ihip_workspace_bytes(OP_PREFILL_LAYER, ctypes.byref(s), 2, chunks, keeps) == \
+        up(P * max(slots, 20 * 4) * 4) + 2 * up(P * 20 * 4) + up(P * 40 * 4)
+
+
 def test_argument_checks_of_the_variants_need_no_gpu(built_lib):
     """Dynamic RoPE, FP8 K/V, paged K/V and pooled selection: what they refuse, before any launch."""
     from paper_2502_08910_amd.binding import Shape, Tensor, RopeStruct, PagedStruct
