@@ -397,8 +397,9 @@ class Layer:
             sm_scale = 1.0 / math.sqrt(self.d) if sm_scale is None else sm_scale
             out = torch.empty((self.B, self.Hq, self.Tq, self.d), dtype=torch.bfloat16, device=self.device)
             lse = torch.empty((self.B, self.Hq, self.Tq), dtype=torch.float32, device=self.device) if want_lse else None
-            if ws is None:
-                ws = self.workspace(OP_ATTN_PREFILL, [block], [max(block_starts.shape[-1], 1)])
+            if ws is None:          # the size query knows blocks of up to 1,024 tokens; the attention needs no scratch
+                ws = self.workspace(OP_ATTN_PREFILL, [block], [max(block_starts.shape[-1], 1)]) if block <= 1024 else \
+                    torch.empty(0, dtype=torch.uint8, device=self.device)
             _check(lib().ihip_sparse_attn_prefill_fp8kv(
                 ctypes.byref(self.shape), _tensor(q, "q"), _tensor8(k, "k"), _tensor8(v, "v"), _ptr(block_starts),
                 block_starts.shape[-1], block, sm_scale, kv_scales[0], kv_scales[1],

@@ -189,3 +189,18 @@ def test_keep_everything_is_dense_causal_on_dequantised_values(ihip, prefix, pag
     ref = torch.nn.functional.scaled_dot_product_attention(
         q.double(), kd.repeat_interleave(G, 1), vd.repeat_interleave(G, 1), attn_mask=mask)
     assert (out.cpu().double() - ref).abs().max().item() <= 2e-2
+
+
+def test_attention_over_blocks_of_more_than_1024_tokens(ihip):
+    """The attention takes blocks of any power of two, the size query those of up to 1,024: a block of 2,048 tokens gives the bits of
+    its two halves (one split both times)."""
+    g = torch.Generator().manual_seed(3)
+    q = torch.randn((1, 8, 128, 128), generator=g).bfloat16().cuda()
+    k, v = (gen.to_e4m3(torch.randn((1, 2, 9000, 128), generator=g).bfloat16(), 1 / 64).cuda() for _ in range(2))
+    L = ihip.Layer(q, k, torch.tensor([9000], dtype=torch.int32, device="cuda"), 64, 64, 256)
+    big = torch.tensor([[64, 64 + 4096]] * 4, dtype=torch.int32, device="cuda")
+    halves = torch.stack([big, big + 1024], dim=-1).view(4, 4).contiguous()
+    got = L.sparse_attn_prefill(q, k, v, big, 2048, want_lse=True, kv_scales=(1 / 64, 1 / 64))
+    want = L.sparse_attn_prefill(q, k, v, halves, 1024, want_lse=True, kv_scales=(1 / 64, 1 / 64),
+                                 ws=torch.empty(256, dtype=torch.uint8, device="cuda"))
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
