@@ -54,14 +54,17 @@
 //
 // KV8 (K and V rows are 128 bytes of E4M3): the direct loads bring the raw rows (16 bytes per
 // lane: 8 lanes a row, 8 rows an instruction, 8 instructions a tile) into a ring of three raw
-// stages; the tile is widened to bf16 (exact) into one of two bf16 K tiles (K(t) has been read when K(t+2) is written) and one
-// of three V tiles, 64 KB with the raw ones, so that two workgroups of four waves share a compute unit (with three K tiles, 72 KB,
-// one: 512 workgroups of 100 tiles, four heads 164 / 139 us, one head 185 / 122, with RoPE 211 / 165 and 325 / 194); every thread
-// 8 bytes of K and 8 of V, in the period the RoPE variant uses for its rotation (and rotated on the way
+// stages; the tile is widened to bf16 (exact) into a K tile and one of three V tiles, every thread 8 bytes of K and 8 of V, in the
+// period the RoPE variant uses for its rotation (and rotated on the way
 // with ROPE), in the swizzled layout the reads below expect.  The raw ring puts requests a period
 // further ahead than ROPE does: tile t+4 is requested at the start of period t, tile t+3 must have
 // landed at its end, tile t+2 is widened during it, K(t+1) and V(t) are read.  The K scale is folded into the softmax scale on the host,
 // the V scale into the final normalisation.
+// Two K tiles serve (K(t) has been read when K(t+2) is written, which takes one barrier more in front of the loop and six periods of code, since
+// three V tiles and two K tiles repeat after six): 64 KB with the raw ones, so that two workgroups of four waves share a compute
+// unit (with three K tiles, 72 KB, one: 512 workgroups of 100 tiles, four heads 164 / 139 us, one head 185 / 122, with RoPE 211 / 165 and
+// 325 / 194).  Workgroups of eight waves are one to a unit by their registers and keep three K tiles and three periods (256
+// workgroups of 292 tiles with RoPE 382 us with two, 380 with three).
 #pragma once
 
 #include "attn_prefill_args.h"
@@ -92,7 +95,8 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
     static_assert(!PAGED || WIDE, "paged pools are addressed with 64-bit offsets");
     static_assert(!KV8 || WIDE, "E4M3 rows are addressed with 64-bit offsets");
     constexpr int kPfStages = KV8 ? kPfVTilesFp8 : ROPE ? kPfStagesRope : kPfStagesPlain;
-    constexpr int kUnroll = KV8 ? 6 : kPfStages;     // periods after which the stages repeat
+    constexpr int kKTiles = KV8 ? pf32_k_tiles_fp8(NQ * G) : kPfStages;
+    constexpr int kUnroll = KV8 && kKTiles == 2 ? 6 : kPfStages;     // periods after which the stages repeat
     constexpr bool kTouch = ROPE || KV8;             // a tile is worked on in LDS between landing and first read
     // A period's operands are requested up front (see there), unless the table pieces that one or two waves hold for their
     // rotations, 64 or 32 registers, leave no room: 1,024 queries, 3,200 key slots each, two waves 164 us in order, 300 with
@@ -100,16 +104,23 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
     // 300 bytes either way: 970 and 936.
     constexpr bool kUpFront = !ROPE || NQ * G > 2 || (NQ * G == 1 && PAGED && !KV8);
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
-    uint16_t *raw0 = smem + (KV8 ? (kPfKTilesFp8 + kPfVTilesFp8) * kPfTileEl : kPfStages * kPfStageEl);       // KV8: the raw stages
+    uint16_t *raw0 = smem + (kKTiles + kPfStages) * kPfTileEl;       // KV8: the raw stages
     int *sPos = reinterpret_cast<int *>(raw0 + (KV8 ? kPfRawStages * kPfTileEl : 0));   // one int per key slot
-    const int slots_cap = a.slots_cap;
+    // (What a launch without splits can compute comes from the arguments it reads first, and its workgroups of whole head groups are
+    // problems as they come: with a.slots_cap, a cold scalar load late in front of everything else, and the mapping for all, 256
+    // eight-wave workgroups of 292 E4M3 tiles with RoPE took 361.5 us instead of 359.6.)
+    const int slots_cap = SPLIT ? a.slots_cap : (a.ge.n_sink + a.n_blocks * a.block + a.ge.n_stream + kPfTile - 1) / kPfTile * kPfTile;
     int *sPage = sPos + slots_cap;                                           // PAGED: one page id per key slot
     // one flag per tile, behind the per-slot arrays
     uint8_t *sMasked = reinterpret_cast<uint8_t *>(sPos + (PAGED ? 2 : 1) * slots_cap);
 
-    const PfWorkgroup wg = pf_workgroup(blockIdx.x, a.ge.G / G);
-    const int p = wg.p, head_part = wg.head_part;
-    if (p >= a.ge.B * a.ge.Hkv * a.ge.Mq) return;
+    int p = blockIdx.x, head_part = 0;
+    if (a.ge.G != G) {
+        const PfWorkgroup wg = pf_workgroup(blockIdx.x, a.ge.G / G);
+        p = wg.p;
+        head_part = wg.head_part;
+        if (p >= a.ge.B * a.ge.Hkv * a.ge.Mq) return;
+    }
     const Problem pr = problem_of(a.ge, p);
     constexpr int NW = NQ * G;
     constexpr int nthreads = 64 * NW;
@@ -182,8 +193,9 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);
     // the stage of a tile (tile % kPfStages) is a compile-time constant in the unrolled loop below,
     // so LDS addresses are per-lane constants plus immediates
-    auto k_stage = [&](int st) { return smem + (KV8 ? (st % kPfKTilesFp8) * kPfTileEl : (st % kPfStages) * kPfStageEl); };
-    auto v_stage = [&](int st) { return smem + (KV8 ? (kPfKTilesFp8 + st % kPfVTilesFp8) * kPfTileEl : (st % kPfStages) * kPfStageEl + kPfTileEl); };
+    constexpr bool kPairs = kKTiles == kPfStages;    // a K tile next to its V tile
+    auto k_stage = [&](int st) { return smem + (kPairs ? (st % kPfStages) * kPfStageEl : (st % kKTiles) * kPfTileEl); };
+    auto v_stage = [&](int st) { return smem + (kPairs ? (st % kPfStages) * kPfStageEl + kPfTileEl : (kKTiles + st % kPfStages) * kPfTileEl); };
     auto raw_of = [&](int st) { return raw0 + (st % kPfRawStages) * kPfTileEl; };
     // key positions of this lane's rows in the loads of a tile (read a period ahead of the request)
     struct Rows { int pos[kLoadsPerWave]; int page[PAGED ? kLoadsPerWave : 1]; };
@@ -436,7 +448,7 @@ __global__ __launch_bounds__(64 * NQ * G, 2) void attn_prefill32_kernel(const At
     if (sMasked[0] != 0) mask_scores(0, s_nxt);
     settle(s_nxt, exponentials(s_nxt, pb), pb);
     int masked_nxt = n_tiles > 1 ? sMasked[1] : 0;      // read a period ahead, like the row positions
-    if constexpr (KV8) __syncthreads();     // K(0) has been read: period 0 writes K(2) in its place
+    if constexpr (KV8 && kKTiles == 2) __syncthreads();     // K(0) has been read: period 0 writes K(2) in its place
     // one tile period; ST = tile % kUnroll
     auto period = [&](auto st_c, int tile) {
         constexpr int ST = decltype(st_c)::value;

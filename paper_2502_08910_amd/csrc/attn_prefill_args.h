@@ -99,7 +99,8 @@ __device__ inline int pf_slot_to_pos(const AttnPrefillArgs &a, const Problem &pr
 // 8 KB; then an int per key slot (two with paged K/V: the page id) and a flag per tile.  The most key
 // slots a kernel can take follow from the 160 KB of a CU (64 bytes are left for static variables).
 constexpr int kPfStagesPlain = 3, kPfStagesRope = 4;
-constexpr int kPfKTilesFp8 = 2, kPfVTilesFp8 = 3;   // E4M3: widened K and V tiles
+constexpr int kPfVTilesFp8 = 3;                     // E4M3: widened V tiles
+constexpr int pf32_k_tiles_fp8(int waves) { return waves == 8 ? 3 : 2; }     // ... and K tiles (attn_prefill32.h)
 constexpr int kPfRawStages = 3;                     // E4M3: raw stages of one K or V tile's size
 constexpr int kPfTileEl = kPfTile * kD;             // elements of one K (or V) tile: 32 rows of 256 bytes
 constexpr int kPfStageEl = 2 * kPfTileEl;           // K tile, then V tile
@@ -110,21 +111,21 @@ constexpr int pf32_max_slots(int stage_bytes, int ints_per_slot)
     return (int)((int64_t)(kPf32MaxLds - 64 - stage_bytes) * kPfTile / (4 * ints_per_slot * kPfTile + 1)) / kPfTile * kPfTile;
 }
 constexpr int kPfStageBytes = kPfStageEl * 2, kPfRawBytes = kPfTileEl * 2;
-constexpr int kPfFp8StageBytes = (kPfKTilesFp8 + kPfVTilesFp8) * kPfRawBytes + kPfRawStages * kPfRawBytes;
+constexpr int pf32_stage_bytes_fp8(int waves) { return (pf32_k_tiles_fp8(waves) + kPfVTilesFp8 + kPfRawStages) * kPfRawBytes; }
 constexpr int kPf32MaxSlots = pf32_max_slots(kPfStagesPlain * kPfStageBytes, 1);            // 28,416
 constexpr int kPf32MaxSlotsRope = pf32_max_slots(kPfStagesRope * kPfStageBytes, 1);         // 24,352
 constexpr int kPf32MaxSlotsPaged = pf32_max_slots(kPfStagesPlain * kPfStageBytes, 2);       // 14,272: a page id per slot as well
 constexpr int kPf32MaxSlotsRopePaged = pf32_max_slots(kPfStagesRope * kPfStageBytes, 2);
-// E4M3, with or without RoPE (the lengths that a third K tile would leave)
-constexpr int kPf32MaxSlotsFp8 = pf32_max_slots(kPfFp8StageBytes + kPfRawBytes, 1);
-constexpr int kPf32MaxSlotsFp8Paged = pf32_max_slots(kPfFp8StageBytes + kPfRawBytes, 2);
+// E4M3, with or without RoPE (the lengths that three K tiles leave, for all workgroups)
+constexpr int kPf32MaxSlotsFp8 = pf32_max_slots(pf32_stage_bytes_fp8(8), 1);
+constexpr int kPf32MaxSlotsFp8Paged = pf32_max_slots(pf32_stage_bytes_fp8(8), 2);
 static_assert(kPf32MaxSlots * 4 + kPf32MaxSlots / kPfTile + kPfStagesPlain * kPfStageBytes + 64 <= kPf32MaxLds, "LDS");
-static_assert(kPf32MaxSlotsFp8Paged * 8 + kPf32MaxSlotsFp8Paged / kPfTile + kPfFp8StageBytes + 64 <= kPf32MaxLds, "LDS");
+static_assert(kPf32MaxSlotsFp8Paged * 8 + kPf32MaxSlotsFp8Paged / kPfTile + pf32_stage_bytes_fp8(8) + 64 <= kPf32MaxLds, "LDS");
 
 // dynamic LDS of a launch: stages, slot positions (and pages), per-tile flags
-inline size_t pf32_lds(int slots, bool rope, bool paged, bool fp8)
+inline size_t pf32_lds(int slots, bool rope, bool paged, bool fp8, int waves)
 {
-    return (fp8 ? kPfFp8StageBytes : (rope ? kPfStagesRope : kPfStagesPlain) * kPfStageBytes) + (size_t)slots * 4 * (paged ? 2 : 1) + slots / kPfTile;
+    return (fp8 ? pf32_stage_bytes_fp8(waves) : (rope ? kPfStagesRope : kPfStagesPlain) * kPfStageBytes) + (size_t)slots * 4 * (paged ? 2 : 1) + slots / kPfTile;
 }
 void launch_attn_prefill32(const AttnPrefillArgs &a, int P, int64_t max_seq_len, hipStream_t st);
 void launch_attn_prefill32_fp8(const AttnPrefillArgs &a, int P, hipStream_t st);   // E4M3 K and V

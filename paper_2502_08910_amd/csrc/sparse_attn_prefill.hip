@@ -473,7 +473,7 @@ int32_t launch_attn_prefill(const ihip_shape &s, const ihip_tensor &q, const ihi
     const bool on_32 = prefill_on_32(s, n_blocks, block, use_rope, paged, fp8);
     PfSplits splits = prefill_splits(s, n_blocks, block, on_32);
     // two workgroups of a compute unit only where its LDS holds both
-    if (on_32 && splits.n > 1 && 2 * pf32_lds(splits.tiles_each * kPfTile, use_rope, paged, fp8) > kPf32MaxLds)
+    if (on_32 && splits.n > 1 && 2 * pf32_lds(splits.tiles_each * kPfTile, use_rope, paged, fp8, splits.waves) > kPf32MaxLds)
         splits = prefill_splits(s, n_blocks, block, on_32, true);
     if (!ws || ((uintptr_t)ws & 15) || ws_bytes < splits.bytes) {      // without scratch: one split
         splits.tiles_each = (int)(((int64_t)s.n_sink + (int64_t)n_blocks * block + s.n_stream + kPfTile - 1) / kPfTile);

@@ -11,7 +11,7 @@ void launch_attn_prefill32(const AttnPrefillArgs &a, int P, int64_t max_seq_len,
     const int parts = a.ge.G / heads_per_wg;
     const dim3 block_dim(64 * NQ * heads_per_wg), grid(parts == 1 ? P : (P + 7) / 8 * 8 * parts, a.n_splits);
     const bool use_rope = a.rope_cos != nullptr, paged = a.paged.block_table != nullptr;
-    const size_t lds = pf32_lds(a.slots_cap, use_rope, paged, false);
+    const size_t lds = pf32_lds(a.slots_cap, use_rope, paged, false, NQ * heads_per_wg);
     const int64_t lim = (int64_t)1 << 31, lim24 = (int64_t)1 << 24;
     const bool wide = paged || max_seq_len >= lim24 || a.k_st < 0 || a.v_st < 0 || a.k_st >= lim24 || a.v_st >= lim24 ||
                       max_seq_len * a.k_st + kD >= lim || max_seq_len * a.v_st + kD >= lim;

@@ -14,7 +14,7 @@ void launch_attn_prefill32_fp8(const AttnPrefillArgs &a, int P, hipStream_t st)
     const int parts = a.ge.G / heads_per_wg;
     const dim3 block_dim(64 * NQ * heads_per_wg), grid(parts == 1 ? P : (P + 7) / 8 * 8 * parts, a.n_splits);
     const bool use_rope = a.rope_cos != nullptr, paged = a.paged.block_table != nullptr;
-    const size_t lds = pf32_lds(a.slots_cap, use_rope, paged, true);
+    const size_t lds = pf32_lds(a.slots_cap, use_rope, paged, true, NQ * heads_per_wg);
 #define IHIP_PF32_S(NQV, GV, RV, PV, SV)                                                                         \
     {                                                                                                        \
         static bool attr_set = false;     /* allow more than 64 KiB of dynamic LDS, once per kernel */       \
