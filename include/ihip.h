@@ -454,7 +454,8 @@ int32_t ihip_decode_layer_static(const ihip_shape *shape, ihip_tensor q, ihip_te
  * ihip_decode_layer_cached is ihip_decode_layer reading K/V through the cache:
  * a resident block is read from its bank, any other row straight from host
  * memory over the host link; the results are bit-identical to the uncached
- * call on the same data whatever the cache holds.  It records which blocks
+ * call on the same data in contiguous rows, both with the reported scratch,
+ * whatever the cache holds.  It records which blocks
  * were touched and which were missing.  ihip_cache_update (same stream, after
  * the layer call) then, per bank, evicts as many least-recently-used slots as
  * there were missed blocks (oldest last-touch call first, lowest slot on a

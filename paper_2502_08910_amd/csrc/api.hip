@@ -87,7 +87,7 @@ void profile_end(hipStream_t st)
 // kernels' host launchers
 int32_t launch_prune_stage(const ihip_shape &, const ihip_tensor &, const ihip_tensor &, const int32_t *,
                            int, int, int, int, float *, int32_t *, const BankView *, const ihip_rope *, hipStream_t,
-                           const KvFormat * = nullptr, const NestArgs * = nullptr);
+                           const KvFormat * = nullptr, const NestArgs * = nullptr, bool = false);
 int32_t launch_subdivide_blocks(const ihip_shape &, const int32_t *, int, int, int32_t *, hipStream_t);
 int32_t launch_select_blocks(const ihip_shape &, const float *, int, const int32_t *, int, int, int, int,
                              int32_t *, bool, hipStream_t);
@@ -306,30 +306,32 @@ static size_t decode_layer_scratch(const ihip_shape &s, int n_stages, const int3
 // stage that is re-run reads the list of the stage before it as it stands, re-run in this call or
 // cached from an earlier one (Alg. 4: a stage is re-run when its counter says so, with the current
 // lists of the earlier stages; a stage that is not due keeps its list).
-// nest_scores: room for the scores of all stages taken together (nest_bytes), or null: each stage on its own.
+// nest: the plan's scores may be taken together (decode_layer_scratch, nest_bytes); nest_scores: room for them, or null: each stage on
+// its own.  The host tier scores stage by stage, but with the arithmetic that contiguous rows in device memory get.
 static int32_t prune_stages_impl(const ihip_shape &s, const ihip_tensor &q, const ihip_tensor &k, int n_stages,
                                  const int32_t *chunks, const int32_t *keeps, uint32_t due,
                                  int32_t *const *stage_out, float *scores, const BankView *bank,
                                  const ihip_rope *rope, bool all_heads, hipStream_t st,
-                                 const KvFormat *fmt = nullptr, float *nest_scores = nullptr)
+                                 const KvFormat *fmt = nullptr, bool nest = false, float *nest_scores = nullptr)
 {
     const uint32_t every = (1u << n_stages) - 1u;
     const bool relative = rope && rope->prune_style == IHIP_ROPE_RELATIVE, paged = fmt && fmt->paged.block_table;
-    if (nest_scores && !bank && (due & every) == every && !(rope && rope->prune_style == IHIP_ROPE_CHUNK_INDEXED) &&
-        nest_pays(s, n_stages, chunks, keeps, fmt && fmt->fp8, relative || paged)) {
+    const bool together = nest && (due & every) == every && !(rope && rope->prune_style == IHIP_ROPE_CHUNK_INDEXED) &&
+                          nest_pays(s, n_stages, chunks, keeps, fmt && fmt->fp8, relative || paged);
+    if (together && nest_scores && !bank) {
         const int slots = stage1_slots(s, chunks[0]);
-        NestArgs nest{};
+        NestArgs args{};
         ChainPlan chain{};
-        nest.top = __builtin_ctz(chunks[0]) - 2;
-        nest.stride = chain.stride = (int)nest_scores_per_problem(s, n_stages, chunks, keeps);
+        args.top = __builtin_ctz(chunks[0]) - 2;
+        args.stride = chain.stride = (int)nest_scores_per_problem(s, n_stages, chunks, keeps);
         chain.n_stages = n_stages;
         chain.pool = all_heads ? s.Hkv : 1;
         chain.scores = nest_scores;
         int at = 0;
         for (int i = 0; i < n_stages; ++i) {
             const int lv = __builtin_ctz(chunks[i]) - 2, n = slots * (chunks[0] / chunks[i]);
-            nest.out[lv] = nest_scores + at;
-            nest.slots[lv] = n;
+            args.out[lv] = nest_scores + at;
+            args.slots[lv] = n;
             chain.at[i] = at;
             chain.out[i] = stage_out[i];
             chain.slots[i] = n;
@@ -338,7 +340,7 @@ static int32_t prune_stages_impl(const ihip_shape &s, const ihip_tensor &q, cons
             chain.keep[i] = keeps[i];
             at += (n + 63) & ~63;
         }
-        const int32_t rc = launch_prune_stage(s, q, k, nullptr, 0, 0, chunks[0], slots, nullptr, nullptr, bank, rope, st, fmt, &nest);
+        const int32_t rc = launch_prune_stage(s, q, k, nullptr, 0, 0, chunks[0], slots, nullptr, nullptr, bank, rope, st, fmt, &args);
         return rc != IHIP_OK ? rc : launch_select_chain(s, chain, st);
     }
     for (int i = 0; i < n_stages; ++i) {
@@ -348,7 +350,7 @@ static int32_t prune_stages_impl(const ihip_shape &s, const ihip_tensor &q, cons
         const int parent_chunk = i == 0 ? 0 : chunks[i - 1];
         const int slots = i == 0 ? stage1_slots(s, chunks[0]) : n_parent * (parent_chunk / chunks[i]);
         int32_t rc = launch_prune_stage(s, q, k, parents, n_parent, parent_chunk, chunks[i], slots, scores,
-                                        nullptr, bank, rope, st, fmt);
+                                        nullptr, bank, rope, st, fmt, nullptr, together && bank);
         if (rc != IHIP_OK) return rc;
         rc = launch_select_blocks(s, scores, slots, parents, n_parent, parent_chunk, chunks[i], keeps[i],
                                   stage_out[i], all_heads, st);
@@ -397,14 +399,14 @@ static int32_t prune_all_subdivided(const ihip_shape &s, const ihip_tensor &q, c
 static int32_t prune_all_impl(const ihip_shape &s, const ihip_tensor &q, const ihip_tensor &k, int n_stages,
                               const int32_t *chunks, const int32_t *keeps, int32_t *out_block_starts,
                               char *ws, const BankView *bank, const ihip_rope *rope, bool all_heads, hipStream_t st,
-                              const KvFormat *fmt = nullptr, float *nest_scores = nullptr)
+                              const KvFormat *fmt = nullptr, bool nest = false, float *nest_scores = nullptr)
 {
     const PlanLayout L = plan_layout(s, n_stages, chunks, keeps);
     int32_t *stage_out[8];
     for (int i = 0; i < n_stages; ++i)
         stage_out[i] = (i + 1 == n_stages) ? out_block_starts : (int32_t *)(ws + L.starts_off[i & 1]);
     return prune_stages_impl(s, q, k, n_stages, chunks, keeps, ~0u, stage_out, (float *)(ws + L.scores_off), bank, rope, all_heads, st, fmt,
-                             nest_scores);
+                             nest, nest_scores);
 }
 
 }  // namespace ihip
@@ -690,7 +692,7 @@ int32_t ihip_prune_all(const ihip_shape *shape, ihip_tensor q, ihip_tensor k, in
         return fail(IHIP_ERR_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", who, need, ws_bytes);
     const size_t nested = nest_bytes(*shape, n_stages, chunk_sizes, keeps);
     return prune_all_impl(*shape, q, k, n_stages, chunk_sizes, keeps, out_block_starts, (char *)ws, nullptr, nullptr,
-                          false, (hipStream_t)stream, nullptr, nested > 0 && ws_bytes >= need + nested ? (float *)((char *)ws + need) : nullptr);
+                          false, (hipStream_t)stream, nullptr, nested > 0, ws_bytes >= need + nested ? (float *)((char *)ws + need) : nullptr);
 }
 
 // stage_starts != NULL: mask caching (the caller's per-stage lists; stages first_stage.. are recomputed,
@@ -722,7 +724,7 @@ static int32_t decode_layer_impl(const char *who, const ihip_shape *shape, ihip_
     size_t nested = 0;
     (void)decode_layer_scratch(*shape, n_stages, chunk_sizes, keeps, &nested);
     auto nest_scores = [&](size_t used) -> float * {      // behind the attention's scratch, where there is room
-        return nested > 0 && !cache && ws_bytes >= align256(used) + nested ? (float *)((char *)ws + align256(used)) : nullptr;
+        return ws_bytes >= align256(used) + nested ? (float *)((char *)ws + align256(used)) : nullptr;
     };
     BankView mask_bank, sa_bank;
     if (cache) {
@@ -744,7 +746,7 @@ static int32_t decode_layer_impl(const char *who, const ihip_shape *shape, ihip_
             if (stage_due ? stage_due[i] != 0 : i >= first_stage) due |= 1u << i;
         rc = prune_stages_impl(*shape, q, k, n_stages, chunk_sizes, keeps, due, stage_out, (float *)ws,
                                cache ? &mask_bank : nullptr, rope, all_heads, (hipStream_t)stream, fmt,
-                               nest_scores(L.scores_bytes + fine_bytes));
+                               nested > 0, nest_scores(L.scores_bytes + fine_bytes));
         if (rc != IHIP_OK) return rc;
         if (out_block_starts &&
             hipMemcpyAsync(out_block_starts, stage_out[last], P * keeps[last] * sizeof(int32_t),
@@ -763,7 +765,7 @@ static int32_t decode_layer_impl(const char *who, const ihip_shape *shape, ihip_
     char *w = (char *)ws;
     int32_t *blocks = out_block_starts ? out_block_starts : (int32_t *)(w + L.total);
     rc = prune_all_impl(*shape, q, k, n_stages, chunk_sizes, keeps, blocks, w, cache ? &mask_bank : nullptr, rope,
-                        all_heads, (hipStream_t)stream, fmt, nest_scores(need - attn_bytes + fine_bytes));
+                        all_heads, (hipStream_t)stream, fmt, nested > 0, nest_scores(need - attn_bytes + fine_bytes));
     if (rc != IHIP_OK) return rc;
     return launch_attn_decode(*shape, q, k, v, blocks, keeps[last], chunk_sizes[last], sm_scale, out, out_lse,
                               w + L.total + blocks_bytes, fine_plan && ws_bytes >= L.total + blocks_bytes + fine_bytes,

@@ -169,11 +169,12 @@ struct CachedRows {
     int gb0;                     // global id of this (sequence, KV head)'s block 0
     const int32_t *host_pages;   // paged host tier: this sequence's row of the block table, else nullptr
     int64_t host_page_stride;
+    __device__ int slot_of(int pos) const { return c.page_table[gb0 + (pos >> c.block_log2)]; }
     // leader: one lane per row does the bookkeeping stores
-    __device__ const uint16_t *row(int pos, bool leader) const
+    __device__ const uint16_t *row(int pos, bool leader) const { return row(pos, leader, slot_of(pos)); }
+    __device__ const uint16_t *row(int pos, bool leader, int slot) const
     {
         const int gb = gb0 + (pos >> c.block_log2);
-        const int slot = c.page_table[gb];
         if (leader) {
             c.touch_flag[gb] = 1;
             if (slot >= 0) c.slot_stamp[slot] = c.stamp;

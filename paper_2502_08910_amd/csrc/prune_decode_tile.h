@@ -1,11 +1,11 @@
 // Decode pruning stage on the matrix cores (b_q == 1): Alg. 3's search and Alg. 2's chunk score, K from device memory
-// (strides or pages), without RoPE or with the relative style.  One query per head makes this a gather, not a contraction: what
+// (strides or pages) or behind the host tier, without RoPE or with the relative style.  One query per head makes this a gather, not a contraction: what
 // it cannot do without are the rows.  The matrix cores take the arithmetic off the vector ALUs: 16 gathered rows
 // against 16 query columns is four v_mfma_f32_16x16x32_bf16 (E4M3 rows are widened, exact), of whose 256 products the 16
 // that are wanted are picked in the registers; the vector form needs some 30 instructions for every four rows (45 with
 // two rotated queries), and with 128-byte rows or two rotated queries those, not the rows, were the time.
 //
-// A wave walks 64 searches, one per lane: 64/G chunks x G heads, in four 16-row tiles.  Tile t, row r = 4*kq + i is owned
+// A wave walks 64 searches, one per lane: 64/G chunks x G heads, in four 16-row tiles (host tier: 16 searches, one tile).  Tile t, row r = 4*kq + i is owned
 // by lane (kq, n = 4t + i): the product's column n, rows 4*kq..+3 are in that lane's accumulator, so with column n
 // holding the query of head n % G the owner finds its own score in register n % 4 -- no value crosses lanes except the
 // row offsets, handed from the owners to the loading lanes (one shuffle per tile and level).
@@ -95,6 +95,12 @@ __device__ inline float pick4(const f32x4 c, int i)      // c[i], in registers
     return (i & 2) ? b : a;
 }
 __device__ inline float row_ror8(float v) { return dpp_f32<0x128>(v); }
+template <int N>
+__device__ inline int64_t row_lane(int64_t v)            // lane N of each row of 16, in all its lanes
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)v, 0x150 + N, 0xf, 0xf, true), hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), 0x150 + N, 0xf, 0xf, true);
+    return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+}
 __device__ inline float other_quad(float v) { return dpp_f32<0x1B>(dpp_f32<0x141>(v)); }   // lane n ^ 4 of a row: half mirror, then each quad reversed
 
 // Where the rows of (sequence, KV head) are, and how a lane's row offset is formed and handed round.  NARROW: byte offsets of 32 bits
@@ -128,6 +134,23 @@ struct DecodeRows {
     }
 };
 
+// SRC 1: rows of the host tier.  A lane's "offset" is the row's address, so that each owner looks its row up, and notes it, once; position
+// -1 (nothing may be noted): a row of the query, which is there
+template <>
+struct DecodeRows<1, false> {
+    CachedRows src;
+    const uint16_t *unread;
+    using off_t = int64_t;
+    __device__ DecodeRows(const PruneArgs &a, const Problem &pr) : src(KeySource<1>::make(a, pr)), unread(a.q + pr.b * a.q_sb) {}
+    // slot: slot_of(max(pos, 0)), whose load several rows may wait for together
+    __device__ off_t at(int pos, int slot) const { return (int64_t)(uintptr_t)(pos >= 0 ? src.row(pos, true, slot) : unread); }
+    __device__ uint4 load(off_t off, int b) const      // named as global memory, which the compiler cannot tell of an address
+    {
+        typedef uint32_t words __attribute__((ext_vector_type(4)));
+        return __builtin_bit_cast(uint4, *(const __attribute__((address_space(1))) words *)((uintptr_t)off + b));
+    }
+};
+
 // What a wave without a single chunk writes for its n <= 64 slots j0..
 template <int G>
 __device__ inline void write_no_chunks(const PruneArgs &a, const Problem &pr, int p, int j0, int n)
@@ -142,6 +165,12 @@ __device__ inline void write_no_chunks(const PruneArgs &a, const Problem &pr, in
     }
 }
 
+// Tiles of a wave.  Host tier: one, whose 16 owners look their rows up in the bank and hand them to the lanes of their row group; four times
+// the waves (8K to 32K keys all in the banks, 64 heads on 8, bf16: 100 -> 80 us a layer, 32 on 8 86 -> 76).  Vector kernel / this one
+// (us): 8K bf16 keys, 32 heads on 8, banks that hold few of them 291 / 273, all 68 / 58, 500K E4M3 with RoPE 64 on 8 all 278 / 219;
+// one head a group is where it loses, up to 5 us of 50 (4K to 12K keys in the banks).
+constexpr int decode_search_tiles(int src) { return src == 1 ? 1 : 4; }
+
 constexpr int kDecodePages = 16;              // page ids of a chunk kept in LDS; further ones are looked up in the table
 
 // Eight heads over bf16 pages with rotated queries: left alone the compiler takes 172 registers, two waves per SIMD; told to
@@ -150,15 +179,16 @@ constexpr int kDecodePages = 16;              // page ids of a chunk kept in LDS
 template <int G, bool ROPE, int SRC, bool KV8, bool NARROW>
 __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) void prune_decode_tile_kernel(const PruneArgs a, const RopeView rope)
 {
-    static_assert(SRC == 0 || !NARROW, "paged pools are addressed with 64-bit offsets");
+    static_assert(SRC == 0 || !NARROW, "paged pools and the host tier are addressed with 64-bit offsets");
     constexpr int PARTS = ROPE ? 3 : 1;
-    constexpr int NT = 4;                     // tiles of a wave
+    constexpr int NT = decode_search_tiles(SRC);
     constexpr int kPerTile = 16 / G;          // chunks of a tile
     constexpr int kChunks = NT * kPerTile;    // chunks of a wave
     constexpr int kLoads = KV8 ? 2 : 4;
     using Rows = DecodeRows<SRC, NARROW>;
     using off_t = typename Rows::off_t;
     __shared__ int32_t sh_pages[SRC == 2 ? 4 * kChunks * kDecodePages : 1];
+    __shared__ uint4 sh_rows[SRC == 1 ? kDecodeTileWaves * 2 * 16 * (KV8 ? 8 : 16) : 1];
     const int p = a.grid.problem();
     const Problem pr = problem_of(a.ge, p);
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -170,7 +200,8 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
     const int r = 4 * kq + (n & 3);
     const int ci = quad * kPerTile + r / G, hd = r % G;
     const int j = j0 + ci;
-    const int start = j < a.max_chunks ? slot_start(pr, a.parent_starts, a.n_parent, a.ratio_log2, a.chunk, p, j) : -1;
+    const bool owner = quad < NT;             // of a search
+    const int start = owner && j < a.max_chunks ? slot_start(pr, a.parent_starts, a.n_parent, a.ratio_log2, a.chunk, p, j) : -1;
     const bool valid = start >= 0;
     const int len = valid ? min(a.chunk, pr.hi - start) : 0;
     // No chunk at all (a sequence that ends before its middle range, an idle place of the batch, the tail of a short list):
@@ -188,7 +219,8 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
         decode_query_operands<KV8, PARTS>(qb, kq, rope, a.ge.n_stream + (n < 8 ? 1 : 0), q);
     }
     const Rows rows(a, pr);
-    const int base = max(start, 0);
+    const int base = SRC == 1 ? start : max(start, 0);
+    const int unread = SRC == 1 ? -1 : base;  // position for a lane that needs no row
     int32_t *pages = &sh_pages[SRC == 2 ? wv * kChunks * kDecodePages : 0];
     if constexpr (SRC == 2) {
         // page ids of every chunk of the wave, 16 lanes a chunk
@@ -208,6 +240,8 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
             int page = pages[ci * kDecodePages + min(idx, kDecodePages - 1)];
             if (idx >= kDecodePages) page = rows.table[pos >> rows.page_log2];      // a chunk of more pages than that
             return rows.at(pos, page);
+        } else if constexpr (SRC == 1) {
+            return rows.at(pos, rows.src.slot_of(max(pos, 0)));
         } else {
             return rows.at(pos, 0);
         }
@@ -216,6 +250,36 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
 #pragma unroll
         for (int i = 0; i < kLoads; ++i) raw[i] = rows.load(off, i * 64 + kq * 16);
     };
+    // Host tier: the 16 rows of the tile, each by neighbouring lanes, 256 or 128 bytes in order, and into operand layout through LDS.
+    // (In operand layout an instruction takes 16 bytes of 16 rows at a time, which the host link sees as requests of their own: 16K
+    // bf16 keys, 32 heads on 8, most rows missed, 685 us a layer instead of 564.)  The lanes of a row group take the rows that its first
+    // four lanes own.
+    constexpr int kPieces = KV8 ? 8 : 16;
+    auto request = [&](off_t off, uint4 (&raw)[kLoads]) {
+        // (handed out by all lanes, before any choice between them: a lane that is switched off hands out zero)
+        const off_t at0 = row_lane<0>(off), at1 = row_lane<1>(off), at2 = row_lane<2>(off), at3 = row_lane<3>(off);
+        if constexpr (KV8) {
+            raw[0] = rows.load(n < 8 ? at0 : at1, (n & 7) * 16);
+            raw[1] = rows.load(n < 8 ? at2 : at3, (n & 7) * 16);
+        } else {
+            raw[0] = rows.load(at0, n * 16);
+            raw[1] = rows.load(at1, n * 16);
+            raw[2] = rows.load(at2, n * 16);
+            raw[3] = rows.load(at3, n * 16);
+        }
+    };
+    auto arrange = [&](uint4 *tile, uint4 (&raw)[kLoads]) {
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            const int r = 4 * kq + (KV8 ? 2 * i + (n >> 3) : i);
+            tile[r * kPieces + ((n ^ r) & (kPieces - 1))] = raw[i];           // piece c of row r at c ^ r
+        }
+        asm volatile("" ::: "memory");        // lanes read what other lanes of the wave wrote (LDS keeps the order)
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) raw[i] = tile[n * kPieces + (((i * 4 + kq) ^ n) & (kPieces - 1))];
+        asm volatile("" ::: "memory");
+    };
+    uint4 *staged = &sh_rows[SRC == 1 ? wv * 2 * 16 * kPieces : 0];           // two tiles
     // a tile's products -> the owners' scores (sL: against the column's query, or q_L; sR: against q_R).  i: the owner's
     // register; ix: the register that the owner in lane n ^ 8 wants
     auto owned = [&](const f32x4 c, int i, int ix, float &sL, float &sR) {
@@ -235,6 +299,12 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
     // scores of the lanes' rows at `off`
     auto score = [&](off_t off, float &sL, float &sR) {
         uint4 raw[NT][kLoads];
+        if constexpr (SRC == 1) {
+            request(off, raw[0]);
+            arrange(staged, raw[0]);
+            owned(decode_products<KV8, PARTS>(raw[0], q), n & 3, n & 3, sL, sR);
+            return;
+        }
 #pragma unroll
         for (int t = 0; t < NT; ++t) fetch(__shfl(off, (n >> 2) * 16 + 4 * t + (n & 3), 64), raw[t]);
 #pragma unroll
@@ -250,7 +320,18 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
     // left: the left key's score as a left branch; value: what the chunk score takes from this head
     float left = 0.f, value = 0.f, rL = 0.f, rR = 0.f;
     const bool has_right = half >= 1 && half < len;
-    {
+    if constexpr (SRC == 1) {
+        // both rows of a search on their way at once
+        const int mid = has_right ? base + half : -1;
+        const int slot0 = rows.src.slot_of(max(base, 0)), slot1 = rows.src.slot_of(max(mid, 0));
+        uint4 r0[kLoads], r1[kLoads];
+        request(rows.at(base, slot0), r0);
+        request(rows.at(mid, slot1), r1);
+        arrange(staged, r0);
+        arrange(staged + 16 * kPieces, r1);
+        owned(decode_products<KV8, PARTS>(r0, q), n & 3, n & 3, left, value);
+        owned(decode_products<KV8, PARTS>(r1, q), n & 3, n & 3, rL, rR);
+    } else {
         const off_t at0 = row_at(base), at1 = row_at(has_right ? base + half : base);
         if constexpr (G == 4) {
             // The first key of a chunk and of its right half are the same rows for all heads: one tile holds the first keys of the
@@ -269,11 +350,11 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
     if (has_right && rR > left) { off = half; left = rL; value = rR; }        // strict: tie keeps left
     for (half >>= 1; half >= 1; half >>= 1) {
         const bool ok = off + half < len;
-        score(row_at(ok ? start + off + half : base), rL, rR);
+        score(row_at(ok ? start + off + half : unread), rL, rR);
         if (ok && rR > left) { off += half; left = rL; value = rR; }
     }
 
-    if (a.out_rep != nullptr && j < a.max_chunks) {
+    if (a.out_rep != nullptr && owner && j < a.max_chunks) {
         const int64_t row = (int64_t)(pr.b * a.ge.Hq + pr.g * G + hd) * a.ge.Mq + pr.m;
         a.out_rep[row * a.max_chunks + j] = valid ? start + off : -1;
     }
@@ -282,7 +363,7 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
     if constexpr (G >= 2) best = fmaxf(best, dpp_f32<0xB1>(best));
     if constexpr (G >= 4) best = fmaxf(best, dpp_f32<0x4E>(best));
     if constexpr (G == 8) best = fmaxf(best, __shfl_xor(best, 16, 64));
-    if (hd == 0 && j < a.max_chunks) a.out_scores[(int64_t)p * a.max_chunks + j] = valid ? (KV8 ? best * a.k_scale : best) : -INFINITY;
+    if (owner && hd == 0 && j < a.max_chunks) a.out_scores[(int64_t)p * a.max_chunks + j] = valid ? (KV8 ? best * a.k_scale : best) : -INFINITY;
 }
 
 // Chunks of four keys: the search reads every row of a chunk anyway (all four unless the heads agree), so a tile is four
@@ -362,21 +443,22 @@ __global__ __launch_bounds__(256, !ROPE && !KV8 ? 5 : 1) void prune_decode_four_
     }
 }
 
-// b_q == 1, K through strides or pages
+// b_q == 1, K through strides or pages; SRC 1: behind the host tier, where chunks of four are searched too (only the rows that
+// the search reads may be noted as touched)
 template <int G, bool ROPE, int SRC, bool KV8, bool NARROW>
 static void launch_decode_tile_n(PruneArgs a, const RopeView &rope, int P, hipStream_t st)
 {
-    const int per_wg = decode_tile_chunks(G, a.chunk, ROPE, KV8) * kDecodeTileWaves;
+    const int per_wg = (SRC == 1 ? decode_search_tiles(SRC) * 16 / G : decode_tile_chunks(G, a.chunk, ROPE, KV8)) * kDecodeTileWaves;
     const int per_problem = (a.max_chunks + per_wg - 1) / per_wg;
-    a.grid = decode_grid(a.ge, per_problem, false);
+    a.grid = decode_grid(a.ge, per_problem, SRC == 1);
     const dim3 grid = a.grid.dims(P, per_problem), block(64 * kDecodeTileWaves);
     KernelTimer timer(stage_name(kNamePruneDecode, a.parent_starts == nullptr, a.chunk), st);
     // contiguous bf16 rows without RoPE: only chunks of four with eight heads come here (decode_on_tiles)
     constexpr bool kPlain = !ROPE && SRC == 0 && !KV8;
-    if constexpr (!kPlain || G == 8)
+    if constexpr (SRC != 1 && (!kPlain || G == 8))
         if (a.chunk == 4) hipLaunchKernelGGL((prune_decode_four_kernel<G, ROPE, SRC, KV8, NARROW>), grid, block, 0, st, a, rope);
     if constexpr (!kPlain)
-        if (a.chunk != 4) hipLaunchKernelGGL((prune_decode_tile_kernel<G, ROPE, SRC, KV8, NARROW>), grid, block, 0, st, a, rope);
+        if (SRC == 1 || a.chunk != 4) hipLaunchKernelGGL((prune_decode_tile_kernel<G, ROPE, SRC, KV8, NARROW>), grid, block, 0, st, a, rope);
 }
 
 template <bool ROPE, int SRC, bool KV8, bool NARROW>
@@ -384,6 +466,17 @@ static void launch_decode_tile_g(const PruneArgs &a, const RopeView &rope, int P
 {
     if (a.ge.G == 4) launch_decode_tile_n<4, ROPE, SRC, KV8, NARROW>(a, rope, P, st);
     else launch_decode_tile_n<8, ROPE, SRC, KV8, NARROW>(a, rope, P, st);
+}
+
+template <bool ROPE, bool KV8>
+static void launch_decode_tile_cached(const PruneArgs &a, const RopeView &rope, int P, hipStream_t st)
+{
+    switch (a.ge.G) {
+    case 1: launch_decode_tile_n<1, ROPE, 1, KV8, false>(a, rope, P, st); break;
+    case 2: launch_decode_tile_n<2, ROPE, 1, KV8, false>(a, rope, P, st); break;
+    case 4: launch_decode_tile_n<4, ROPE, 1, KV8, false>(a, rope, P, st); break;
+    default: launch_decode_tile_n<8, ROPE, 1, KV8, false>(a, rope, P, st); break;
+    }
 }
 
 template <bool ROPE, bool KV8>

@@ -13,4 +13,14 @@ void launch_prune_decode_tile(const PruneArgs &a, int P, bool fp8, const RopeVie
     else launch_decode_tile<false, false>(a, none, P, max_seq_len, st);
 }
 
+// any group size, K behind the host tier
+void launch_prune_decode_tile_cached(const PruneArgs &a, int P, bool fp8, const RopeView *rope, hipStream_t st)
+{
+    const RopeView none{nullptr, nullptr, 0};
+    if (rope && fp8) launch_decode_tile_cached<true, true>(a, *rope, P, st);
+    else if (rope) launch_decode_tile_cached<true, false>(a, *rope, P, st);
+    else if (fp8) launch_decode_tile_cached<false, true>(a, none, P, st);
+    else launch_decode_tile_cached<false, false>(a, none, P, st);
+}
+
 }  // namespace ihip

@@ -233,12 +233,14 @@ static void launch_decode(const PruneArgs &a, int P, bool fp8, hipStream_t st)
 }
 
 void launch_prune_decode_tile(const PruneArgs &a, int P, bool fp8, const RopeView *rope, int64_t max_seq_len, hipStream_t st);
+void launch_prune_decode_tile_cached(const PruneArgs &a, int P, bool fp8, const RopeView *rope, hipStream_t st);
 void launch_prune_decode_nest(const PruneArgs &a, const NestArgs &nest, int P, bool fp8, const RopeView *rope, int64_t max_seq_len, hipStream_t st);
 int32_t launch_prune_stage_rope(const PruneArgs &a, const RopeView &rope, int style, int P, bool fp8, hipStream_t st);
 void launch_prune_prefill_fp8(const PruneArgs &a, int P, int b_q, const RopeView *rope, int style, hipStream_t st);
 
-// Which decode stages (K through strides or pages; no RoPE or the relative style) go to the matrix-core kernels of
-// prune_decode_tile.h.  Their waves do a fifth of the vector instructions for 64 searches at a time, but a level of
+// Which decode stages (no RoPE or the relative style) go to the matrix-core kernels of
+// prune_decode_tile.h.  The lines are those of K through strides or pages; the host tier, whose link is the bound, follows
+// contiguous rows, so that its scores are the same bits.  Their waves do a fifth of the vector instructions for 64 searches at a time, but a level of
 // theirs is a longer chain, their loads take 64 bytes of 16 rows where the vector kernels take whole rows, and their
 // workgroups are a quarter (4 heads) or half as many: they win where instructions are the bound (128-byte rows, two rotated
 // queries, page lookups, 8 heads) and workgroups are no longer scarce, so the lines are drawn in workgroups of theirs per compute
@@ -280,11 +282,12 @@ static bool decode_on_tiles(const PruneArgs &a, int P, bool fp8, bool relative)
     return (at_least(0.75) && at_most(1)) || at_least(2.5);                       // 0.94-1.09, 1.02-1.16; between them 0.89-1.05, 0.93-1.26
 }
 
-// nest: score this decode stage and the ones after it together (no host tier, no chunk-indexed style)
+// nest: score this decode stage and the ones after it together (no host tier, no chunk-indexed style).  like_nest: the host tier's stage of
+// a plan that contiguous rows in device memory would be scored for that way: on the matrix cores, for the same bits.
 int32_t launch_prune_stage(const ihip_shape &s, const ihip_tensor &q, const ihip_tensor &k,
                            const int32_t *parent_starts, int n_parent, int parent_chunk, int chunk,
                            int max_chunks, float *out_scores, int32_t *out_rep, const BankView *bank,
-                           const ihip_rope *rope, hipStream_t st, const KvFormat *fmt, const NestArgs *nest)
+                           const ihip_rope *rope, hipStream_t st, const KvFormat *fmt, const NestArgs *nest, bool like_nest)
 {
     PruneArgs a;
     const bool fp8 = fmt && fmt->fp8;
@@ -327,8 +330,9 @@ int32_t launch_prune_stage(const ihip_shape &s, const ihip_tensor &q, const ihip
             launch_prune_decode_nest(a, *nest, P, fp8, &rope_view, s.max_seq_len, st);
             return check_launch("prune_stage (decode, several stages, relative RoPE)");
         }
-        if (s.b_q == 1 && style == IHIP_ROPE_RELATIVE && !bank && decode_on_tiles(a, P, fp8, true)) {
-            launch_prune_decode_tile(a, P, fp8, &rope_view, s.max_seq_len, st);
+        if (s.b_q == 1 && style == IHIP_ROPE_RELATIVE && (like_nest || decode_on_tiles(a, P, fp8, true))) {
+            if (bank) launch_prune_decode_tile_cached(a, P, fp8, &rope_view, st);
+            else launch_prune_decode_tile(a, P, fp8, &rope_view, s.max_seq_len, st);
             return check_launch("prune_stage (decode, relative RoPE)");
         }
         if (s.b_q == 1) return launch_prune_stage_rope(a, rope_view, style, P, fp8, st);
@@ -338,8 +342,9 @@ int32_t launch_prune_stage(const ihip_shape &s, const ihip_tensor &q, const ihip
         launch_prune_decode_nest(a, *nest, P, fp8, nullptr, s.max_seq_len, st);
         return check_launch("prune_stage (decode, several stages)");
     }
-    if (s.b_q == 1 && !bank && decode_on_tiles(a, P, fp8, false)) {
-        launch_prune_decode_tile(a, P, fp8, nullptr, s.max_seq_len, st);
+    if (s.b_q == 1 && (like_nest || decode_on_tiles(a, P, fp8, false))) {
+        if (bank) launch_prune_decode_tile_cached(a, P, fp8, nullptr, st);
+        else launch_prune_decode_tile(a, P, fp8, nullptr, s.max_seq_len, st);
         return check_launch("prune_stage (decode)");
     }
     if (s.b_q == 1) {

@@ -355,3 +355,75 @@ def test_paged_host_tier_equals_resident_and_follows_lru(ihip, orc, page, fp8):
                 assert pt.tolist() == sim[bank].page_table and sb.tolist() == sim[bank].slot_block, (call, name)
     finally:
         cache.close()
+
+
+def rounding_rows(shape, fp8, g):
+    """Rows that are permutations of one another inside the halves of the dims, against queries (`rounding_query`) that are constant
+    there: all scores are equal but for the rounding of their sums, which alone decides every search and every selection."""
+    n = 1
+    for x in shape[:-1]:
+        n *= x
+    half = lambda: torch.randn(64, generator=g) * 2.0 ** torch.randint(-6, 7, (64,), generator=g)  # noqa: E731
+    parts = [v[torch.rand((n, 64), generator=g).argsort(1)] for v in (half(), half())]
+    rows = torch.cat(parts, 1).view(shape)
+    return rows.clamp(-448, 448).to(torch.float8_e4m3fn).view(torch.uint8) if fp8 else rows.bfloat16()
+
+
+def rounding_query(shape):
+    q = torch.ones(shape)
+    q[..., 64:] = 2.0 ** -11
+    q[:, 1::2] *= -1
+    return q.bfloat16()
+
+
+@pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
+@pytest.mark.parametrize("relative", [False, True], ids=["plain", "relative"])
+@pytest.mark.parametrize("Hq,Hkv", [(4, 4), (4, 2), (8, 2), (16, 2)])
+def test_scores_are_rounded_as_on_the_resident_path(ihip, Hq, Hkv, relative, fp8):
+    """Layers whose resident call scores all stages in one pass, and one (T = 40,000) that does not."""
+    g = torch.Generator().manual_seed(Hq)
+    scales = (0.5, 0.25) if fp8 else None
+    for lens, stages in (([4099, 2000], ((64, 30), (16, 40), (4, 60))), ([3001, 3001], ((256, 5), (32, 17), (8, 33), (4, 50))),
+                         ([40000, 39001], ((64, 300), (4, 200)))):
+        T = max(lens)
+        q = rounding_query((2, Hq, 1, 128)).cuda()
+        k, v = rounding_rows((2, Hkv, T, 128), fp8, g), rounding_rows((2, Hkv, T, 128), fp8, g)
+        rope = ihip.Rope(torch.ones(T, 64).cuda(), torch.zeros(T, 64).cuda(), ihip.ROPE_RELATIVE, ihip.ROPE_NONE) if relative else None
+        chunks, keeps = [s[0] for s in stages], [s[1] for s in stages]
+        cache = ihip.HostKVCache(k.pin_memory(), v.pin_memory(), 64, 100, 50)
+        try:
+            kd, vd = k.cuda(), v.cuda()
+            L = ihip.Layer(q, kd, torch.tensor(lens, dtype=torch.int32, device="cuda"), 1, 64, 256)
+            want_lists, got_lists = L.mask_state(keeps), L.mask_state(keeps)
+            kw = dict(rope=rope, kv_scales=scales, pooling=ihip.POOL_KV_HEAD, first_stage=0)
+            want = L.decode_layer(q, kd, vd, chunks, keeps, stage_starts=want_lists, **kw)
+            for _ in range(2):                       # from host memory, then partly from the banks
+                got = L.decode_layer(q, None, None, chunks, keeps, stage_starts=got_lists, cache=cache, **kw)
+                cache.update()
+                assert torch.equal(got_lists, want_lists) and torch.equal(got, want), stages
+        finally:
+            cache.close()
+
+
+@pytest.mark.parametrize("fp8,relative", [(True, False), (False, True), (False, False)], ids=["fp8", "relative", "plain"])
+@pytest.mark.parametrize("Hq,Hkv", [(8, 2), (16, 2)])
+def test_stage_scores_are_rounded_as_on_the_resident_path(ihip, Hq, Hkv, fp8, relative):
+    """Single stages, few chunks and so many that the resident ones go to the matrix cores."""
+    g = torch.Generator().manual_seed(7)
+    T = 150000
+    q = rounding_query((1, Hq, 1, 128)).cuda()
+    k = rounding_rows((1, Hkv, T, 128), fp8, g)
+    rope = ihip.Rope(torch.ones(2048, 64).cuda(), torch.zeros(2048, 64).cuda(), ihip.ROPE_RELATIVE, ihip.ROPE_NONE) if relative else None
+    cache = ihip.HostKVCache(k.pin_memory(), k.pin_memory(), 64, 500, 50)
+    try:
+        kd = k.cuda()
+        L = ihip.Layer(q, kd, torch.tensor([T - 13], dtype=torch.int32, device="cuda"), 1, 100, 256)
+        parents = 100 + 64 * torch.arange(0, 2300, 3, dtype=torch.int32, device="cuda").repeat(Hkv, 1)
+        for chunk in (1, 4, 16, 64, 256):
+            for p in (None, parents) if chunk < 64 else (None,):
+                want, want_rep = L.prune_stage(q, kd, chunk, p, 64 if p is not None else 0, want_rep=True, rope=rope, k_scale=0.5 if fp8 else None)
+                got, got_rep = ihip.prune_stage_cached(L, q, cache, chunk, p, 64 if p is not None else 0, want_rep=True, rope=rope,
+                                                       k_scale=0.5 if fp8 else 1.0)
+                assert torch.equal(got, want) and torch.equal(got_rep, want_rep), (chunk, p is not None)
+    finally:
+        cache.close()
