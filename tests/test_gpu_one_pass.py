@@ -1,7 +1,9 @@
 """Decode plans whose stages are scored in one pass over the middle range (prune_decode_nest.h, select_chain.hip) against the
 stage-by-stage kernels.  The same call takes the one or the other by its workspace: the scores of the one pass come last, and a
-byte less than ihip_workspace_bytes says leaves no room for them.  Inputs are small whole numbers (and quarter turns), so every
-score is exact in both and the lists and outputs have to be the same bits, ties included."""
+byte less than ihip_workspace_bytes says leaves no room for them.  Inputs are whole numbers (and quarter turns), so every
+score is exact in both and the lists and outputs have to be the same bits, ties included.  With N(0,1) inputs the list is
+compared with an exact selection among the scores that the one pass left in its workspace."""
+import numpy as np
 import pytest
 import torch
 
@@ -15,6 +17,18 @@ def ihip():
     import paper_2502_08910_amd as pkg
     pkg.lib()
     return pkg
+
+
+def _kernels(ihip, run):
+    """Launches of the pruning and of the selection kernels in one call."""
+    ihip.profile_read()
+    ihip.profile_enable(True)
+    try:
+        run()
+    finally:
+        ihip.profile_enable(False)
+    launches = {name: n for name, (_, n) in ihip.profile_read().items()}
+    return tuple(sum(n for name, n in launches.items() if name.startswith(kind)) for kind in ("prune_decode", "select_blocks"))
 
 
 def _case(ihip, Hq, Hkv, lens, stages, fmt, rope, spread=3, n_sink=64, n_stream=256, pooling=None, seed=0):
@@ -53,15 +67,13 @@ def _case(ihip, Hq, Hkv, lens, stages, fmt, rope, spread=3, n_sink=64, n_stream=
     L = ihip.Layer(q, shape, torch.tensor(lens, dtype=torch.int32, device="cuda"), 1, n_sink, n_stream)
     need = L.workspace_bytes(ihip.OP_DECODE_LAYER, chunks, keeps)
     got = []
-    for size in (need, need - 1):
+    for size, launches in ((need, (1, 1)), (need - 1, (len(stages), len(stages)))):
         ws = torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda")
         blocks = torch.empty((L.P, keeps[-1]), dtype=torch.int32, device="cuda")
         lse = torch.empty((B, Hq), dtype=torch.float32, device="cuda")
-        out = L.decode_layer(q, k, v, chunks, keeps, ws=ws, out_blocks=blocks, lse=lse, **kw)
-        torch.cuda.synchronize()
-        # the tail of the workspace says which way the call went
-        got.append((out.cpu(), lse.cpu(), blocks.cpu(), bool((ws[-256:] == 0xA5).all()) if size == need else None))
-    assert not got[0][3], "the plan was not scored in one pass"
+        out = torch.empty((B, Hq, 1, D), dtype=torch.bfloat16, device="cuda")
+        assert _kernels(ihip, lambda: L.decode_layer(q, k, v, chunks, keeps, ws=ws, out=out, out_blocks=blocks, lse=lse, **kw)) == launches
+        got.append((out.cpu(), lse.cpu(), blocks.cpu()))
     assert torch.equal(got[0][2], got[1][2])
     assert torch.equal(got[0][0].view(torch.int16), got[1][0].view(torch.int16)) and torch.equal(got[0][1], got[1][1])
     return got[0][2]
@@ -79,7 +91,7 @@ def test_storage_rope_and_groups(ihip, Hq, Hkv, fmt, rope):
 
 @pytest.mark.parametrize("stages", [
     ((256, 5), (16, 30), (4, 60)), ((128, 9), (32, 17), (8, 33)), ((32, 50), (4, 100)), ((16, 64), (8, 65)), ((8, 200), (4, 200)),
-    ((256, 6), (64, 12), (16, 24), (4, 48)), ((64, 2048), (16, 1024), (4, 2048)), ((64, 1), (4, 1)),
+    ((256, 6), (64, 12), (16, 24), (4, 48)), ((64, 512), (16, 512), (4, 512)), ((64, 1), (4, 1)),
 ], ids=lambda s: "-".join("%d:%d" % x for x in s))
 @pytest.mark.parametrize("T", [4099, 5000, 400])
 def test_plans_and_lengths(ihip, stages, T):
@@ -105,6 +117,59 @@ def test_heavy_ties(ihip):
     """All scores equal (more candidates in one bin than threads): the lowest positions are kept."""
     blocks = _case(ihip, 8, 2, [9000], ((8, 800), (4, 900)), "bf16", False, spread=0)
     assert torch.equal(blocks[0], 64 + 4 * torch.arange(900, dtype=torch.int32))
+
+
+# candidates of a selection on either side of the steps from one to two and four per thread, and the most of the two (2,048)
+SIZES = [(1, 512, ((8, 256), (4, 200))), (2, 513, ((8, 257), (4, 200))), (3, 1024, ((8, 512), (4, 300))), (4, 1025, ((8, 513), (4, 300))),
+         (5, 1500, ((8, 750), (4, 1001))), (6, 2048, ((8, 1024), (4, 700))), (7, 600, ((64, 512), (16, 512), (4, 512))), (8, 375, ((16, 375), (4, 1400)))]
+
+
+def _length(n_slots, stages):                    # the middle range ends inside its last chunk
+    return 64 + 256 + (n_slots - 1) * stages[0][0] + stages[0][0] // 2 + 1
+
+
+@pytest.mark.parametrize("seed,n_slots,stages", SIZES, ids=lambda x: None if isinstance(x, tuple) else str(x))
+def test_selection_sizes(ihip, seed, n_slots, stages):
+    """Scores that hardly ever tie: whole numbers up to 100 in the inputs, exact sums far below 2^24."""
+    _case(ihip, 8, 2, [_length(n_slots, stages)], stages, "bf16", False, spread=100, seed=seed)
+
+
+@pytest.mark.parametrize("seed,n_slots,stages", SIZES + [(9, 300, ((64, 64), (16, 128), (4, 128)))],
+                         ids=lambda x: None if isinstance(x, tuple) else str(x))
+@pytest.mark.parametrize("G", [4, 8])
+def test_lists_are_the_best_of_the_scores(ihip, G, seed, n_slots, stages):
+    """N(0,1) inputs, two sequences of unlike lengths: the list is the exact choice, stage by stage, among the scores of the pass."""
+    n_sink, n_stream, Hkv = 64, 256, 2
+    lens = [_length(n_slots, stages), max(400, _length(n_slots, stages) * 5 // 8)]
+    g = torch.Generator().manual_seed(seed)
+    q = torch.randn((2, Hkv * G, 1, 128), generator=g).bfloat16().cuda()
+    k, v = (torch.randn((2, Hkv, lens[0], 128), generator=g).bfloat16().cuda() for _ in range(2))
+    chunks, keeps = [s[0] for s in stages], [s[1] for s in stages]
+    L = ihip.Layer(q, k, torch.tensor(lens, dtype=torch.int32, device="cuda"), 1, n_sink, n_stream)
+    ws = torch.full((L.workspace_bytes(ihip.OP_DECODE_LAYER, chunks, keeps),), 0xA5, dtype=torch.uint8, device="cuda")
+    blocks = torch.empty((L.P, keeps[-1]), dtype=torch.int32, device="cuda")
+    assert _kernels(ihip, lambda: L.decode_layer(q, k, v, chunks, keeps, ws=ws, out_blocks=blocks)) == (1, 1)
+    # the scores come last: a problem's stages one after the other, each rounded up to 64
+    n = [n_slots * (chunks[0] // c) for c in chunks]
+    stride = sum((x + 63) // 64 * 64 for x in n)
+    nbytes = L.P * stride * 4
+    at = ws.numel() - (nbytes + 255) // 256 * 256
+    scores = ws[at:at + nbytes].view(torch.float32).view(L.P, stride).cpu().numpy()
+    for p in range(L.P):
+        kept, first, lo = None, 0, n_sink
+        hi = lens[p // Hkv] - n_stream
+        for i, (c, keep) in enumerate(stages):
+            ratio = chunks[i - 1] // c if i else 1
+            cand = np.arange(n[0]) if i == 0 else (kept[:, None] * ratio + np.arange(ratio)).ravel()
+            s = scores[p, first + cand]
+            there = lo + cand * c < hi
+            assert np.isfinite(s[there]).all() and (s[~there] == -np.inf).all()
+            cand, s = cand[there], s[there]
+            kept = np.sort(cand[np.lexsort((cand, -s))[:keep]])
+            first += (n[i] + 63) // 64 * 64
+        want = np.full(keeps[-1], -1)
+        want[:len(kept)] = lo + kept * chunks[-1]
+        assert (blocks[p].cpu().numpy() == want).all(), p
 
 
 def test_several_single_query_blocks(ihip):
