@@ -13,7 +13,7 @@ constexpr int kChainMaxKeep = 2048;
 struct ChainPlan {
     int n_stages;
     int pool;                             // 1, or Hkv: one selection for all KV heads of a sequence (scores max-pooled)
-    const float *scores;                  // [P][stride]: per stage the the scores of all chunks of the middle range
+    const float *scores;                  // [P][stride]: per stage the scores of all chunks of the middle range
     int stride;
     int at[kChainMaxStages];              // where a stage's scores begin, multiples of 64
     // per stage: where the list goes, scores, children per parent, chunk size, most kept

@@ -21,15 +21,16 @@ struct ChainArgs {
 };
 
 constexpr int kChainBins = 512;            // eight per lane
+// One sequence of 8K keys, a layer (us): 512 threads 24.2, 256 24.8, 1024 26.4
+constexpr int kChainThreads = 512;
 
-template <int NT>
 struct ChainShared {
     float score[kChainMaxScores];
     int32_t index[2][kChainMaxKeep];          // what a stage kept: slots in its score row, which is the middle range in order
     uint32_t hist[kChainMaxStages][kChainBins];
-    uint2 cand[NT];                           // key and candidate
-    uint32_t ncand[kChainMaxStages], total[NT / 64];
-    SelectScratch<NT> scratch;
+    uint2 cand[kChainThreads];                           // key and candidate
+    uint32_t ncand[kChainMaxStages], total[kChainThreads / 64];
+    SelectScratch<kChainThreads> scratch;
 };
 
 // Monotone map fp32 -> u32 (larger float <=> larger key); -0.0 maps with +0.0.
@@ -40,10 +41,10 @@ __device__ inline uint32_t chain_key(float f)
 }
 
 // Selects stage s of the chain from n candidates, children of the n_from chunks that the stage before it kept.  -> how many are kept
-template <int NT, int ITEMS>
-__device__ inline int chain_stage(const ChainPlan &c, int s, int n, int n_from, const float *score, float low, float scale, ChainShared<NT> &sh)
+template <int ITEMS>
+__device__ inline int chain_stage(const ChainPlan &c, int s, int n, int n_from, const float *score, float low, float scale, ChainShared &sh)
 {
-    constexpr int kWaves = NT / 64;
+    constexpr int NT = kChainThreads, kWaves = NT / 64;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int32_t *from_index = sh.index[(s & 1) ^ 1];
     int32_t *to_index = sh.index[s & 1];
@@ -134,10 +135,10 @@ __device__ inline int chain_stage(const ChainPlan &c, int s, int n, int n_from, 
     return keep;
 }
 
-template <int NT>
-__global__ __launch_bounds__(NT) void select_chain_kernel(const ChainArgs args)
+__global__ __launch_bounds__(kChainThreads) void select_chain_kernel(const ChainArgs args)
 {
-    __shared__ ChainShared<NT> sh;
+    constexpr int NT = kChainThreads;
+    __shared__ ChainShared sh;
     const Geometry &ge = args.ge;
     const ChainPlan &c = args.plan;
     const int p0 = c.pool > 1 ? blockIdx.x * ge.Hkv : blockIdx.x;      // the first problem of a pooled set; decode: one block per sequence
@@ -177,9 +178,9 @@ __global__ __launch_bounds__(NT) void select_chain_kernel(const ChainArgs args)
         const float *score = sh.score + c.at[s];
         const float lo = s == 0 ? low[0] : s == 1 ? low[1] : s == 2 ? low[2] : low[3];
         const float sc = s == 0 ? scale[0] : s == 1 ? scale[1] : s == 2 ? scale[2] : scale[3];
-        if (n <= NT) kept = chain_stage<NT, 1>(c, s, n, kept, score, lo, sc, sh);
-        else if (n <= 2 * NT) kept = chain_stage<NT, 2>(c, s, n, kept, score, lo, sc, sh);
-        else kept = chain_stage<NT, 4>(c, s, n, kept, score, lo, sc, sh);
+        if (n <= NT) kept = chain_stage<1>(c, s, n, kept, score, lo, sc, sh);
+        else if (n <= 2 * NT) kept = chain_stage<2>(c, s, n, kept, score, lo, sc, sh);
+        else kept = chain_stage<4>(c, s, n, kept, score, lo, sc, sh);
         for (int g = 0; g < c.pool; ++g) {
             int32_t *out = c.out[s] + (int64_t)(p0 + g) * c.keep[s];
             for (int i = tid; i < c.keep[s]; i += NT) out[i] = i < kept ? pr.lo + sh.index[s & 1][i] * c.chunk[s] : -1;
@@ -192,8 +193,7 @@ int32_t launch_select_chain(const ihip_shape &s, const ChainPlan &plan, hipStrea
     const int P = s.B * (plan.pool > 1 ? 1 : s.Hkv);
     KernelTimer timer(stage_name(kNameSelect, true, plan.chunk[0]), st);
     const ChainArgs args{make_geometry(s), plan};
-    // 512 threads for every plan (one sequence of 8K keys 24.2 us a layer, 256 threads 24.8)
-    hipLaunchKernelGGL(select_chain_kernel<512>, dim3(P), dim3(512), 0, st, args);
+    hipLaunchKernelGGL(select_chain_kernel, dim3(P), dim3(kChainThreads), 0, st, args);
     return check_launch("select_blocks (several stages)");
 }
 
