@@ -264,29 +264,51 @@ static size_t nest_scores_per_problem(const ihip_shape &s, int n_stages, const i
     return scores <= kChainMaxScores ? (size_t)scores : 0;
 }
 
-// Where one pass over all keys is the faster way.  It saves some 9 us of launches and latencies (more where the searches are
-// bound by instructions: E4M3 rows, RoPE, pages), and costs the keys that the stage-by-stage way does not read: all
-// but about 0.7 of the rows that the later stages' searches touch, at some 5.5 TB/s.  Stage by stage / in one pass (us) around the
-// lines, bf16 rows, 8 heads: 1 sequence of 24K keys 41.1 / 35.3, of 32K 41.5 / 38.9, 4 of 8K 54.0 / 45.3, of 16K 55.5 / 58.1,
-// 16 of 8K 117 / 108, of 16K 137 / 176; pages and RoPE 4 of 16K 72.0 / 69.2; E4M3 rows 4 of 16K 53.2 / 46.6, with pages and RoPE
-// 66.9 / 58.6, 16 of 16K 150.5 / 148.8.  Beyond some 400 MB of bf16 rows even short sequences gain nothing (32 of 8K 208.9 / 211.7).
-static bool nest_pays(const ihip_shape &s, int n_stages, const int32_t *chunks, const int32_t *keeps, bool fp8, bool heavy)
+// Rows that the halving searches of G heads read in a chunk of l keys: at a level with n midpoints each head takes one of them
+static double search_rows(int l, int G)
 {
-    const int64_t slots = stage1_slots(s, chunks[0]);
-    double later = 0;                         // rows that the later stages' searches touch, about 3.2 per level beyond the first
-    int64_t n = slots;
-    for (int i = 1; i < n_stages; ++i) {
-        n = std::min<int64_t>(keeps[i - 1], n) * (chunks[i - 1] / chunks[i]);
-        later += (double)n * std::min<double>(chunks[i], 2 + 3.2 * (__builtin_ctz(chunks[i]) - 1));
+    double rows = 1;
+    for (int n = 1; 2 * n <= l; n *= 2) {
+        double none = 1.0 - 1.0 / n;          // that a midpoint is not head 1's, ..., not one of G heads'
+        for (int g = 1; g < G; g *= 2) none *= none;
+        rows += n * (1 - none);
     }
-    const double keys = (double)slots * chunks[0], row = fp8 ? 128 : 256, mega = 1.0 / (1 << 20), all = (double)s.B * s.Hkv * row * mega;
-    return all * keys <= 400 && all * (keys - 0.7 * later) <= (fp8 ? 120 : heavy ? 70 : 42);
+    return rows;
 }
 
+// Where one pass over all keys is the faster way.  It saves some 6 us of launches and chains of latencies a stage after the first, and the
+// rows that the searches read; it costs all keys: us, and us a megabyte.  Fitted to 7,600 pairs of measurements (8 KV heads, 1 to 8 heads a
+// group, 2 to 4 stages, 3K to 64K keys in batches of 1 to 64, every storage, rows that the caches hold and rows that they do not, 256
+// CUs).  Of 5,740 plans that it sends here 103 lose more than 2 % (worst 1.12), of the others 129 would gain more than 2 % (best 1.17); a
+// line that knew neither heads nor stages sent 450 more here that lost (one head a group, two stages, E4M3 with RoPE: 1.43) and kept 430 away that
+// gain (1.73).  Stage by stage / in one pass (us), three stages, 8 KV heads: 32 heads, bf16 rows, one sequence of 32K keys 38.6 / 32.3, of
+// 48K 39.2 / 37.4, 4 of 16K 46.3 / 45.9, 16 of 8K 79.0 / 80.3; one head a group, E4M3 with RoPE, one of 16K 36.8 / 38.2, 16 of 8K 53.0 /
+// 60.4.  Nothing beyond 400 MB of rows was measured.
+static bool nest_pays(const ihip_shape &s, int n_stages, const int32_t *chunks, const int32_t *keeps, bool fp8, bool rope, bool paged)
+{
+    const int G = s.Hq / s.Hkv;
+    int64_t n = stage1_slots(s, chunks[0]);
+    const double keys = (double)n * chunks[0];
+    double searched = n * search_rows(chunks[0], G);
+    for (int i = 1; i < n_stages; ++i) {
+        n = std::min<int64_t>(keeps[i - 1], n) * (chunks[i - 1] / chunks[i]);
+        searched += n * search_rows(chunks[i], G);
+    }
+    const double mb = (double)s.B * s.Hkv * (fp8 ? 128 : 256) / (1 << 20);      // a key of all problems
+    const double saved = (paged ? 6.7 : 6.0) * (n_stages - 1) - 1.5 - 1.0 * rope + 1.2 * paged;
+    const double key = fp8 ? 0.17 + 0.07 * rope + 0.01 * paged : 0.165 + 0.01 * rope + 0.02 * paged;
+    const double row = fp8 ? 0.205 + 0.1 * rope : 0.135 + 0.007 * G + 0.015 * rope + 0.03 * paged;
+    return mb * keys <= 400 && saved > mb * (key * keys - row * searched);
+}
+
+// Scores of all stages taken together, whatever the storage and style are
 static size_t nest_bytes(const ihip_shape &s, int n_stages, const int32_t *chunks, const int32_t *keeps)
 {
     const size_t scores = nest_scores_per_problem(s, n_stages, chunks, keeps);
-    return scores && nest_pays(s, n_stages, chunks, keeps, true, true) ? align256((size_t)s.B * s.Hkv * scores * sizeof(float)) : 0;
+    if (scores == 0) return 0;
+    for (int v = 0; v < 8; ++v)
+        if (nest_pays(s, n_stages, chunks, keeps, v & 1, v & 2, v & 4)) return align256((size_t)s.B * s.Hkv * scores * sizeof(float));
+    return 0;
 }
 
 // Scratch of a decode layer.  The scores of all stages taken together come last and are left out where a plan fits the
@@ -317,7 +339,7 @@ static int32_t prune_stages_impl(const ihip_shape &s, const ihip_tensor &q, cons
     const uint32_t every = (1u << n_stages) - 1u;
     const bool relative = rope && rope->prune_style == IHIP_ROPE_RELATIVE, paged = fmt && fmt->paged.block_table;
     const bool together = nest && (due & every) == every && !(rope && rope->prune_style == IHIP_ROPE_CHUNK_INDEXED) &&
-                          nest_pays(s, n_stages, chunks, keeps, fmt && fmt->fp8, relative || paged);
+                          nest_pays(s, n_stages, chunks, keeps, fmt && fmt->fp8, relative, paged);
     if (together && nest_scores && !bank) {
         const int slots = stage1_slots(s, chunks[0]);
         NestArgs args{};

@@ -6,8 +6,8 @@
 // before the other's selection is known: every key is read once, in order, and all levels follow from the
 // keys' scores in the registers.  Keys of parts that the selections drop are read for nothing; what it saves is a chain:
 // log2(l) row latencies per stage become one, and all launches but one and all selections' but one (select_chain.hip) go.
-// Layers of three stages, 32 heads on 8, stage by stage / in one pass (us): one sequence of 4K bf16 keys 38.4 / 27.9, 8K
-// 38.8 / 28.8, 32K 41.5 / 38.9, 16 of 4K 100 / 79; E4M3 pages with RoPE 4K 44.8 / 30.2, 32K 50.1 / 41.3, 16 of 8K 117 / 98.
+// Layers of three stages, 32 heads on 8, stage by stage / in one pass (us): one sequence of 4K bf16 keys 35.5 / 23.2, 8K
+// 37.2 / 24.0, 32K 38.6 / 32.3, 16 of 4K 69.5 / 56.7; E4M3 pages with RoPE 4K 41.0 / 25.3, 32K 45.5 / 34.8, 16 of 8K 83.2 / 76.5.
 //
 // Arithmetic as in prune_decode_tile.h: 16 keys x 16 query columns on the matrix cores; column n is head n % G (relative style:
 // columns 0..7 against q_L, 8..15 against q_R, exchanged by a row rotation), and the lane (n, kq) holds keys 4*kq..+3

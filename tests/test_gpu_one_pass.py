@@ -182,3 +182,29 @@ def test_several_single_query_blocks(ihip):
     for t in range(3):
         one = q[:, :, t:t + 1].contiguous()
         assert torch.equal(got[:, :, t], layer(one, 2 - t).prune_all(one, k, chunks, keeps).view(2, 2, -1)), t
+
+
+@pytest.mark.parametrize("Hq,Hkv,B,T,fmt,rope,stages,one_pass", [
+    (32, 8, 1, 32768, "bf16", False, ((64, 64), (16, 64), (4, 128)), True),
+    (8, 8, 1, 32768, "bf16", False, ((32, 50), (4, 100)), False),          # two stages, one head a group: the searches read few rows
+    (8, 8, 4, 16384, "fp8", True, ((32, 50), (4, 100)), False),
+    (64, 8, 4, 16384, "fp8", True, ((64, 96), (8, 200)), True),            # eight heads: they read most of them
+    (32, 8, 2, 131072, "bf16", False, ((64, 64), (16, 64), (4, 128)), False),
+], ids=["4-heads", "1-head", "1-head-fp8-rope", "8-heads-fp8-rope", "long"])
+def test_which_plans_go_in_one_pass(ihip, Hq, Hkv, B, T, fmt, rope, stages, one_pass):
+    """Either way the lists of a batch of equal sequences are equal."""
+    g = torch.Generator(device="cuda").manual_seed(2)
+    q = torch.randn((1, Hq, 1, 128), generator=g, device="cuda").bfloat16().expand(B, -1, -1, -1).contiguous()
+    k = torch.randn((1, Hkv, T, 128), generator=g, device="cuda").bfloat16()
+    kw = {}
+    if fmt == "fp8":
+        k, kw["kv_scales"] = k.to(torch.float8_e4m3fn).view(torch.uint8), (1.0, 1.0)
+    k = k.expand(B, -1, -1, -1).contiguous()
+    if rope:
+        kw["rope"] = ihip.Rope(torch.ones(4096, 64).cuda(), torch.zeros(4096, 64).cuda(), ihip.ROPE_RELATIVE, ihip.ROPE_STREAMING)
+    chunks, keeps = [s[0] for s in stages], [s[1] for s in stages]
+    L = ihip.Layer(q, k, torch.full((B,), T, dtype=torch.int32, device="cuda"), 1, 128, 1024)
+    blocks = torch.empty((L.P, keeps[-1]), dtype=torch.int32, device="cuda")
+    n = 1 if one_pass else len(stages)
+    assert _kernels(ihip, lambda: L.decode_layer(q, k, k, chunks, keeps, out_blocks=blocks, **kw)) == (n, n)
+    assert (blocks.view(B, -1) == blocks.view(B, -1)[:1]).all() and (blocks >= 0).all()
