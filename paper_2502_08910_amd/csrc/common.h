@@ -70,7 +70,7 @@ struct DecodeGrid {
     __device__ int part() const { return problems_first ? blockIdx.y : blockIdx.x; }
     dim3 dims(int P, int per_problem) const { return problems_first ? dim3(P, per_problem) : dim3(per_problem, P); }
 };
-inline DecodeGrid decode_grid(const Geometry &ge, int per_problem, bool host_tier) { return DecodeGrid{!host_tier && ge.Hkv % 8 == 0 && per_problem <= 65535}; }
+inline DecodeGrid decode_grid(const Geometry &ge, int per_problem, bool parts_first) { return DecodeGrid{!parts_first && ge.Hkv % 8 == 0 && per_problem <= 65535}; }
 
 struct Problem {
     int b, g, m;

@@ -28,6 +28,19 @@ struct PruneArgs {
                               // count 2-byte units of the byte rows)
 };
 
+// The grid of a decode stage's launch, K behind the host tier or not, in E4M3 or not.  Over bf16 pages a stage that covers more than
+// 768K keys of a head keeps the part fastest: dealt out problem by problem, a batch of different lengths ends with a few long
+// sequences whose pages are all still to be looked up.  Layers over bf16 pages, 8 KV heads, part / problem fastest (us), runs of
+// one length and ragged: 4 sequences of 64K 64.2 / 61.7 and 65.4 / 62.1, 16 of 32K 129.2 / 129.4 and 126.1 / 126.8, 4 of
+// 250K 111.5 / 112.0 and 104.8 / 108.3, 12 of 333K 314 / 317 and 279 / 287, 8 of 500K 302 / 301 and 268 / 280.  Contiguous rows of any
+// size have no such loss (8 of 500K 303 / 297 and 277 / 276), nor E4M3 in pages (237 / 236 and 221 / 222).
+inline DecodeGrid prune_grid(const PruneArgs &a, int P, int per_problem, bool fp8)
+{
+    const bool long_pages = a.paged.block_table != nullptr && !fp8 &&
+                            (int64_t)(P / a.ge.Hkv) * a.max_chunks * a.chunk > (int64_t)3 << 18;
+    return decode_grid(a.ge, per_problem, long_pages || a.bank.page_table != nullptr);
+}
+
 // Decode on the matrix cores (prune_decode_tile.h): chunks a wave works on, and waves of a workgroup
 constexpr int kDecodeTileWaves = 4;
 __host__ __device__ constexpr int decode_tile_chunks(int G, int chunk, bool rope, bool fp8)

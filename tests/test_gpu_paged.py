@@ -83,6 +83,23 @@ def test_paged_decode_matches_oracle_and_contiguous_path(ihip, orc, page, T, B):
             assert np.abs(got - ref[:, 0]).max() <= 2e-2
 
 
+@pytest.mark.parametrize("Hq,chunk", [(32, 128), (32, 16), (64, 64), (8, 128)])
+@pytest.mark.parametrize("T", [262144 + 512, 262144 + 1568])
+def test_long_ragged_batches_score_as_contiguous_rows(ihip, Hq, chunk, T):
+    """Three sequences to either side of 768K keys, where the order of the grid changes (shared pages keep the pool small)."""
+    B, Hkv, page = 3, 8, 16
+    g = torch.Generator(device="cuda").manual_seed(T + Hq + chunk)
+    pool = torch.randint(-3, 4, (4096, Hkv, page, 128), generator=g, device="cuda").to(torch.bfloat16)
+    table = torch.randint(0, 4096, (B, T // page), generator=g, device="cuda").to(torch.int32)
+    k = torch.stack([pool[t.long()].transpose(0, 1).reshape(Hkv, T, 128) for t in table])
+    q = torch.randint(-3, 4, (B, Hq, 1, 128), generator=g, device="cuda").to(torch.bfloat16)
+    sl = torch.tensor([T - 70001, T, T - 131], dtype=torch.int32, device="cuda")
+    L = ihip.Layer(q, k, sl, 1, 128, 1024)
+    want, want_rep = L.prune_stage(q, k, chunk, want_rep=True)
+    got, got_rep = L.prune_stage(q, None, chunk, want_rep=True, paged=ihip.PagedKV(pool, pool, table))
+    assert torch.equal(got, want) and torch.equal(got_rep, want_rep)
+
+
 def test_short_block_table_is_refused(ihip):
     w = configs.shrink(configs.CFG1, T=2048, n_needles=0)
     q, k, v, sl, _ = configs.make_inputs(w, 0, kind="int")
