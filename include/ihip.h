@@ -257,6 +257,9 @@ int32_t ihip_sparse_attn_decode(const ihip_shape *shape, ihip_tensor q, ihip_ten
  * [P, n_blocks] with P = B*Hkv*Mq; out is bf16 [B, Hq, Tq, d] contiguous;
  * out_lse fp32 [B, Hq, Tq] or NULL.  QK^T and PV run on the matrix cores
  * (bf16 inputs, fp32 accumulation), softmax in fp32.
+ *   ws, ws_bytes device scratch of ihip_workspace_bytes(IHIP_OP_ATTN_PREFILL, ...), 16-byte aligned; may be NULL.  A
+ *                launch that would leave the chip idle splits the key lists over it and merges the parts there; with
+ *                NULL, less or a misaligned pointer nothing is split (slower; equal up to rounding, see ihip_workspace_bytes).
  */
 int32_t ihip_sparse_attn_prefill(const ihip_shape *shape, ihip_tensor q, ihip_tensor k, ihip_tensor v,
                                  const int32_t *block_starts, int32_t n_blocks, int32_t block,
@@ -266,12 +269,22 @@ int32_t ihip_sparse_attn_prefill(const ihip_shape *shape, ihip_tensor q, ihip_te
 /*
  * Scratch bytes an operation needs.  n_stages / chunk_sizes / keeps describe
  * the stage plan (for the attention-only ops pass n_stages = 1 with
- * chunk_sizes[0] = block and keeps[0] = n_blocks).  Returns 0 on bad arguments.
- * Decode attention splits the key list over the chip and merges the parts; with the bytes reported here it cuts it as fine as
- * it can use.  Calls that get less, but enough for parts of at least 256 keys, cut it coarser (results equal up to fp32
- * rounding; calls with at least the reported bytes give identical bits).  One exception: a decode layer whose scratch
- * fits IHIP_STATIC_SCRATCH_BYTES with the coarse parts but not with the fine ones is always cut coarse, and the coarse
- * bytes are reported, so that ihip_decode_layer_static takes it and gives the same bits.
+ * chunk_sizes[0] = block and keeps[0] = n_blocks; chunks and blocks of up to 1,024 tokens).  Returns 0 on bad
+ * arguments, never otherwise.  Calls that overlap on a GPU need scratch of their own.
+ * Calls with at least the reported bytes give identical bits.  Part of them only buys speed; a call that gets less, but
+ * what it cannot do without, is accepted:
+ *   decode attention splits the key list over the chip and merges the parts, with the bytes reported here as fine as it can
+ *     use; with less, but enough for parts of at least 256 keys, coarser (results equal up to fp32 rounding);
+ *   prefill attention (IHIP_OP_ATTN_PREFILL, and what IHIP_OP_PREFILL_LAYER holds beyond the scores, lists and final blocks)
+ *     splits only with all of it.  The probabilities are rounded to bf16 against another maximum then: results differ by
+ *     that rounding, a few units of the bf16 result's last place;
+ *   IHIP_OP_PRUNE_ALL and IHIP_OP_DECODE_LAYER: where it pays, all stages of a short decode plan are scored at once,
+ *     with the bytes behind the ones that a stage-by-stage run needs.  The two add up a score in another order (equal up to
+ *     fp32 rounding): chunks whose scores tie to within that may be kept one for the other, and the output follows the
+ *     kept blocks.
+ * Two exceptions, so that ihip_decode_layer_static takes a plan and gives the same bits: where a decode layer's scratch fits
+ * IHIP_STATIC_SCRATCH_BYTES with the coarse parts but not with the fine ones, it is always cut coarse and the coarse bytes
+ * are reported; where it fits only without the scores of all stages at once, every call scores stage by stage.
  */
 size_t ihip_workspace_bytes(int32_t op, const ihip_shape *shape, int32_t n_stages,
                             const int32_t *chunk_sizes, const int32_t *keeps);
@@ -285,7 +298,8 @@ size_t ihip_workspace_bytes(int32_t op, const ihip_shape *shape, int32_t n_stage
  * enqueue.  chunk_sizes / keeps are host int32 [n_stages] (l_c and K = k/l_c per
  * stage; each chunk size divides the previous one).  out_block_starts is
  * device int32 [P, keeps[n_stages-1]]: the last stage's kept blocks, as
- * ihip_sparse_attn_* take them.  Scratch from ihip_workspace_bytes(IHIP_OP_PRUNE_ALL, ...).
+ * ihip_sparse_attn_* take them.  Scratch from ihip_workspace_bytes(IHIP_OP_PRUNE_ALL, ...); less than that may change
+ * selections at near ties (see there).
  */
 int32_t ihip_prune_all(const ihip_shape *shape, ihip_tensor q, ihip_tensor k,
                        int32_t n_stages, const int32_t *chunk_sizes, const int32_t *keeps,
@@ -305,7 +319,8 @@ int32_t ihip_decode_layer(const ihip_shape *shape, ihip_tensor q, ihip_tensor k,
  * One chunked-prefill layer call: ihip_prune_all followed by
  * ihip_sparse_attn_prefill (Alg. 1 per query block, then block-sparse
  * attention).  out / out_lse as in ihip_sparse_attn_prefill; out_block_starts
- * device int32 [P, keeps[last]] or NULL.
+ * device int32 [P, keeps[last]] or NULL.  Scratch from ihip_workspace_bytes(IHIP_OP_PREFILL_LAYER, ...), 16-byte aligned;
+ * without its last part, the attention's, nothing is split there.
  */
 int32_t ihip_prefill_layer(const ihip_shape *shape, ihip_tensor q, ihip_tensor k, ihip_tensor v,
                            int32_t n_stages, const int32_t *chunk_sizes, const int32_t *keeps,
