@@ -28,17 +28,27 @@ struct PruneArgs {
                               // count 2-byte units of the byte rows)
 };
 
-// The grid of a decode stage's launch, K behind the host tier or not, in E4M3 or not.  Over bf16 pages a stage that covers more than
-// 768K keys of a head keeps the part fastest: dealt out problem by problem, a batch of different lengths ends with a few long
-// sequences whose pages are all still to be looked up.  Layers over bf16 pages, 8 KV heads, part / problem fastest (us), runs of
-// one length and ragged: 4 sequences of 64K 64.2 / 61.7 and 65.4 / 62.1, 16 of 32K 129.2 / 129.4 and 126.1 / 126.8, 4 of
-// 250K 111.5 / 112.0 and 104.8 / 108.3, 12 of 333K 314 / 317 and 279 / 287, 8 of 500K 302 / 301 and 268 / 280.  Contiguous rows of any
-// size have no such loss (8 of 500K 303 / 297 and 277 / 276), nor E4M3 in pages (237 / 236 and 221 / 222).
-inline DecodeGrid prune_grid(const PruneArgs &a, int P, int per_problem, bool fp8)
+// The grid of a decode stage's launch.  Where the heads of a token lie beside each other (token-major rows, pages) problems dealt out
+// first read the same few rows of memory at once from all XCDs, and over pages a ragged batch also ends with a few long sequences
+// whose pages are all still to be looked up: there the part stays fastest on long contexts.  Layers, 8 KV heads, part / problem
+// fastest (us, second pair ragged):
+//   bf16 pages, and token-major bf16 rows without RoPE, by the keys of all sequences, line 768K: pages, 4 sequences of 64K 64.2 / 61.7 and
+//     65.4 / 62.1, 16 of 32K 129.2 / 129.4 and 126.1 / 126.8, 4 of 250K 111.5 / 112.0 and 104.8 / 108.3, 8 of 500K 302 / 301 and
+//     268 / 280; rows, 4 of 64K 61.1 / 57.6, 4 of 250K 110.8 / 108.7 and 100.5 / 101.9, one of 1M 96.2 / 103.9, 8 of 500K 287 / 310 and 264 / 287
+//   token-major rows with RoPE, by the keys of a sequence, line 288K for E4M3 and 384K for bf16: E4M3, 16 of 128K 288.7 / 294.6, 12 of
+//     333K 290 / 301 and 285 / 294, 8 of 500K 224 / 243 and 219 / 235; bf16, 16 of 128K 269.0 / 240.0, 12 of 333K 348 / 331 and
+//     328 / 316, 8 of 500K 312 / 313 and 291 / 298, one of 1M 107 / 115
+// E4M3 pages (8 of 500K with RoPE 237 / 236 and 221 / 222), token-major E4M3 without RoPE (198.6 / 180.1) and rows of a head in a row
+// (303 / 297 and 277 / 276; RoPE 315.6 / 292.8) have no such loss.  Compare with buffers that lie alike: where a process's memory
+// falls moves the largest of these by 3 %.
+inline DecodeGrid prune_grid(const PruneArgs &a, int P, int per_problem, bool fp8, bool rope)
 {
-    const bool long_pages = a.paged.block_table != nullptr && !fp8 &&
-                            (int64_t)(P / a.ge.Hkv) * a.max_chunks * a.chunk > (int64_t)3 << 18;
-    return decode_grid(a.ge, per_problem, long_pages || a.bank.page_table != nullptr);
+    const bool paged = a.paged.block_table != nullptr, token_major = !paged && std::abs(a.k_st) > std::abs(a.k_sh);
+    const int64_t each = (int64_t)a.max_chunks * a.chunk, all = P / a.ge.Hkv * each;
+    bool parts_first = a.bank.page_table != nullptr;
+    if (paged || (token_major && !rope)) parts_first |= !fp8 && all > (int64_t)3 << 18;
+    else if (token_major) parts_first |= each > (fp8 ? (int64_t)9 << 15 : (int64_t)3 << 17);
+    return decode_grid(a.ge, per_problem, parts_first);
 }
 
 // Decode on the matrix cores (prune_decode_tile.h): chunks a wave works on, and waves of a workgroup

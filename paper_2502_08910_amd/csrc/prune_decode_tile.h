@@ -450,7 +450,7 @@ static void launch_decode_tile_n(PruneArgs a, const RopeView &rope, int P, hipSt
 {
     const int per_wg = (SRC == 1 ? decode_search_tiles(SRC) * 16 / G : decode_tile_chunks(G, a.chunk, ROPE, KV8)) * kDecodeTileWaves;
     const int per_problem = (a.max_chunks + per_wg - 1) / per_wg;
-    a.grid = prune_grid(a, P, per_problem, KV8);
+    a.grid = prune_grid(a, P, per_problem, KV8, ROPE);
     const dim3 grid = a.grid.dims(P, per_problem), block(64 * kDecodeTileWaves);
     KernelTimer timer(stage_name(kNamePruneDecode, a.parent_starts == nullptr, a.chunk), st);
     // contiguous bf16 rows without RoPE: only chunks of four with eight heads come here (decode_on_tiles)

@@ -201,7 +201,7 @@ template <int G, int U>
 static void launch_decode_u(PruneArgs a, int P, bool fp8, hipStream_t st)
 {
     const int per_problem = (a.max_chunks + 16 * U - 1) / (16 * U);
-    a.grid = prune_grid(a, P, per_problem, fp8);
+    a.grid = prune_grid(a, P, per_problem, fp8, false);
     const dim3 grid = a.grid.dims(P, per_problem);
     KernelTimer timer(stage_name(kNamePruneDecode, a.parent_starts == nullptr, a.chunk), st);
     if constexpr (U == 1) {

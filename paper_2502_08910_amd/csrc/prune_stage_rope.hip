@@ -263,7 +263,7 @@ template <int G, int SRC, bool KV8, int U>
 static void launch_rope_u(PruneArgs a, const RopeView &rope, int style, int P, hipStream_t st)
 {
     const int per_problem = (a.max_chunks + 16 * U - 1) / (16 * U);
-    a.grid = prune_grid(a, P, per_problem, KV8);
+    a.grid = prune_grid(a, P, per_problem, KV8, true);
     const dim3 grid = a.grid.dims(P, per_problem);
     KernelTimer timer(stage_name(kNamePruneDecode, a.parent_starts == nullptr, a.chunk), st);
     if (style == 1) hipLaunchKernelGGL((prune_decode_rope_kernel<G, U, 1, SRC, KV8>), grid, dim3(256), 0, st, a, rope);

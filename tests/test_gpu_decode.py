@@ -380,3 +380,28 @@ def test_attention_splits_at_the_static_array(ihip):
     assert torch.isfinite(outs[0]).all() and torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
     with pytest.raises(ihip.IhipError):
         L.decode_layer(q, k, v, [1], [keep], ws=torch.empty(need - 1, dtype=torch.uint8, device="cuda"))
+
+
+@pytest.mark.parametrize("B,T", [(3, 262144 + 512), (3, 262144 + 1568), (1, 294912 + 1000), (1, 294912 + 1500), (1, 393216 + 1000), (1, 393216 + 1500)])
+@pytest.mark.parametrize("fp8,rope", [(False, False), (False, True), (True, True)])
+def test_long_token_major_rows_score_as_head_major_ones(ihip, B, T, fp8, rope):
+    """To either side of the lengths where the order of the grid changes; 8 KV heads, chunks for the vector and the matrix-core kernels."""
+    Hq, Hkv = 32, 8
+    g = torch.Generator(device="cuda").manual_seed(B * T + 2 * fp8 + rope)
+    k = torch.randint(-3, 4, (B, T, Hkv, 128), generator=g, device="cuda", dtype=torch.int8)
+    k = k.to(torch.float8_e4m3fn).view(torch.uint8) if fp8 else k.to(torch.bfloat16)
+    token_major, head_major = k.transpose(1, 2), k.transpose(1, 2).contiguous()
+    q = torch.randint(-3, 4, (B, Hq, 1, 128), generator=g, device="cuda").to(torch.bfloat16)
+    sl = torch.tensor([T, T - 70001, T - 131][:B], dtype=torch.int32, device="cuda")
+    L = ihip.Layer(q, head_major, sl, 1, 128, 1024)
+    kw = {"kv_scales": (1.0, 1.0)} if fp8 else {}
+    if rope:
+        cos, sin = gen.quarter_turn_table(16384, 128)
+        kw["rope"] = ihip.Rope(cos.cuda(), sin.cuda(), ihip.ROPE_RELATIVE, ihip.ROPE_STREAMING)
+    for chunk in (128, 16):
+        got = []
+        for rows in (head_major, token_major):
+            blocks = torch.empty((B * Hkv, 96), dtype=torch.int32, device="cuda")
+            out = L.decode_layer(q, rows, rows, [chunk], [96], out_blocks=blocks, **kw)
+            got.append((out, blocks))
+        assert torch.equal(got[0][1], got[1][1]) and torch.equal(got[0][0], got[1][0])
