@@ -168,7 +168,8 @@ __device__ inline void write_no_chunks(const PruneArgs &a, const Problem &pr, in
 // Tiles of a wave.  Host tier: one, whose 16 owners look their rows up in the bank and hand them to the lanes of their row group; four times
 // the waves (8K to 32K keys all in the banks, 64 heads on 8, bf16: 100 -> 80 us a layer, 32 on 8 86 -> 76).  Vector kernel / this one
 // (us): 8K bf16 keys, 32 heads on 8, banks that hold few of them 291 / 273, all 68 / 58, 500K E4M3 with RoPE 64 on 8 all 278 / 219;
-// one head a group is where it loses, up to 5 us of 50 (4K to 12K keys in the banks).
+// one head a group is where it loses, up to 5 us of 50 (4K to 12K keys in the banks), a layer of four stages on 17K keys 96 / 108; it
+// is taken there too, for the bits that contiguous rows give.
 constexpr int decode_search_tiles(int src) { return src == 1 ? 1 : 4; }
 
 constexpr int kDecodePages = 16;              // page ids of a chunk kept in LDS; further ones are looked up in the table
