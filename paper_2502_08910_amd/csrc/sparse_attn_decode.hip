@@ -1,22 +1,36 @@
 // Block-sparse decode attention over sink + kept blocks + window.
 //
-// HBM-bound gather of K and V rows (512 B per attended token, shared by the G
-// query heads of the KV head).  Flash-decoding layout: the attended tokens of
-// a problem form a virtual slot list  [sink | kept blocks | window];  the list
-// is cut into splits, one workgroup each; inside a workgroup every 16-lane
-// group owns one token at a time (16 B of the K row and of the V row per
-// lane) and keeps an online-softmax state for all G heads; groups are merged
-// through LDS, splits by a second small kernel (log-sum-exp merge).
-#include "common.h"
+// HBM-bound gather of K and V rows (512 B per attended token, shared by the G query heads of the KV head).  Flash-decoding layout: the
+// attended tokens of a problem form a virtual slot list  [sink | kept blocks | window];  the list is cut into splits, one workgroup
+// each; a wave takes 16 slots at a time, and every 16-lane row group reads four of their rows whole (16 B of a bf16 row per lane).
+//
+// On the vector ALUs a token costs some 26 instructions per 16 lanes and head -- dot, row reduction, a softmax that all lanes
+// repeat, and 8 multiply-adds per head --, which was more than the rows' time with E4M3 rows, rotations or 8 heads.  The products are done
+// on the matrix cores instead, in layouts between which no value crosses lanes:
+//   scores   16 K rows x 16 columns (four v_mfma_f32_16x16x32_bf16; column n is head n % 4): lane (n, kq) gets its head's scores of
+//            tokens 4 * kq .. + 3, the very tokens whose V rows its row group holds.  K goes to operand layout through LDS.
+//   softmax  four scores a lane; the reference of the exponentials, and the sum, are the row group's own
+//   output   v_mfma_f32_4x4x4_16B_bf16: 16 blocks of 4 heads x 4 tokens x 4 dims; a lane's four probabilities are its row of
+//            the left operand, its 8 dims of the four V rows, in pairs of tokens, the columns of eight right ones.  A probability
+//            goes in as three bf16 parts (24 bits), so nothing of it is rounded away.
+// With RoPE the keys are turned in fp32 and would need three parts as well (tried: 56 -> 63 us with four heads, 20 -> 29 with one), so
+// their scores stay on the vector ALUs.  Split and merge, before / now (us): four heads, 16 sequences of 3,200 slots, bf16 45.8 / 38.9
+// (5.4 TB/s), in pages 46.3 / 40.6, E4M3 38.4 / 26.3, bf16 with RoPE 56.4 / 43.5; 8 heads 75.6 / 41.4, 72.2 / 31.0, 96.9 / 52.3; one
+// head 39.0 / 38.1; 4 sequences of 5,248 slots bf16 25.8 / 22.5, E4M3 24.4 / 16.9, bf16 with RoPE 33.1 / 27.1; one of 1,664 9.9 / 8.8.
+// The rows of the next 16 slots are requested as soon as the registers of these are free (K once it is in LDS, V once it is
+// in the products); a whole second set of registers leaves two waves per SIMD instead of four.
+//
+// Row groups and waves are merged at the end through row swaps and LDS, splits by a second small kernel (log-sum-exp merge).
+#include "prune_decode_tile.h"
 #include <algorithm>
 #include <type_traits>
 
 namespace ihip {
 
 constexpr int kAttnThreads = 256;
-constexpr int kAttnGroups = kAttnThreads / kRowLanes;   // 16 tokens in flight per step
 constexpr int kAttnMaxSplit = 1024;                      // most slots of one split (a multiple of 16)
 constexpr int kAttnMinSplit = 256, kAttnMinSplitFine = 64;      // fewest; see decode_splits
+constexpr float kSlack = 8.f;                            // log2 units that a score may stand above the reference of the exponentials
 constexpr float kNegBig = -1.0e30f;                      // finite stand-in for -inf in running maxima
 
 struct AttnDecodeArgs {
@@ -79,6 +93,42 @@ template <> struct KvSource<2> {
     }
 };
 
+typedef short bf16x4 __attribute__((ext_vector_type(4)));
+
+// 8 dims turned, fp32
+__device__ inline void turn8(float (&x)[8], const float4 c, const float4 sn)
+{
+    const float cc[4] = {c.x, c.y, c.z, c.w}, ss[4] = {sn.x, sn.y, sn.z, sn.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float e = x[2 * i], o = x[2 * i + 1];
+        x[2 * i] = e * cc[i] - o * ss[i];
+        x[2 * i + 1] = e * ss[i] + o * cc[i];
+    }
+}
+// Sums over the 16 lanes of a row, of G values: lane n gets that of value n % 4 % G.  A step halves the values that a lane holds where
+// there are any to halve: 44 instructions for the four heads of four tokens, 64 and a choice among the heads otherwise.
+template <int G>
+__device__ inline float head_sum(const float (&d)[G], int n)
+{
+    float x;
+    if constexpr (G == 1) {
+        x = d[0] + dpp_f32<0xB1>(d[0]);       // quad_perm [1,0,3,2]
+        x += dpp_f32<0x4E>(x);                // quad_perm [2,3,0,1]
+    } else {
+        const bool odd = n & 1, high = n & 2;
+        x = (odd ? d[1] : d[0]) + dpp_f32<0xB1>(odd ? d[0] : d[1]);
+        if constexpr (G == 4) {
+            const float y = (odd ? d[3] : d[2]) + dpp_f32<0xB1>(odd ? d[2] : d[3]);
+            x = (high ? y : x) + dpp_f32<0x4E>(high ? x : y);
+        } else {
+            x += dpp_f32<0x4E>(x);
+        }
+    }
+    x += dpp_f32<0x128>(x);                   // row_ror:8
+    return x + dpp_f32<0x124>(x);             // row_ror:4
+}
+
 // slot -> key position, or -1
 __device__ inline int slot_to_pos(const AttnDecodeArgs &a, const Problem &pr, int p, int slot,
                                   int n_sink_eff, int w0)
@@ -100,164 +150,282 @@ __device__ inline int slot_to_pos(const AttnDecodeArgs &a, const Problem &pr, in
 // order, are rotated to positions 0, 1, ..., n-1 and the query to n-1.  Attended slots are a
 // prefix of the block part of the slot list (blocks are ascending, empty ones last, only the last
 // one can be cut short), so a key's id is its slot, less the empty block slots for window keys.
-// KV8: K and V rows are 128 bytes of E4M3 (8 bytes per lane), repacked exactly as bf16 for the dot.
+// KV8: K and V rows are 128 bytes of E4M3, widened exactly to bf16.
 template <int G, int SRC, bool ROPE, bool KV8>
-__global__ __launch_bounds__(kAttnThreads) void attn_decode_split_kernel(const AttnDecodeArgs a)
+__global__ __launch_bounds__(kAttnThreads, G == 8 ? 2 : ROPE ? 3 : 4) void attn_decode_split_kernel(const AttnDecodeArgs a)
 {
-    using piece_t = typename std::conditional<KV8, uint2, uint4>::type;     // a lane's share of a row
-    constexpr int kLaneOff = KV8 ? 4 : 8;                                   // in 2-byte units
+    constexpr int NW = kAttnThreads / kWave;
+    constexpr int kSets = G == 8 ? 2 : 1;                                   // of four heads (fewer: the four rows of a product repeat them)
+    constexpr int kLoads = KV8 ? 2 : 4, kPieces = KV8 ? 8 : 16;             // of a lane for 16 K rows; 16-byte pieces of a row
+    using v_t = typename std::conditional<KV8, uint2, uint4>::type;         // a lane's 8 dims of a V row
     const int p = a.grid.problem(), split = a.grid.part();
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, kq = lane >> 4;
+    const int s0 = split * a.slots_per_split;
+    const int block_slots = a.n_blocks << a.block_log2;
+    const int32_t *starts = a.block_starts + (int64_t)p * a.n_blocks;
+
+    // The blocks of this thread's slots are asked for at once, next to the sequence's length, with the whole sink there (which only
+    // a sequence shorter than it has not).
+    constexpr int kSlots = kAttnMaxSplit / kAttnThreads;
+    int start_of[kSlots];
+#pragma unroll
+    for (int k = 0; k < kSlots; ++k) {
+        const int i = tid + k * kAttnThreads, at = s0 + i - a.ge.n_sink;
+        start_of[k] = i < a.slots_per_split && at >= 0 && at < block_slots ? starts[at >> a.block_log2] : -1;
+    }
     const Problem pr = problem_of(a.ge, p);
-    const int l16 = threadIdx.x & 15, grp = threadIdx.x >> 4;
     const int n_sink_eff = min(a.ge.n_sink, pr.E);
     const int w0 = max(pr.hi, a.ge.n_sink);
 
-    // this lane's 8 dims of the G query vectors, kept packed (bf16 pairs) for the dot2 instruction
-    uint4 qp[G];
-    {
-        const uint16_t *qb = a.q + pr.b * a.q_sb + (int64_t)(pr.g * G) * a.q_sh;
-#pragma unroll
-        for (int h = 0; h < G; ++h) qp[h] = load_row16(qb, h * a.q_sh, l16);
-    }
-    // ROPE: tokens in the kept blocks (so that window keys and the query know their ids) and the
-    // rotated queries, fp32
+    __shared__ __attribute__((aligned(16))) int sh_pos[kAttnMaxSplit];      // key position of every slot of this split, -1 without one
+    __shared__ __attribute__((aligned(16))) int sh_page[SRC == 2 ? kAttnMaxSplit : 4];       // paged K/V: the slot's page id
+    __shared__ uint4 sh_rows[ROPE ? 1 : NW * 16 * kPieces];                 // 16 K rows of each wave on their way to operand layout
     __shared__ int sh_block_tokens;
-    float qr[ROPE ? G : 1][8];
-    int block_slots = 0, block_tokens = 0;
-    if (ROPE) {
-        if (threadIdx.x == 0) sh_block_tokens = 0;
-        __syncthreads();
-        int mine = 0;
-        for (int i = threadIdx.x; i < a.n_blocks; i += kAttnThreads) {
-            const int bs = a.block_starts[(int64_t)p * a.n_blocks + i];
-            if (bs >= 0 && bs < pr.hi) mine += min(a.block, pr.hi - bs);
-        }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) mine += __shfl_xor(mine, d, 64);
-        if ((threadIdx.x & 63) == 0 && mine > 0) atomicAdd(&sh_block_tokens, mine);
-        __syncthreads();
-        block_slots = a.n_blocks << a.block_log2;
-        block_tokens = sh_block_tokens;
-        const int n_sel = n_sink_eff + block_tokens + max(0, pr.E - w0);
-        const int64_t q_at = (int64_t)max(n_sel - 1, 0) * (kD / 2) + l16 * 4;      // (an empty sequence attends to nothing)
-        const float4 c = *reinterpret_cast<const float4 *>(a.rope_cos + q_at);
-        const float4 sn = *reinterpret_cast<const float4 *>(a.rope_sin + q_at);
-        const float cc[4] = {c.x, c.y, c.z, c.w}, ss[4] = {sn.x, sn.y, sn.z, sn.w};
-#pragma unroll
-        for (int h = 0; h < G; ++h) {
-            float x[8];
-            unpack8(qp[h], x);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                qr[h][2 * i] = x[2 * i] * cc[i] - x[2 * i + 1] * ss[i];
-                qr[h][2 * i + 1] = x[2 * i] * ss[i] + x[2 * i + 1] * cc[i];
-            }
-        }
-    }
     const typename KvSource<SRC>::type ksrc = KvSource<SRC>::k(a, pr);
     const typename KvSource<SRC>::type vsrc = KvSource<SRC>::v(a, pr);
-
-    float m[G], l[G], acc[G][8];
+    // The queries, asked for now: column n's head of each set as an operand (head n % 4, n % G with fewer), or (ROPE) this lane's 8
+    // dims of every head
+    bf16x8 q[ROPE ? 1 : kSets][1][4];
+    uint4 q_raw[ROPE ? G : 1];
+    if constexpr (ROPE) {
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-        m[h] = kNegBig; l[h] = 0.f;
+        for (int h = 0; h < G; ++h) q_raw[h] = load_row16(a.q + pr.b * a.q_sb + (int64_t)(pr.g * G + h) * a.q_sh, 0, n);
+    } else {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc[h][i] = 0.f;
+        for (int s = 0; s < kSets; ++s)
+            decode_query_operands<KV8, 1>(a.q + pr.b * a.q_sb + (int64_t)(pr.g * G + s * 4 + (n & 3) % G) * a.q_sh, kq, RopeView{}, 0, q[s]);
     }
-
-    constexpr int UNR = 4;
-    const int s0 = split * a.slots_per_split;
-    const int s1 = s0 + a.slots_per_split;
-    // key position of every slot of this split, computed up front, so that the main loop has no
-    // dependent global loads (block start -> row address)
-    __shared__ int sh_pos[kAttnMaxSplit];
-    __shared__ int sh_page[SRC == 2 ? kAttnMaxSplit : 1];    // paged K/V: the slot's page id, looked up here once
-    for (int i = threadIdx.x; i < a.slots_per_split; i += kAttnThreads) {
-        const int pos = slot_to_pos(a, pr, p, s0 + i, n_sink_eff, w0);
+    int block_tokens = 0;
+    if constexpr (ROPE) {
+        // tokens in the kept blocks, so that window keys and the query know their ids
+        if (tid == 0) sh_block_tokens = 0;
+        __syncthreads();
+        int mine = 0;
+        for (int i0 = 0; i0 < a.n_blocks; i0 += 4 * kAttnThreads) {
+            int bs[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) bs[k] = i0 + k * kAttnThreads + tid < a.n_blocks ? starts[i0 + k * kAttnThreads + tid] : -1;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) mine += bs[k] >= 0 && bs[k] < pr.hi ? min(a.block, pr.hi - bs[k]) : 0;
+        }
+        mine = (int)wave_sum_u32((uint32_t)mine);
+        if (lane == 0 && mine > 0) atomicAdd(&sh_block_tokens, mine);
+    }
+#pragma unroll
+    for (int k = 0; k < kSlots; ++k) {
+        const int i = tid + k * kAttnThreads;
+        if (i >= a.slots_per_split) break;
+        int slot = s0 + i, pos;
+        if (n_sink_eff == a.ge.n_sink) {
+            const int at = slot - n_sink_eff;
+            if (at < 0) pos = slot;
+            else if (at < block_slots) {
+                pos = start_of[k] + (at & (a.block - 1));
+                pos = start_of[k] >= 0 && pos < pr.hi ? pos : -1;
+            } else {
+                pos = w0 + (at - block_slots);
+                pos = pos < pr.E ? pos : -1;
+            }
+        } else {
+            pos = slot_to_pos(a, pr, p, slot, n_sink_eff, w0);
+        }
         sh_pos[i] = pos;
         if constexpr (SRC == 2) sh_page[i] = pos >= 0 ? ksrc.table_entry(pos) : 0;
     }
     __syncthreads();
-    for (int base = s0 + grp; base < s1; base += kAttnGroups * UNR) {
-        piece_t kr[UNR], vr[UNR];
-        bool ok[UNR];
+
+    f32x4 acc[kSets][8];                      // [dim of this lane's 8][head of the set]: of this row group's tokens
+    float m[kSets], l[kSets];                 // of this row group's tokens, head n % 4: reference of the exponentials (log2 units), sum
 #pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            const int slot = base + u * kAttnGroups;
-            const int pos = slot < s1 ? sh_pos[slot - s0] : -1;
-            ok[u] = pos >= 0;
-            kr[u] = piece_t{};
-            vr[u] = piece_t{};
-            if (ok[u]) {
-                if constexpr (SRC == 2) {
-                    const int page = sh_page[slot - s0];
-                    kr[u] = *reinterpret_cast<const piece_t *>(ksrc.row_in_page(page, pos) + l16 * kLaneOff);
-                    vr[u] = *reinterpret_cast<const piece_t *>(vsrc.row_in_page(page, pos) + l16 * kLaneOff);
-                } else {
-                    kr[u] = *reinterpret_cast<const piece_t *>(ksrc.row(pos, l16 == 0) + l16 * kLaneOff);
-                    vr[u] = *reinterpret_cast<const piece_t *>(vsrc.row(pos, false) + l16 * kLaneOff);   // K did the bookkeeping
+    for (int s = 0; s < kSets; ++s) {
+        m[s] = kNegBig; l[s] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[s][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+
+    // 16 slots at a time, a wave's own.  Row group kq reads the K and V rows of slots 4 * kq .. + 3.
+    uint4 *stage = &sh_rows[wv * 16 * kPieces];
+    uint4 kr[ROPE ? 1 : kLoads];
+    v_t kv[ROPE ? 4 : 1], vr[4];              // ROPE: K rows as V rows, and their turns
+    float4 tc[ROPE ? 4 : 1], ts[ROPE ? 4 : 1];
+    auto four = [&](const int *of, int tile, int (&x)[4]) {
+        const int4 w = *reinterpret_cast<const int4 *>(&of[tile * 16 + kq * 4]);
+        x[0] = w.x; x[1] = w.y; x[2] = w.z; x[3] = w.w;
+    };
+    // id of the key of a slot: the slot, less the empty block slots if it is a window key
+    auto key_id = [&](int slot, int pos) { return pos < 0 ? 0 : slot < n_sink_eff + block_slots ? slot : slot - (block_slots - block_tokens); };
+    auto load_k = [&](int tile) {
+        int pos[4], page[4] = {0, 0, 0, 0};
+        four(sh_pos, tile, pos);
+        if constexpr (SRC == 2) four(sh_page, tile, page);
+        if constexpr (ROPE) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                kv[u] = v_t{};
+                if (pos[u] >= 0) {
+                    if constexpr (SRC == 2) kv[u] = *reinterpret_cast<const v_t *>(ksrc.row_in_page(page[u], pos[u]) + n * (KV8 ? 4 : 8));
+                    else kv[u] = *reinterpret_cast<const v_t *>(ksrc.row(pos[u], n == 0) + n * (KV8 ? 4 : 8));
                 }
             }
+            return;
         }
-        // scores of the UNR tokens for all heads (log2 units), then one running-max update per batch
-        float sc[UNR][G];
-        if (ROPE) {
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) {
-                const int slot = base + u * kAttnGroups;
-                // id of the key: its slot, less the empty block slots if it is a window key
-                const int id = ok[u] ? (slot < n_sink_eff + block_slots ? slot : slot - (block_slots - block_tokens)) : 0;
-                const float4 c = *reinterpret_cast<const float4 *>(a.rope_cos + (int64_t)id * (kD / 2) + l16 * 4);
-                const float4 sn = *reinterpret_cast<const float4 *>(a.rope_sin + (int64_t)id * (kD / 2) + l16 * 4);
-                const float cc[4] = {c.x, c.y, c.z, c.w}, ss[4] = {sn.x, sn.y, sn.z, sn.w};
-                float x[8], kt[8];
-                unpack8(kr[u], x);
+        for (int i = 0; i < kLoads; ++i) {
+            const bool second = KV8 && n >= 8;                  // E4M3: two rows of 8 lanes each
+            const int at = KV8 ? (second ? pos[2 * i + 1] : pos[2 * i]) : pos[i];
+            const int pg = KV8 ? (second ? page[2 * i + 1] : page[2 * i]) : page[i];
+            kr[i] = make_uint4(0, 0, 0, 0);
+            if (at >= 0) {
+                if constexpr (SRC == 2) kr[i] = *reinterpret_cast<const uint4 *>(ksrc.row_in_page(pg, at) + (n & (kPieces - 1)) * 8);
+                else kr[i] = *reinterpret_cast<const uint4 *>(ksrc.row(at, (n & (kPieces - 1)) == 0) + (n & (kPieces - 1)) * 8);
+            }
+        }
+    };
+    auto load_turns = [&](int tile) {
+        int pos[4];
+        four(sh_pos, tile, pos);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    kt[2 * i] = x[2 * i] * cc[i] - x[2 * i + 1] * ss[i];
-                    kt[2 * i + 1] = x[2 * i] * ss[i] + x[2 * i + 1] * cc[i];
-                }
+        for (int u = 0; u < 4; ++u) {
+            const int64_t at = (int64_t)key_id(s0 + tile * 16 + kq * 4 + u, pos[u]) * (kD / 2) + n * 4;
+            tc[u] = *reinterpret_cast<const float4 *>(a.rope_cos + at);
+            ts[u] = *reinterpret_cast<const float4 *>(a.rope_sin + at);
+        }
+    };
+    auto load_v = [&](int tile) {
+        int pos[4], page[4] = {0, 0, 0, 0};
+        four(sh_pos, tile, pos);
+        if constexpr (SRC == 2) four(sh_page, tile, page);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            vr[u] = v_t{};
+            if (pos[u] >= 0) {
+                if constexpr (SRC == 2) vr[u] = *reinterpret_cast<const v_t *>(vsrc.row_in_page(page[u], pos[u]) + n * (KV8 ? 4 : 8));
+                else vr[u] = *reinterpret_cast<const v_t *>(vsrc.row(pos[u], false) + n * (KV8 ? 4 : 8));      // K did the bookkeeping
+            }
+        }
+    };
+    const int tiles = a.slots_per_split >> 4;
+    float4 q_cos, q_sin;
+    if constexpr (ROPE) {
+        block_tokens = sh_block_tokens;
+        const int64_t at = (int64_t)max(n_sink_eff + block_tokens + max(0, pr.E - w0) - 1, 0) * (kD / 2) + n * 4;       // (an empty sequence attends to nothing)
+        q_cos = *reinterpret_cast<const float4 *>(a.rope_cos + at);
+        q_sin = *reinterpret_cast<const float4 *>(a.rope_sin + at);
+    }
+    if (wv < tiles) {
+        load_k(wv);
+        if constexpr (ROPE) load_turns(wv);
+        load_v(wv);
+    }
+    float qr[ROPE ? G : 1][8];
+    if constexpr (ROPE) {
+#pragma unroll
+        for (int h = 0; h < G; ++h) {
+            unpack8(q_raw[h], qr[h]);
+            turn8(qr[h], q_cos, q_sin);
+        }
+    }
+#pragma unroll 1
+    for (int tile = wv; tile < tiles; tile += NW) {
+        const bool more = tile + NW < tiles;
+        f32x4 c[kSets];                       // of column n's head against tokens 4 * kq .. + 3
+        if constexpr (ROPE) {
+            float d[4][G];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                float x[8];
+                unpack8(kv[u], x);
+                turn8(x, tc[u], ts[u]);
 #pragma unroll
                 for (int h = 0; h < G; ++h) {
-                    float d8 = kt[0] * qr[h][0];
+                    d[u][h] = x[0] * qr[h][0];
 #pragma unroll
-                    for (int i = 1; i < 8; ++i) d8 = fmaf(kt[i], qr[h][i], d8);
-                    sc[u][h] = ok[u] ? row16_sum(d8) * a.scale_log2e : kNegBig;
+                    for (int i = 1; i < 8; ++i) d[u][h] = fmaf(x[i], qr[h][i], d[u][h]);
+                }
+            }
+            if (more) load_k(tile + NW);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if constexpr (G <= 4) c[0][u] = head_sum<G>(d[u], n);
+                else {
+#pragma unroll
+                    for (int s = 0; s < kSets; ++s) {
+                        const float of[4] = {d[u][4 * s], d[u][4 * s + 1], d[u][4 * s + 2], d[u][4 * s + 3]};
+                        c[s][u] = head_sum<4>(of, n);
+                    }
                 }
             }
         } else {
+            // K to operand layout: piece c of row r at c ^ r
 #pragma unroll
-            for (int u = 0; u < UNR; ++u)
-#pragma unroll
-                for (int h = 0; h < G; ++h)
-                    sc[u][h] = ok[u] ? row16_sum(dot8_bf16(as_bf16x8(kr[u]), qp[h])) * a.scale_log2e : kNegBig;
-        }
-        float pw[UNR][G], corr[G];
-#pragma unroll
-        for (int h = 0; h < G; ++h) {
-            float mn = m[h];
-#pragma unroll
-            for (int u = 0; u < UNR; ++u) mn = fmaxf(mn, sc[u][h]);
-            corr[h] = __builtin_amdgcn_exp2f(m[h] - mn);
-            m[h] = mn;
-            float ps = 0.f;
-#pragma unroll
-            for (int u = 0; u < UNR; ++u) {
-                pw[u][h] = ok[u] ? __builtin_amdgcn_exp2f(sc[u][h] - mn) : 0.f;
-                ps += pw[u][h];
+            for (int i = 0; i < kLoads; ++i) {
+                const int r = 4 * kq + (KV8 ? 2 * i + (n >> 3) : i);
+                stage[r * kPieces + ((n ^ r) & (kPieces - 1))] = kr[i];
             }
-            l[h] = l[h] * corr[h] + ps;
+            asm volatile("" ::: "memory");        // lanes read what other lanes of the wave wrote (LDS keeps the order)
+            if (more) load_k(tile + NW);
+            uint4 raw[kLoads];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) acc[h][i] *= corr[h];
+            for (int i = 0; i < kLoads; ++i) raw[i] = stage[n * kPieces + (((i * 4 + kq) ^ n) & (kPieces - 1))];
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int s = 0; s < kSets; ++s) c[s] = decode_products<KV8, 1>(raw, q[s]);
+        }
+        int pos[4];
+        four(sh_pos, tile, pos);
+        const bool ok[4] = {pos[0] >= 0, pos[1] >= 0, pos[2] >= 0, pos[3] >= 0};
+        bf16x4 part[kSets][3];                // the four tokens' probabilities, in three parts (24 bits)
+#pragma unroll
+        for (int s = 0; s < kSets; ++s) {
+            float sc[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sc[i] = ok[i] ? c[s][i] * a.scale_log2e : kNegBig;
+            const float top = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
+            if (__ballot(top > m[s] + kSlack) != 0) {           // the reference follows where the scores outgrow it
+                const float mn = fmaxf(m[s], top);
+                const float corr = __builtin_amdgcn_exp2f(m[s] - mn);
+                m[s] = mn;
+                l[s] *= corr;
+                const f32x4 ch = {dpp_f32<0x00>(corr), dpp_f32<0x55>(corr), dpp_f32<0xAA>(corr), dpp_f32<0xFF>(corr)};
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) acc[s][i][h] *= ch[h];
+            }
+            float w[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = ok[i] ? __builtin_amdgcn_exp2f(sc[i] - m[s]) : 0.f;
+            l[s] += (w[0] + w[1]) + (w[2] + w[3]);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const uint32_t lo = pack_bf16x2(w[0], w[1]), hi = pack_bf16x2(w[2], w[3]);
+                part[s][j] = __builtin_bit_cast(bf16x4, make_uint2(lo, hi));
+                if (j == 2) break;
+                w[0] -= __uint_as_float(lo << 16); w[1] -= __uint_as_float(lo & 0xffff0000u);       // exact
+                w[2] -= __uint_as_float(hi << 16); w[3] -= __uint_as_float(hi & 0xffff0000u);
+            }
+        }
+        uint32_t v[4][4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint4 x = as_bf16x8(vr[u]);
+            v[u][0] = x.x; v[u][1] = x.y; v[u][2] = x.z; v[u][3] = x.w;
         }
 #pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            float vf[8];
-            unpack8(vr[u], vf);
+        for (int i = 0; i < 8; ++i) {
+            const int w = i >> 1;
+            const uint32_t sel = (i & 1) ? 0x07060302u : 0x05040100u;
+            const bf16x4 vt = __builtin_bit_cast(bf16x4, make_uint2(__builtin_amdgcn_perm(v[1][w], v[0][w], sel), __builtin_amdgcn_perm(v[3][w], v[2][w], sel)));
 #pragma unroll
-            for (int h = 0; h < G; ++h)
+            for (int s = 0; s < kSets; ++s)
 #pragma unroll
-                for (int i = 0; i < 8; ++i) acc[h][i] = fmaf(pw[u][h], vf[i], acc[h][i]);
+                for (int j = 2; j >= 0; --j)
+                    acc[s][i] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(part[s][j], vt, acc[s][i], 0, 0, 0);
+        }
+        if (more) {
+            if constexpr (ROPE) load_turns(tile + NW);
+            load_v(tile + NW);
         }
     }
 
@@ -274,39 +442,38 @@ __global__ __launch_bounds__(kAttnThreads) void attn_decode_split_kernel(const A
             a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
         }
     };
-#pragma unroll
-    for (int d = 16; d <= 32; d <<= 1) {
-#pragma unroll
-        for (int h = 0; h < G; ++h) {
-            float ma, mb, la, lb;
-            both(m[h], d, ma, mb);
-            both(l[h], d, la, lb);
-            const float mn = fmaxf(ma, mb);
-            const float wa = __builtin_amdgcn_exp2f(ma - mn), wb = __builtin_amdgcn_exp2f(mb - mn);
-            l[h] = la * wa + lb * wb;
-            m[h] = mn;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                float xa, xb;
-                both(acc[h][i], d, xa, xb);
-                acc[h][i] = xa * wa + xb * wb;
-            }
-        }
-    }
-    // then the waves through LDS
-    constexpr int NW = kAttnThreads / kWave;
     __shared__ float sh_m[NW][G], sh_l[NW][G];
     __shared__ float sh_acc[NW][G][kD];
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (lane == 0) {
 #pragma unroll
-        for (int h = 0; h < G; ++h) { sh_m[wv][h] = m[h]; sh_l[wv][h] = l[h]; }
-    }
-    if (lane < 16) {
+    for (int s = 0; s < kSets; ++s) {
 #pragma unroll
-        for (int h = 0; h < G; ++h)
+        for (int d = 16; d <= 32; d <<= 1) {
+            float ma, mb, la, lb;
+            both(m[s], d, ma, mb);
+            both(l[s], d, la, lb);
+            const float mn = fmaxf(ma, mb);
+            const float wa = __builtin_amdgcn_exp2f(ma - mn), wb = __builtin_amdgcn_exp2f(mb - mn);
+            l[s] = la * wa + lb * wb;
+            m[s] = mn;
+            const float wah[4] = {dpp_f32<0x00>(wa), dpp_f32<0x55>(wa), dpp_f32<0xAA>(wa), dpp_f32<0xFF>(wa)};
+            const float wbh[4] = {dpp_f32<0x00>(wb), dpp_f32<0x55>(wb), dpp_f32<0xAA>(wb), dpp_f32<0xFF>(wb)};
 #pragma unroll
-            for (int i = 0; i < 8; ++i) sh_acc[wv][h][l16 * 8 + i] = acc[h][i];
+            for (int h = 0; h < (G < 4 ? G : 4); ++h)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    float xa, xb;
+                    both(acc[s][i][h], d, xa, xb);
+                    acc[s][i][h] = xa * wah[h] + xb * wbh[h];
+                }
+        }
+        // then the waves through LDS
+        if (lane < (G < 4 ? G : 4)) { sh_m[wv][s * 4 + lane] = m[s]; sh_l[wv][s * 4 + lane] = l[s]; }
+        if (lane < 16) {
+#pragma unroll
+            for (int h = 0; h < (G < 4 ? G : 4); ++h)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) sh_acc[wv][s * 4 + h][n * 8 + i] = acc[s][i][h];
+        }
     }
     __syncthreads();
 
@@ -410,8 +577,8 @@ __global__ __launch_bounds__(kD * GROUPS) void attn_decode_merge_kernel(const At
 // 4 heads, 8 problems of 1,664 slots 19.4/14.7/15.1, 8 of 5,248 20.7/19.0/19.5, 32 of 1,664 21.0/22.0/19.7; 8 heads
 // 25.6/17.8/17.4, 26.7/25.0/24.8, 27.0/30.8/25.1, 16 of 3,200 27.2/30.3/25.4.  Finer splits take more scratch; with
 // scratch for the coarse ones only, those are used.
-// wg_per_cu: 4 for the plain kernels, 3 for the RoPE instantiations (more registers).  The workspace
-// is sized for 4, which gives the most splits.
+// wg_per_cu: what the instantiation's registers leave room for (attn_decode_per_cu).  The workspace is sized for 4, which gives the
+// most splits.
 static int decode_splits(const ihip_shape &s, int n_blocks, int block, bool fine, int *slots_per_split, int wg_per_cu = 4)
 {
     const int n_cu = compute_units();
@@ -424,6 +591,14 @@ static int decode_splits(const ihip_shape &s, int n_blocks, int block, bool fine
     per = std::min(kAttnMaxSplit, std::max(least, per));
     *slots_per_split = per;
     return (total + per - 1) / per;
+}
+
+// Workgroups on a compute unit: waves per SIMD by the registers of the instantiation.  Eight heads, 16 sequences of 3,200 slots, splits for
+// four / for this many: bf16 45.1 / 41.0 us, E4M3 34.5 / 31.0, bf16 with RoPE 60.1 / 52.4.
+static int attn_decode_per_cu(int G, bool rope, bool fp8)
+{
+    if (G == 8) return fp8 && !rope ? 3 : 2;
+    return rope ? 3 : 4;
 }
 
 // scratch for the partial results of the fine or the coarse splits
@@ -477,7 +652,7 @@ int32_t launch_attn_decode(const ihip_shape &s, const ihip_tensor &q, const ihip
     a.block = block;
     a.block_log2 = __builtin_ctz(block);
     a.scale_log2e = sm_scale * 1.44269504088896340736f * (fp8 ? fmt->k_scale : 1.0f);
-    a.n_splits = decode_splits(s, n_blocks, block, fine, &a.slots_per_split, use_rope ? 3 : 4);
+    a.n_splits = decode_splits(s, n_blocks, block, fine, &a.slots_per_split, attn_decode_per_cu(a.ge.G, use_rope, fp8));
     const int P = s.B * s.Hkv;
     const int G = a.ge.G;
     a.part_ml = (float *)ws;
