@@ -79,6 +79,7 @@ __global__ __launch_bounds__(256) void prune_decode_nest_kernel(const PruneArgs 
     const bool across = nest.top >= 5;        // the waves of the workgroup meet at the end
     if (f0 >= n_keys && !across) return;
     __shared__ float sh_part[4][4][16];
+    __shared__ uint4 sh_rows[4 * 16 * decode_row_pieces(KV8)];
     auto position = [&](int f) { return f < n_keys && pr.lo + f < pr.hi ? pr.lo + f : -1; };
     NestPart whole{-INFINITY, -INFINITY, -INFINITY, -1};      // of the wave's 64 keys
     // chunk score of a part: max over the heads
@@ -102,14 +103,15 @@ __global__ __launch_bounds__(256) void prune_decode_nest_kernel(const PruneArgs 
     } else {
     const Rows rows(a, pr);
     uint4 raw[NT][kLoads];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int key = max(position(f0 + t * 16 + n), 0);        // as the loader of row n; without a key: key 0 of the sequence, which is there
+    {
+        // lane (n, kq) finds row 4 * kq + n % 4 of tile n / 4; without a key: key 0 of the sequence, which is there
+        const int key = max(position(f0 + (n >> 2) * 16 + kq * 4 + (n & 3)), 0);
         int page = 0;
         if constexpr (SRC == 2) page = rows.table[key >> rows.page_log2];
-#pragma unroll
-        for (int i = 0; i < kLoads; ++i) raw[t][i] = rows.load(rows.at(key, page), i * 64 + kq * 16);
+        const auto off = rows.at(key, page);
+        for_each_tile<NT>([&](auto t) { request_tile<t, KV8>(rows, off, n, raw[t]); });
     }
+    uint4 *staged = &sh_rows[wv * 16 * decode_row_pieces(KV8)];
     const int hd = G == 8 ? (n & 7) : n % G;
     bf16x8 q[PARTS][4];
     decode_query_operands<KV8, PARTS>(a.q + pr.b * a.q_sb + (int64_t)(pr.g * G + hd) * a.q_sh + (int64_t)pr.m * a.q_st, kq, rope,
@@ -118,6 +120,7 @@ __global__ __launch_bounds__(256) void prune_decode_nest_kernel(const PruneArgs 
     float s4[NT], s8[NT], s16[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
+        arrange_tile<KV8>(staged, n, kq, raw[t]);
         const f32x4 c = decode_products<KV8, PARTS>(raw[t], q);
         f32x4 sL = c, sR = c;
         if constexpr (ROPE) {

@@ -8,14 +8,19 @@
 // A wave walks 64 searches, one per lane: 64/G chunks x G heads, in four 16-row tiles (host tier: 16 searches, one tile).  Tile t, row r = 4*kq + i is owned
 // by lane (kq, n = 4t + i): the product's column n, rows 4*kq..+3 are in that lane's accumulator, so with column n
 // holding the query of head n % G the owner finds its own score in register n % 4 -- no value crosses lanes except the
-// row offsets, handed from the owners to the loading lanes (one shuffle per tile and level).
+// row offsets, handed from the owners to the lanes of their row group (register broadcasts within 16 lanes).
+//
+// Rows are fetched whole, by neighbouring lanes, and reach operand layout through LDS.  Fetched in operand layout a load names 16 rows
+// at once, 16 bytes of each to a lane whose neighbour wants another row: 64 look-ups in the L1 instead of 16 (8 with E4M3 rows), which was
+// the time of a search level.  Four sequences of 250K keys in E4M3 pages with relative RoPE, operand layout / whole rows (us): stages of
+// 256, 64, 16 and 4 keys 25.3 / 22.3, 20.0 / 17.3, 13.9 / 12.8, 13.8 / 11.8; one pass over 8K keys (prune_decode_nest.h) 5.7 / 4.8.
 // Relative style (see prune_relative.h): columns 0..7 hold q_L, 8..15 q_R; the two halves are exchanged by one row rotation.
 // The rotated queries are fp32, kept as three bf16 operands (value, rest, rest of the rest: 24 bits and more), so that a score is as
 // good as an fp32 one.
 //
 // Operand layout: lane (n, kq) holds 8 dims of row or column n; any assignment of dims to (step, kq) serves as long as both
-// sides agree.  bf16 rows: step ks, dims 32*ks + 8*kq.. (a 16-byte load per step, 64 contiguous bytes of 16 rows an
-// instruction).  E4M3 rows: a 16-byte load j brings dims 64*j + 16*kq..+15, steps 2j and 2j+1.
+// sides agree.  bf16 rows: step ks, dims 32*ks + 8*kq.. (one 16-byte piece).  E4M3 rows: piece j brings dims 64*j + 16*kq..+15,
+// steps 2j and 2j+1.
 #pragma once
 
 #include "prune_prefill.h"
@@ -67,7 +72,7 @@ __device__ inline void decode_query_operands(const uint16_t *q_row, int kq, cons
     }
 }
 
-// 16 rows x 16 columns; raw: this lane's loads of row n16 (bf16: one per step, E4M3: one per two steps)
+// 16 rows x 16 columns; raw: this lane's pieces of row n16 (bf16: one per step, E4M3: one per two steps)
 template <bool KV8, int PARTS>
 __device__ inline f32x4 decode_products(const uint4 (&raw)[KV8 ? 2 : 4], const bf16x8 (&q)[PARTS][4])
 {
@@ -95,11 +100,23 @@ __device__ inline float pick4(const f32x4 c, int i)      // c[i], in registers
     return (i & 2) ? b : a;
 }
 __device__ inline float row_ror8(float v) { return dpp_f32<0x128>(v); }
+// lane N of each row of 16, in all its lanes
 template <int N>
-__device__ inline int64_t row_lane(int64_t v)            // lane N of each row of 16, in all its lanes
+__device__ inline int row_lane(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x150 + N, 0xf, 0xf, true); }
+template <int N>
+__device__ inline uint32_t row_lane(uint32_t v) { return (uint32_t)row_lane<N>((int)v); }
+template <int N>
+__device__ inline int64_t row_lane(int64_t v)
 {
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)v, 0x150 + N, 0xf, 0xf, true), hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), 0x150 + N, 0xf, 0xf, true);
-    return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+    return (int64_t)(((uint64_t)row_lane<N>((uint32_t)(v >> 32)) << 32) | row_lane<N>((uint32_t)v));
+}
+template <int N, class F>
+__device__ inline void for_each_tile(F f)                // f(0), ..., f(N - 1), each a constant
+{
+    if constexpr (N > 0) {
+        for_each_tile<N - 1>(f);
+        f(std::integral_constant<int, N - 1>{});
+    }
 }
 __device__ inline float other_quad(float v) { return dpp_f32<0x1B>(dpp_f32<0x141>(v)); }   // lane n ^ 4 of a row: half mirror, then each quad reversed
 
@@ -151,6 +168,39 @@ struct DecodeRows<1, false> {
     }
 };
 
+// The 16 rows of tile T on their way: row 4 * kq + i, whole, by the lanes of row group kq, whose lane 4 * T + i has its offset in `off`.
+// (All lanes take part: a lane that is switched off hands out zero.)
+template <int T, bool KV8, class Rows>
+__device__ inline void request_tile(const Rows &rows, typename Rows::off_t off, int n, uint4 (&raw)[KV8 ? 2 : 4])
+{
+    const auto at0 = row_lane<4 * T>(off), at1 = row_lane<4 * T + 1>(off), at2 = row_lane<4 * T + 2>(off), at3 = row_lane<4 * T + 3>(off);
+    if constexpr (KV8) {
+        raw[0] = rows.load(n < 8 ? at0 : at1, (n & 7) * 16);
+        raw[1] = rows.load(n < 8 ? at2 : at3, (n & 7) * 16);
+    } else {
+        raw[0] = rows.load(at0, n * 16);
+        raw[1] = rows.load(at1, n * 16);
+        raw[2] = rows.load(at2, n * 16);
+        raw[3] = rows.load(at3, n * 16);
+    }
+}
+// ... and into operand layout through `tile`, 16 rows of the wave's own in LDS
+template <bool KV8>
+__device__ inline void arrange_tile(uint4 *tile, int n, int kq, uint4 (&raw)[KV8 ? 2 : 4])
+{
+    constexpr int kLoads = KV8 ? 2 : 4, kPieces = KV8 ? 8 : 16;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+        const int r = 4 * kq + (KV8 ? 2 * i + (n >> 3) : i);
+        tile[r * kPieces + ((n ^ r) & (kPieces - 1))] = raw[i];           // piece c of row r at c ^ r
+    }
+    asm volatile("" ::: "memory");            // lanes read what other lanes of the wave wrote (LDS keeps the order)
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) raw[i] = tile[n * kPieces + (((i * 4 + kq) ^ n) & (kPieces - 1))];
+    asm volatile("" ::: "memory");
+}
+constexpr int decode_row_pieces(bool fp8) { return fp8 ? 8 : 16; }
+
 // What a wave without a single chunk writes for its n <= 64 slots j0..
 template <int G>
 __device__ inline void write_no_chunks(const PruneArgs &a, const Problem &pr, int p, int j0, int n)
@@ -189,7 +239,7 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
     using Rows = DecodeRows<SRC, NARROW>;
     using off_t = typename Rows::off_t;
     __shared__ int32_t sh_pages[SRC == 2 ? 4 * kChunks * kDecodePages : 1];
-    __shared__ uint4 sh_rows[SRC == 1 ? kDecodeTileWaves * 2 * 16 * (KV8 ? 8 : 16) : 1];
+    __shared__ uint4 sh_rows[kDecodeTileWaves * 16 * decode_row_pieces(KV8)];
     const int p = a.grid.problem();
     const Problem pr = problem_of(a.ge, p);
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -247,40 +297,11 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
             return rows.at(pos, 0);
         }
     };
-    auto fetch = [&](off_t off, uint4 (&raw)[kLoads]) {
-#pragma unroll
-        for (int i = 0; i < kLoads; ++i) raw[i] = rows.load(off, i * 64 + kq * 16);
+    uint4 *staged = &sh_rows[wv * 16 * decode_row_pieces(KV8)];
+    auto products = [&](uint4 (&raw)[kLoads]) {
+        arrange_tile<KV8>(staged, n, kq, raw);
+        return decode_products<KV8, PARTS>(raw, q);
     };
-    // Host tier: the 16 rows of the tile, each by neighbouring lanes, 256 or 128 bytes in order, and into operand layout through LDS.
-    // (In operand layout an instruction takes 16 bytes of 16 rows at a time, which the host link sees as requests of their own: 16K
-    // bf16 keys, 32 heads on 8, most rows missed, 685 us a layer instead of 564.)  The lanes of a row group take the rows that its first
-    // four lanes own.
-    constexpr int kPieces = KV8 ? 8 : 16;
-    auto request = [&](off_t off, uint4 (&raw)[kLoads]) {
-        // (handed out by all lanes, before any choice between them: a lane that is switched off hands out zero)
-        const off_t at0 = row_lane<0>(off), at1 = row_lane<1>(off), at2 = row_lane<2>(off), at3 = row_lane<3>(off);
-        if constexpr (KV8) {
-            raw[0] = rows.load(n < 8 ? at0 : at1, (n & 7) * 16);
-            raw[1] = rows.load(n < 8 ? at2 : at3, (n & 7) * 16);
-        } else {
-            raw[0] = rows.load(at0, n * 16);
-            raw[1] = rows.load(at1, n * 16);
-            raw[2] = rows.load(at2, n * 16);
-            raw[3] = rows.load(at3, n * 16);
-        }
-    };
-    auto arrange = [&](uint4 *tile, uint4 (&raw)[kLoads]) {
-#pragma unroll
-        for (int i = 0; i < kLoads; ++i) {
-            const int r = 4 * kq + (KV8 ? 2 * i + (n >> 3) : i);
-            tile[r * kPieces + ((n ^ r) & (kPieces - 1))] = raw[i];           // piece c of row r at c ^ r
-        }
-        asm volatile("" ::: "memory");        // lanes read what other lanes of the wave wrote (LDS keeps the order)
-#pragma unroll
-        for (int i = 0; i < kLoads; ++i) raw[i] = tile[n * kPieces + (((i * 4 + kq) ^ n) & (kPieces - 1))];
-        asm volatile("" ::: "memory");
-    };
-    uint4 *staged = &sh_rows[SRC == 1 ? wv * 2 * 16 * kPieces : 0];           // two tiles
     // a tile's products -> the owners' scores (sL: against the column's query, or q_L; sR: against q_R).  i: the owner's
     // register; ix: the register that the owner in lane n ^ 8 wants
     auto owned = [&](const f32x4 c, int i, int ix, float &sL, float &sR) {
@@ -300,18 +321,11 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
     // scores of the lanes' rows at `off`
     auto score = [&](off_t off, float &sL, float &sR) {
         uint4 raw[NT][kLoads];
-        if constexpr (SRC == 1) {
-            request(off, raw[0]);
-            arrange(staged, raw[0]);
-            owned(decode_products<KV8, PARTS>(raw[0], q), n & 3, n & 3, sL, sR);
-            return;
-        }
-#pragma unroll
-        for (int t = 0; t < NT; ++t) fetch(__shfl(off, (n >> 2) * 16 + 4 * t + (n & 3), 64), raw[t]);
+        for_each_tile<NT>([&](auto t) { request_tile<t, KV8>(rows, off, n, raw[t]); });
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             float l, rr;
-            owned(decode_products<KV8, PARTS>(raw[t], q), n & 3, n & 3, l, rr);
+            owned(products(raw[t]), n & 3, n & 3, l, rr);
             sL = quad == t ? l : sL;
             sR = quad == t ? rr : sR;
         }
@@ -326,23 +340,24 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
         const int mid = has_right ? base + half : -1;
         const int slot0 = rows.src.slot_of(max(base, 0)), slot1 = rows.src.slot_of(max(mid, 0));
         uint4 r0[kLoads], r1[kLoads];
-        request(rows.at(base, slot0), r0);
-        request(rows.at(mid, slot1), r1);
-        arrange(staged, r0);
-        arrange(staged + 16 * kPieces, r1);
-        owned(decode_products<KV8, PARTS>(r0, q), n & 3, n & 3, left, value);
-        owned(decode_products<KV8, PARTS>(r1, q), n & 3, n & 3, rL, rR);
+        request_tile<0, KV8>(rows, rows.at(base, slot0), n, r0);
+        request_tile<0, KV8>(rows, rows.at(mid, slot1), n, r1);
+        owned(products(r0), n & 3, n & 3, left, value);
+        owned(products(r1), n & 3, n & 3, rL, rR);
     } else {
         const off_t at0 = row_at(base), at1 = row_at(has_right ? base + half : base);
         if constexpr (G == 4) {
             // The first key of a chunk and of its right half are the same rows for all heads: one tile holds the first keys of the
             // wave's 16 chunks, row 4*kq + t that of chunk (t, kq), so that the owner finds its score in register t.
+            auto first_of = [&](off_t at) {           // lane t of a row group: the offset of its lane 4 * t
+                const off_t a0 = row_lane<0>(at), a1 = row_lane<4>(at), a2 = row_lane<8>(at), a3 = row_lane<12>(at);   // (by all lanes)
+                return (n & 2) ? ((n & 1) ? a3 : a2) : (n & 1) ? a1 : a0;
+            };
             uint4 r0[kLoads], r1[kLoads];
-            const int src = (n >> 2) * 16 + 4 * (n & 3);
-            fetch(__shfl(at0, src, 64), r0);
-            fetch(__shfl(at1, src, 64), r1);
-            owned(decode_products<KV8, PARTS>(r0, q), quad, quad ^ 2, left, value);
-            owned(decode_products<KV8, PARTS>(r1, q), quad, quad ^ 2, rL, rR);
+            request_tile<0, KV8>(rows, first_of(at0), n, r0);
+            request_tile<0, KV8>(rows, first_of(at1), n, r1);
+            owned(products(r0), quad, quad ^ 2, left, value);
+            owned(products(r1), quad, quad ^ 2, rL, rR);
         } else {
             score(at0, left, value);
             score(at1, rL, rR);
@@ -368,8 +383,7 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
 }
 
 // Chunks of four keys: the search reads every row of a chunk anyway (all four unless the heads agree), so a tile is four
-// whole chunks, one load of which brings 64 bytes of each of 16 rows in order, and a head's four scores of a
-// chunk are the four registers of one lane: no dependent loads, nothing crosses lanes.
+// whole chunks, and a head's four scores of a chunk are the four registers of one lane: no dependent loads.
 template <int G, bool ROPE, int SRC, bool KV8, bool NARROW>
 __global__ __launch_bounds__(256, !ROPE && !KV8 ? 5 : 1) void prune_decode_four_kernel(const PruneArgs a, const RopeView rope)
 {
@@ -385,18 +399,12 @@ __global__ __launch_bounds__(256, !ROPE && !KV8 ? 5 : 1) void prune_decode_four_
     const int j0 = (a.grid.part() * (blockDim.x >> 6) + wv) * NT * 4;
     if (j0 >= a.max_chunks) return;
     const Rows rows(a, pr);
-    // as the loader of row n: key n % 4 of chunk n / 4 of the tile (its first key where the chunk is cut short; without a
-    // chunk key 0 of the sequence, unless the whole wave has none: see prune_decode_tile_kernel)
-    int key[NT];
-    bool any = false;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int j = j0 + t * 4 + (n >> 2);
-        const int start = j < a.max_chunks ? slot_start(pr, a.parent_starts, a.n_parent, a.ratio_log2, a.chunk, p, j) : -1;
-        key[t] = start >= 0 ? (start + (n & 3) < pr.hi ? start + (n & 3) : start) : 0;
-        any = any || start >= 0;
-    }
-    if (__ballot(any) == 0) {
+    // Lane (n, kq) finds row 4 * kq + n % 4 of tile n / 4: key n % 4 of chunk kq of the tile (its first key where the chunk is cut
+    // short; without a chunk key 0 of the sequence, unless the whole wave has none: see prune_decode_tile_kernel)
+    const int j_own = j0 + (n >> 2) * 4 + kq;
+    const int start_own = (n >> 2) < NT && j_own < a.max_chunks ? slot_start(pr, a.parent_starts, a.n_parent, a.ratio_log2, a.chunk, p, j_own) : -1;
+    const int key = start_own >= 0 ? (start_own + (n & 3) < pr.hi ? start_own + (n & 3) : start_own) : 0;
+    if (__ballot(start_own >= 0) == 0) {
         write_no_chunks<G>(a, pr, p, j0, NT * 4);
         return;
     }
@@ -404,19 +412,20 @@ __global__ __launch_bounds__(256, !ROPE && !KV8 ? 5 : 1) void prune_decode_four_
     bf16x8 q[PARTS][4];
     decode_query_operands<KV8, PARTS>(a.q + pr.b * a.q_sb + (int64_t)(pr.g * G + hd) * a.q_sh + (int64_t)pr.m * a.q_st, kq, rope,
                                       a.ge.n_stream + (n < 8 ? 1 : 0), q);
+    __shared__ uint4 sh_rows[kDecodeTileWaves * 16 * decode_row_pieces(KV8)];
+    uint4 *staged = &sh_rows[wv * 16 * decode_row_pieces(KV8)];
     uint4 raw[NT][kLoads];
+    int page = 0;
+    if constexpr (SRC == 2) page = rows.table[key >> rows.page_log2];
+    const auto off_own = rows.at(key, page);
+    for_each_tile<NT>([&](auto t) { request_tile<t, KV8>(rows, off_own, n, raw[t]); });
+    int starts[NT];
+    for_each_tile<NT>([&](auto t) { starts[t] = row_lane<4 * t>(start_own); });
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-        int page = 0;
-        if constexpr (SRC == 2) page = rows.table[key[t] >> rows.page_log2];
-#pragma unroll
-        for (int i = 0; i < kLoads; ++i) raw[t][i] = rows.load(rows.at(key[t], page), i * 64 + kq * 16);
-    }
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int j = j0 + t * 4 + kq;        // as the owner: chunk kq of the tile, column n's head
-        const int start = j < a.max_chunks ? slot_start(pr, a.parent_starts, a.n_parent, a.ratio_log2, a.chunk, p, j) : -1;
+        const int j = j0 + t * 4 + kq, start = starts[t];       // as the owner: chunk kq of the tile, column n's head
         const int len = start >= 0 ? min(4, pr.hi - start) : 0;
+        arrange_tile<KV8>(staged, n, kq, raw[t]);
         const f32x4 c = decode_products<KV8, PARTS>(raw[t], q);
         f32x4 sL = c, sR = c;
         if constexpr (ROPE) {

@@ -241,7 +241,7 @@ void launch_prune_prefill_fp8(const PruneArgs &a, int P, int b_q, const RopeView
 // Which decode stages (no RoPE or the relative style) go to the matrix-core kernels of
 // prune_decode_tile.h.  The lines are those of K through strides or pages; the host tier, whose link is the bound, follows
 // contiguous rows, so that its scores are the same bits.  Their waves do a fifth of the vector instructions for 64 searches at a time, but a level of
-// theirs is a longer chain, their loads take 64 bytes of 16 rows where the vector kernels take whole rows, and their
+// theirs is a longer chain, and their
 // workgroups are a quarter (4 heads) or half as many: they win where instructions are the bound (128-byte rows, two rotated
 // queries, page lookups, 8 heads) and workgroups are no longer scarce, so the lines are drawn in workgroups of theirs per compute
 // unit.  Beside each: time of the vector kernel / time of theirs, below the line and from it on (stages of 1 to 256 keys in layers
