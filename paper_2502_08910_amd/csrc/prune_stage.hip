@@ -14,8 +14,12 @@
 
 namespace ihip {
 
-// KV8: K rows are 128 bytes of E4M3 (8 bytes per lane); the dot products run on the decoded values
-// and the chunk score is multiplied by the tensor's scale.
+// KV8: K rows are 128 bytes of E4M3 (8 bytes per lane), widened exactly to bf16; the chunk score is multiplied by the tensor's scale.
+//
+// The dot products are four v_dot2_f32_bf16 a lane (exact products, fp32 sums; error against 64 bits as with multiply-adds of widened
+// values, 4.7e-8 rms) instead of 16 instructions: a search level of a small launch is its instructions as much as its
+// rows.  Multiply-adds / dot2 (us): 256 chunks of 64 bf16 keys a problem, 32 heads on 8 6.0 / 5.4, 64 on 8 8.5 / 7.5; 8 heads, chunks of 16
+// 39.2 / 34.6; large first stages 0-2 %.
 template <int G, int U, int SRC, bool KV8>
 __global__ __launch_bounds__(256) void prune_decode_kernel(const PruneArgs a)
 {
@@ -27,13 +31,13 @@ __global__ __launch_bounds__(256) void prune_decode_kernel(const PruneArgs a)
     const int j0 = (a.grid.part() * 16 + grp) * U;
     if (j0 >= a.max_chunks) return;
 
-    // this lane's 8 dims of the G query vectors
-    float qf[G][8];
+    // this lane's 8 dims of the G query vectors, packed
+    uint4 qp[G];
     {
         const uint16_t *qb = a.q + pr.b * a.q_sb + (int64_t)(pr.g * G) * a.q_sh +
                              (int64_t)(pr.m * a.ge.b_q) * a.q_st;
 #pragma unroll
-        for (int h = 0; h < G; ++h) unpack8(load_row16(qb, h * a.q_sh, l16), qf[h]);
+        for (int h = 0; h < G; ++h) qp[h] = load_row16(qb, h * a.q_sh, l16);
     }
     const typename KeySource<SRC>::type src = KeySource<SRC>::make(a, pr);
     const bool leader = l16 == 0;
@@ -102,8 +106,8 @@ __global__ __launch_bounds__(256) void prune_decode_kernel(const PruneArgs a)
         for (int u = 0; u < U; ++u) {
 #pragma unroll
             for (int h = 0; h < G; ++h) {
-                const float s0 = row16_sum(dot8(r0[u], qf[h]));
-                const float s1 = row16_sum(dot8(r1[u], qf[h]));
+                const float s0 = row16_sum(dot8_bf16(as_bf16x8(r0[u]), qp[h]));
+                const float s1 = row16_sum(dot8_bf16(as_bf16x8(r1[u]), qp[h]));
                 const bool right = (mid >= 1 && mid < len[u]) && s1 > s0;   // strict: tie keeps left
                 off[u][h] = right ? mid : 0;
                 sigma[u][h] = right ? s1 : s0;
@@ -134,7 +138,7 @@ __global__ __launch_bounds__(256) void prune_decode_kernel(const PruneArgs a)
         for (int u = 0; u < U; ++u) {
 #pragma unroll
             for (int h = 0; h < G; ++h) {
-                const float s = row16_sum(dot8(r[u][h], qf[h]));
+                const float s = row16_sum(dot8_bf16(as_bf16x8(r[u][h]), qp[h]));
                 if (ok[u][h] && s > sigma[u][h]) {
                     off[u][h] += half;
                     sigma[u][h] = s;
