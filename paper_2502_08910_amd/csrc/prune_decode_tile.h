@@ -463,12 +463,13 @@ static void launch_decode_tile_n(PruneArgs a, const RopeView &rope, int P, hipSt
     a.grid = prune_grid(a, P, per_problem, KV8, ROPE);
     const dim3 grid = a.grid.dims(P, per_problem), block(64 * kDecodeTileWaves);
     KernelTimer timer(stage_name(kNamePruneDecode, a.parent_starts == nullptr, a.chunk), st);
-    // contiguous bf16 rows without RoPE: only chunks of four with eight heads come here (decode_on_tiles)
-    constexpr bool kPlain = !ROPE && SRC == 0 && !KV8;
-    if constexpr (SRC != 1 && (!kPlain || G == 8))
-        if (a.chunk == 4) hipLaunchKernelGGL((prune_decode_four_kernel<G, ROPE, SRC, KV8, NARROW>), grid, block, 0, st, a, rope);
-    if constexpr (!kPlain)
-        if (SRC == 1 || a.chunk != 4) hipLaunchKernelGGL((prune_decode_tile_kernel<G, ROPE, SRC, KV8, NARROW>), grid, block, 0, st, a, rope);
+    if constexpr (SRC != 1) {
+        if (a.chunk == 4) {
+            hipLaunchKernelGGL((prune_decode_four_kernel<G, ROPE, SRC, KV8, NARROW>), grid, block, 0, st, a, rope);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((prune_decode_tile_kernel<G, ROPE, SRC, KV8, NARROW>), grid, block, 0, st, a, rope);
 }
 
 template <bool ROPE, int SRC, bool KV8, bool NARROW>

@@ -196,11 +196,9 @@ static void launch_prefill(const PruneArgs &a, int P, int64_t max_seq_len, const
 }
 
 // U chunks per 16-lane group.  What counts is the number of row loads in flight per SIMD, waves x
-// 4 groups x U x G, and how finely the work is cut: U = 1 (64 registers, 8 waves per SIMD) is best
-// for every later stage, for small problems, for E4M3 rows and for pages; U = 3 (127 registers, 4
-// waves, half as many loads again in flight) wins on the large first stage over contiguous bf16 rows
-// (cfg3: 278 us against 283 us with U = 1 and 294 us with U = 2, whose 97 registers miss the fifth
-// wave by one).
+// 4 groups x U x G, and how finely the work is cut: U = 1 is best for every later stage, for small problems, for E4M3 rows and
+// for pages; U = 3 (half as many loads again in flight) wins on the large first stage over contiguous bf16 rows with one or two heads a
+// group (with more it goes to the matrix cores: four heads, 8 x 1M keys, chunks of 256 278 us with U = 3, 262 there).
 template <int G, int U>
 static void launch_decode_u(PruneArgs a, int P, bool fp8, hipStream_t st)
 {
@@ -229,11 +227,14 @@ static void launch_decode_u(PruneArgs a, int P, bool fp8, hipStream_t st)
 template <int G>
 static void launch_decode(const PruneArgs &a, int P, bool fp8, hipStream_t st)
 {
-    const bool plain = !fp8 && a.paged.block_table == nullptr && a.bank.page_table == nullptr;
-    if (plain && a.parent_starts == nullptr && a.chunk >= 128 && (int64_t)P * a.max_chunks >= 65536)
-        launch_decode_u<G, 3>(a, P, fp8, st);
-    else
-        launch_decode_u<G, 1>(a, P, fp8, st);
+    if constexpr (G <= 2) {
+        const bool plain = !fp8 && a.paged.block_table == nullptr && a.bank.page_table == nullptr;
+        if (plain && a.parent_starts == nullptr && a.chunk >= 128 && (int64_t)P * a.max_chunks >= 65536) {
+            launch_decode_u<G, 3>(a, P, fp8, st);
+            return;
+        }
+    }
+    launch_decode_u<G, 1>(a, P, fp8, st);
 }
 
 void launch_prune_decode_tile(const PruneArgs &a, int P, bool fp8, const RopeView *rope, int64_t max_seq_len, hipStream_t st);
@@ -245,45 +246,42 @@ void launch_prune_prefill_fp8(const PruneArgs &a, int P, int b_q, const RopeView
 // Which decode stages (no RoPE or the relative style) go to the matrix-core kernels of
 // prune_decode_tile.h.  The lines are those of K through strides or pages; the host tier, whose link is the bound, follows
 // contiguous rows, so that its scores are the same bits.  Their waves do a fifth of the vector instructions for 64 searches at a time, but a level of
-// theirs is a longer chain, and their
-// workgroups are a quarter (4 heads) or half as many: they win where instructions are the bound (128-byte rows, two rotated
-// queries, page lookups, 8 heads) and workgroups are no longer scarce, so the lines are drawn in workgroups of theirs per compute
-// unit.  Beside each: time of the vector kernel / time of theirs, below the line and from it on (stages of 1 to 256 keys in layers
-// of 1 to 32 sequences of 16K to 1M keys, 4 and 8 KV heads, 256 CUs).
+// theirs is a longer chain, and their workgroups are a quarter (4 heads) or half as many: they win once workgroups are no longer
+// scarce, the sooner the more instructions a row takes (rotated queries, 8 heads, widening, pages), so the lines are drawn in workgroups of
+// theirs per compute unit.  Beside each: time of the vector kernel / time of theirs, below the line and from it on (580 stages in
+// layers and alone of 1 to 31 sequences of 11K to 1M keys, 8 KV heads, 256 CUs; the timing of one stage varies by up to 5 %).
 static bool decode_on_tiles(const PruneArgs &a, int P, bool fp8, bool relative)
 {
     const int G = a.ge.G, chunk = a.chunk;
     if (G < 4) return false;                 // one or two heads: the vector kernels won at every size
-    const bool paged = a.paged.block_table != nullptr, many = G == 8;
+    const bool paged = a.paged.block_table != nullptr, many = G == 8, first = a.parent_starts == nullptr;
     const int per_wg = decode_tile_chunks(G, chunk, relative, fp8) * kDecodeTileWaves;
     const int64_t wgs = (int64_t)P * ((a.max_chunks + per_wg - 1) / per_wg), cu = compute_units();
     auto at_least = [&](double per_cu) { return (double)wgs >= per_cu * (double)cu; };
-    auto at_most = [&](double per_cu) { return (double)wgs <= per_cu * (double)cu; };
     if (chunk == 4) {                        // prune_decode_four_kernel
-        if (many) return at_least(1);        // 0.78-1.18 / 1.00-4.22
-        if (!fp8 && !paged && !relative) return false;                            // 0.72-0.95 throughout
-        return at_least(relative && !fp8 ? 4 : 2);                                // 0.73-1.08 / 1.01-1.95
+        if (many) return at_least(0.25);                                          // 1.10-6.0
+        if (paged) return at_least(0.5);                                          // 0.95 / 1.04-2.6
+        if (fp8 || relative) return at_least(0.75);                               // 0.91-0.98 / 1.10-2.1
+        return at_least(4);                                                       // 0.89 / 1.04-1.05
     }
-    if (relative && many && chunk < 4) return at_least(5);                        // 0.75-1.26 / 0.97-1.38
-    if (relative && paged) return at_least(!many ? 1.5 : fp8 && chunk >= 16 ? 0.75 : 1.25);      // 0.64-1.17 / 0.99-2.2
-    if (relative && fp8) return at_least(many ? 1.25 : 1.875);                    // 0.55-1.08 / 1.01-2.4
-    if (relative) {
-        if (chunk <= 16) return at_least(1.5);                                    // 0.67-1.05 / 0.98-1.5
-        return many && chunk <= 64 && at_least(5);                                // 0.70-1.22 / 1.02-1.25; longer ones 0.55-1.09
+    if (chunk < 4) {                         // (lines from before the rows were fetched whole)
+        if (many) return relative ? at_least(5) : fp8 && at_least(4);             // 0.75-1.26 / 0.97-1.38, 0.91-1.14 / 1.03-1.54
+        if (relative) return at_least(paged || !fp8 ? 1.5 : 1.875);               // 0.64-1.17 / 0.98-1.5
+        return (fp8 || paged) && at_least(2);                                     // 0.86-1.14 / 1.03-1.54
     }
-    if (fp8 && chunk < 4) return at_least(many ? 4 : 2);                          // 0.91-1.14 / 1.03-1.54
-    if (fp8 && paged) return at_least(0.25);                                      // 1.03-1.88
-    if (fp8) return a.parent_starts != nullptr && at_least(many ? 0.75 : 1.5);    // 0.89-1.2 / 0.96-1.47; first stages 0.93-1.36
-    if (!paged) return false;                                                     // 0.44-1.06 throughout
-    if (!many) {
-        if (chunk <= 16) return at_least(2);                                      // 0.86-1.07 / 1.03-1.32
-        // long chunks: a tie at best, except where two workgroups on every CU leave none idle and none with one more
-        // (1.06-1.19; 0.81-0.95 between one and two, 0.80-1.07 beyond)
-        return at_least(1.875) && at_most(2);
+    if (many) {
+        if (relative) return at_least(fp8 ? (paged ? 1 : 1.25) : 0.75);           // 0.95-1.17 / 1.05-4.4
+        if (fp8) return at_least(0.25);                                           // 0.98-3.5
+        if (paged) return at_least(0.75);                                         // 0.91 / 0.99-1.15
+        return first && at_least(2);                                              // 0.88-1.01 / 1.02-1.08; later stages 0.89-1.00
     }
-    if (chunk < 4) return false;                                                  // 0.79-1.02 throughout
-    if (chunk < 16) return at_least(3);                                           // 0.94-1.03 / 1.10-1.18
-    return (at_least(0.75) && at_most(1)) || at_least(2.5);                       // 0.94-1.09, 1.02-1.16; between them 0.89-1.05, 0.93-1.26
+    if (paged) {
+        if (fp8) return at_least(relative ? 0.6 : 0.25);                          // 0.89-1.07 / 1.03-2.3, 1.05-3.4
+        return at_least(relative || first ? 0.75 : 1);                            // 0.80-1.05 / 0.91-1.57; without RoPE 1.03 on the average
+    }
+    if (fp8) return at_least(relative ? 0.8 : 0.6);                               // 0.70-0.83 / 1.00-1.9, 0.88-1.01 / 1.02-1.38
+    if (relative) return at_least(first ? 3 : 1);                                 // 0.91-0.99 / 1.00-1.06, 0.68-1.02 / 1.00-1.24
+    return first && at_least(1.25);                                               // 1.01-1.06; later stages 0.78-1.01
 }
 
 // nest: score this decode stage and the ones after it together (no host tier, no chunk-indexed style).  like_nest: the host tier's stage of
