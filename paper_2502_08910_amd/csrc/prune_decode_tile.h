@@ -475,6 +475,10 @@ static void launch_decode_tile_n(PruneArgs a, const RopeView &rope, int P, hipSt
 template <bool ROPE, int SRC, bool KV8, bool NARROW>
 static void launch_decode_tile_g(const PruneArgs &a, const RopeView &rope, int P, hipStream_t st)
 {
+    if constexpr (KV8) {                      // one and two heads: E4M3 rows only (decode_on_tiles)
+        if (a.ge.G == 1) return launch_decode_tile_n<1, ROPE, SRC, KV8, NARROW>(a, rope, P, st);
+        if (a.ge.G == 2) return launch_decode_tile_n<2, ROPE, SRC, KV8, NARROW>(a, rope, P, st);
+    }
     if (a.ge.G == 4) launch_decode_tile_n<4, ROPE, SRC, KV8, NARROW>(a, rope, P, st);
     else launch_decode_tile_n<8, ROPE, SRC, KV8, NARROW>(a, rope, P, st);
 }

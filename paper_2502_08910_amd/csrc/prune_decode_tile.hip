@@ -3,7 +3,7 @@
 
 namespace ihip {
 
-// G in {4, 8}, K through strides or pages (the caller checks); rope: relative style, or nullptr
+// K through strides or pages, four or eight heads (E4M3 rows: any number; the caller checks); rope: relative style, or nullptr
 void launch_prune_decode_tile(const PruneArgs &a, int P, bool fp8, const RopeView *rope, int64_t max_seq_len, hipStream_t st)
 {
     const RopeView none{nullptr, nullptr, 0};

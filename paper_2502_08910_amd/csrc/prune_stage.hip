@@ -248,16 +248,22 @@ void launch_prune_prefill_fp8(const PruneArgs &a, int P, int b_q, const RopeView
 // contiguous rows, so that its scores are the same bits.  Their waves do a fifth of the vector instructions for 64 searches at a time, but a level of
 // theirs is a longer chain, and their workgroups are a quarter (4 heads) or half as many: they win once workgroups are no longer
 // scarce, the sooner the more instructions a row takes (rotated queries, 8 heads, widening, pages), so the lines are drawn in workgroups of
-// theirs per compute unit.  Beside each: time of the vector kernel / time of theirs, below the line and from it on (580 stages in
+// theirs per compute unit.  Beside each: time of the vector kernel / time of theirs, below the line and from it on (800 stages in
 // layers and alone of 1 to 31 sequences of 11K to 1M keys, 8 KV heads, 256 CUs; the timing of one stage varies by up to 5 %).
 static bool decode_on_tiles(const PruneArgs &a, int P, bool fp8, bool relative)
 {
     const int G = a.ge.G, chunk = a.chunk;
-    if (G < 4) return false;                 // one or two heads: the vector kernels won at every size
     const bool paged = a.paged.block_table != nullptr, many = G == 8, first = a.parent_starts == nullptr;
     const int per_wg = decode_tile_chunks(G, chunk, relative, fp8) * kDecodeTileWaves;
     const int64_t wgs = (int64_t)P * ((a.max_chunks + per_wg - 1) / per_wg), cu = compute_units();
     auto at_least = [&](double per_cu) { return (double)wgs >= per_cu * (double)cu; };
+    if (G < 4) {                             // one or two heads: a row of bf16 keys takes too few instructions (0.44-1.08 throughout)
+        if (!fp8 || chunk < 4) return false;
+        if (chunk == 4) return at_least(2);                                       // 0.83-1.24 / 0.99-1.9
+        if (paged) return at_least(relative ? 1.25 : 1);                          // 0.50-1.04, 0.65-0.95 / 1.06-2.0
+        if (relative && first && G == 1) return chunk < 128 && at_least(3);       // 0.56-0.95 / 1.26; longer ones go three at a time
+        return at_least(1.25);                                                    // 0.56-1.19 / 0.99-1.5
+    }
     if (chunk == 4) {                        // prune_decode_four_kernel
         if (many) return at_least(0.25);                                          // 1.10-6.0
         if (paged) return at_least(0.5);                                          // 0.95 / 1.04-2.6
