@@ -9,8 +9,13 @@
 // exactly by (score descending, slot ascending).  Any range serves for the bins, since scores beyond it go into the outermost
 // ones: it is that of 64 scores of the stage, and half as much again above (more is kept of low scores than of high ones), so
 // that no pass over all of them and no exchange between the waves is needed for it.  512 bins are what a wave can sum by
-// itself, so every wave finds the K-th best's bin without a barrier.  Heavy ties (more candidates in that bin than
-// threads) go through the radix selection of block_select.h.  Four barriers a stage.
+// itself, and so are the few candidates of a bin, one to a lane: every wave finds the K-th best's bin and the last slot that is kept of it
+// without a barrier.  Heavy ties (more candidates in that bin than lanes) go through the radix selection of block_select.h.  Four
+// barriers a stage.  A wave's candidates lie together, item after item, so that ballots put the kept ones in order.
+//
+// What bounds it is a chain of latencies, of which code that runs for the first time is a part: instructions come from beyond the
+// instruction cache, so a stage's code is short and the same for all stages.  Two stages of 2,048 candidates, 512 kept (us): candidates
+// ranked by their owners, a loop for each item, scores fetched in three turns 14.2; this way 8.8; 256 candidates each 6.8 / 6.0.
 #include "select_chain.h"
 
 namespace ihip {
@@ -28,7 +33,7 @@ struct ChainShared {
     float score[kChainMaxScores];
     int32_t index[2][kChainMaxKeep];          // what a stage kept: slots in its score row, which is the middle range in order
     uint32_t hist[kChainMaxStages][kChainBins];
-    uint2 cand[kChainThreads];                           // key and candidate
+    uint2 cand[64];                           // key and slot
     uint32_t ncand[kChainMaxStages], total[kChainThreads / 64];
     SelectScratch<kChainThreads> scratch;
 };
@@ -45,7 +50,7 @@ template <int ITEMS>
 __device__ inline int chain_stage(const ChainPlan &c, int s, int n, int n_from, const float *score, float low, float scale, ChainShared &sh)
 {
     constexpr int NT = kChainThreads, kWaves = NT / 64;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int32_t *from_index = sh.index[(s & 1) ^ 1];
     int32_t *to_index = sh.index[s & 1];
     uint32_t *hist = sh.hist[s];
@@ -53,78 +58,68 @@ __device__ inline int chain_stage(const ChainPlan &c, int s, int n, int n_from, 
     // candidate i: its slot in the score row
     auto slot_of = [&](int i) { return s > 0 ? (from_index[i >> ratio_log2] << ratio_log2) | (i & mask) : i; };
     const int limit = s > 0 ? min(n, n_from << ratio_log2) : n;
-    const int i0 = tid * ITEMS;
+    const int i0 = wv * 64 * ITEMS + lane;    // a wave's candidates lie together, item k of all lanes after item k - 1
     float v[ITEMS];
     int b[ITEMS], slot[ITEMS];
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) slot[i] = slot_of(i0 + i < limit ? i0 + i : 0);
+    for (int k = 0; k < ITEMS; ++k) slot[k] = slot_of(i0 + 64 * k < limit ? i0 + 64 * k : 0);
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) v[i] = i0 + i < limit ? score[slot[i]] : -INFINITY;
+    for (int k = 0; k < ITEMS; ++k) v[k] = i0 + 64 * k < limit ? score[slot[k]] : -INFINITY;
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        b[i] = v[i] > -INFINITY ? max(0, min(kChainBins - 1, (int)((v[i] - low) * scale))) : -1;
-        if (b[i] >= 0) atomicAdd(&hist[b[i]], 1u);
+    for (int k = 0; k < ITEMS; ++k) {
+        b[k] = v[k] > -INFINITY ? max(0, min(kChainBins - 1, (int)((v[k] - low) * scale))) : -1;
+        if (b[k] >= 0) atomicAdd(&hist[b[k]], 1u);
     }
     __syncthreads();
-    // Every wave by itself: lane l sums the bins from 511 - 8 l down
-    uint32_t h[8], sum = 0;
+    // Every wave by itself: lane l sums the bins from 511 - 8 l down; of the eight in which the K-th best lies lanes 0..7 take one each
+    uint32_t sum;
     {
         const uint4 *h4 = reinterpret_cast<const uint4 *>(&hist[kChainBins - 8 * (lane + 1)]);
         const uint4 x = h4[0], y = h4[1];
-        h[0] = y.w; h[1] = y.z; h[2] = y.y; h[3] = y.x; h[4] = x.w; h[5] = x.z; h[6] = x.y; h[7] = x.x;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) sum += h[j];
+        sum = ((x.x + x.y) + (x.z + x.w)) + ((y.x + y.y) + (y.z + y.w));
     }
     const uint32_t upto = wave_scan_u32(sum, lane);
     const int keep = min(__builtin_amdgcn_readlane((int)upto, 63), c.keep[s]);
     if (keep > 0) {
         const int at = __ffsll((unsigned long long)__ballot(upto >= (uint32_t)keep)) - 1;
-        uint32_t run = upto - sum, above_l = 0, count_l = 0;
-        int bin_l = -1;
+        const int top = kChainBins - 1 - 8 * at;
+        const uint32_t h = lane < 8 ? hist[top - lane] : 0u;
+        const uint32_t run = (uint32_t)__builtin_amdgcn_readlane((int)(upto - sum), at) + wave_scan_u32(h, lane);
+        const int j = __ffsll((unsigned long long)__ballot(run >= (uint32_t)keep)) - 1;
+        const int tb = top - j;
+        const uint32_t n_cand = (uint32_t)__builtin_amdgcn_readlane((int)h, j);
+        const uint32_t need = keep - ((uint32_t)__builtin_amdgcn_readlane((int)run, j) - n_cand);
+        if (n_cand <= 64u) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const bool here = bin_l < 0 && run + h[j] >= (uint32_t)keep;
-            bin_l = here ? kChainBins - 1 - 8 * lane - j : bin_l;
-            above_l = here ? run : above_l;
-            count_l = here ? h[j] : count_l;
-            run += h[j];
-        }
-        const int tb = __builtin_amdgcn_readlane(bin_l, at);
-        const uint32_t need = keep - (uint32_t)__builtin_amdgcn_readlane((int)above_l, at), n_cand = (uint32_t)__builtin_amdgcn_readlane((int)count_l, at);
-        if (n_cand <= (uint32_t)NT) {
-#pragma unroll
-            for (int i = 0; i < ITEMS; ++i)
-                if (b[i] == tb) {
-                    const uint32_t at = atomicAdd(&sh.ncand[s], 1u);
-                    sh.cand[at] = make_uint2(chain_key(v[i]), i0 + i);
-                }
+            for (int k = 0; k < ITEMS; ++k)
+                if (b[k] == tb) sh.cand[atomicAdd(&sh.ncand[s], 1u)] = make_uint2(chain_key(v[k]), (uint32_t)slot[k]);
             __syncthreads();
-            bool take[ITEMS];
-            uint32_t cnt = 0;
-#pragma unroll
-            for (int i = 0; i < ITEMS; ++i) {
-                take[i] = b[i] > tb;
-                if (b[i] == tb) {             // ranked among the bin's candidates by its owner
-                    const uint32_t mk = chain_key(v[i]), me = i0 + i;
-                    uint32_t rank = 0;
-                    for (uint32_t j = 0; j < n_cand; j += 4) {
-                        uint2 o[4];           // read together
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) o[k] = sh.cand[min(j + k, (uint32_t)NT - 1)];
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) rank += j + k < n_cand && (o[k].x > mk || (o[k].x == mk && o[k].y < me));
-                    }
-                    take[i] = rank < need;
-                }
-                cnt += take[i];
+            // every wave ranks them for itself, one a lane, and finds the last one kept
+            const uint2 me = sh.cand[min((uint32_t)lane, n_cand - 1)];
+            uint32_t rank = 0;
+            for (uint32_t o = 0; o < n_cand; ++o) {
+                const uint32_t okey = (uint32_t)__builtin_amdgcn_readlane((int)me.x, (int)o), oslot = (uint32_t)__builtin_amdgcn_readlane((int)me.y, (int)o);
+                rank += okey > me.x || (okey == me.x && oslot < me.y);
             }
-            const uint32_t incl = wave_scan_u32(cnt, lane);
-            if (lane == 63) sh.total[wv] = incl;
-            __syncthreads();
-            uint32_t pos = incl - cnt + wave_sum_u32(lane < wv ? sh.total[lane & (kWaves - 1)] : 0u);
+            const int last = __ffsll((unsigned long long)__ballot((uint32_t)lane < n_cand && rank == need - 1)) - 1;
+            const uint32_t last_key = (uint32_t)__builtin_amdgcn_readlane((int)me.x, last);
+            const int last_slot = __builtin_amdgcn_readlane((int)me.y, last);
+            uint64_t m[ITEMS];
+            int cnt = 0;
 #pragma unroll
-            for (int i = 0; i < ITEMS; ++i)
-                if (take[i]) to_index[pos++] = slot[i];
+            for (int k = 0; k < ITEMS; ++k) {
+                const uint32_t key = chain_key(v[k]);
+                m[k] = __ballot(b[k] > tb || (b[k] == tb && (key > last_key || (key == last_key && slot[k] <= last_slot))));
+                cnt += __popcll(m[k]);
+            }
+            if (lane == 0) sh.total[wv] = cnt;
+            __syncthreads();
+            int pos = (int)wave_sum_u32(lane < wv ? sh.total[lane & (kWaves - 1)] : 0u);
+#pragma unroll
+            for (int k = 0; k < ITEMS; ++k) {
+                if ((m[k] >> lane) & 1) to_index[pos + __builtin_amdgcn_mbcnt_hi((uint32_t)(m[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[k], 0u))] = slot[k];
+                pos += __popcll(m[k]);
+            }
         } else {
             block_select_largest<NT>(
                 limit, keep, [&](int i) { return chain_key(score[slot_of(i)]); },
@@ -138,49 +133,48 @@ __device__ inline int chain_stage(const ChainPlan &c, int s, int n, int n_from, 
 __global__ __launch_bounds__(kChainThreads) void select_chain_kernel(const ChainArgs args)
 {
     constexpr int NT = kChainThreads;
-    __shared__ ChainShared sh;
+    __shared__ __attribute__((aligned(16))) ChainShared sh;
     const Geometry &ge = args.ge;
     const ChainPlan &c = args.plan;
     const int p0 = c.pool > 1 ? blockIdx.x * ge.Hkv : blockIdx.x;      // the first problem of a pooled set; decode: one block per sequence
     const int tid = threadIdx.x, lane = tid & 63;
-    const Problem pr = problem_of(ge, p0);
-    for (int i = tid; i < kChainMaxStages * kChainBins / 4; i += NT) reinterpret_cast<uint4 *>(sh.hist[0])[i] = make_uint4(0, 0, 0, 0);
-    if (tid < kChainMaxStages) sh.ncand[tid] = 0u;
     {
-        const float *row = c.scores + (int64_t)p0 * c.stride;
-        constexpr int kAhead = 8;
-        for (int i0 = tid; i0 < c.stride; i0 += kAhead * NT) {
-            float x[kAhead];
+        // all scores are asked for at once (rows are whole 256 bytes)
+        const float4 *row = reinterpret_cast<const float4 *>(c.scores + (int64_t)p0 * c.stride);
+        const int n4 = c.stride >> 2;
+        float4 *to = reinterpret_cast<float4 *>(sh.score);
+        constexpr int kAhead = kChainMaxScores / 4 / NT;
+        float4 x[kAhead];
 #pragma unroll
-            for (int k = 0; k < kAhead; ++k) x[k] = row[min(i0 + k * NT, c.stride - 1)];
-            for (int g = 1; g < c.pool; ++g)
-#pragma unroll
-                for (int k = 0; k < kAhead; ++k) x[k] = fmaxf(x[k], row[(int64_t)g * c.stride + min(i0 + k * NT, c.stride - 1)]);
+        for (int k = 0; k < kAhead; ++k)
+            if (k * NT < n4) x[k] = row[min(tid + k * NT, n4 - 1)];
+        for (int i = tid; i < kChainMaxStages * kChainBins / 4; i += NT) reinterpret_cast<uint4 *>(sh.hist[0])[i] = make_uint4(0, 0, 0, 0);
+        if (tid < kChainMaxStages) sh.ncand[tid] = 0u;
+        for (int g = 1; g < c.pool; ++g) {
+            const float4 *other = row + (int64_t)g * n4;
 #pragma unroll
             for (int k = 0; k < kAhead; ++k)
-                if (i0 + k * NT < c.stride) sh.score[i0 + k * NT] = x[k] + 0.0f;                  // -0.0 -> +0.0
+                if (k * NT < n4) {
+                    const float4 y = other[min(tid + k * NT, n4 - 1)];
+                    x[k] = make_float4(fmaxf(x[k].x, y.x), fmaxf(x[k].y, y.y), fmaxf(x[k].z, y.z), fmaxf(x[k].w, y.w));
+                }
         }
-    }
-    __syncthreads();
-    // the bins of every stage, from 64 of its scores (every wave for itself)
-    float low[kChainMaxStages], scale[kChainMaxStages];
 #pragma unroll
-    for (int s = 0; s < kChainMaxStages; ++s) {
-        const int of = s < c.n_stages ? s : 0;           // without a branch, so that the stages' steps interleave
-        const float x = sh.score[c.at[of] + (int)((uint32_t)lane * (uint32_t)c.slots[of] >> 6)];
-        const float mn = wave_min_f32(x > -INFINITY ? x : INFINITY), mx = wave_max_f32(x);
-        low[s] = mn;
-        scale[s] = mx > mn ? (float)kChainBins / (1.5f * (mx - mn)) : 0.f;
+        for (int k = 0; k < kAhead; ++k)          // -0.0 -> +0.0
+            if (tid + k * NT < n4) to[tid + k * NT] = make_float4(x[k].x + 0.0f, x[k].y + 0.0f, x[k].z + 0.0f, x[k].w + 0.0f);
     }
+    const Problem pr = problem_of(ge, p0);
+    __syncthreads();
     int kept = 0;
     for (int s = 0; s < c.n_stages; ++s) {
         const int n = s == 0 ? c.slots[0] : c.keep[s - 1] << c.ratio_log2[s];
         const float *score = sh.score + c.at[s];
-        const float lo = s == 0 ? low[0] : s == 1 ? low[1] : s == 2 ? low[2] : low[3];
-        const float sc = s == 0 ? scale[0] : s == 1 ? scale[1] : s == 2 ? scale[2] : scale[3];
-        if (n <= NT) kept = chain_stage<1>(c, s, n, kept, score, lo, sc, sh);
-        else if (n <= 2 * NT) kept = chain_stage<2>(c, s, n, kept, score, lo, sc, sh);
-        else kept = chain_stage<4>(c, s, n, kept, score, lo, sc, sh);
+        // the bins, from 64 of the stage's scores (every wave for itself)
+        const float x = score[(int)((uint32_t)lane * (uint32_t)c.slots[s] >> 6)];
+        const float low = wave_min_f32(x > -INFINITY ? x : INFINITY), high = wave_max_f32(x);
+        const float scale = high > low ? (float)kChainBins / (1.5f * (high - low)) : 0.f;
+        if (n <= NT) kept = chain_stage<1>(c, s, n, kept, score, low, scale, sh);
+        else kept = chain_stage<4>(c, s, n, kept, score, low, scale, sh);
         for (int g = 0; g < c.pool; ++g) {
             int32_t *out = c.out[s] + (int64_t)(p0 + g) * c.keep[s];
             for (int i = tid; i < c.keep[s]; i += NT) out[i] = i < kept ? pr.lo + sh.index[s & 1][i] * c.chunk[s] : -1;
