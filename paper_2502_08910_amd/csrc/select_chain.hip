@@ -32,7 +32,7 @@ constexpr int kChainThreads = 512;
 struct ChainShared {
     float score[kChainMaxScores];
     int32_t index[2][kChainMaxKeep];          // what a stage kept: slots in its score row, which is the middle range in order
-    uint32_t hist[kChainMaxStages][kChainBins];
+    alignas(16) uint32_t hist[kChainMaxStages][kChainBins];       // read four bins at a time
     uint2 cand[64];                           // key and slot
     uint32_t ncand[kChainMaxStages], total[kChainThreads / 64];
     SelectScratch<kChainThreads> scratch;
@@ -150,13 +150,19 @@ __global__ __launch_bounds__(kChainThreads) void select_chain_kernel(const Chain
             if (k * NT < n4) x[k] = row[min(tid + k * NT, n4 - 1)];
         for (int i = tid; i < kChainMaxStages * kChainBins / 4; i += NT) reinterpret_cast<uint4 *>(sh.hist[0])[i] = make_uint4(0, 0, 0, 0);
         if (tid < kChainMaxStages) sh.ncand[tid] = 0u;
-        for (int g = 1; g < c.pool; ++g) {
-            const float4 *other = row + (int64_t)g * n4;
+        // Pooled heads, seven at once: one trip to memory for each 2,048 scores of eight heads, where head after head is seven for each
+        // 16,384.  Layers, head after head / so (us): 16 heads on 8, 15K bf16 keys in pages 34.1 / 28.8; 64 on 8, 5 of 20K E4M3 54.4 / 49.3
+        for (int g = 1; g < c.pool; g += 7) {
 #pragma unroll
             for (int k = 0; k < kAhead; ++k)
                 if (k * NT < n4) {
-                    const float4 y = other[min(tid + k * NT, n4 - 1)];
-                    x[k] = make_float4(fmaxf(x[k].x, y.x), fmaxf(x[k].y, y.y), fmaxf(x[k].z, y.z), fmaxf(x[k].w, y.w));
+                    const float4 *others = row + min(tid + k * NT, n4 - 1);
+                    float4 y[7];
+#pragma unroll
+                    for (int h = 0; h < 7; ++h) y[h] = others[(int64_t)min(g + h, c.pool - 1) * n4];
+#pragma unroll
+                    for (int h = 0; h < 7; ++h)
+                        x[k] = make_float4(fmaxf(x[k].x, y[h].x), fmaxf(x[k].y, y[h].y), fmaxf(x[k].z, y[h].z), fmaxf(x[k].w, y[h].w));
                 }
         }
 #pragma unroll

@@ -33,3 +33,28 @@ def test_equal_scores_at_the_threshold(ties, n_slots, pooling):
     best = torch.sort(value, descending=True, stable=True).indices[:keep].sort().values
     want = (n_sink + best.view(-1, 1) * 8 + torch.tensor([0, 4])).flatten().to(torch.int32)
     assert torch.equal(blocks.cpu(), want.expand(Hkv, -1))
+
+
+@pytest.mark.parametrize("n_slots", [300, 1500])
+@pytest.mark.parametrize("Hkv", [3, 7, 8, 9, 15, 16])
+def test_one_list_for_many_heads(Hkv, n_slots):
+    """Every chunk is good for one head only, any of them: the list is that of the largest over all heads, fetched seven at a time."""
+    import paper_2502_08910_amd as ihip
+    n_sink, n_stream, D = 64, 256, 128
+    T = n_sink + n_stream + 8 * n_slots
+    g = torch.Generator().manual_seed(Hkv)
+    value = torch.randperm(n_slots, generator=g) + 64
+    owner = torch.randint(0, Hkv, (n_slots,), generator=g)
+    v = torch.where(torch.arange(Hkv).view(-1, 1) == owner, value, torch.tensor(1)).repeat_interleave(8, dim=1)
+    q, k = torch.zeros((1, 2 * Hkv, 1, D)), torch.zeros((1, Hkv, T, D))
+    q[..., 0], q[..., 1] = 64, 1
+    k[0, :, n_sink:T - n_stream, 0], k[0, :, n_sink:T - n_stream, 1] = (v // 64).float(), (v % 64).float()
+    q, k = q.bfloat16().cuda(), k.bfloat16().cuda()
+    keep = n_slots // 4
+    chunks, keeps = [8, 4], [keep, 2 * keep]
+    L = ihip.Layer(q, k, torch.tensor([T], dtype=torch.int32, device="cuda"), 1, n_sink, n_stream)
+    blocks = torch.empty((L.P, keeps[-1]), dtype=torch.int32, device="cuda")
+    L.decode_layer(q, k, k, chunks, keeps, out_blocks=blocks, pooling=ihip.binding.POOL_ALL_HEADS)
+    best = torch.sort(value, descending=True, stable=True).indices[:keep].sort().values
+    want = (n_sink + best.view(-1, 1) * 8 + torch.tensor([0, 4])).flatten().to(torch.int32)
+    assert torch.equal(blocks.cpu(), want.expand(Hkv, -1))
