@@ -278,7 +278,8 @@ int32_t ihip_sparse_attn_prefill(const ihip_shape *shape, ihip_tensor q, ihip_te
  *   prefill attention (IHIP_OP_ATTN_PREFILL, and what IHIP_OP_PREFILL_LAYER holds beyond the scores, lists and final blocks)
  *     splits only with all of it.  The probabilities are rounded to bf16 against another maximum then: results differ by
  *     that rounding, a few units of the bf16 result's last place;
- *   IHIP_OP_PRUNE_ALL and IHIP_OP_DECODE_LAYER: where it pays, all stages of a short decode plan are scored at once,
+ *   IHIP_OP_PRUNE_ALL and IHIP_OP_DECODE_LAYER: where it pays, all stages of a short decode plan, or the last two
+ *     of a longer one, are scored at once,
  *     with the bytes behind the ones that a stage-by-stage run needs.  The two add up a score in another order (equal up to
  *     fp32 rounding): chunks whose scores tie to within that may be kept one for the other, and the output follows the
  *     kept blocks.

@@ -247,19 +247,22 @@ static bool layer_splits_fine(const ihip_shape &s, int n_stages, const int32_t *
            base + attn_decode_workspace(s, keeps[last], chunks[last], false) > (size_t)IHIP_STATIC_SCRATCH_BYTES;
 }
 
-// ---- all stages in one pass (prune_decode_nest.h, select_chain.hip) -------------
-// Scores per problem of all stages of a plan, 0 where the two kernels do not take it (ihip_prune_all also takes several
+// ---- all stages, or the last two, in one pass (prune_decode_nest.h, select_chain.hip) -------------
+// Scores per problem of the stages of a plan from `from` on, 0 where the two kernels do not take it (ihip_prune_all also takes several
 // single-query blocks, which the two kernels do not know).  Rows of whole 256 bytes: a line is then one workgroup's.
-static size_t nest_scores_per_problem(const ihip_shape &s, int n_stages, const int32_t *chunks, const int32_t *keeps)
+static size_t nest_scores_per_problem(const ihip_shape &s, int from, int n_stages, const int32_t *chunks, const int32_t *keeps)
 {
-    if (s.b_q != 1 || s.Tq != 1 || n_stages < 2 || n_stages > kChainMaxStages || chunks[n_stages - 1] < 4 || chunks[0] > (4 << (kNestLevels - 1))) return 0;
-    const int64_t slots = stage1_slots(s, chunks[0]);
+    if (s.b_q != 1 || s.Tq != 1 || n_stages - from < 2 || n_stages - from > kChainMaxStages || chunks[n_stages - 1] < 4 ||
+        chunks[from] > (4 << (kNestLevels - 1)))
+        return 0;
+    if (from > 0 && (chunks[from - 1] < 64 || keeps[from - 1] > kChainMaxParents)) return 0;
+    const int64_t slots = from == 0 ? stage1_slots(s, chunks[0]) : (int64_t)keeps[from - 1] * (chunks[from - 1] / chunks[from]);
     if (slots == 0 || slots > kChainMaxSlots) return 0;
     int64_t scores = 0;
-    for (int i = 0; i < n_stages; ++i) {
-        scores += (slots * (chunks[0] / chunks[i]) + 63) & ~63ll;
+    for (int i = from; i < n_stages; ++i) {
+        scores += (slots * (chunks[from] / chunks[i]) + 63) & ~63ll;
         if (keeps[i] > kChainMaxKeep) return 0;
-        if (i > 0 && (chunks[i] == chunks[i - 1] || (int64_t)keeps[i - 1] * (chunks[i - 1] / chunks[i]) > kChainMaxSlots)) return 0;
+        if (i > from && (chunks[i] == chunks[i - 1] || (int64_t)keeps[i - 1] * (chunks[i - 1] / chunks[i]) > kChainMaxSlots)) return 0;
     }
     return scores <= kChainMaxScores ? (size_t)scores : 0;
 }
@@ -301,14 +304,44 @@ static bool nest_pays(const ihip_shape &s, int n_stages, const int32_t *chunks, 
     return mb * keys <= 400 && saved > mb * (key * keys - row * searched);
 }
 
-// Scores of all stages taken together, whatever the storage and style are
+// Where the last two stages are scored together, from the keys of the chunks kept before them: where the pass reads no more rows than the
+// two stages' searches would, half of which are the same rows (four heads, chunks of 16 and 4: where 0.4 of the former are kept; eight
+// heads 0.2, two 0.65, one 0.9).  A launch and a selection less, too: stage by stage / together (us), 200 drawn layers of which 60 are of
+// this kind, 0.85-0.99 of the time; with more rows than that from 0.87 (one sequence) to 1.5 (12 of 28K keys, one head a group).
+static bool tail_pays(const ihip_shape &s, int from, const int32_t *chunks, const int32_t *keeps)
+{
+    const int G = s.Hq / s.Hkv;
+    const double slots = (double)keeps[from - 1] * (chunks[from - 1] / chunks[from]);
+    const double later = std::min<double>(keeps[from], slots) * (chunks[from] / chunks[from + 1]);
+    return slots * search_rows(chunks[from], G) + later * search_rows(chunks[from + 1], G) >= slots * chunks[from];
+}
+
+// Scores per problem that a plan's scratch has room for, whatever the storage and style are: those of all stages where one pass over
+// all keys pays for any of them, else those of the last two
+static size_t together_scores(const ihip_shape &s, int n_stages, const int32_t *chunks, const int32_t *keeps)
+{
+    const size_t all = nest_scores_per_problem(s, 0, n_stages, chunks, keeps);
+    for (int v = 0; all > 0 && v < 8; ++v)
+        if (nest_pays(s, n_stages, chunks, keeps, v & 1, v & 2, v & 4)) return all;
+    const int from = n_stages - 2;
+    return from >= 1 && tail_pays(s, from, chunks, keeps) ? nest_scores_per_problem(s, from, n_stages, chunks, keeps) : 0;
+}
 static size_t nest_bytes(const ihip_shape &s, int n_stages, const int32_t *chunks, const int32_t *keeps)
 {
-    const size_t scores = nest_scores_per_problem(s, n_stages, chunks, keeps);
-    if (scores == 0) return 0;
-    for (int v = 0; v < 8; ++v)
-        if (nest_pays(s, n_stages, chunks, keeps, v & 1, v & 2, v & 4)) return align256((size_t)s.B * s.Hkv * scores * sizeof(float));
-    return 0;
+    return align256((size_t)s.B * s.Hkv * together_scores(s, n_stages, chunks, keeps) * sizeof(float));
+}
+
+// The first of the stages that are scored together when those in `due` are, or n_stages
+static int together_from(const ihip_shape &s, int n_stages, const int32_t *chunks, const int32_t *keeps, uint32_t due, bool fp8, bool rope, bool paged)
+{
+    const uint32_t every = (1u << n_stages) - 1u;
+    if ((due & every) == every && nest_scores_per_problem(s, 0, n_stages, chunks, keeps) > 0 &&
+        nest_pays(s, n_stages, chunks, keeps, fp8, rope, paged))
+        return 0;
+    const int from = n_stages - 2;
+    if (from < 1 || ((due >> from) & 3u) != 3u || !tail_pays(s, from, chunks, keeps)) return n_stages;
+    const size_t scores = nest_scores_per_problem(s, from, n_stages, chunks, keeps);
+    return scores > 0 && scores <= together_scores(s, n_stages, chunks, keeps) ? from : n_stages;
 }
 
 // Scratch of a decode layer.  The scores of all stages taken together come last and are left out where a plan fits the
@@ -328,7 +361,7 @@ static size_t decode_layer_scratch(const ihip_shape &s, int n_stages, const int3
 // stage that is re-run reads the list of the stage before it as it stands, re-run in this call or
 // cached from an earlier one (Alg. 4: a stage is re-run when its counter says so, with the current
 // lists of the earlier stages; a stage that is not due keeps its list).
-// nest: the plan's scores may be taken together (decode_layer_scratch, nest_bytes); nest_scores: room for them, or null: each stage on
+// nest: scores may be taken together (decode_layer_scratch, nest_bytes); nest_scores: room for them, or null: each stage on
 // its own.  The host tier scores stage by stage, but with the arithmetic that contiguous rows in device memory get.
 static int32_t prune_stages_impl(const ihip_shape &s, const ihip_tensor &q, const ihip_tensor &k, int n_stages,
                                  const int32_t *chunks, const int32_t *keeps, uint32_t due,
@@ -336,43 +369,46 @@ static int32_t prune_stages_impl(const ihip_shape &s, const ihip_tensor &q, cons
                                  const ihip_rope *rope, bool all_heads, hipStream_t st,
                                  const KvFormat *fmt = nullptr, bool nest = false, float *nest_scores = nullptr)
 {
-    const uint32_t every = (1u << n_stages) - 1u;
     const bool relative = rope && rope->prune_style == IHIP_ROPE_RELATIVE, paged = fmt && fmt->paged.block_table;
-    const bool together = nest && (due & every) == every && !(rope && rope->prune_style == IHIP_ROPE_CHUNK_INDEXED) &&
-                          nest_pays(s, n_stages, chunks, keeps, fmt && fmt->fp8, relative, paged);
-    if (together && nest_scores && !bank) {
-        const int slots = stage1_slots(s, chunks[0]);
+    const int from = nest && !(rope && rope->prune_style == IHIP_ROPE_CHUNK_INDEXED)
+                         ? together_from(s, n_stages, chunks, keeps, due, fmt && fmt->fp8, relative, paged) : n_stages;
+    auto score_together = [&]() -> int32_t {
+        const int n_parent = from == 0 ? 0 : keeps[from - 1], parent_chunk = from == 0 ? 0 : chunks[from - 1];
+        const int slots = from == 0 ? stage1_slots(s, chunks[0]) : n_parent * (parent_chunk / chunks[from]);
         NestArgs args{};
         ChainPlan chain{};
-        args.top = __builtin_ctz(chunks[0]) - 2;
-        args.stride = chain.stride = (int)nest_scores_per_problem(s, n_stages, chunks, keeps);
-        chain.n_stages = n_stages;
+        const ChainParents parents{from == 0 ? nullptr : stage_out[from - 1], n_parent, from == 0 ? 0 : __builtin_ctz(parent_chunk)};
+        args.top = __builtin_ctz(chunks[from]) - 2;
+        args.stride = chain.stride = (int)nest_scores_per_problem(s, from, n_stages, chunks, keeps);
+        chain.n_stages = n_stages - from;
         chain.pool = all_heads ? s.Hkv : 1;
         chain.scores = nest_scores;
         int at = 0;
-        for (int i = 0; i < n_stages; ++i) {
-            const int lv = __builtin_ctz(chunks[i]) - 2, n = slots * (chunks[0] / chunks[i]);
+        for (int i = from; i < n_stages; ++i) {
+            const int lv = __builtin_ctz(chunks[i]) - 2, n = slots * (chunks[from] / chunks[i]), c = i - from;
             args.out[lv] = nest_scores + at;
             args.slots[lv] = n;
-            chain.at[i] = at;
-            chain.out[i] = stage_out[i];
-            chain.slots[i] = n;
-            chain.ratio_log2[i] = i == 0 ? 0 : __builtin_ctz(chunks[i - 1] / chunks[i]);
-            chain.chunk[i] = chunks[i];
-            chain.keep[i] = keeps[i];
+            chain.at[c] = at;
+            chain.out[c] = stage_out[i];
+            chain.slots[c] = n;
+            chain.ratio_log2[c] = c == 0 ? 0 : __builtin_ctz(chunks[i - 1] / chunks[i]);
+            chain.chunk[c] = chunks[i];
+            chain.keep[c] = keeps[i];
             at += (n + 63) & ~63;
         }
-        const int32_t rc = launch_prune_stage(s, q, k, nullptr, 0, 0, chunks[0], slots, nullptr, nullptr, bank, rope, st, fmt, &args);
-        return rc != IHIP_OK ? rc : launch_select_chain(s, chain, st);
-    }
+        const int32_t rc = launch_prune_stage(s, q, k, parents.starts, n_parent, parent_chunk, chunks[from], slots, nullptr, nullptr, nullptr, rope, st,
+                                              fmt, &args);
+        return rc != IHIP_OK ? rc : launch_select_chain(s, chain, parents, st);
+    };
     for (int i = 0; i < n_stages; ++i) {
         if (!((due >> i) & 1u)) continue;
+        if (i == from && nest_scores && !bank) return score_together();
         const int32_t *parents = i == 0 ? nullptr : stage_out[i - 1];
         const int n_parent = i == 0 ? 0 : keeps[i - 1];
         const int parent_chunk = i == 0 ? 0 : chunks[i - 1];
         const int slots = i == 0 ? stage1_slots(s, chunks[0]) : n_parent * (parent_chunk / chunks[i]);
         int32_t rc = launch_prune_stage(s, q, k, parents, n_parent, parent_chunk, chunks[i], slots, scores,
-                                        nullptr, bank, rope, st, fmt, nullptr, together && bank);
+                                        nullptr, bank, rope, st, fmt, nullptr, bank && i >= from);
         if (rc != IHIP_OK) return rc;
         rc = launch_select_blocks(s, scores, slots, parents, n_parent, parent_chunk, chunks[i], keeps[i],
                                   stage_out[i], all_heads, st);

@@ -1,4 +1,5 @@
-// All stages of a decode plan in one pass over the middle range (b_q == 1, K from device memory, no RoPE or the relative style).
+// All stages of a decode plan in one pass over the middle range, or its last two in one over the chunks kept before them (b_q == 1, K from
+// device memory, no RoPE or the relative style).
 //
 // SelectRep of a chunk compares the first keys of its halves and goes on inside the winner, so what it does inside a
 // part is SelectRep of that part: once the parts of a chunk have their scores, the chunk's is that of one of them, chosen by the
@@ -8,6 +9,8 @@
 // log2(l) row latencies per stage become one, and all launches but one and all selections' but one (select_chain.hip) go.
 // Layers of three stages, 32 heads on 8, stage by stage / in one pass (us): one sequence of 4K bf16 keys 35.5 / 23.2, 8K
 // 37.2 / 24.0, 32K 38.6 / 32.3, 16 of 4K 69.5 / 56.7; E4M3 pages with RoPE 4K 41.0 / 25.3, 32K 45.5 / 34.8, 16 of 8K 83.2 / 76.5.
+// The last two stages of longer plans (together_from in api.hip), 128 chunks of 64 kept, 256 of 16, 512 of 4: 13 sequences of 135K, E4M3
+// pages 153.8 / 143.5; 256 of 64, 512 of 16, 1,024 of 4: 64 heads on 8, 5 of 835K, E4M3 pages 389 / 375, 8 of 1M bf16 437.6 / 433.4.
 //
 // Arithmetic as in prune_decode_tile.h: 16 keys x 16 query columns on the matrix cores; column n is head n % G (relative style:
 // columns 0..7 against q_L, 8..15 against q_R, exchanged by a row rotation), and the lane (n, kq) holds keys 4*kq..+3
@@ -61,7 +64,8 @@ __device__ inline NestPart nest_join_rows(const NestPart &p)
     return nest_join<ROPE>(a, b);
 }
 
-template <int G, bool ROPE, int SRC, bool KV8, bool NARROW>
+// PARENTS: the keys are those of the chunks that the stage before kept (as a branch of one kernel: passes over the middle range 1-2 % longer)
+template <int G, bool ROPE, int SRC, bool KV8, bool NARROW, bool PARENTS>
 __global__ __launch_bounds__(256) void prune_decode_nest_kernel(const PruneArgs a, const NestArgs nest, const RopeView rope)
 {
     static_assert(SRC == 0 || !NARROW, "paged pools are addressed with 64-bit offsets");
@@ -74,13 +78,20 @@ __global__ __launch_bounds__(256) void prune_decode_nest_kernel(const PruneArgs 
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int n = lane & 15, kq = lane >> 4;
     const int log2l = nest.top + 2;
-    // key f of the middle range is key f % l of chunk f / l
+    // key f of the middle range, or of the parents one after the other, is key f % l of chunk f / l
     const int f0 = (a.grid.part() * 4 + wv) * (NT * 16), n_keys = a.max_chunks << log2l;
     const bool across = nest.top >= 5;        // the waves of the workgroup meet at the end
     if (f0 >= n_keys && !across) return;
     __shared__ float sh_part[4][4][16];
     __shared__ uint4 sh_rows[4 * 16 * decode_row_pieces(KV8)];
-    auto position = [&](int f) { return f < n_keys && pr.lo + f < pr.hi ? pr.lo + f : -1; };
+    // where the wave's keys begin: in the middle range, or inside one parent (of 64 keys or more)
+    int w0 = pr.lo + f0;
+    if constexpr (PARENTS) {
+        const int parent_log2 = log2l + a.ratio_log2, i = f0 >> parent_log2;
+        const int ps = i < a.n_parent ? a.parent_starts[(int64_t)p * a.n_parent + i] : -1;
+        w0 = ps >= 0 ? ps + (f0 & ((1 << parent_log2) - 1)) : 1 << 30;
+    }
+    auto position = [&](int f) { return f < n_keys && w0 + (f - f0) < pr.hi ? w0 + (f - f0) : -1; };
     NestPart whole{-INFINITY, -INFINITY, -INFINITY, -1};      // of the wave's 64 keys
     // chunk score of a part: max over the heads
     auto over_heads = [&](const NestPart &x) {
@@ -180,7 +191,9 @@ static void launch_nest_n(PruneArgs a, const NestArgs &nest, const RopeView &rop
     const int per_problem = (int)((((int64_t)a.max_chunks << (nest.top + 2)) + 255) / 256);
     a.grid = DecodeGrid{0};                   // in order: a problem's keys by one XCD are 16 sequences of 16K keys 148 -> 178 us a layer
     KernelTimer timer(stage_name(kNamePruneDecode, true, a.chunk), st);
-    hipLaunchKernelGGL((prune_decode_nest_kernel<G, ROPE, SRC, KV8, NARROW>), a.grid.dims(P, per_problem), dim3(256), 0, st, a, nest, rope);
+    const dim3 grid = a.grid.dims(P, per_problem);
+    if (a.parent_starts != nullptr) hipLaunchKernelGGL((prune_decode_nest_kernel<G, ROPE, SRC, KV8, NARROW, true>), grid, dim3(256), 0, st, a, nest, rope);
+    else hipLaunchKernelGGL((prune_decode_nest_kernel<G, ROPE, SRC, KV8, NARROW, false>), grid, dim3(256), 0, st, a, nest, rope);
 }
 template <bool ROPE, int SRC, bool KV8, bool NARROW>
 static void launch_nest_g(const PruneArgs &a, const NestArgs &nest, const RopeView &rope, int P, hipStream_t st)

@@ -29,13 +29,15 @@ constexpr int kChainBins = 512;            // eight per lane
 // One sequence of 8K keys, a layer (us): 512 threads 24.2, 256 24.8, 1024 26.4
 constexpr int kChainThreads = 512;
 
+template <bool PARENTS>
 struct ChainShared {
     float score[kChainMaxScores];
-    int32_t index[2][kChainMaxKeep];          // what a stage kept: slots in its score row, which is the middle range in order
+    int32_t index[2][kChainMaxKeep];          // what a stage kept: slots in its score row, which is the middle range, or the parents' keys, in order
     alignas(16) uint32_t hist[kChainMaxStages][kChainBins];       // read four bins at a time
     uint2 cand[64];                           // key and slot
     uint32_t ncand[kChainMaxStages], total[kChainThreads / 64];
     SelectScratch<kChainThreads> scratch;
+    int32_t parent[PARENTS ? kChainMaxParents : 1];
 };
 
 // Monotone map fp32 -> u32 (larger float <=> larger key); -0.0 maps with +0.0.
@@ -46,8 +48,8 @@ __device__ inline uint32_t chain_key(float f)
 }
 
 // Selects stage s of the chain from n candidates, children of the n_from chunks that the stage before it kept.  -> how many are kept
-template <int ITEMS>
-__device__ inline int chain_stage(const ChainPlan &c, int s, int n, int n_from, const float *score, float low, float scale, ChainShared &sh)
+template <int ITEMS, class Shared>
+__device__ inline int chain_stage(const ChainPlan &c, int s, int n, int n_from, const float *score, float low, float scale, Shared &sh)
 {
     constexpr int NT = kChainThreads, kWaves = NT / 64;
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -130,10 +132,11 @@ __device__ inline int chain_stage(const ChainPlan &c, int s, int n, int n_from, 
     return keep;
 }
 
-__global__ __launch_bounds__(kChainThreads) void select_chain_kernel(const ChainArgs args)
+template <bool PARENTS>
+__global__ __launch_bounds__(kChainThreads) void select_chain_kernel(const ChainArgs args, const ChainParents parents)
 {
     constexpr int NT = kChainThreads;
-    __shared__ __attribute__((aligned(16))) ChainShared sh;
+    __shared__ __attribute__((aligned(16))) ChainShared<PARENTS> sh;
     const Geometry &ge = args.ge;
     const ChainPlan &c = args.plan;
     const int p0 = c.pool > 1 ? blockIdx.x * ge.Hkv : blockIdx.x;      // the first problem of a pooled set; decode: one block per sequence
@@ -150,6 +153,8 @@ __global__ __launch_bounds__(kChainThreads) void select_chain_kernel(const Chain
             if (k * NT < n4) x[k] = row[min(tid + k * NT, n4 - 1)];
         for (int i = tid; i < kChainMaxStages * kChainBins / 4; i += NT) reinterpret_cast<uint4 *>(sh.hist[0])[i] = make_uint4(0, 0, 0, 0);
         if (tid < kChainMaxStages) sh.ncand[tid] = 0u;
+        if constexpr (PARENTS)
+            for (int i = tid; i < parents.n; i += NT) sh.parent[i] = parents.starts[(int64_t)p0 * parents.n + i];
         // Pooled heads, seven at once: one trip to memory for each 2,048 scores of eight heads, where head after head is seven for each
         // 16,384.  Layers, head after head / so (us): 16 heads on 8, 15K bf16 keys in pages 34.1 / 28.8; 64 on 8, 5 of 20K E4M3 54.4 / 49.3
         for (int g = 1; g < c.pool; g += 7) {
@@ -183,17 +188,25 @@ __global__ __launch_bounds__(kChainThreads) void select_chain_kernel(const Chain
         else kept = chain_stage<4>(c, s, n, kept, score, low, scale, sh);
         for (int g = 0; g < c.pool; ++g) {
             int32_t *out = c.out[s] + (int64_t)(p0 + g) * c.keep[s];
-            for (int i = tid; i < c.keep[s]; i += NT) out[i] = i < kept ? pr.lo + sh.index[s & 1][i] * c.chunk[s] : -1;
+            for (int i = tid; i < c.keep[s]; i += NT) {
+                if constexpr (PARENTS) {
+                    const int f = i < kept ? sh.index[s & 1][i] * c.chunk[s] : 0;
+                    out[i] = i < kept ? sh.parent[f >> parents.log2] + (f & ((1 << parents.log2) - 1)) : -1;
+                } else {
+                    out[i] = i < kept ? pr.lo + sh.index[s & 1][i] * c.chunk[s] : -1;
+                }
+            }
         }
     }
 }
 
-int32_t launch_select_chain(const ihip_shape &s, const ChainPlan &plan, hipStream_t st)
+int32_t launch_select_chain(const ihip_shape &s, const ChainPlan &plan, const ChainParents &parents, hipStream_t st)
 {
     const int P = s.B * (plan.pool > 1 ? 1 : s.Hkv);
     KernelTimer timer(stage_name(kNameSelect, true, plan.chunk[0]), st);
     const ChainArgs args{make_geometry(s), plan};
-    hipLaunchKernelGGL(select_chain_kernel, dim3(P), dim3(kChainThreads), 0, st, args);
+    if (parents.starts != nullptr) hipLaunchKernelGGL(select_chain_kernel<true>, dim3(P), dim3(kChainThreads), 0, st, args, parents);
+    else hipLaunchKernelGGL(select_chain_kernel<false>, dim3(P), dim3(kChainThreads), 0, st, args, parents);
     return check_launch("select_blocks (several stages)");
 }
 
