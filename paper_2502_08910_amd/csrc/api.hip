@@ -279,14 +279,27 @@ static double search_rows(int l, int G)
     return rows;
 }
 
+// Where the last two stages are scored together, from the keys of the chunks kept before them: where the pass reads no more rows than the
+// two stages' searches would, half of which are the same rows (four heads, chunks of 16 and 4: where 0.4 of the former are kept; eight
+// heads 0.2, two 0.65, one 0.9).  A launch and a selection less, too: stage by stage / together (us), 200 drawn layers of which 60 are of
+// this kind, 0.85-0.99 of the time; with more rows than that from 0.87 (one sequence) to 1.5 (12 of 28K keys, one head a group).
+static bool tail_pays(const ihip_shape &s, int from, const int32_t *chunks, const int32_t *keeps)
+{
+    const int G = s.Hq / s.Hkv;
+    const double slots = (double)keeps[from - 1] * (chunks[from - 1] / chunks[from]);
+    const double later = std::min<double>(keeps[from], slots) * (chunks[from] / chunks[from + 1]);
+    return slots * search_rows(chunks[from], G) + later * search_rows(chunks[from + 1], G) >= slots * chunks[from];
+}
+
 // Where one pass over all keys is the faster way.  It saves some 6 us of launches and chains of latencies a stage after the first, and the
-// rows that the searches read; it costs all keys: us, and us a megabyte.  Fitted to 7,600 pairs of measurements (8 KV heads, 1 to 8 heads a
-// group, 2 to 4 stages, 3K to 64K keys in batches of 1 to 64, every storage, rows that the caches hold and rows that they do not, 256
-// CUs).  Of 5,740 plans that it sends here 103 lose more than 2 % (worst 1.12), of the others 129 would gain more than 2 % (best 1.17); a
-// line that knew neither heads nor stages sent 450 more here that lost (one head a group, two stages, E4M3 with RoPE: 1.43) and kept 430 away that
-// gain (1.73).  Stage by stage / in one pass (us), three stages, 8 KV heads: 32 heads, bf16 rows, one sequence of 32K keys 38.6 / 32.3, of
-// 48K 39.2 / 37.4, 4 of 16K 46.3 / 45.9, 16 of 8K 79.0 / 80.3; one head a group, E4M3 with RoPE, one of 16K 36.8 / 38.2, 16 of 8K 53.0 /
-// 60.4.  Nothing beyond 400 MB of rows was measured.
+// rows that the searches read; it costs all keys: us, and us a megabyte.  Where the last two stages would be scored together otherwise, a
+// launch and a selection less (4 us) are saved.  Fitted to 7,600 pairs of measurements (8 KV heads, 1 to 8 heads a group, 2 to 4 stages, 3K to
+// 64K keys in batches of 1 to 64, every storage, rows that the caches hold and rows that they do not, 256 CUs) and, as the kernels
+// became faster, to 800 more; of 800 others 8 of those sent here lose more than 2 % (worst 1.22), of the rest 22 would gain more
+// (best 1.15), and any line between the two ways would be 0.3 % faster at most.  Stage by stage / in one pass (us), three stages, 8 KV
+// heads: 32 heads, bf16 rows, one sequence of 15K keys 40.5 / 26.9, of 39K 39.0 / 35.7, 2 of 37K 41.0 / 42.1, 10 of 18K 63.9 / 84.5; one
+// head a group, E4M3 pages with RoPE, 2 of 9K 38.2 / 28.3, one of 53K 33.4 / 33.4, 24 of 12K 92.0 / 107.9.  Nothing beyond 400 MB of rows
+// was measured.
 static bool nest_pays(const ihip_shape &s, int n_stages, const int32_t *chunks, const int32_t *keeps, bool fp8, bool rope, bool paged)
 {
     const int G = s.Hq / s.Hkv;
@@ -298,22 +311,12 @@ static bool nest_pays(const ihip_shape &s, int n_stages, const int32_t *chunks, 
         searched += n * search_rows(chunks[i], G);
     }
     const double mb = (double)s.B * s.Hkv * (fp8 ? 128 : 256) / (1 << 20);      // a key of all problems
-    const double saved = (paged ? 6.7 : 6.0) * (n_stages - 1) - 1.5 - 1.0 * rope + 1.2 * paged;
-    const double key = fp8 ? 0.17 + 0.07 * rope + 0.01 * paged : 0.165 + 0.01 * rope + 0.02 * paged;
+    const int from = n_stages - 2;
+    const bool tail = from >= 1 && tail_pays(s, from, chunks, keeps) && nest_scores_per_problem(s, from, n_stages, chunks, keeps) > 0;
+    const double saved = (paged ? 6.7 : 6.0) * (n_stages - 1) - 1.5 - 1.0 * rope + 1.2 * paged - 4.0 * tail;
+    const double key = fp8 ? 0.17 + 0.07 * rope + 0.01 * paged : 0.145 + 0.01 * rope + 0.02 * paged;
     const double row = fp8 ? 0.205 + 0.1 * rope : 0.135 + 0.007 * G + 0.015 * rope + 0.03 * paged;
     return mb * keys <= 400 && saved > mb * (key * keys - row * searched);
-}
-
-// Where the last two stages are scored together, from the keys of the chunks kept before them: where the pass reads no more rows than the
-// two stages' searches would, half of which are the same rows (four heads, chunks of 16 and 4: where 0.4 of the former are kept; eight
-// heads 0.2, two 0.65, one 0.9).  A launch and a selection less, too: stage by stage / together (us), 200 drawn layers of which 60 are of
-// this kind, 0.85-0.99 of the time; with more rows than that from 0.87 (one sequence) to 1.5 (12 of 28K keys, one head a group).
-static bool tail_pays(const ihip_shape &s, int from, const int32_t *chunks, const int32_t *keeps)
-{
-    const int G = s.Hq / s.Hkv;
-    const double slots = (double)keeps[from - 1] * (chunks[from - 1] / chunks[from]);
-    const double later = std::min<double>(keeps[from], slots) * (chunks[from] / chunks[from + 1]);
-    return slots * search_rows(chunks[from], G) + later * search_rows(chunks[from + 1], G) >= slots * chunks[from];
 }
 
 // Scores per problem that a plan's scratch has room for, whatever the storage and style are: those of all stages where one pass over

@@ -7,8 +7,8 @@
 // before the other's selection is known: every key is read once, in order, and all levels follow from the
 // keys' scores in the registers.  Keys of parts that the selections drop are read for nothing; what it saves is a chain:
 // log2(l) row latencies per stage become one, and all launches but one and all selections' but one (select_chain.hip) go.
-// Layers of three stages, 32 heads on 8, stage by stage / in one pass (us): one sequence of 4K bf16 keys 35.5 / 23.2, 8K
-// 37.2 / 24.0, 32K 38.6 / 32.3, 16 of 4K 69.5 / 56.7; E4M3 pages with RoPE 4K 41.0 / 25.3, 32K 45.5 / 34.8, 16 of 8K 83.2 / 76.5.
+// Layers of three stages, 32 heads on 8, stage by stage / in one pass (us): one sequence of 5K bf16 keys 35.1 / 22.7, 10K
+// 36.5 / 24.3, 39K 39.0 / 35.7, 10 of 4K 57.4 / 39.1, 14 of 8K 96.6 / 69.9.
 // The last two stages of longer plans (together_from in api.hip), 128 chunks of 64 kept, 256 of 16, 512 of 4: 13 sequences of 135K, E4M3
 // pages 153.8 / 143.5; 256 of 64, 512 of 16, 1,024 of 4: 64 heads on 8, 5 of 835K, E4M3 pages 389 / 375, 8 of 1M bf16 437.6 / 433.4.
 //
