@@ -3,6 +3,10 @@
 // HBM-bound gather of K and V rows (512 B per attended token, shared by the G query heads of the KV head).  Flash-decoding layout: the
 // attended tokens of a problem form a virtual slot list  [sink | kept blocks | window];  the list is cut into splits, one workgroup
 // each; a wave takes 16 slots at a time, and every 16-lane row group reads four of their rows whole (16 B of a bf16 row per lane).
+// The slots are dealt to the row groups in turn: token 4 * kq + u of the sixteen is slot 4 * u + kq, so that one load of the wave
+// brings the rows of neighbouring slots.  HBM does not care, but over the host link 128-byte rows that a load names apart are
+// requests of their own: host tier, 3,200 slots of 8 heads, nothing resident (us), four neighbouring slots to a row group / in turn:
+// E4M3 149 / 120, with RoPE 165 / 120; bf16 239 / 237.
 //
 // On the vector ALUs a token costs some 26 instructions per 16 lanes and head -- dot, row reduction, a softmax that all lanes
 // repeat, and 8 multiply-adds per head --, which was more than the rows' time with E4M3 rows, rotations or 8 heads.  The products are done
@@ -129,6 +133,9 @@ __device__ inline float head_sum(const float (&d)[G], int n)
     return x + dpp_f32<0x124>(x);             // row_ror:4
 }
 
+// Where the slot i of a split stands among its wave's tokens: 4 * kq + u for slot 4 * u + kq of sixteen
+__device__ inline int slot_place(int i) { return (i & ~15) | ((i & 3) << 2) | ((i >> 2) & 3); }
+
 // slot -> key position, or -1
 __device__ inline int slot_to_pos(const AttnDecodeArgs &a, const Problem &pr, int p, int slot,
                                   int n_sink_eff, int w0)
@@ -178,7 +185,7 @@ __global__ __launch_bounds__(kAttnThreads, G == 8 ? 2 : ROPE ? 3 : 4) void attn_
     const int n_sink_eff = min(a.ge.n_sink, pr.E);
     const int w0 = max(pr.hi, a.ge.n_sink);
 
-    __shared__ __attribute__((aligned(16))) int sh_pos[kAttnMaxSplit];      // key position of every slot of this split, -1 without one
+    __shared__ __attribute__((aligned(16))) int sh_pos[kAttnMaxSplit];      // key position of every slot of this split, at slot_place, -1 without one
     __shared__ __attribute__((aligned(16))) int sh_page[SRC == 2 ? kAttnMaxSplit : 4];       // paged K/V: the slot's page id
     __shared__ uint4 sh_rows[ROPE ? 1 : NW * 16 * kPieces];                 // 16 K rows of each wave on their way to operand layout
     __shared__ int sh_block_tokens;
@@ -230,8 +237,8 @@ __global__ __launch_bounds__(kAttnThreads, G == 8 ? 2 : ROPE ? 3 : 4) void attn_
         } else {
             pos = slot_to_pos(a, pr, p, slot, n_sink_eff, w0);
         }
-        sh_pos[i] = pos;
-        if constexpr (SRC == 2) sh_page[i] = pos >= 0 ? ksrc.table_entry(pos) : 0;
+        sh_pos[slot_place(i)] = pos;
+        if constexpr (SRC == 2) sh_page[slot_place(i)] = pos >= 0 ? ksrc.table_entry(pos) : 0;
     }
     __syncthreads();
 
@@ -244,7 +251,7 @@ __global__ __launch_bounds__(kAttnThreads, G == 8 ? 2 : ROPE ? 3 : 4) void attn_
         for (int i = 0; i < 8; ++i) acc[s][i] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
-    // 16 slots at a time, a wave's own.  Row group kq reads the K and V rows of slots 4 * kq .. + 3.
+    // 16 slots at a time, a wave's own.  Row group kq reads the K and V rows of tokens 4 * kq .. + 3, slots kq, 4 + kq, 8 + kq and 12 + kq.
     uint4 *stage = &sh_rows[wv * 16 * kPieces];
     uint4 kr[ROPE ? 1 : kLoads];
     v_t kv[ROPE ? 4 : 1], vr[4];              // ROPE: K rows as V rows, and their turns
@@ -287,7 +294,7 @@ __global__ __launch_bounds__(kAttnThreads, G == 8 ? 2 : ROPE ? 3 : 4) void attn_
         four(sh_pos, tile, pos);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int64_t at = (int64_t)key_id(s0 + tile * 16 + kq * 4 + u, pos[u]) * (kD / 2) + n * 4;
+            const int64_t at = (int64_t)key_id(s0 + tile * 16 + u * 4 + kq, pos[u]) * (kD / 2) + n * 4;
             tc[u] = *reinterpret_cast<const float4 *>(a.rope_cos + at);
             ts[u] = *reinterpret_cast<const float4 *>(a.rope_sin + at);
         }
