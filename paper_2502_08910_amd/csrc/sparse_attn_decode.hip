@@ -34,7 +34,9 @@ namespace ihip {
 constexpr int kAttnThreads = 256;
 constexpr int kAttnMaxSplit = 1024;                      // most slots of one split (a multiple of 16)
 constexpr int kAttnMinSplit = 256, kAttnMinSplitFine = 64;      // fewest; see decode_splits
-constexpr float kSlack = 8.f;                            // log2 units that a score may stand above the reference of the exponentials
+// Log2 units that the reference of the exponentials is set above the scores that outgrew it, so that it seldom has to follow.  A
+// probability is at most 1 then: sums of V rows overflow no sooner than with the maximum itself as the reference.
+constexpr float kSlack = 8.f;
 constexpr float kNegBig = -1.0e30f;                      // finite stand-in for -inf in running maxima
 
 struct AttnDecodeArgs {
@@ -389,8 +391,8 @@ __global__ __launch_bounds__(kAttnThreads, G == 8 ? 2 : ROPE ? 3 : 4) void attn_
 #pragma unroll
             for (int i = 0; i < 4; ++i) sc[i] = ok[i] ? c[s][i] * a.scale_log2e : kNegBig;
             const float top = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
-            if (__ballot(top > m[s] + kSlack) != 0) {           // the reference follows where the scores outgrow it
-                const float mn = fmaxf(m[s], top);
+            if (__ballot(top > m[s]) != 0) {                    // the reference follows where the scores outgrow it
+                const float mn = top > m[s] ? top + kSlack : m[s];
                 const float corr = __builtin_amdgcn_exp2f(m[s] - mn);
                 m[s] = mn;
                 l[s] *= corr;

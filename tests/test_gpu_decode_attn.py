@@ -1,6 +1,7 @@
 """Decode attention alone (sparse_attn_decode.hip) against plain attention in float64, where its tiles of 16 slots, four-token row
 groups and splits end: lists that fill no tile, one tile, one wave more than a tile, several splits; blocks cut short at the end
-of the middle range, absent blocks, a sink longer than the sequence; and scores that outgrow the reference of the exponentials.
+of the middle range, absent blocks, a sink longer than the sequence; scores that outgrow the reference of the exponentials; and V
+near both ends of what bf16 holds.
 
 Bounds.  Scores and sums are fp32 and the probabilities go into the products whole (24 bits): an output is the fp32 result
 rounded to bf16, half a unit in the last of 8 bits <= 2^-8 of it, and fp32 sums of n products add up to about n 2^-24 of the
@@ -29,7 +30,7 @@ def _turn(x, pos, cos, sin):
     return torch.stack((e * c - o * s, e * s + o * c), dim=-1).flatten(-2)
 
 
-def _check(ihip, G, fmt, rope, lens, n_sink, n_stream, block, n_blocks, grow=0.0, seed=0):
+def _check(ihip, G, fmt, rope, lens, n_sink, n_stream, block, n_blocks, grow=0.0, seed=0, v_unit=1.0, step=False):
     g = torch.Generator().manual_seed(seed)
     Hkv, B, T = 2, len(lens), max(lens)
     Hq = Hkv * G
@@ -37,7 +38,12 @@ def _check(ihip, G, fmt, rope, lens, n_sink, n_stream, block, n_blocks, grow=0.0
     k, v = (torch.randn((B, Hkv, T, D), generator=g) for _ in range(2))
     if grow:                                          # keys along the first head, longer and longer: scores climb with the position
         k = k + q[:, ::G, 0].float().unsqueeze(2) * torch.linspace(-grow, grow, T).view(1, 1, T, 1)
-    kw = {}
+    if step:                                          # the window 8 * 7.25 / sqrt(128) higher, in a dim that RoPE hardly turns
+        q, k[..., 126] = torch.zeros_like(q), 7.25 * (torch.arange(T) >= T - n_stream).float()
+        q[..., 126] = 8
+        v = v.sign() * (1 + torch.rand(v.shape, generator=g))
+    v = v * v_unit                                    # a power of two
+    kw = {"ws": torch.empty(B * Hq * (D + 2) * 4, dtype=torch.uint8, device="cuda")} if step else {}        # one coarse split
     if fmt == "fp8":
         k, v = (t.clamp(-448, 448).to(torch.float8_e4m3fn) for t in (k, v))
         kw["kv_scales"] = (1.0, 1.0)
@@ -87,7 +93,7 @@ def _check(ihip, G, fmt, rope, lens, n_sink, n_stream, block, n_blocks, grow=0.0
             s = kk @ qq / math.sqrt(D)
             r = torch.logsumexp(s, 0)
             want = (s - r).exp() @ v[b, h // G, pos].double()
-            bound = 2.0 ** -8 * want.abs() + 2.0 ** -10
+            bound = 2.0 ** -8 * want.abs() + 2.0 ** -10 * v_unit
             over = ((out[b, h, 0] - want).abs() - bound).max().item()
             assert over <= 0, (b, h, over)
             assert abs(lse[b, h, 0] - r) <= 1e-5 * max(1.0, r.abs().item()), (b, h, lse[b, h, 0], r)
@@ -121,3 +127,14 @@ def test_scores_that_outgrow_the_reference(ihip, G):
     _check(ihip, G, "bf16", False, [1500], 16, 64, 4, 300, grow=8.0, seed=3)
     _check(ihip, G, "fp8", False, [1500], 16, 64, 4, 300, grow=8.0, seed=4)
     _check(ihip, G, "bf16", True, [1500], 16, 64, 4, 300, grow=8.0, seed=5)
+
+
+@pytest.mark.parametrize("rope", [False, True], ids=["plain", "streaming"])
+@pytest.mark.parametrize("unit", [2.0 ** 122, 2.0 ** -118])
+@pytest.mark.parametrize("G", [1, 4, 8])
+def test_large_and_small_v(ihip, G, unit, rope):
+    """224 tokens, then 16 whose scores are 7.4 log2 units higher, in one split, so that a wave sees them after others: no
+    probability may stand far above one, whatever the reference of the exponentials is, or its product with V overflows where
+    neither the output (2^123) nor the sum (2^127) does.  Seen from the other end, a probability far below one must not push V's
+    products out of the fp32 range."""
+    _check(ihip, G, "bf16", rope, [240], 64, 16, 4, 40, seed=6, v_unit=unit, step=True)
