@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256) void prune_decode_nest_kernel(const PruneArgs 
     if constexpr (PARENTS) {
         const int parent_log2 = log2l + a.ratio_log2, i = f0 >> parent_log2;
         const int ps = i < a.n_parent ? a.parent_starts[(int64_t)p * a.n_parent + i] : -1;
-        w0 = ps >= 0 ? ps + (f0 & ((1 << parent_log2) - 1)) : 1 << 30;
+        w0 = ps >= 0 ? ps + (f0 & ((1 << parent_log2) - 1)) : INT32_MAX - (NT * 16 - 1);     // no key of any sequence
     }
     auto position = [&](int f) { return f < n_keys && w0 + (f - f0) < pr.hi ? w0 + (f - f0) : -1; };
     NestPart whole{-INFINITY, -INFINITY, -INFINITY, -1};      // of the wave's 64 keys

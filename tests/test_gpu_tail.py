@@ -169,3 +169,23 @@ def test_host_tier_rounds_alike(ihip, Hq, fp8):
             assert torch.equal(lists[0], lists[1]) and torch.equal(got.view(torch.int16), want[0].view(torch.int16))
     finally:
         cache.close()
+
+
+def test_absent_parents_of_very_long_sequences(ihip):
+    """An absent parent (-1 in a cached first list) stands for no key, also where a sequence has more than 2^30 of them.  The
+    tokens of a head share one row (stride 0), so the keys that an absent parent must not be taken for score as well as any."""
+    T, chunks, keeps = (1 << 30) + (1 << 20), [s[0] for s in PLAN], [s[1] for s in PLAN]
+    g = torch.Generator().manual_seed(1)
+    q = torch.randint(-3, 4, (1, 8, 1, D), generator=g).bfloat16().cuda()
+    k, v = (torch.randint(-3, 4, (1, 2, 1, D), generator=g).bfloat16().cuda().expand(1, 2, T, D) for _ in range(2))
+    L = ihip.Layer(q, torch.empty((1, 2, T, 0), dtype=torch.bfloat16), torch.tensor([T], dtype=torch.int32, device="cuda"), 1, 64, 256)
+    state = L.mask_state(keeps)
+    first = torch.full((2, keeps[0]), -1, dtype=torch.int32)
+    first[:, :10] = 64 + 64 * torch.arange(10) * (1 << 20)
+    state[:2 * keeps[0]] = first.flatten().cuda()
+    assert _launches(ihip, lambda: L.decode_layer_masked(q, k, v, chunks, keeps, 1, state)) == 1
+    second, third = state[2 * keeps[0]:].cpu().split([2 * keeps[1], 2 * keeps[2]])
+    want = (first[:, :10, None] + 16 * torch.arange(4)).flatten(1)
+    assert torch.equal(second.view(2, -1)[:, :40], want) and (second.view(2, -1)[:, 40:] == -1).all()
+    want = (want[:, :, None] + 4 * torch.arange(4)).flatten(1)[:, :100]
+    assert torch.equal(third.view(2, -1), want)
