@@ -32,7 +32,8 @@
 namespace ihip {
 
 constexpr int kAttnThreads = 256;
-constexpr int kAttnMaxSplit = 1024;                      // most slots of one split (a multiple of 16)
+constexpr int kAttnMaxSplit = 1536, kAttnUsualSplit = 1024;     // most slots of one split (multiples of 16); see decode_splits
+constexpr int kAttnSplitCost = 64;                       // what beginning and ending a split costs, in slots
 constexpr int kAttnMinSplit = 256, kAttnMinSplitFine = 64;      // fewest; see decode_splits
 // Log2 units that the reference of the exponentials is set above the scores that outgrew it, so that it seldom has to follow.  A
 // probability is at most 1 then: sums of V rows overflow no sooner than with the maximum itself as the reference.
@@ -161,7 +162,7 @@ __device__ inline int slot_to_pos(const AttnDecodeArgs &a, const Problem &pr, in
 // one can be cut short), so a key's id is its slot, less the empty block slots for window keys.
 // KV8: K and V rows are 128 bytes of E4M3, widened exactly to bf16.
 template <int G, int SRC, bool ROPE, bool KV8>
-__global__ __launch_bounds__(kAttnThreads, G == 8 ? 2 : ROPE ? 3 : 4) void attn_decode_split_kernel(const AttnDecodeArgs a)
+__global__ __launch_bounds__(kAttnThreads, G == 8 ? 2 : ROPE && !(KV8 && G <= 2) ? 3 : 4) void attn_decode_split_kernel(const AttnDecodeArgs a)
 {
     constexpr int NW = kAttnThreads / kWave;
     constexpr int kSets = G == 8 ? 2 : 1;                                   // of four heads (fewer: the four rows of a product repeat them)
@@ -180,6 +181,7 @@ __global__ __launch_bounds__(kAttnThreads, G == 8 ? 2 : ROPE ? 3 : 4) void attn_
     int start_of[kSlots];
 #pragma unroll
     for (int k = 0; k < kSlots; ++k) {
+        if (SRC != 2 && k * kAttnThreads >= a.slots_per_split) break;       // (over pages the branches cost what they save)
         const int i = tid + k * kAttnThreads, at = s0 + i - a.ge.n_sink;
         start_of[k] = i < a.slots_per_split && at >= 0 && at < block_slots ? starts[at >> a.block_log2] : -1;
     }
@@ -191,6 +193,7 @@ __global__ __launch_bounds__(kAttnThreads, G == 8 ? 2 : ROPE ? 3 : 4) void attn_
     __shared__ __attribute__((aligned(16))) int sh_page[SRC == 2 ? kAttnMaxSplit : 4];       // paged K/V: the slot's page id
     __shared__ uint4 sh_rows[ROPE ? 1 : NW * 16 * kPieces];                 // 16 K rows of each wave on their way to operand layout
     __shared__ int sh_block_tokens;
+    __shared__ __attribute__((aligned(16))) int sh_any[NW];                 // does a wave's share of the slots hold a key?
     const typename KvSource<SRC>::type ksrc = KvSource<SRC>::k(a, pr);
     const typename KvSource<SRC>::type vsrc = KvSource<SRC>::v(a, pr);
     // The queries, asked for now: column n's head of each set as an operand (head n % 4, n % G with fewer), or (ROPE) this lane's 8
@@ -221,10 +224,12 @@ __global__ __launch_bounds__(kAttnThreads, G == 8 ? 2 : ROPE ? 3 : 4) void attn_
         mine = (int)wave_sum_u32((uint32_t)mine);
         if (lane == 0 && mine > 0) atomicAdd(&sh_block_tokens, mine);
     }
+    bool any = false;
 #pragma unroll
     for (int k = 0; k < kSlots; ++k) {
         const int i = tid + k * kAttnThreads;
-        if (i >= a.slots_per_split) break;
+        if (SRC != 2 && k * kAttnThreads >= a.slots_per_split) break;
+        if (i >= a.slots_per_split) continue;
         int slot = s0 + i, pos;
         if (n_sink_eff == a.ge.n_sink) {
             const int at = slot - n_sink_eff;
@@ -239,10 +244,21 @@ __global__ __launch_bounds__(kAttnThreads, G == 8 ? 2 : ROPE ? 3 : 4) void attn_
         } else {
             pos = slot_to_pos(a, pr, p, slot, n_sink_eff, w0);
         }
+        any |= pos >= 0;
         sh_pos[slot_place(i)] = pos;
         if constexpr (SRC == 2) sh_page[slot_place(i)] = pos >= 0 ? ksrc.table_entry(pos) : 0;
     }
+    any = __ballot(any) != 0;
+    if (lane == 0) sh_any[wv] = any;
     __syncthreads();
+    const int64_t pbase = ((int64_t)p * a.n_splits + split) * G;
+    // A split of absent blocks, as a plan for longer sequences has many: nothing to wait for.  One head a group, 27 sequences of 6,000 keys
+    // with 9,152 slots, splits without keys walked / left: bf16 115 / 111 us, E4M3 77 / 61
+    if ((sh_any[0] | sh_any[1] | sh_any[2] | sh_any[3]) == 0) {
+        for (int idx = tid; idx < G * kD; idx += kAttnThreads) a.part_acc[pbase * kD + idx] = 0.f;
+        if (tid < 2 * G) a.part_ml[pbase * 2 + tid] = (tid & 1) ? 0.f : kNegBig;
+        return;
+    }
 
     f32x4 acc[kSets][8];                      // [dim of this lane's 8][head of the set]: of this row group's tokens
     float m[kSets], l[kSets];                 // of this row group's tokens, head n % 4: reference of the exponentials (log2 units), sum
@@ -486,7 +502,6 @@ __global__ __launch_bounds__(kAttnThreads, G == 8 ? 2 : ROPE ? 3 : 4) void attn_
     }
     __syncthreads();
 
-    const int64_t pbase = ((int64_t)p * a.n_splits + split) * G;
     for (int idx = threadIdx.x; idx < G * kD; idx += kAttnThreads) {
         const int h = idx / kD, c = idx % kD;
         float M = kNegBig;
@@ -575,10 +590,12 @@ __global__ __launch_bounds__(kD * GROUPS) void attn_decode_merge_kernel(const At
         a.out_lse[(int64_t)b * a.ge.Hq + hq] = (M + log2f(L)) * 0.69314718055994530942f;
 }
 
-// Splits of the slot list: as many workgroups as the chip holds at once (4 workgroups of 4 waves
-// per CU with the plain kernel's registers), so that no workgroup has to wait for a free slot and
+// Splits of the slot list: as many workgroups as the chip holds at once, so that no workgroup has to wait for a free place and
 // run its whole latency chain after the others have drained -- with 256-slot splits the cfg3 shape
-// had 1344 workgroups for 1024 places.  Between 256 and 1024 slots per split, a multiple of 16.
+// had 1344 workgroups for 1024 places.  At least 256 slots per split, a multiple of 16; lists that fill the chip several times over go
+// in the rounds that take the least time, each as full as can be, and up to 1,536 slots a split are better than a second round that
+// is half empty.  At most 1,024 slots a split / so (us): 32 sequences of 5,248 slots, one head a group, E4M3 75.7 / 66.5, four heads, E4M3
+// 79.2 / 69.4; 32 of 3,200, four heads, bf16 with RoPE 106.5 / 91.5; 4 of 33,920, one head, E4M3 68.6 / 56.2, bf16 with RoPE 130 / 118.
 // `fine`: where splits of 256 slots would not even give every CU one workgroup, the kernel is one chain of latencies and a
 // split walks its loop four times while most of the chip is idle; splits then go down to 64 slots, one batch of loads of
 // every 16-lane group, to two workgroups per CU at most (more of them share what a CU has and cost the merge) and to 64 splits,
@@ -586,35 +603,51 @@ __global__ __launch_bounds__(kD * GROUPS) void attn_decode_merge_kernel(const At
 // 4 heads, 8 problems of 1,664 slots 19.4/14.7/15.1, 8 of 5,248 20.7/19.0/19.5, 32 of 1,664 21.0/22.0/19.7; 8 heads
 // 25.6/17.8/17.4, 26.7/25.0/24.8, 27.0/30.8/25.1, 16 of 3,200 27.2/30.3/25.4.  Finer splits take more scratch; with
 // scratch for the coarse ones only, those are used.
-// wg_per_cu: what the instantiation's registers leave room for (attn_decode_per_cu).  The workspace is sized for 4, which gives the
-// most splits.
-static int decode_splits(const ihip_shape &s, int n_blocks, int block, bool fine, int *slots_per_split, int wg_per_cu = 4)
+// wg_per_cu: what the instantiation's registers leave room for (attn_decode_per_cu); 0: the most splits of any, which the workspace is
+// sized for.
+static int decode_splits(const ihip_shape &s, int n_blocks, int block, bool fine, int *slots_per_split, int wg_per_cu)
 {
     const int n_cu = compute_units();
     const int total = s.n_sink + n_blocks * block + s.n_stream;
     const int P = std::max(1, s.B * s.Hkv);
     const bool spread = fine && (int64_t)P * ((total + kAttnMinSplit - 1) / kAttnMinSplit) < n_cu;
-    const int places = std::max(1, n_cu * (spread ? 2 : wg_per_cu) / P);      // splits per problem that run at once
-    int per = ((total + places - 1) / places + 15) / 16 * 16;
-    const int least = spread ? std::min(kAttnMinSplit, std::max(kAttnMinSplitFine, ((total + 63) / 64 + 15) & ~15)) : kAttnMinSplit;
-    per = std::min(kAttnMaxSplit, std::max(least, per));
+    auto slots = [&](int splits) { return ((total + splits - 1) / splits + 15) / 16 * 16; };
+    if (spread) {
+        const int least = std::min(kAttnMinSplit, std::max(kAttnMinSplitFine, ((total + 63) / 64 + 15) & ~15));
+        *slots_per_split = std::max(least, slots(std::max(1, n_cu * 2 / P)));
+        return (total + *slots_per_split - 1) / *slots_per_split;
+    }
+    int per = std::min(kAttnUsualSplit, std::max(kAttnMinSplit, slots(std::max(1, n_cu * 4 / P))));
+    const int most = (total + per - 1) / per, fewest = (total + kAttnMaxSplit - 1) / kAttnMaxSplit;
+    if (wg_per_cu == 0) return most;
+    const int64_t places = (int64_t)n_cu * wg_per_cu;
+    int64_t best = INT64_MAX;
+    for (int64_t rounds = (P * (int64_t)fewest + places - 1) / places, last = rounds + 2; rounds <= last; ++rounds) {
+        const int n = slots((int)std::min<int64_t>(most, rounds * places / P)), size = std::max(n, kAttnMinSplit);
+        const int64_t time = rounds * (size + kAttnSplitCost);
+        if (time < best) {
+            best = time;
+            per = size;
+        }
+    }
     *slots_per_split = per;
     return (total + per - 1) / per;
 }
 
-// Workgroups on a compute unit: waves per SIMD by the registers of the instantiation.  Eight heads, 16 sequences of 3,200 slots, splits for
+// Workgroups on a compute unit: waves per SIMD that the instantiation is compiled for (its launch bounds; eight heads over E4M3 rows fit
+// one more).  Eight heads, 16 sequences of 3,200 slots, splits for
 // four / for this many: bf16 45.1 / 41.0 us, E4M3 34.5 / 31.0, bf16 with RoPE 60.1 / 52.4.
 static int attn_decode_per_cu(int G, bool rope, bool fp8)
 {
     if (G == 8) return fp8 && !rope ? 3 : 2;
-    return rope ? 3 : 4;
+    return rope && !(fp8 && G <= 2) ? 3 : 4;
 }
 
 // scratch for the partial results of the fine or the coarse splits
 size_t attn_decode_workspace(const ihip_shape &s, int n_blocks, int block, bool fine)
 {
     int per;
-    const int ns = decode_splits(s, n_blocks, block, fine, &per);
+    const int ns = decode_splits(s, n_blocks, block, fine, &per, 0);
     const size_t P = (size_t)s.B * s.Hkv;
     const size_t G = s.Hq / s.Hkv;
     return P * ns * G * (2 + kD) * sizeof(float);

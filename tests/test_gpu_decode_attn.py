@@ -30,7 +30,7 @@ def _turn(x, pos, cos, sin):
     return torch.stack((e * c - o * s, e * s + o * c), dim=-1).flatten(-2)
 
 
-def _check(ihip, G, fmt, rope, lens, n_sink, n_stream, block, n_blocks, grow=0.0, seed=0, v_unit=1.0, step=False):
+def _check(ihip, G, fmt, rope, lens, n_sink, n_stream, block, n_blocks, grow=0.0, seed=0, v_unit=1.0, step=False, only=None):
     g = torch.Generator().manual_seed(seed)
     Hkv, B, T = 2, len(lens), max(lens)
     Hq = Hkv * G
@@ -80,7 +80,7 @@ def _check(ihip, G, fmt, rope, lens, n_sink, n_stream, block, n_blocks, grow=0.0
         kw["paged"] = ihip.PagedKV(pools[0], pools[1], order.to(torch.int32).view(B, n).contiguous().cuda())
     out, lse = L.sparse_attn_decode(q.cuda(), kd, vd, starts.cuda(), block, want_lse=True, **kw)
     out, lse = out.cpu().double(), lse.cpu().double()
-    for b in range(B):
+    for b in range(B) if only is None else only:
         E = lens[b]
         hi = E - n_stream
         for h in range(Hq):
@@ -119,6 +119,14 @@ def test_groups_and_storage(ihip, G, fmt, rope):
 @pytest.mark.parametrize("rope", [False, True], ids=["plain", "streaming"])
 def test_ends_of_tiles_and_splits(ihip, lens, n_sink, n_stream, block, n_blocks, rope):
     _check(ihip, 4, "bf16", rope, lens, n_sink, n_stream, block, n_blocks, seed=len(lens))
+
+
+@pytest.mark.parametrize("fmt,rope", [("bf16", False), ("bf16", True), ("fp8", False), ("paged", False)])
+@pytest.mark.parametrize("G", [1, 4])
+def test_long_splits_and_splits_without_keys(ihip, G, fmt, rope):
+    """128 problems of 8,857 slots, more than a GPU of 256 compute units takes at once in splits of 1,024: 1,120 slots and more to a split.
+    Four fifths of the blocks are absent, so most splits hold no key at all."""
+    _check(ihip, G, fmt, rope, [1700] * 62 + [9, 0], 20, 37, 4, 2200, seed=G, only=(0, 30, 61, 62))
 
 
 @pytest.mark.parametrize("G", [1, 4, 8])
