@@ -303,15 +303,17 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
         return decode_products<KV8, PARTS>(raw, q);
     };
     // a tile's products -> the owners' scores (sL: against the column's query, or q_L; sR: against q_R).  i: the owner's
-    // register; ix: the register that the owner in lane n ^ 8 wants
-    auto owned = [&](const f32x4 c, int i, int ix, float &sL, float &sR) {
-        float v = pick4(c, i);
-        if constexpr (G == 8) {               // heads 0..3 are in the even quads' columns, and in rows of even kq
-            const float w = other_quad(v);
-            v = ((quad ^ kq) & 1) ? w : v;
-        }
+    // register; ix, i4: the registers that the owners in lanes n ^ 8 and n ^ 4 want
+    auto owned = [&](const f32x4 c, int i, int ix, int i4, float &sL, float &sR) {
+        auto of_head = [&](int r, int r4) {
+            const float v = pick4(c, r);
+            if constexpr (G < 8) return v;
+            const float w = other_quad(pick4(c, r4));        // heads 0..3 are in the even quads' columns, and in rows of even kq
+            return ((quad ^ kq) & 1) ? w : v;
+        };
+        const float v = of_head(i, i4);
         if constexpr (ROPE) {
-            const float w = row_ror8(i == ix ? v : pick4(c, ix));
+            const float w = row_ror8(i == ix ? v : of_head(ix, i4 ^ i ^ ix));
             sL = n < 8 ? v : w;
             sR = n < 8 ? w : v;
         } else {
@@ -325,7 +327,7 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             float l, rr;
-            owned(products(raw[t]), n & 3, n & 3, l, rr);
+            owned(products(raw[t]), n & 3, n & 3, n & 3, l, rr);
             sL = quad == t ? l : sL;
             sR = quad == t ? rr : sR;
         }
@@ -342,13 +344,15 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
         uint4 r0[kLoads], r1[kLoads];
         request_tile<0, KV8>(rows, rows.at(base, slot0), n, r0);
         request_tile<0, KV8>(rows, rows.at(mid, slot1), n, r1);
-        owned(products(r0), n & 3, n & 3, left, value);
-        owned(products(r1), n & 3, n & 3, rL, rR);
+        owned(products(r0), n & 3, n & 3, n & 3, left, value);
+        owned(products(r1), n & 3, n & 3, n & 3, rL, rR);
     } else {
         const off_t at0 = row_at(base), at1 = row_at(has_right ? base + half : base);
-        if constexpr (G == 4) {
+        if constexpr (G >= 4) {
             // The first key of a chunk and of its right half are the same rows for all heads: one tile holds the first keys of the
-            // wave's 16 chunks, row 4*kq + t that of chunk (t, kq), so that the owner finds its score in register t.
+            // wave's chunks, row 4*kq + t that of the chunk of quad t in row group kq (four heads: 16 chunks; eight: 8, each in
+            // two row groups), so that the owner finds its score in register t.  Eight heads, a tile for each owner's first key / so (us),
+            // 16 sequences of 8 KV heads, 8,192 chunks of two keys each: E4M3 175 / 108, bf16 pages with RoPE 350 / 218.
             auto first_of = [&](off_t at) {           // lane t of a row group: the offset of its lane 4 * t
                 const off_t a0 = row_lane<0>(at), a1 = row_lane<4>(at), a2 = row_lane<8>(at), a3 = row_lane<12>(at);   // (by all lanes)
                 return (n & 2) ? ((n & 1) ? a3 : a2) : (n & 1) ? a1 : a0;
@@ -356,8 +360,8 @@ __global__ __launch_bounds__(256, G == 8 && ROPE && SRC == 2 && !KV8 ? 3 : 1) vo
             uint4 r0[kLoads], r1[kLoads];
             request_tile<0, KV8>(rows, first_of(at0), n, r0);
             request_tile<0, KV8>(rows, first_of(at1), n, r1);
-            owned(products(r0), quad, quad ^ 2, left, value);
-            owned(products(r1), quad, quad ^ 2, rL, rR);
+            owned(products(r0), quad, quad ^ 2, quad ^ 1, left, value);
+            owned(products(r1), quad, quad ^ 2, quad ^ 1, rL, rR);
         } else {
             score(at0, left, value);
             score(at1, rL, rR);
