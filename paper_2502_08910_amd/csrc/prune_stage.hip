@@ -270,10 +270,9 @@ static bool decode_on_tiles(const PruneArgs &a, int P, bool fp8, bool relative)
         if (fp8 || relative) return at_least(0.75);                               // 0.91-0.98 / 1.10-2.1
         return at_least(4);                                                       // 0.89 / 1.04-1.05
     }
-    if (chunk < 4) {                         // (lines from before the rows were fetched whole)
-        if (many) return relative ? at_least(5) : fp8 && at_least(4);             // 0.75-1.26 / 0.97-1.38, 0.91-1.14 / 1.03-1.54
-        if (relative) return at_least(paged || !fp8 ? 1.5 : 1.875);               // 0.64-1.17 / 0.98-1.5
-        return (fp8 || paged) && at_least(2);                                     // 0.86-1.14 / 1.03-1.54
+    if (chunk < 4) {                         // 8 KV heads, 1 to 32 sequences, 512 to 8,192 chunks a problem
+        if (relative) return at_least(2);                                         // 0.82-1.19 / 1.20-2.8
+        return at_least(!many && (fp8 || paged) ? 2 : 4);                         // 0.89-1.25 / 1.07-1.66
     }
     if (many) {
         if (relative) return at_least(fp8 ? (paged ? 1 : 1.25) : 0.75);           // 0.95-1.17 / 1.05-4.4
