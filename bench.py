@@ -14,7 +14,8 @@ Prints one JSON line.  `value` is microseconds per layer call for the whole
 batch.  `roofline` is for the kernel with the largest share of the step:
  - decode: algorithmic bytes per launch (distinct K rows the search must
    score, counted by the CPU oracle on a sample of problems, x 256 B, plus the
-   scores it writes) / mean launch duration, against 8 TB/s of HBM;
+   scores it writes; a launch that scores several stages at once: every key of
+   its chunks) / mean launch duration, against 8 TB/s of HBM;
  - prefill: matrix-core flops per launch (2*d per query-key pair actually
    multiplied) / mean launch duration, against 2.5 PFLOP/s dense bf16.
 The mean launch duration comes from HIP events recorded around every launch
@@ -156,6 +157,24 @@ def step_spread(step, steps, torch, first=0):
     pick = lambda f: t[min(len(t) - 1, int(f * len(t)))]      # noqa: E731
     progress("per-step spread done")
     return {"p10": pick(0.1), "median": pick(0.5), "p90": pick(0.9), "n": len(t), "unit": "us"}
+
+
+def decode_kernel_bytes(chunks, keeps, slots, rows, keys, row_bytes, ran):
+    """Bytes that one problem of each pruning and selection launch has to move: rows scored, scores and lists.  rows[i]: rows
+    that stage i's searches read; keys: of the middle range.  A stage whose own kernels are not among those that `ran` (empty: every
+    stage's did) was scored with the stage before it, whose launch then reads every key of its chunks once and leaves the scores of
+    all these stages; one launch selects for them."""
+    out, i = {}, 0
+    while i < len(chunks):
+        j = i + 1
+        while ran and j < len(chunks) and f"prune_decode.l{chunks[j]}" not in ran:
+            j += 1
+        name = f"{'.first' if i == 0 else ''}.l{chunks[i]}"
+        scores = sum(slots[i] * (chunks[i] // chunks[m]) for m in range(i, j)) * 4
+        out["prune_decode" + name] = (rows[i] if j == i + 1 else min(keys, slots[i] * chunks[i])) * row_bytes + scores
+        out["select_blocks" + name] = scores + sum(keeps[i:j]) * 4
+        i = j
+    return out
 
 
 def dominant(kernels):
@@ -333,15 +352,13 @@ def bench_decode(args, w, torch, ihip, configs):
     row_bytes = w.d * (1 if kv_scales else 2)
     roofline = whole = None
     if sample is not None and refresh is None:
-        alg = {}
         slots = [L.stage1_slots(chunks[0])] + [keeps[i - 1] * (chunks[i - 1] // chunks[i])
                                                  for i in range(1, len(chunks))]
-        for i, c in enumerate(chunks):
-            first = ".first" if i == 0 else ""
-            alg[f"prune_decode{first}.l{c}"] = P * (sample["rows_per_problem"][i] * row_bytes + slots[i] * 4)
-            alg[f"select_blocks{first}.l{c}"] = P * (slots[i] * 4 + keeps[i] * 4)
-        alg["attn_decode_split"] = P * sample["tokens_per_problem"] * 2 * row_bytes
-        total_alg = sum(alg.values())
+        attn = sample["tokens_per_problem"] * 2 * row_bytes
+        per_problem = lambda ran: {**decode_kernel_bytes(chunks, keeps, slots, sample["rows_per_problem"],  # noqa: E731
+                                                         w.T - w.n_sink - w.n_stream, row_bytes, ran), "attn_decode_split": attn}
+        total_alg = P * sum(per_problem(()).values())          # what the path cannot do without: the searches' rows
+        alg = {n: P * b for n, b in per_problem(kernels).items()}
         gbs = total_alg / (us_per_layer * 1e-6) / 1e9
         whole = {"algorithmic_bytes_per_layer": total_alg, "achieved_GBps": gbs,
                  "frac_of_hbm_peak": gbs / HBM_PEAK_GBS}

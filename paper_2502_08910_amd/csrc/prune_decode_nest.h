@@ -190,7 +190,7 @@ static void launch_nest_n(PruneArgs a, const NestArgs &nest, const RopeView &rop
 {
     const int per_problem = (int)((((int64_t)a.max_chunks << (nest.top + 2)) + 255) / 256);
     a.grid = DecodeGrid{0};                   // in order: a problem's keys by one XCD are 16 sequences of 16K keys 148 -> 178 us a layer
-    KernelTimer timer(stage_name(kNamePruneDecode, true, a.chunk), st);
+    KernelTimer timer(stage_name(kNamePruneDecode, a.parent_starts == nullptr, a.chunk), st);
     const dim3 grid = a.grid.dims(P, per_problem);
     if (a.parent_starts != nullptr) hipLaunchKernelGGL((prune_decode_nest_kernel<G, ROPE, SRC, KV8, NARROW, true>), grid, dim3(256), 0, st, a, nest, rope);
     else hipLaunchKernelGGL((prune_decode_nest_kernel<G, ROPE, SRC, KV8, NARROW, false>), grid, dim3(256), 0, st, a, nest, rope);

@@ -203,7 +203,7 @@ __global__ __launch_bounds__(kChainThreads) void select_chain_kernel(const Chain
 int32_t launch_select_chain(const ihip_shape &s, const ChainPlan &plan, const ChainParents &parents, hipStream_t st)
 {
     const int P = s.B * (plan.pool > 1 ? 1 : s.Hkv);
-    KernelTimer timer(stage_name(kNameSelect, true, plan.chunk[0]), st);
+    KernelTimer timer(stage_name(kNameSelect, parents.starts == nullptr, plan.chunk[0]), st);
     const ChainArgs args{make_geometry(s), plan};
     if (parents.starts != nullptr) hipLaunchKernelGGL(select_chain_kernel<true>, dim3(P), dim3(kChainThreads), 0, st, args, parents);
     else hipLaunchKernelGGL(select_chain_kernel<false>, dim3(P), dim3(kChainThreads), 0, st, args, parents);

@@ -18,14 +18,18 @@ def ihip():
     return pkg
 
 
-def _launches(ihip, run):
+def _kernels(ihip, run):
     ihip.profile_read()
     ihip.profile_enable(True)
     try:
         run()
     finally:
         ihip.profile_enable(False)
-    return sum(n for name, (_, n) in ihip.profile_read().items() if name.startswith("prune_decode"))
+    return {name: n for name, (_, n) in ihip.profile_read().items()}
+
+
+def _launches(ihip, run):
+    return sum(n for name, n in _kernels(ihip, run).items() if name.startswith("prune_decode"))
 
 
 def _inputs(ihip, Hq, Hkv, lens, fmt, rope, n_pos, seed=0, page=16):
@@ -130,6 +134,14 @@ def test_cached_first_stage(ihip):
         assert _launches(ihip, lambda: L.decode_layer_masked(q, k, v, chunks, keeps, 1, state, ws=ws, out=out)) == launches
         got.append((state.cpu(), out.cpu().view(torch.int16)))
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+def test_kernels_are_named_by_the_stage_they_begin_with(ihip):
+    q, k, v, kw = _inputs(ihip, 8, 2, [150003], "bf16", False, 0)
+    L = ihip.Layer(q, torch.empty((1, 2, 150003, 0), dtype=torch.bfloat16), torch.tensor([150003], dtype=torch.int32, device="cuda"), 1, 64, 256)
+    got = _kernels(ihip, lambda: L.decode_layer(q, k, v, [s[0] for s in PLAN], [s[1] for s in PLAN]))
+    assert got == {n: 1 for n in ("prune_decode.first.l64", "select_blocks.first.l64", "prune_decode.l16", "select_blocks.l16",
+                                  "attn_decode_split", "attn_decode_merge")}
 
 
 @pytest.mark.parametrize("Hq,Hkv,stages,together", [
