@@ -84,13 +84,14 @@ def _check(ihip, Hq, Hkv, lens, stages, fmt="bf16", rope=False, n_sink=64, n_str
 
 
 PLAN = ((64, 40), (16, 80), (4, 100))                 # 160 candidates of 16 keys, half of them kept
+MOST = ((64, 40), (16, 150), (4, 100))                # nearly all of them: with one and two heads the searches read fewer rows otherwise
 
 
 @pytest.mark.parametrize("fmt", ["bf16", "fp8", "paged", "fp8-paged"])
 @pytest.mark.parametrize("rope", [False, True], ids=["plain", "relative"])
-@pytest.mark.parametrize("Hq,Hkv", [(8, 2), (16, 2)])
-def test_storage_rope_and_groups(ihip, Hq, Hkv, fmt, rope):
-    _check(ihip, Hq, Hkv, [150003, 99001], PLAN, fmt, rope)
+@pytest.mark.parametrize("Hq,Hkv,plan", [(2, 2, MOST), (4, 2, MOST), (8, 2, PLAN), (16, 2, PLAN)])
+def test_storage_rope_and_groups(ihip, Hq, Hkv, plan, fmt, rope):
+    _check(ihip, Hq, Hkv, [150003, 99001], plan, fmt, rope)
 
 
 @pytest.mark.parametrize("stages", [
@@ -109,6 +110,15 @@ def test_ragged_batch_with_idle_places_and_cut_chunks(ihip):
     for b, T in enumerate(lens):
         assert (blocks.view(len(lens), 2, -1)[b] >= 0).any() == (T > 320), (b, T)
     _check(ihip, 8, 2, lens, PLAN, "fp8-paged", True)
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "fp8", "paged", "fp8-paged"])
+@pytest.mark.parametrize("rope", [False, True], ids=["plain", "relative"])
+@pytest.mark.parametrize("stages", [((256, 8), (128, 16), (4, 30)), ((512, 8), (256, 16), (8, 40))], ids=["128", "256"])
+def test_chunks_of_more_than_a_wave(ihip, stages, rope, fmt):
+    """Chunks of 128 and 256 keys, of which a wave scores 64: the waves of a workgroup meet in LDS.  The short sequences keep all of
+    their first stage's chunks, the last one cut short by the end of the middle range, inside and at the end of a wave's keys."""
+    _check(ihip, 16, 2, [150003, 64 + 256 + 256 * 7 + 133, 64 + 256 + 256 * 5 + 64, 64 + 256 + 3], stages, fmt, rope, seed=stages[0][0])
 
 
 def test_pooled_over_all_heads(ihip):
