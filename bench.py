@@ -44,20 +44,21 @@ N_QUERY_SETS = 32
 # WRITE_SIZE x 1.0).  Counters cannot be read inside this process, so the figure is carried from the
 # summary named in `traffic_source`, which also gives the date and commit it was taken at; a kernel that
 # has no current summary reports traffic null.
-TRAFFIC_SOURCE = "profiles/decode_cfg3_and_prefill_cfg4_kernel_trace_and_hbm_counters.txt"
+CFG3_TRAFFIC = "profiles/decode_cfg3_kernel_trace_and_hbm_counters.txt"
+CFG4_TRAFFIC = "profiles/decode_cfg3_and_prefill_cfg4_kernel_trace_and_hbm_counters.txt"
 MEASURED_TRAFFIC_BYTES = {
-    ("cfg3-decode-1m-b8", "prune_decode.first.l256"): (781758.3 * 2.0 + 1225.5) * 1024.0,
-    ("cfg4-prefill-4k-on-256k", "prune_prefill.first.l64"): (765662.2 * 2.0 + 10655.5) * 1024.0,
-    ("cfg4-prefill-4k-on-256k", "prune_prefill.l16"): (469639.2 * 2.0 + 2048.0) * 1024.0,
-    ("cfg4-prefill-4k-on-256k", "attn_prefill"): (636708.9 * 2.0 + 32769.9) * 1024.0,
+    ("cfg3-decode-1m-b8", "prune_decode.first.l256"): ((782676.1 * 2.0 + 1241.9) * 1024.0, CFG3_TRAFFIC),
+    ("cfg4-prefill-4k-on-256k", "prune_prefill.first.l64"): ((765662.2 * 2.0 + 10655.5) * 1024.0, CFG4_TRAFFIC),
+    ("cfg4-prefill-4k-on-256k", "prune_prefill.l16"): ((469639.2 * 2.0 + 2048.0) * 1024.0, CFG4_TRAFFIC),
+    ("cfg4-prefill-4k-on-256k", "attn_prefill"): ((636708.9 * 2.0 + 32769.9) * 1024.0, CFG4_TRAFFIC),
 }
 
 
 def measured_traffic(workload, kernel):
-    t = MEASURED_TRAFFIC_BYTES.get((workload, kernel))
-    if t is None:
+    if (workload, kernel) not in MEASURED_TRAFFIC_BYTES:
         return {"traffic": None}
-    return {"traffic": t, "traffic_source": TRAFFIC_SOURCE}
+    traffic, source = MEASURED_TRAFFIC_BYTES[(workload, kernel)]
+    return {"traffic": traffic, "traffic_source": source}
 
 
 def parse():

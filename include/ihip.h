@@ -285,7 +285,8 @@ int32_t ihip_sparse_attn_prefill(const ihip_shape *shape, ihip_tensor q, ihip_te
  *     kept blocks.
  * Two exceptions, so that ihip_decode_layer_static takes a plan and gives the same bits: where a decode layer's scratch fits
  * IHIP_STATIC_SCRATCH_BYTES with the coarse parts but not with the fine ones, it is always cut coarse and the coarse bytes
- * are reported; where it fits only without the scores of all stages at once, every call scores stage by stage.
+ * are reported; where it fits only without the scores of stages taken together, all of them or the last two, every call scores
+ * stage by stage.
  */
 size_t ihip_workspace_bytes(int32_t op, const ihip_shape *shape, int32_t n_stages,
                             const int32_t *chunk_sizes, const int32_t *keeps);

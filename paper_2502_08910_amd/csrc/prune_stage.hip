@@ -198,7 +198,7 @@ static void launch_prefill(const PruneArgs &a, int P, int64_t max_seq_len, const
 // U chunks per 16-lane group.  What counts is the number of row loads in flight per SIMD, waves x
 // 4 groups x U x G, and how finely the work is cut: U = 1 is best for every later stage, for small problems, for E4M3 rows and
 // for pages; U = 3 (half as many loads again in flight) wins on the large first stage over contiguous bf16 rows with one or two heads a
-// group (with more it goes to the matrix cores: four heads, 8 x 1M keys, chunks of 256 278 us with U = 3, 262 there).
+// group (with more it goes to the matrix cores: four heads, 8 x 1M keys, chunks of 256, the same buffers in turn: 274.8 us with U = 3, 272.0 there).
 template <int G, int U>
 static void launch_decode_u(PruneArgs a, int P, bool fp8, hipStream_t st)
 {

@@ -16,7 +16,8 @@
 //   softmax  four scores a lane; the reference of the exponentials, and the sum, are the row group's own
 //   output   v_mfma_f32_4x4x4_16B_bf16: 16 blocks of 4 heads x 4 tokens x 4 dims; a lane's four probabilities are its row of
 //            the left operand, its 8 dims of the four V rows, in pairs of tokens, the columns of eight right ones.  A probability
-//            goes in as three bf16 parts (24 bits), so nothing of it is rounded away.
+//            goes in as three bf16 parts (24 bits), so nothing of it is rounded away (with finite V: the later parts are of
+//            either sign or zero, and an infinite V gives NaN).
 // With RoPE the keys are turned in fp32 and would need three parts as well (tried: 56 -> 63 us with four heads, 20 -> 29 with one), so
 // their scores stay on the vector ALUs.  Split and merge, before / now (us): four heads, 16 sequences of 3,200 slots, bf16 45.8 / 38.9
 // (5.4 TB/s), in pages 46.3 / 40.6, E4M3 38.4 / 26.3, bf16 with RoPE 56.4 / 43.5; 8 heads 75.6 / 41.4, 72.2 / 31.0, 96.9 / 52.3; one
