@@ -176,13 +176,12 @@ __global__ __launch_bounds__(kAttnThreads, G == 8 ? 2 : ROPE && !(KV8 && G <= 2)
     const int block_slots = a.n_blocks << a.block_log2;
     const int32_t *starts = a.block_starts + (int64_t)p * a.n_blocks;
 
-    // The blocks of this thread's slots are asked for at once, next to the sequence's length, with the whole sink there (which only
-    // a sequence shorter than it has not).
-    constexpr int kSlots = kAttnMaxSplit / kAttnThreads;
+    // The blocks of this thread's slots (of a split of the usual size) are asked for at once, next to the sequence's length, with the
+    // whole sink there (which only a sequence shorter than it has not).
+    constexpr int kSlots = kAttnUsualSplit / kAttnThreads;
     int start_of[kSlots];
 #pragma unroll
     for (int k = 0; k < kSlots; ++k) {
-        if (SRC != 2 && k * kAttnThreads >= a.slots_per_split) break;       // (over pages the branches cost what they save)
         const int i = tid + k * kAttnThreads, at = s0 + i - a.ge.n_sink;
         start_of[k] = i < a.slots_per_split && at >= 0 && at < block_slots ? starts[at >> a.block_log2] : -1;
     }
@@ -226,11 +225,15 @@ __global__ __launch_bounds__(kAttnThreads, G == 8 ? 2 : ROPE && !(KV8 && G <= 2)
         if (lane == 0 && mine > 0) atomicAdd(&sh_block_tokens, mine);
     }
     bool any = false;
+    auto put = [&](int i, int pos) {
+        any |= pos >= 0;
+        sh_pos[slot_place(i)] = pos;
+        if constexpr (SRC == 2) sh_page[slot_place(i)] = pos >= 0 ? ksrc.table_entry(pos) : 0;
+    };
 #pragma unroll
     for (int k = 0; k < kSlots; ++k) {
         const int i = tid + k * kAttnThreads;
-        if (SRC != 2 && k * kAttnThreads >= a.slots_per_split) break;
-        if (i >= a.slots_per_split) continue;
+        if (i >= a.slots_per_split) break;
         int slot = s0 + i, pos;
         if (n_sink_eff == a.ge.n_sink) {
             const int at = slot - n_sink_eff;
@@ -245,17 +248,19 @@ __global__ __launch_bounds__(kAttnThreads, G == 8 ? 2 : ROPE && !(KV8 && G <= 2)
         } else {
             pos = slot_to_pos(a, pr, p, slot, n_sink_eff, w0);
         }
-        any |= pos >= 0;
-        sh_pos[slot_place(i)] = pos;
-        if constexpr (SRC == 2) sh_page[slot_place(i)] = pos >= 0 ? ksrc.table_entry(pos) : 0;
+        put(i, pos);
     }
-    any = __ballot(any) != 0;
-    if (lane == 0) sh_any[wv] = any;
+    for (int i = tid + kAttnUsualSplit; i < a.slots_per_split; i += kAttnThreads) put(i, slot_to_pos(a, pr, p, s0 + i, n_sink_eff, w0));
+    const bool look = a.slots_per_split > kAttnMinSplit;
+    if (look) {
+        any = __ballot(any) != 0;
+        if (lane == 0) sh_any[wv] = any;
+    }
     __syncthreads();
     const int64_t pbase = ((int64_t)p * a.n_splits + split) * G;
-    // A split of absent blocks, as a plan for longer sequences has many: nothing to wait for.  One head a group, 27 sequences of 6,000 keys
-    // with 9,152 slots, splits without keys walked / left: bf16 115 / 111 us, E4M3 77 / 61
-    if ((sh_any[0] | sh_any[1] | sh_any[2] | sh_any[3]) == 0) {
+    // A split of absent blocks, as a plan for longer sequences has many: nothing to wait for (looked for where the chip is full).  One
+    // head a group, 27 sequences of 6,000 keys with 9,152 slots, splits without keys walked / left: bf16 115 / 111 us, E4M3 77 / 61
+    if (look && (sh_any[0] | sh_any[1] | sh_any[2] | sh_any[3]) == 0) {
         for (int idx = tid; idx < G * kD; idx += kAttnThreads) a.part_acc[pbase * kD + idx] = 0.f;
         if (tid < 2 * G) a.part_ml[pbase * 2 + tid] = (tid & 1) ? 0.f : kNegBig;
         return;
@@ -638,10 +643,13 @@ static int decode_splits(const ihip_shape &s, int n_blocks, int block, bool fine
 // Workgroups on a compute unit: waves per SIMD that the instantiation is compiled for (its launch bounds; eight heads over E4M3 rows fit
 // one more).  Eight heads, 16 sequences of 3,200 slots, splits for
 // four / for this many: bf16 45.1 / 41.0 us, E4M3 34.5 / 31.0, bf16 with RoPE 60.1 / 52.4.
-static int attn_decode_per_cu(int G, bool rope, bool fp8)
+// E4M3 rows with RoPE and one or two heads: four where the list fills them with splits of the least size, or three larger ones are better.
+// One head, 13 problems of 17,536 slots for three / for four (us): 27.4 / 34.4, 26 of them 45.9 / 42.1.
+static int attn_decode_per_cu(int G, bool rope, bool fp8, int64_t slots)
 {
     if (G == 8) return fp8 && !rope ? 3 : 2;
-    return rope && !(fp8 && G <= 2) ? 3 : 4;
+    const bool four = fp8 && G <= 2 && slots >= (int64_t)4 * kAttnMinSplit * compute_units();
+    return rope && !four ? 3 : 4;
 }
 
 // scratch for the partial results of the fine or the coarse splits
@@ -695,8 +703,9 @@ int32_t launch_attn_decode(const ihip_shape &s, const ihip_tensor &q, const ihip
     a.block = block;
     a.block_log2 = __builtin_ctz(block);
     a.scale_log2e = sm_scale * 1.44269504088896340736f * (fp8 ? fmt->k_scale : 1.0f);
-    a.n_splits = decode_splits(s, n_blocks, block, fine, &a.slots_per_split, attn_decode_per_cu(a.ge.G, use_rope, fp8));
     const int P = s.B * s.Hkv;
+    const int64_t slots = (int64_t)P * (s.n_sink + n_blocks * block + s.n_stream);
+    a.n_splits = decode_splits(s, n_blocks, block, fine, &a.slots_per_split, attn_decode_per_cu(a.ge.G, use_rope, fp8, slots));
     const int G = a.ge.G;
     a.part_ml = (float *)ws;
     a.part_acc = a.part_ml + (size_t)P * a.n_splits * G * 2;
