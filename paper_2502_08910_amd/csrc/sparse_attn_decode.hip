@@ -34,7 +34,7 @@ namespace ihip {
 
 constexpr int kAttnThreads = 256;
 constexpr int kAttnMaxSplit = 1536, kAttnUsualSplit = 1024;     // most slots of one split (multiples of 16); see decode_splits
-constexpr int kAttnSplitCost = 64;                       // what beginning and ending a split costs, in slots
+constexpr int kAttnSplitCost = 128;                      // what beginning and ending a split costs, in slots; see decode_splits
 constexpr int kAttnMinSplit = 256, kAttnMinSplitFine = 64;      // fewest; see decode_splits
 // Log2 units that the reference of the exponentials is set above the scores that outgrew it, so that it seldom has to follow.  A
 // probability is at most 1 then: sums of V rows overflow no sooner than with the maximum itself as the reference.
@@ -602,6 +602,8 @@ __global__ __launch_bounds__(kD * GROUPS) void attn_decode_merge_kernel(const At
 // in the rounds that take the least time, each as full as can be, and up to 1,536 slots a split are better than a second round that
 // is half empty.  At most 1,024 slots a split / so (us): 32 sequences of 5,248 slots, one head a group, E4M3 75.7 / 66.5, four heads, E4M3
 // 79.2 / 69.4; 32 of 3,200, four heads, bf16 with RoPE 106.5 / 91.5; 4 of 33,920, one head, E4M3 68.6 / 56.2, bf16 with RoPE 130 / 118.
+// (With 64 slots for a split's beginning and end two full rounds win over one that is nearly full, and should not: eight heads, bf16,
+// 138 problems of 2,324 slots 43.4 / 38.7.  800 drawn lists: 64, 128 and 256 on the average within 0.3 % of each other.)
 // `fine`: where splits of 256 slots would not even give every CU one workgroup, the kernel is one chain of latencies and a
 // split walks its loop four times while most of the chip is idle; splits then go down to 64 slots, one batch of loads of
 // every 16-lane group, to two workgroups per CU at most (more of them share what a CU has and cost the merge) and to 64 splits,
