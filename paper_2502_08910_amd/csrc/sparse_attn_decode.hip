@@ -251,15 +251,16 @@ __global__ __launch_bounds__(kAttnThreads, G == 8 ? 2 : ROPE && !(KV8 && G <= 2)
         put(i, pos);
     }
     for (int i = tid + kAttnUsualSplit; i < a.slots_per_split; i += kAttnThreads) put(i, slot_to_pos(a, pr, p, s0 + i, n_sink_eff, w0));
-    const bool look = a.slots_per_split > kAttnMinSplit;
+    const bool look = a.slots_per_split >= kAttnMinSplit;
     if (look) {
         any = __ballot(any) != 0;
         if (lane == 0) sh_any[wv] = any;
     }
     __syncthreads();
     const int64_t pbase = ((int64_t)p * a.n_splits + split) * G;
-    // A split of absent blocks, as a plan for longer sequences has many: nothing to wait for (looked for where the chip is full).  One
-    // head a group, 27 sequences of 6,000 keys with 9,152 slots, splits without keys walked / left: bf16 115 / 111 us, E4M3 77 / 61
+    // A split of absent blocks, as a plan for longer sequences has many: nothing to wait for (fine splits, which all run at once,
+    // are not looked at).  One head a group, splits without keys walked / left (us): 27 sequences of 6,000 keys with 9,152 slots, bf16 115 / 111,
+    // E4M3 77 / 61; layers of 7 sequences of 355 keys with 16,640 slots, bf16 24.4 / 21.9, E4M3 24.4 / 21.0
     if (look && (sh_any[0] | sh_any[1] | sh_any[2] | sh_any[3]) == 0) {
         for (int idx = tid; idx < G * kD; idx += kAttnThreads) a.part_acc[pbase * kD + idx] = 0.f;
         if (tid < 2 * G) a.part_ml[pbase * 2 + tid] = (tid & 1) ? 0.f : kNegBig;
