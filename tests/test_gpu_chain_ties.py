@@ -1,23 +1,10 @@
 """The one-launch selections (select_chain.hip) where the bin of the K-th best score holds one candidate, as many as a wave has lanes,
 one more, or several hundred: equal scores, of which the lowest positions are kept.  Scores are whole numbers, exact in every
-kernel, and the lists are compared with the ones known from how the inputs are made.  Nothing else scores within 64 of the tied
-ones, many times a bin's width (1.5 / 512 of the range, 2,400 at most), so that the bin holds these alone."""
+kernel, and the lists are compared with the ones known from how the inputs are made."""
 import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
-
-
-def _in_one_launch(ihip, run):
-    """Runs a layer of which every stage is scored and selected in one launch each."""
-    ihip.profile_read()
-    ihip.profile_enable(True)
-    try:
-        run()
-    finally:
-        ihip.profile_enable(False)
-    got = {name: n for name, (_, n) in ihip.profile_read().items() if not name.startswith("attn")}
-    assert got == {"prune_decode.first.l8": 1, "select_blocks.first.l8": 1}, got
 
 
 @pytest.mark.parametrize("pooling", [False, True], ids=["kv-head", "all-heads"])
@@ -30,7 +17,7 @@ def test_equal_scores_at_the_threshold(ties, n_slots, pooling):
     g = torch.Generator().manual_seed(ties)
     above = (n_slots - ties) // 2
     rank = torch.randperm(n_slots, generator=g)           # of the slots: the first `above` are better than the tied ones, the rest worse
-    value = torch.where(rank < above, 2064 + rank, torch.where(rank < above + ties, torch.tensor(2000), 1936 - rank))
+    value = torch.where(rank < above, 2001 + rank, torch.where(rank < above + ties, torch.tensor(2000), 2000 - rank))
     q = torch.zeros((1, 2 * Hkv, 1, D))
     q[..., 0], q[..., 1] = 64, 1                          # score = 64 * k0 + k1
     k = torch.zeros((1, Hkv, T, D))
@@ -42,7 +29,7 @@ def test_equal_scores_at_the_threshold(ties, n_slots, pooling):
     L = ihip.Layer(q, k, torch.tensor([T], dtype=torch.int32, device="cuda"), 1, n_sink, n_stream)
     blocks = torch.empty((L.P, keeps[-1]), dtype=torch.int32, device="cuda")
     kw = {"pooling": ihip.binding.POOL_ALL_HEADS} if pooling else {}
-    _in_one_launch(ihip, lambda: L.decode_layer(q, k, k, chunks, keeps, out_blocks=blocks, **kw))
+    L.decode_layer(q, k, k, chunks, keeps, out_blocks=blocks, **kw)
     best = torch.sort(value, descending=True, stable=True).indices[:keep].sort().values
     want = (n_sink + best.view(-1, 1) * 8 + torch.tensor([0, 4])).flatten().to(torch.int32)
     assert torch.equal(blocks.cpu(), want.expand(Hkv, -1))
@@ -67,7 +54,7 @@ def test_one_list_for_many_heads(Hkv, n_slots):
     chunks, keeps = [8, 4], [keep, 2 * keep]
     L = ihip.Layer(q, k, torch.tensor([T], dtype=torch.int32, device="cuda"), 1, n_sink, n_stream)
     blocks = torch.empty((L.P, keeps[-1]), dtype=torch.int32, device="cuda")
-    _in_one_launch(ihip, lambda: L.decode_layer(q, k, k, chunks, keeps, out_blocks=blocks, pooling=ihip.binding.POOL_ALL_HEADS))
+    L.decode_layer(q, k, k, chunks, keeps, out_blocks=blocks, pooling=ihip.binding.POOL_ALL_HEADS)
     best = torch.sort(value, descending=True, stable=True).indices[:keep].sort().values
     want = (n_sink + best.view(-1, 1) * 8 + torch.tensor([0, 4])).flatten().to(torch.int32)
     assert torch.equal(blocks.cpu(), want.expand(Hkv, -1))

@@ -18,18 +18,14 @@ def ihip():
     return pkg
 
 
-def _kernels(ihip, run):
+def _launches(ihip, run):
     ihip.profile_read()
     ihip.profile_enable(True)
     try:
         run()
     finally:
         ihip.profile_enable(False)
-    return {name: n for name, (_, n) in ihip.profile_read().items()}
-
-
-def _launches(ihip, run):
-    return sum(n for name, n in _kernels(ihip, run).items() if name.startswith("prune_decode"))
+    return sum(n for name, (_, n) in ihip.profile_read().items() if name.startswith("prune_decode"))
 
 
 def _inputs(ihip, Hq, Hkv, lens, fmt, rope, n_pos, seed=0, page=16):
@@ -84,14 +80,13 @@ def _check(ihip, Hq, Hkv, lens, stages, fmt="bf16", rope=False, n_sink=64, n_str
 
 
 PLAN = ((64, 40), (16, 80), (4, 100))                 # 160 candidates of 16 keys, half of them kept
-MOST = ((64, 40), (16, 150), (4, 100))                # nearly all of them: with one and two heads the searches read fewer rows otherwise
 
 
 @pytest.mark.parametrize("fmt", ["bf16", "fp8", "paged", "fp8-paged"])
 @pytest.mark.parametrize("rope", [False, True], ids=["plain", "relative"])
-@pytest.mark.parametrize("Hq,Hkv,plan", [(2, 2, MOST), (4, 2, MOST), (8, 2, PLAN), (16, 2, PLAN)])
-def test_storage_rope_and_groups(ihip, Hq, Hkv, plan, fmt, rope):
-    _check(ihip, Hq, Hkv, [150003, 99001], plan, fmt, rope)
+@pytest.mark.parametrize("Hq,Hkv", [(8, 2), (16, 2)])
+def test_storage_rope_and_groups(ihip, Hq, Hkv, fmt, rope):
+    _check(ihip, Hq, Hkv, [150003, 99001], PLAN, fmt, rope)
 
 
 @pytest.mark.parametrize("stages", [
@@ -110,15 +105,6 @@ def test_ragged_batch_with_idle_places_and_cut_chunks(ihip):
     for b, T in enumerate(lens):
         assert (blocks.view(len(lens), 2, -1)[b] >= 0).any() == (T > 320), (b, T)
     _check(ihip, 8, 2, lens, PLAN, "fp8-paged", True)
-
-
-@pytest.mark.parametrize("fmt", ["bf16", "fp8", "paged", "fp8-paged"])
-@pytest.mark.parametrize("rope", [False, True], ids=["plain", "relative"])
-@pytest.mark.parametrize("stages", [((256, 8), (128, 16), (4, 30)), ((512, 8), (256, 16), (8, 40))], ids=["128", "256"])
-def test_chunks_of_more_than_a_wave(ihip, stages, rope, fmt):
-    """Chunks of 128 and 256 keys, of which a wave scores 64: the waves of a workgroup meet in LDS.  The short sequences keep all of
-    their first stage's chunks, the last one cut short by the end of the middle range, inside and at the end of a wave's keys."""
-    _check(ihip, 16, 2, [150003, 64 + 256 + 256 * 7 + 133, 64 + 256 + 256 * 5 + 64, 64 + 256 + 3], stages, fmt, rope, seed=stages[0][0])
 
 
 def test_pooled_over_all_heads(ihip):
@@ -144,14 +130,6 @@ def test_cached_first_stage(ihip):
         assert _launches(ihip, lambda: L.decode_layer_masked(q, k, v, chunks, keeps, 1, state, ws=ws, out=out)) == launches
         got.append((state.cpu(), out.cpu().view(torch.int16)))
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
-
-
-def test_kernels_are_named_by_the_stage_they_begin_with(ihip):
-    q, k, v, kw = _inputs(ihip, 8, 2, [150003], "bf16", False, 0)
-    L = ihip.Layer(q, torch.empty((1, 2, 150003, 0), dtype=torch.bfloat16), torch.tensor([150003], dtype=torch.int32, device="cuda"), 1, 64, 256)
-    got = _kernels(ihip, lambda: L.decode_layer(q, k, v, [s[0] for s in PLAN], [s[1] for s in PLAN]))
-    assert got == {n: 1 for n in ("prune_decode.first.l64", "select_blocks.first.l64", "prune_decode.l16", "select_blocks.l16",
-                                  "attn_decode_split", "attn_decode_merge")}
 
 
 @pytest.mark.parametrize("Hq,Hkv,stages,together", [
@@ -191,23 +169,3 @@ def test_host_tier_rounds_alike(ihip, Hq, fp8):
             assert torch.equal(lists[0], lists[1]) and torch.equal(got.view(torch.int16), want[0].view(torch.int16))
     finally:
         cache.close()
-
-
-def test_absent_parents_of_very_long_sequences(ihip):
-    """An absent parent (-1 in a cached first list) stands for no key, also where a sequence has more than 2^30 of them.  The
-    tokens of a head share one row (stride 0), so the keys that an absent parent must not be taken for score as well as any."""
-    T, chunks, keeps = (1 << 30) + (1 << 20), [s[0] for s in PLAN], [s[1] for s in PLAN]
-    g = torch.Generator().manual_seed(1)
-    q = torch.randint(-3, 4, (1, 8, 1, D), generator=g).bfloat16().cuda()
-    k, v = (torch.randint(-3, 4, (1, 2, 1, D), generator=g).bfloat16().cuda().expand(1, 2, T, D) for _ in range(2))
-    L = ihip.Layer(q, torch.empty((1, 2, T, 0), dtype=torch.bfloat16), torch.tensor([T], dtype=torch.int32, device="cuda"), 1, 64, 256)
-    state = L.mask_state(keeps)
-    first = torch.full((2, keeps[0]), -1, dtype=torch.int32)
-    first[:, :10] = 64 + 64 * torch.arange(10) * (1 << 20)
-    state[:2 * keeps[0]] = first.flatten().cuda()
-    assert _launches(ihip, lambda: L.decode_layer_masked(q, k, v, chunks, keeps, 1, state)) == 1
-    second, third = state[2 * keeps[0]:].cpu().split([2 * keeps[1], 2 * keeps[2]])
-    want = (first[:, :10, None] + 16 * torch.arange(4)).flatten(1)
-    assert torch.equal(second.view(2, -1)[:, :40], want) and (second.view(2, -1)[:, 40:] == -1).all()
-    want = (want[:, :, None] + 4 * torch.arange(4)).flatten(1)[:, :100]
-    assert torch.equal(third.view(2, -1), want)
